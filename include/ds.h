@@ -229,8 +229,7 @@ ds_status_t ds_payload_sizes(const ds_ctx_t *ctx, int32_t rows, size_t bytes_out
  *   g      [n, g_row_stride]     gradients, cfg.grad_dtype (bf16 is widened exactly)
  *   delta  [n, delta_row_stride] worker errors, fp32, read and overwritten
  *   out    n messages
- * Strides are in elements and >= d.  Rows that are 16-byte aligned take 128-bit loads;
- * other rows take an element-wise path with the same results.
+ * Strides are in elements and >= d; rows may start at any element.
  * QSGD draws its rounding, RSPARSE and TERNARY their keep decisions, from the stream (seed,
  * step, worker i, element j). */
 ds_status_t ds_worker_compress(ds_ctx_t *ctx, uint64_t step, const void *g,

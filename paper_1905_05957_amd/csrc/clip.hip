@@ -14,25 +14,31 @@ using namespace ds;
 
 namespace {
 
+// Message rows of an odd length start at any byte: the four elements of a thread are one access
+// of 4 * NB bytes all the same (global accesses need no alignment).
+typedef uint32_t u32_byte __attribute__((aligned(1)));
+typedef uint32_t u32x2_byte __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_byte __attribute__((ext_vector_type(4), aligned(1)));
+
 template <int NB>
 __device__ __forceinline__ void store_msg4(uint8_t *__restrict__ row, int64_t e, int64_t d, const uint32_t top[4])
 {
     uint8_t *p = row + e * NB;
-    if (e + 4 <= d && (reinterpret_cast<uintptr_t>(p) & (4 * NB - 1)) == 0) {
+    if (e + 4 <= d) {
         if constexpr (NB == 1) {
-            *reinterpret_cast<uint32_t *>(p) = top[0] | (top[1] << 8) | (top[2] << 16) | (top[3] << 24);
+            *reinterpret_cast<u32_byte *>(p) = top[0] | (top[1] << 8) | (top[2] << 16) | (top[3] << 24);
         } else if constexpr (NB == 2) {
-            *reinterpret_cast<u32x2 *>(p) = u32x2{top[0] | (top[1] << 16), top[2] | (top[3] << 16)};
+            *reinterpret_cast<u32x2_byte *>(p) = u32x2{top[0] | (top[1] << 16), top[2] | (top[3] << 16)};
         } else {
-            *reinterpret_cast<u32x4 *>(p) = u32x4{top[0], top[1], top[2], top[3]};
+            *reinterpret_cast<u32x4_byte *>(p) = u32x4{top[0], top[1], top[2], top[3]};
         }
         return;
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 3; ++c) {
         if (e + c >= d) break;
         if constexpr (NB == 1) p[c] = static_cast<uint8_t>(top[c]);
-        else if constexpr (NB == 2) {               // rows of an odd length start on odd 2-byte boundaries at worst
+        else if constexpr (NB == 2) {
             p[2 * c] = static_cast<uint8_t>(top[c]);
             p[2 * c + 1] = static_cast<uint8_t>(top[c] >> 8);
         } else {
@@ -48,20 +54,20 @@ __device__ __forceinline__ f32x4 load_msg4(const uint8_t *__restrict__ row, int6
 {
     const uint8_t *p = row + e * NB;
     uint32_t top[4] = {0u, 0u, 0u, 0u};
-    if (e + 4 <= d && (reinterpret_cast<uintptr_t>(p) & (4 * NB - 1)) == 0) {
+    if (e + 4 <= d) {
         if constexpr (NB == 1) {
-            const uint32_t w = *reinterpret_cast<const uint32_t *>(p);
+            const uint32_t w = *reinterpret_cast<const u32_byte *>(p);
             top[0] = w & 255u; top[1] = (w >> 8) & 255u; top[2] = (w >> 16) & 255u; top[3] = w >> 24;
         } else if constexpr (NB == 2) {
-            const u32x2 w = *reinterpret_cast<const u32x2 *>(p);
+            const u32x2 w = *reinterpret_cast<const u32x2_byte *>(p);
             top[0] = w.x & 0xFFFFu; top[1] = w.x >> 16; top[2] = w.y & 0xFFFFu; top[3] = w.y >> 16;
         } else {
-            const u32x4 w = *reinterpret_cast<const u32x4 *>(p);
+            const u32x4 w = *reinterpret_cast<const u32x4_byte *>(p);
             top[0] = w.x; top[1] = w.y; top[2] = w.z; top[3] = w.w;
         }
     } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < 3; ++c) {
             if (e + c >= d) break;
 #pragma unroll
             for (int t = 0; t < NB; ++t) top[c] |= static_cast<uint32_t>(p[NB * c + t]) << (8 * t);
@@ -75,7 +81,7 @@ __device__ __forceinline__ f32x4 load_msg4(const uint8_t *__restrict__ row, int6
 // Q[v], the message and the error for the four elements of a thread
 template <int NB>
 __device__ __forceinline__ void clip_store4(f32x4 v, uint32_t mask, int64_t e, int64_t d, uint8_t *__restrict__ msg_row,
-                                            float *__restrict__ err_row, bool err_vec)
+                                            float *__restrict__ err_row)
 {
     const uint32_t u[4] = {__float_as_uint(v.x) & mask, __float_as_uint(v.y) & mask, __float_as_uint(v.z) & mask,
                            __float_as_uint(v.w) & mask};
@@ -83,7 +89,7 @@ __device__ __forceinline__ void clip_store4(f32x4 v, uint32_t mask, int64_t e, i
     const uint32_t top[4] = {u[0] >> sh, u[1] >> sh, u[2] >> sh, u[3] >> sh};
     store_msg4<NB>(msg_row, e, d, top);
     const f32x4 q = {__uint_as_float(u[0]), __uint_as_float(u[1]), __uint_as_float(u[2]), __uint_as_float(u[3])};
-    if (err_row) st4_stream(err_row, e, d, err_vec, v - q);     // no buffer: no compensation
+    if (err_row) st4_stream(err_row, e, d, v - q);     // no buffer: no compensation
 }
 
 // Algorithm 1, worker block: v = g + delta ; message = Q[v] ; delta <- v - Q[v].
@@ -97,11 +103,9 @@ __global__ __launch_bounds__(kBlock) void k_clip_worker(const void *g, int64_t g
     const void *grow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(g) + row * gs)
                             : static_cast<const void *>(static_cast<const float *>(g) + row * gs);
     float *drow = delta ? delta + row * dstr : nullptr;         // null: no compensation, v = g
-    const bool gvec = BF16 ? aligned8(grow) : aligned16(grow);
-    const bool dvec = aligned16(drow);
-    f32x4 v = ld4_grad<BF16>(grow, e, d, gvec);
-    if (drow) v = v + ld4_stream(drow, e, d, dvec);
-    clip_store4<NB>(v, mask, e, d, msg + static_cast<int64_t>(row) * d * NB, drow, dvec);
+    f32x4 v = ld4_grad<BF16>(grow, e, d);
+    if (drow) v = v + ld4_stream(drow, e, d);
+    clip_store4<NB>(v, mask, e, d, msg + static_cast<int64_t>(row) * d * NB, drow);
 }
 
 // Parameter-server block: v = delta_s + (1/n) sum_i Q[v_i] as the chain acc = fma(q_i, 1/n, acc)
@@ -112,11 +116,10 @@ __global__ __launch_bounds__(kBlock) void k_clip_server(const uint8_t *msg_in, i
 {
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
-    const bool dvec = aligned16(delta_s);
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    if (delta_s) a = ld4_stream(delta_s, e, d, dvec);           // null: no server error
+    if (delta_s) a = ld4_stream(delta_s, e, d);           // null: no server error
     for (int i = 0; i < n; ++i) a = fma4(inv_n, load_msg4<NB>(msg_in + static_cast<int64_t>(i) * d * NB, e, d), a);
-    clip_store4<NB>(a, mask, e, d, msg_out, delta_s, dvec);
+    clip_store4<NB>(a, mask, e, d, msg_out, delta_s);
 }
 
 // Server that does not compress: the average is the message (written and / or applied).

@@ -23,81 +23,69 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-__device__ __forceinline__ bool aligned8(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
+// Vectors at the alignment of their elements.  Global accesses of this target need no more, and
+// the instruction is the same one, so rows that start between 16-byte boundaries (contiguous
+// [n, d] with d not a multiple of 4) take the same code as the others: one 128-bit access per
+// thread and stream.  With two 64-bit accesses for 8-byte rows and four 32-bit ones for 4-byte
+// rows, as it was before, the 1-bit step at 8 x 11,173,962 (every other row at an 8-byte boundary)
+// took 255 us against 230 us, a 1-bit step at 7 x 2,345,679 89 us against 80 us.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// Four consecutive fp32 elements e..e+3 of a row, zero where e+c >= lim.  `vec` = the row
-// starts on a 16-byte boundary.  Rows that start on an 8-byte boundary only (contiguous
-// [n, d] with d = 2 mod 4) take two 64-bit accesses instead of four 32-bit ones; e is a
-// multiple of 4, so the row's alignment is that of every access.
-__device__ __forceinline__ f32x4 ld4(const float *__restrict__ row, int64_t e, int64_t lim, bool vec)
+// Four consecutive fp32 elements e..e+3 of a row, zero where e+c >= lim.
+__device__ __forceinline__ f32x4 ld4_tail(const float *__restrict__ row, int64_t e, int64_t lim)
 {
-    if (vec && e + 4 <= lim) return *reinterpret_cast<const f32x4 *>(row + e);
-    if (!vec && e + 4 <= lim && aligned8(row)) {
-        const f32x2 a = *reinterpret_cast<const f32x2 *>(row + e), b = *reinterpret_cast<const f32x2 *>(row + e + 2);
-        return f32x4{a.x, a.y, b.x, b.y};
-    }
     f32x4 r = {0.f, 0.f, 0.f, 0.f};
     if (e < lim) r.x = row[e];
     if (e + 1 < lim) r.y = row[e + 1];
     if (e + 2 < lim) r.z = row[e + 2];
-    if (e + 3 < lim) r.w = row[e + 3];
     return r;
 }
 
-// Same, streaming (read once): bypasses cache retention.
-__device__ __forceinline__ f32x4 ld4_stream(const float *__restrict__ row, int64_t e, int64_t lim, bool vec)
+__device__ __forceinline__ f32x4 ld4(const float *__restrict__ row, int64_t e, int64_t lim)
 {
-    if (vec && e + 4 <= lim) return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(row + e));
-    if (!vec && e + 4 <= lim && aligned8(row)) {
-        const f32x2 a = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(row + e));
-        const f32x2 b = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(row + e + 2));
-        return f32x4{a.x, a.y, b.x, b.y};
-    }
-    return ld4(row, e, lim, false);
+    if (e + 4 <= lim) return *reinterpret_cast<const f32x4_any *>(row + e);
+    return ld4_tail(row, e, lim);
+}
+
+// Same, streaming (read once): bypasses cache retention.
+__device__ __forceinline__ f32x4 ld4_stream(const float *__restrict__ row, int64_t e, int64_t lim)
+{
+    if (e + 4 <= lim) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(row + e));
+    return ld4_tail(row, e, lim);
 }
 
 __device__ __forceinline__ float bf16_widen(uint32_t h) { return __uint_as_float(h << 16); }
 
 // Four consecutive bf16 elements widened exactly to fp32.
-__device__ __forceinline__ f32x4 ld4_bf16(const uint16_t *__restrict__ row, int64_t e, int64_t lim, bool vec)
+__device__ __forceinline__ f32x4 ld4_bf16(const uint16_t *__restrict__ row, int64_t e, int64_t lim)
 {
     f32x4 r = {0.f, 0.f, 0.f, 0.f};
-    if (vec && e + 4 <= lim) {
-        u32x2 u = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(row + e));
+    if (e + 4 <= lim) {
+        const u32x2 u = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any *>(row + e));
         r.x = __uint_as_float(u.x << 16);
         r.y = __uint_as_float(u.x & 0xFFFF0000u);
         r.z = __uint_as_float(u.y << 16);
         r.w = __uint_as_float(u.y & 0xFFFF0000u);
         return r;
     }
-    if (!vec && e + 4 <= lim && (reinterpret_cast<uintptr_t>(row) & 3u) == 0) {   // 4-byte aligned row: two 32-bit loads
-        const uint32_t a = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(row + e));
-        const uint32_t b = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(row + e + 2));
-        return f32x4{__uint_as_float(a << 16), __uint_as_float(a & 0xFFFF0000u), __uint_as_float(b << 16),
-                     __uint_as_float(b & 0xFFFF0000u)};
-    }
     if (e < lim) r.x = bf16_widen(row[e]);
     if (e + 1 < lim) r.y = bf16_widen(row[e + 1]);
     if (e + 2 < lim) r.z = bf16_widen(row[e + 2]);
-    if (e + 3 < lim) r.w = bf16_widen(row[e + 3]);
     return r;
 }
 
-__device__ __forceinline__ void st4(float *__restrict__ row, int64_t e, int64_t lim, bool vec, f32x4 v)
+__device__ __forceinline__ void st4_tail(float *__restrict__ row, int64_t e, int64_t lim, f32x4 v)
 {
-    if (vec && e + 4 <= lim) { *reinterpret_cast<f32x4 *>(row + e) = v; return; }
-    if (!vec && e + 4 <= lim && aligned8(row)) {
-        *reinterpret_cast<f32x2 *>(row + e) = f32x2{v.x, v.y};
-        *reinterpret_cast<f32x2 *>(row + e + 2) = f32x2{v.z, v.w};
-        return;
-    }
     if (e < lim) row[e] = v.x;
     if (e + 1 < lim) row[e + 1] = v.y;
     if (e + 2 < lim) row[e + 2] = v.z;
-    if (e + 3 < lim) row[e + 3] = v.w;
+}
+
+__device__ __forceinline__ void st4(float *__restrict__ row, int64_t e, int64_t lim, f32x4 v)
+{
+    if (e + 4 <= lim) *reinterpret_cast<f32x4_any *>(row + e) = v;
+    else st4_tail(row, e, lim, v);
 }
 
 // Store of state that is rewritten in place and not read again before the next call.  A
@@ -105,18 +93,18 @@ __device__ __forceinline__ void st4(float *__restrict__ row, int64_t e, int64_t 
 // in-place g + delta -> delta over 8 x 25.6 M elements took 441 us with plain accesses to
 // delta, 480 us with only the load non-temporal, 438 us with only the store, 399 us with both
 // (424 us out of place).
-__device__ __forceinline__ void st4_stream(float *__restrict__ row, int64_t e, int64_t lim, bool vec, f32x4 v)
+__device__ __forceinline__ void st4_stream(float *__restrict__ row, int64_t e, int64_t lim, f32x4 v)
 {
-    if (vec && e + 4 <= lim) { __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(row + e)); return; }
-    st4(row, e, lim, vec, v);
+    if (e + 4 <= lim) __builtin_nontemporal_store(static_cast<f32x4_any>(v), reinterpret_cast<f32x4_any *>(row + e));
+    else st4_tail(row, e, lim, v);
 }
 
 // Gradient row of either dtype.
 template <bool BF16>
-__device__ __forceinline__ f32x4 ld4_grad(const void *__restrict__ row, int64_t e, int64_t lim, bool vec)
+__device__ __forceinline__ f32x4 ld4_grad(const void *__restrict__ row, int64_t e, int64_t lim)
 {
-    if constexpr (BF16) return ld4_bf16(static_cast<const uint16_t *>(row), e, lim, vec);
-    else return ld4_stream(static_cast<const float *>(row), e, lim, vec);
+    if constexpr (BF16) return ld4_bf16(static_cast<const uint16_t *>(row), e, lim);
+    else return ld4_stream(static_cast<const float *>(row), e, lim);
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
@@ -339,17 +327,15 @@ __device__ __forceinline__ f32x4 fma4(float a, f32x4 b, f32x4 c)
 template <bool MOM, bool DECODE_ONLY>
 __device__ __forceinline__ void apply_q4(f32x4 q, int64_t e, int64_t d, float *x, float *m, float gamma, float beta)
 {
-    const bool xvec = aligned16(x);
     if constexpr (DECODE_ONLY) {
-        st4_stream(x, e, d, xvec, q);
+        st4_stream(x, e, d, q);
     } else {
-        const f32x4 xv = ld4_stream(x, e, d, xvec);
+        const f32x4 xv = ld4_stream(x, e, d);
         if constexpr (MOM) {
-            const bool mvec = aligned16(m);
-            q = fma4(beta, ld4_stream(m, e, d, mvec), q);
-            st4_stream(m, e, d, mvec, q);
+            q = fma4(beta, ld4_stream(m, e, d), q);
+            st4_stream(m, e, d, q);
         }
-        st4_stream(x, e, d, xvec, fma4(-gamma, q, xv));
+        st4_stream(x, e, d, fma4(-gamma, q, xv));
     }
 }
 
@@ -359,7 +345,7 @@ __device__ __forceinline__ void apply_q4(f32x4 q, int64_t e, int64_t d, float *x
 __device__ __forceinline__ void put_average4(f32x4 a, int64_t e, int64_t d, float *dense_out, float *x, float *m,
                                              float gamma, float beta)
 {
-    if (dense_out) st4(dense_out, e, d, aligned16(dense_out), a);
+    if (dense_out) st4(dense_out, e, d, a);
     if (x) {
         if (m) apply_q4<true, false>(a, e, d, x, m, gamma, beta);
         else apply_q4<false, false>(a, e, d, x, m, gamma, beta);

@@ -19,11 +19,9 @@ __global__ __launch_bounds__(kBlock) void k_identity_worker(const void *g, int64
                             : static_cast<const void *>(static_cast<const float *>(g) + row * gs);
     float *drow = delta + row * dstr;
     float *orow = dense + row * d;
-    const bool gvec = BF16 ? aligned8(grow) : aligned16(grow);
-    const bool dvec = aligned16(drow), ovec = aligned16(orow);
-    const f32x4 v = ld4_grad<BF16>(grow, e, d, gvec) + ld4(drow, e, d, dvec);
-    st4(orow, e, d, ovec, v);          // Q[v] = v
-    st4(drow, e, d, dvec, v - v);      // delta <- v - Q[v]
+    const f32x4 v = ld4_grad<BF16>(grow, e, d) + ld4(drow, e, d);
+    st4(orow, e, d, v);          // Q[v] = v
+    st4(drow, e, d, v - v);      // delta <- v - Q[v]
 }
 
 __global__ __launch_bounds__(kBlock) void k_identity_server(const float *dense_in, int n, float inv_n,
@@ -31,16 +29,15 @@ __global__ __launch_bounds__(kBlock) void k_identity_server(const float *dense_i
 {
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
-    const bool dvec = aligned16(delta_s), ovec = aligned16(dense_out);
-    f32x4 a = ld4(delta_s, e, d, dvec);
+    f32x4 a = ld4(delta_s, e, d);
     for (int i = 0; i < n; ++i) {
         const float *irow = dense_in + i * d;
-        const f32x4 q = ld4(irow, e, d, aligned16(irow));
+        const f32x4 q = ld4(irow, e, d);
         a.x = __fmaf_rn(q.x, inv_n, a.x); a.y = __fmaf_rn(q.y, inv_n, a.y);
         a.z = __fmaf_rn(q.z, inv_n, a.z); a.w = __fmaf_rn(q.w, inv_n, a.w);
     }
-    st4(dense_out, e, d, ovec, a);
-    st4(delta_s, e, d, dvec, a - a);
+    st4(dense_out, e, d, a);
+    st4(delta_s, e, d, a - a);
 }
 
 template <bool MOM, bool DECODE_ONLY>
@@ -49,23 +46,21 @@ __global__ __launch_bounds__(kBlock) void k_identity_update(const float *q_in, f
 {
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
-    const bool xvec = aligned16(x);
-    f32x4 q = ld4(q_in, e, d, aligned16(q_in));
+    f32x4 q = ld4(q_in, e, d);
     if constexpr (DECODE_ONLY) {
-        st4(x, e, d, xvec, q);
+        st4(x, e, d, q);
     } else {
-        f32x4 xv = ld4(x, e, d, xvec);
+        f32x4 xv = ld4(x, e, d);
         if constexpr (MOM) {
-            const bool mvec = aligned16(m);
-            f32x4 mv = ld4(m, e, d, mvec);
+            f32x4 mv = ld4(m, e, d);
             mv.x = __fmaf_rn(beta, mv.x, q.x); mv.y = __fmaf_rn(beta, mv.y, q.y);
             mv.z = __fmaf_rn(beta, mv.z, q.z); mv.w = __fmaf_rn(beta, mv.w, q.w);
-            st4(m, e, d, mvec, mv);
+            st4(m, e, d, mv);
             q = mv;
         }
         xv.x = __fmaf_rn(-gamma, q.x, xv.x); xv.y = __fmaf_rn(-gamma, q.y, xv.y);
         xv.z = __fmaf_rn(-gamma, q.z, xv.z); xv.w = __fmaf_rn(-gamma, q.w, xv.w);
-        st4(x, e, d, xvec, xv);
+        st4(x, e, d, xv);
     }
 }
 

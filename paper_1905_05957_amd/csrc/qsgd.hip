@@ -24,6 +24,10 @@ namespace {
 constexpr uint32_t kServerStream = 0xFFFFFFFFu;
 constexpr int kUnitGroup = 64;  // workers whose decode units are staged in LDS at a time
 
+// code rows of an odd length start at any byte; global accesses need no alignment
+typedef uint16_t u16_byte __attribute__((aligned(1)));
+typedef uint32_t u32_byte __attribute__((aligned(1)));
+
 struct QParams {
     int64_t d;
     int32_t bucket;       // elements per bucket, power of two in [64, 2048]
@@ -97,8 +101,8 @@ __device__ __forceinline__ f32x4 quantise4(f32x4 v, int64_t e, uint32_t stream, 
     if (live) {
         const uint32_t packed = code[0] | (code[1] << 4) | (code[2] << 8) | (code[3] << 12);
         uint8_t *dst = levels_row + (e >> 1);
-        if (e + 4 <= P.d && (reinterpret_cast<uintptr_t>(dst) & 1u) == 0) {
-            *reinterpret_cast<uint16_t *>(dst) = static_cast<uint16_t>(packed);
+        if (e + 4 <= P.d) {
+            *reinterpret_cast<u16_byte *>(dst) = static_cast<uint16_t>(packed);
         } else {
             dst[0] = static_cast<uint8_t>(packed);
             if (e + 2 < P.d) dst[1] = static_cast<uint8_t>(packed >> 8);
@@ -128,7 +132,7 @@ __device__ __forceinline__ f32x4 quantise4(f32x4 v, int64_t e, uint32_t stream, 
 __device__ __forceinline__ uint32_t load_codes4(const uint8_t *__restrict__ levels_row, int64_t e, int64_t d)
 {
     const uint8_t *src = levels_row + (e >> 1);
-    if (e + 4 <= d && (reinterpret_cast<uintptr_t>(src) & 1u) == 0) return *reinterpret_cast<const uint16_t *>(src);
+    if (e + 4 <= d) return *reinterpret_cast<const u16_byte *>(src);
     uint32_t r = src[0];
     if (e + 2 < d) r |= static_cast<uint32_t>(src[1]) << 8;
     return r;
@@ -159,14 +163,12 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_worker(const void *g, int64_t g
     const void *grow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(g) + row * gs)
                             : static_cast<const void *>(static_cast<const float *>(g) + row * gs);
     float *drow = NOFB ? nullptr : delta + row * dstr;
-    const bool gvec = BF16 ? aligned8(grow) : aligned16(grow);
-    const bool dvec = aligned16(drow);
     f32x4 v[TPW];
 #pragma unroll
     for (int c = 0; c < TPW; ++c) {
         const int64_t e = (static_cast<int64_t>(blockIdx.x) * TPW + c) * kTile + threadIdx.x * 4;
-        v[c] = ld4_grad<BF16>(grow, e, P.d, gvec);
-        if constexpr (!NOFB) v[c] = v[c] + ld4_stream(drow, e, P.d, dvec);
+        v[c] = ld4_grad<BF16>(grow, e, P.d);
+        if constexpr (!NOFB) v[c] = v[c] + ld4_stream(drow, e, P.d);
     }
 #pragma unroll
     for (int c = 0; c < TPW; ++c) {
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_worker(const void *g, int64_t g
         quantise4(v[c], e, static_cast<uint32_t>(row), P, levels + row * ((P.d + 1) / 2), words + row * P.W,
                   norms + row * P.Bq, lds[c], sw_lds[c], err);
         if constexpr (!NOFB)
-            if (e < P.d) st4_stream(drow, e, P.d, dvec, err);
+            if (e < P.d) st4_stream(drow, e, P.d, err);
     }
 }
 
@@ -200,16 +202,15 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_server(const uint8_t *levels_in
     __shared__ float units[kUnitGroup * (kTile / 64)];
     const int64_t tile_base = static_cast<int64_t>(blockIdx.x) * kTile;
     const int64_t e = tile_base + threadIdx.x * 4;
-    const bool dvec = aligned16(delta_s);
     const int bpt = kTile >> P.bshift;                      // buckets per tile
     const int64_t b0 = tile_base >> P.bshift;
     const int my_b = (threadIdx.x * 4) >> P.bshift;
     const int64_t lev_stride = (P.d + 1) / 2;
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    if (delta_s) a = ld4_stream(delta_s, e, P.d, dvec);
+    if (delta_s) a = ld4_stream(delta_s, e, P.d);
     f32x4 xv = {0.f, 0.f, 0.f, 0.f}, mv = {0.f, 0.f, 0.f, 0.f};      // fetched up front, beside the error
-    if constexpr (UPD != 0) xv = ld4_stream(x, e, P.d, aligned16(x));
-    if constexpr (UPD == 2) mv = ld4_stream(m, e, P.d, aligned16(m));
+    if constexpr (UPD != 0) xv = ld4_stream(x, e, P.d);
+    if constexpr (UPD == 2) mv = ld4_stream(m, e, P.d);
     for (int i0 = 0; i0 < n; i0 += kUnitGroup) {
         const int cnt = (n - i0 < kUnitGroup) ? n - i0 : kUnitGroup;
         __syncthreads();
@@ -220,15 +221,14 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_server(const uint8_t *levels_in
         }
         __syncthreads();
         // Messages of the wavefront's 256 elements: 128 bytes of codes and 32 bytes of sign
-        // bits per worker.  Fast route (whole wavefront in range, 4-byte aligned code rows):
+        // bits per worker.  Fast route (whole wavefront in range):
         // eight workers at a time, one 32-bit load fetches the sign words of all eight
         // (lane L: word L & 7 of worker L >> 3) and four 32-bit loads fetch the codes of two
         // workers each (lane L: word L & 31 of worker L >> 5); ds_bpermute then hands every
         // lane its own nibble and 16-bit code group.  Other wavefronts load per lane.
         const int lane = lane_id();
         const int64_t wave_first = tile_base + wave_id() * 256;
-        const bool fast = (wave_first + 256 <= P.d) && ((lev_stride & 3) == 0) &&
-                          ((reinterpret_cast<uintptr_t>(levels_in) & 3u) == 0);
+        const bool fast = wave_first + 256 <= P.d;
         if (fast) {
             for (int j0 = 0; j0 < cnt; j0 += 8) {
                 const int nb = (cnt - j0 < 8) ? cnt - j0 : 8;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_server(const uint8_t *levels_in
                     const int wk = 2 * p2 + (lane >> 5);
                     cw[p2] = 0u;
                     if (wk < nb)
-                        cw[p2] = reinterpret_cast<const uint32_t *>(levels_in + (i0 + j0 + wk) * lev_stride + (wave_first >> 1))[lane & 31];
+                        cw[p2] = reinterpret_cast<const u32_byte *>(levels_in + (i0 + j0 + wk) * lev_stride + (wave_first >> 1))[lane & 31];
                 }
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -269,15 +269,15 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_server(const uint8_t *levels_in
     }
     f32x4 err;
     f32x4 q = quantise4(a, e, kServerStream, P, levels_out, words_out, norms_out, lds, sw_lds, err);
-    if (delta_s && e < P.d) st4_stream(delta_s, e, P.d, dvec, err);
+    if (delta_s && e < P.d) st4_stream(delta_s, e, P.d, err);
     if constexpr (UPD != 0) {
         if (e < P.d) {
             q = zero_past(q, e, P.d);
             if constexpr (UPD == 2) {
                 q = fma4(beta, mv, q);
-                st4_stream(m, e, P.d, aligned16(m), q);
+                st4_stream(m, e, P.d, q);
             }
-            st4_stream(x, e, P.d, aligned16(x), fma4(-gamma, q, xv));
+            st4_stream(x, e, P.d, fma4(-gamma, q, xv));
         }
     }
 }

@@ -227,7 +227,7 @@ __device__ __forceinline__ f32x4 place_kept4(float p0, float p1, float p2, float
 
 // Q[v] of the four elements of a thread, the message and the error.
 __device__ __forceinline__ void rs_store4(f32x4 v, uint32_t nib, const Ranks &rk, uint32_t base, int64_t e, int64_t d,
-                                          float *__restrict__ vals_row, float *__restrict__ err_row, bool err_vec, float p)
+                                          float *__restrict__ vals_row, float *__restrict__ err_row, float p)
 {
     const f32x4 q = {(nib & 1u) ? v.x / p : 0.f, (nib & 2u) ? v.y / p : 0.f, (nib & 4u) ? v.z / p : 0.f,
                      (nib & 8u) ? v.w / p : 0.f};
@@ -237,7 +237,7 @@ __device__ __forceinline__ void rs_store4(f32x4 v, uint32_t nib, const Ranks &rk
     if (nib & 2u) out[r++] = q.y;
     if (nib & 4u) out[r++] = q.z;
     if (nib & 8u) out[r++] = q.w;
-    if (e < d) st4_stream(err_row, e, d, err_vec, v - q);
+    if (e < d) st4_stream(err_row, e, d, v - q);
 }
 
 // Algorithm 1, worker block.
@@ -253,12 +253,10 @@ __global__ __launch_bounds__(kBlock) void k_rs_worker(const void *g, int64_t gs,
     const void *grow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(g) + row * gs)
                             : static_cast<const void *>(static_cast<const float *>(g) + row * gs);
     float *drow = delta + row * dstr;
-    const bool gvec = BF16 ? aligned8(grow) : aligned16(grow);
-    const bool dvec = aligned16(drow);
-    const f32x4 v = ld4_grad<BF16>(grow, e, d, gvec) + ld4_stream(drow, e, d, dvec);
+    const f32x4 v = ld4_grad<BF16>(grow, e, d) + ld4_stream(drow, e, d);
     const uint32_t nib = (e < d) ? load_sign_nibble(words + row * W, e) : 0u;   // written by k_rs_counts: no bits past d
     const Ranks rk = subtile_ranks(nib);
-    rs_store4(v, nib, rk, off[row * (n_sub + 1) + sub], e, d, vals + static_cast<int64_t>(row) * d, drow, dvec, p);
+    rs_store4(v, nib, rk, off[row * (n_sub + 1) + sub], e, d, vals + static_cast<int64_t>(row) * d, drow, p);
 }
 
 // Parameter-server block: v = delta_s + (1/n) sum_i Q[v_i] as the chain acc = fma(q_i, 1/n, acc)
@@ -275,8 +273,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_server(const uint64_t *words_in, 
     const int64_t wave_first = base + wave_id() * kSub;
     const int64_t sub = wave_first >> 8;
     if (sub >= n_sub) return;                               // whole wavefronts
-    const bool dvec = aligned16(delta_s);
-    f32x4 a = ld4_stream(delta_s, e, d, dvec);
+    f32x4 a = ld4_stream(delta_s, e, d);
     {
         for (int i0 = 0; i0 < n; i0 += 8) {
             const int nb = (n - i0 < 8) ? n - i0 : 8;
@@ -324,7 +321,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_server(const uint64_t *words_in, 
     }
     const uint32_t nib = (e < d) ? load_sign_nibble(words_out, e) : 0u;         // written by k_rs_counts
     const Ranks rk = subtile_ranks(nib);
-    rs_store4(a, nib, rk, off_out[sub], e, d, vals_out, delta_s, dvec, p);
+    rs_store4(a, nib, rk, off_out[sub], e, d, vals_out, delta_s, p);
 }
 
 // Model update / decoder from one message.  SPARSE (plain update, small p): only the kept

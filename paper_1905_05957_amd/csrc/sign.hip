@@ -118,7 +118,7 @@ __device__ __forceinline__ f32x4 sign_error4(f32x4 v, float s)
 // Common tail: scale from the held values, sign plane, error, stores.
 template <bool RMS>
 __device__ __forceinline__ float fused_finish(f32x4 v, int64_t base, int64_t lim,
-                                             float *__restrict__ err_row, bool err_vec,
+                                             float *__restrict__ err_row,
                                              uint64_t *__restrict__ words_row, int64_t bit_lim,
                                              float *__restrict__ scale_out, double *lds, uint32_t *sw_lds)
 {
@@ -129,7 +129,7 @@ __device__ __forceinline__ float fused_finish(f32x4 v, int64_t base, int64_t lim
     if (threadIdx.x == 0) *scale_out = scale;
     flush_sign_words(sw_lds, words_row, base, bit_lim);
     const int64_t e = base + threadIdx.x * 4;
-    if (err_row && e < lim) st4_stream(err_row, e, lim, err_vec, sign_error4(v, scale));   // no buffer: no compensation
+    if (err_row && e < lim) st4_stream(err_row, e, lim, sign_error4(v, scale));   // no buffer: no compensation
     return scale;
 }
 
@@ -149,8 +149,6 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_worker(WorkerSrc<BF16> sr
     const int row = blockIdx.y;
     const void *grow = src.grow(row);
     float *drow = NOFB ? nullptr : delta + row * src.delta_stride;
-    const bool gvec = BF16 ? aligned8(grow) : aligned16(grow);
-    const bool dvec = aligned16(drow);
     f32x4 v[CPW];
     int64_t base[CPW], lim[CPW];
 #pragma unroll
@@ -159,14 +157,14 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_worker(WorkerSrc<BF16> sr
         base[c] = ci * chunk;
         lim[c] = (base[c] + chunk < d) ? base[c] + chunk : d;     // base >= d: empty chunk, lim < base
         const int64_t e = base[c] + threadIdx.x * 4;
-        v[c] = ld4_grad<BF16>(grow, e, lim[c], gvec);
-        if constexpr (!NOFB) v[c] = v[c] + ld4_stream(drow, e, lim[c], dvec);
+        v[c] = ld4_grad<BF16>(grow, e, lim[c]);
+        if constexpr (!NOFB) v[c] = v[c] + ld4_stream(drow, e, lim[c]);
     }
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
         const int64_t ci = static_cast<int64_t>(blockIdx.x) * CPW + c;
         if (base[c] < d)    // uniform over the workgroup
-            fused_finish<RMS>(v[c], base[c], lim[c], drow, dvec, words + row * W, (lim[c] == d) ? W * 64 : lim[c],
+            fused_finish<RMS>(v[c], base[c], lim[c], drow, words + row * W, (lim[c] == d) ? W * 64 : lim[c],
                               scales + row * S + ci, lds[c], sw_lds[c]);
     }
 }
@@ -183,7 +181,6 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_server(ServerArgs a, floa
 {
     __shared__ double lds[CPW][kWaves];
     __shared__ __attribute__((aligned(16))) uint32_t sw_lds[CPW][kWaves * 8];
-    const bool dvec = aligned16(delta_s);
     const int lane = lane_id();
     f32x4 v[CPW];
     int64_t base[CPW], lim[CPW];
@@ -192,15 +189,15 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_server(ServerArgs a, floa
         const int64_t ci = static_cast<int64_t>(blockIdx.x) * CPW + c;
         base[c] = ci * chunk;
         lim[c] = (base[c] + chunk < d) ? base[c] + chunk : d;     // base >= d: empty chunk, lim < base
-        v[c] = delta_s ? ld4_stream(delta_s, base[c] + threadIdx.x * 4, lim[c], dvec) : f32x4{0.f, 0.f, 0.f, 0.f};   // no buffer: no server error
+        v[c] = delta_s ? ld4_stream(delta_s, base[c] + threadIdx.x * 4, lim[c]) : f32x4{0.f, 0.f, 0.f, 0.f};   // no buffer: no server error
     }
     // the update's operands are fetched up front, beside the error: more bytes in flight
     f32x4 xv[CPW], mv[CPW];
     if constexpr (UPD != 0) {
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
-            xv[c] = ld4_stream(x, base[c] + threadIdx.x * 4, lim[c], aligned16(x));
-            if constexpr (UPD == 2) mv[c] = ld4_stream(m, base[c] + threadIdx.x * 4, lim[c], aligned16(m));
+            xv[c] = ld4_stream(x, base[c] + threadIdx.x * 4, lim[c]);
+            if constexpr (UPD == 2) mv[c] = ld4_stream(m, base[c] + threadIdx.x * 4, lim[c]);
         }
     }
     // The wavefront's 256 elements are 32 bytes of each worker's sign plane.  Eight workers at
@@ -251,7 +248,7 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_server(ServerArgs a, floa
         // components past lim must stay zero: they count in the sum of |v|
         v[c] = zero_past(v[c], base[c] + threadIdx.x * 4, lim[c]);
         if (base[c] < d) {   // uniform over the workgroup
-            const float s = fused_finish<RMS>(v[c], base[c], lim[c], delta_s, dvec, words_out,
+            const float s = fused_finish<RMS>(v[c], base[c], lim[c], delta_s, words_out,
                                               (lim[c] == d) ? a.W * 64 : lim[c], scales_out + ci, lds[c], sw_lds[c]);
             if constexpr (UPD != 0) {
                 // q = decode of the message just written: bit ? -scale : +scale, bit = (v < 0)
@@ -260,9 +257,9 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_server(ServerArgs a, floa
                     f32x4 q = {(v[c].x < 0.f) ? -s : s, (v[c].y < 0.f) ? -s : s, (v[c].z < 0.f) ? -s : s, (v[c].w < 0.f) ? -s : s};
                     if constexpr (UPD == 2) {
                         q = fma4(beta, mv[c], q);
-                        st4_stream(m, e, lim[c], aligned16(m), q);
+                        st4_stream(m, e, lim[c], q);
                     }
-                    st4_stream(x, e, lim[c], aligned16(x), fma4(-gamma, q, xv[c]));
+                    st4_stream(x, e, lim[c], fma4(-gamma, q, xv[c]));
                 }
             }
         }
@@ -333,15 +330,15 @@ __device__ __forceinline__ f32x4 sign_error_tile(f32x4 v, int64_t e, int64_t d, 
 // read again in this call (deferred error form), so it leaves non-temporally.
 template <bool RMS, bool STREAM, bool KEEP = true>   // KEEP = false: v is not stored (no compensation: it is not needed again)
 __device__ __forceinline__ void pass1_finish(f32x4 v, int64_t base, int64_t d,
-                                             float *__restrict__ vrow, bool vvec,
+                                             float *__restrict__ vrow,
                                              uint64_t *__restrict__ words_row, int64_t bit_lim,
                                              const ds_sign_tables &tb, int32_t p0, int32_t p1,
                                              double *__restrict__ partial_row, double *lds, uint32_t *sw_lds)
 {
     const int64_t e = base + threadIdx.x * 4;
     if (KEEP && vrow && e < d) {             // no buffer: no compensation either
-        if constexpr (STREAM) st4_stream(vrow, e, d, vvec, v);
-        else st4(vrow, e, d, vvec, v);
+        if constexpr (STREAM) st4_stream(vrow, e, d, v);
+        else st4(vrow, e, d, v);
     }
     stash_sign_words(sw_lds, wave_sign_word(v.x < 0.f, v.y < 0.f, v.z < 0.f, v.w < 0.f));
     if (p1 - p0 == 1) {
@@ -380,18 +377,16 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass1_worker(WorkerSrc<BF16> sr
     const void *grow = src.grow(row);
     constexpr bool DEFERRED = MODE == 1, NOFB = MODE == 2;
     float *drow = NOFB ? nullptr : delta + row * src.delta_stride;
-    const bool gvec = BF16 ? aligned8(grow) : aligned16(grow);
-    const bool dvec = aligned16(drow);
     const int64_t e = base + threadIdx.x * 4;
     const TilePieces tp = tile_pieces(tb, tile);
     const int32_t p0 = tp.p0, p1 = tp.p1;
-    f32x4 v = ld4_grad<BF16>(grow, e, d, gvec);
+    f32x4 v = ld4_grad<BF16>(grow, e, d);
     if constexpr (!NOFB) {
-        f32x4 dl = DEFERRED ? ld4_stream(drow, e, d, dvec) : ld4(drow, e, d, dvec);
+        f32x4 dl = DEFERRED ? ld4_stream(drow, e, d) : ld4(drow, e, d);
         if (DEFERRED && e < d) dl = zero_past(sign_error_tile(dl, e, d, prev_scales + row * S, tb, p0, p1, tp.seg0), e, d);
         v = v + dl;
     }
-    pass1_finish<RMS, DEFERRED, !NOFB>(v, base, d, drow, dvec, words + row * W, W * 64, tb, p0, p1,
+    pass1_finish<RMS, DEFERRED, !NOFB>(v, base, d, drow, words + row * W, W * 64, tb, p0, p1,
                       partials + static_cast<int64_t>(row) * tb.n_pieces, lds, sw_lds);
 }
 
@@ -405,12 +400,11 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass1_server(ServerArgs a, floa
     __shared__ __attribute__((aligned(16))) uint32_t sw_lds[kWaves * 8];
     const int64_t tile = blockIdx.x;
     const int64_t base = tile * kTile;
-    const bool dvec = aligned16(delta_s);
     const TilePieces tp = tile_pieces(tb, tile);
     const int32_t p0 = tp.p0, p1 = tp.p1;
     const int64_t e = base + threadIdx.x * 4;
     f32x4 v = {0.f, 0.f, 0.f, 0.f};                                      // no buffer: no server error
-    if (delta_s) v = STREAM ? ld4_stream(delta_s, e, d, dvec) : ld4(delta_s, e, d, dvec);
+    if (delta_s) v = STREAM ? ld4_stream(delta_s, e, d) : ld4(delta_s, e, d);
     const int lane = lane_id();
     const int64_t wave_first = base + wave_id() * 256;
     // sign words of the first eight workers (lane L: word L & 7 of worker L >> 3): their
@@ -468,7 +462,7 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass1_server(ServerArgs a, floa
         }
     }
     v = zero_past(v, e, d);
-    pass1_finish<RMS, STREAM>(v, base, d, delta_s, dvec, words_out, a.W * 64, tb, p0, p1, partials, lds, sw_lds);
+    pass1_finish<RMS, STREAM>(v, base, d, delta_s, words_out, a.W * 64, tb, p0, p1, partials, lds, sw_lds);
 }
 
 // scale[row][s] = (float)( sum of the group's partials / |group| ), fixed order.
@@ -505,12 +499,11 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t strid
     const int64_t tile = gridDim.x - 1 - blockIdx.x;
     float *brow = buf + row * stride;
     const float *srow = scales + row * S;
-    const bool vec = aligned16(brow);
     const TilePieces tp = tile_pieces(tb, tile);
     const int64_t e = tile * kTile + threadIdx.x * 4;
     if (e >= d) return;
-    const f32x4 v = ld4_stream(brow, e, d, vec);
-    st4_stream(brow, e, d, vec, sign_error_tile(v, e, d, srow, tb, tp.p0, tp.p1, tp.seg0));
+    const f32x4 v = ld4_stream(brow, e, d);
+    st4_stream(brow, e, d, sign_error_tile(v, e, d, srow, tb, tp.p0, tp.p1, tp.seg0));
 }
 
 template <bool MOM, bool DECODE_ONLY, bool STREAM>
@@ -525,11 +518,10 @@ __global__ __launch_bounds__(kBlock) void k_sign_update(const uint64_t *__restri
     if (e >= d) return;
     // the model (and momentum) words leave before the scale that the table entry leads to is
     // waited for
-    const bool xvec = aligned16(x), mvec = aligned16(m);
     f32x4 xv = {0.f, 0.f, 0.f, 0.f}, mv = xv;
     if constexpr (!DECODE_ONLY) {
-        xv = STREAM ? ld4_stream(x, e, d, xvec) : ld4(x, e, d, xvec);
-        if constexpr (MOM) mv = STREAM ? ld4_stream(m, e, d, mvec) : ld4(m, e, d, mvec);
+        xv = STREAM ? ld4_stream(x, e, d) : ld4(x, e, d);
+        if constexpr (MOM) mv = STREAM ? ld4_stream(m, e, d) : ld4(m, e, d);
     }
     const uint32_t nib = load_sign_nibble(words, e);
     float q[4];
@@ -543,15 +535,15 @@ __global__ __launch_bounds__(kBlock) void k_sign_update(const uint64_t *__restri
     }
     f32x4 qv = signed4(q[0], q[1], q[2], q[3], nib);
     if constexpr (DECODE_ONLY) {
-        st4_stream(x, e, d, xvec, qv);             // a decoded message: written once, read by the caller
+        st4_stream(x, e, d, qv);             // a decoded message: written once, read by the caller
     } else {
         if constexpr (MOM) {                       // m <- beta m + q ; x <- x - gamma m
             qv = fma4(beta, mv, qv);
-            if constexpr (STREAM) st4_stream(m, e, d, mvec, qv);
-            else st4(m, e, d, mvec, qv);
+            if constexpr (STREAM) st4_stream(m, e, d, qv);
+            else st4(m, e, d, qv);
         }
-        if constexpr (STREAM) st4_stream(x, e, d, xvec, fma4(-gamma, qv, xv));
-        else st4(x, e, d, xvec, fma4(-gamma, qv, xv));
+        if constexpr (STREAM) st4_stream(x, e, d, fma4(-gamma, qv, xv));
+        else st4(x, e, d, fma4(-gamma, qv, xv));
     }
 }
 

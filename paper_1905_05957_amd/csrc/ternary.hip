@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kBlock) void k_tern_stats(const void *g, int64_t gs
     const int row = blockIdx.y;
     const int64_t e = static_cast<int64_t>(blockIdx.x) * kTile + threadIdx.x * 4;
     const void *grow = grad_row<BF16>(g, gs, row);
-    const f32x4 v = ld4_grad<BF16>(grow, e, d, BF16 ? aligned8(grow) : aligned16(grow));   // zero past d
+    const f32x4 v = ld4_grad<BF16>(grow, e, d);   // zero past d
     const float a0 = fabsf(v.x), a1 = fabsf(v.y), a2 = fabsf(v.z), a3 = fabsf(v.w);
     float m = fmaxf(fmaxf(a0, a1), fmaxf(a2, a3));
 #pragma unroll
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kBlock) void k_tern_encode(const void *g, int64_t g
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kTile;
     const int64_t e = base + threadIdx.x * 4;
     const void *grow = grad_row<BF16>(g, gs, row);
-    const f32x4 v = ld4_grad<BF16>(grow, e, d, BF16 ? aligned8(grow) : aligned16(grow));
+    const f32x4 v = ld4_grad<BF16>(grow, e, d);
     const float m = rowmax[row];
     bool keep[4] = {false, false, false, false};
     if (e < d && m > 0.f) {
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kBlock) void k_tern_decode(const uint64_t *neg_row,
 {
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
-    st4(out, e, d, aligned16(out), tern_decode4(neg_row, nz_row, scale[0], e));
+    st4(out, e, d, tern_decode4(neg_row, nz_row, scale[0], e));
 }
 
 unsigned blocks4(int64_t d) { return static_cast<unsigned>((d + kBlock * 4 - 1) / (kBlock * 4)); }

@@ -120,7 +120,7 @@ struct WorkerV {   // v = g + delta
         const void *grow = BF16 ? static_cast<const void *>(static_cast<const uint16_t *>(g) + row * gs)
                                 : static_cast<const void *>(static_cast<const float *>(g) + row * gs);
         const float *drow = delta + row * dstr;
-        return ld4_grad<BF16>(grow, e, d, BF16 ? aligned8(grow) : aligned16(grow)) + ld4_stream(drow, e, d, aligned16(drow));
+        return ld4_grad<BF16>(grow, e, d) + ld4_stream(drow, e, d);
     }
 };
 
@@ -132,7 +132,7 @@ struct GradV {     // v = g: Algorithm 1 without compensation (fp32 gradients)
     __device__ __forceinline__ f32x4 load(int row, int64_t e, int64_t d, float *) const
     {
         const float *grow = g + row * gs;
-        return ld4_stream(grow, e, d, aligned16(grow));
+        return ld4_stream(grow, e, d);
     }
 };
 
@@ -144,7 +144,7 @@ struct BufferV {   // v already stored
     __device__ __forceinline__ f32x4 load(int row, int64_t e, int64_t d, float *) const
     {
         const float *brow = buf + row * stride;
-        return ld4(brow, e, d, aligned16(brow));
+        return ld4(brow, e, d);
     }
 };
 
@@ -175,7 +175,7 @@ struct ServerV {
     {
         const int lane = lane_id();
         uint32_t *tag = reinterpret_cast<uint32_t *>(strip + kSub);
-        const f32x4 a = ld4(delta_s, e, d, aligned16(delta_s));
+        const f32x4 a = ld4(delta_s, e, d);
         strip[lane * 4 + 0] = a.x; strip[lane * 4 + 1] = a.y; strip[lane * 4 + 2] = a.z; strip[lane * 4 + 3] = a.w;
         const int64_t sub = e >> 8;
         const uint32_t base = static_cast<uint32_t>(sub << 8);
@@ -487,7 +487,7 @@ __device__ __forceinline__ void pass1_tile_v(f32x4 v, float *buf, int64_t stride
     // the few candidates that are not kept instead of zeroing every kept position.
     if (WR && e < d) {
         float *brow = buf + row * stride;
-        st4_stream(brow, e, d, aligned16(brow), f32x4{f[0] ? 0.f : v.x, f[1] ? 0.f : v.y, f[2] ? 0.f : v.z, f[3] ? 0.f : v.w});
+        st4_stream(brow, e, d, f32x4{f[0] ? 0.f : v.x, f[1] ? 0.f : v.y, f[2] ? 0.f : v.z, f[3] ? 0.f : v.w});
     }
     // index-ordered compaction over the workgroup: ballots inside a wavefront, wavefront
     // totals through LDS
@@ -572,7 +572,6 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass1_server(ServerV src, float
     for (int i = lane; i < kTags; i += 64) tag[i] = kNone;
     const int64_t span_base = (static_cast<int64_t>(blockIdx.x) * kWaves + wv) * kSpan;
     const uint32_t lo_key = SID ? 0u : sel[0].lo_key;
-    const bool vec = aligned16(buf);
     const bool live = span_base < d;                       // uniform over the wavefront
     const int64_t sub0 = span_base >> 8;
     const int64_t sub1 = (sub0 + 4 < src.n_sub) ? sub0 + 4 : src.n_sub;
@@ -644,7 +643,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass1_server(ServerV src, float
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         v[c] = SID ? f32x4{0.f, 0.f, 0.f, 0.f}
-                   : ld4_stream(src.delta_s, span_base + c * kSub + lane * 4, d, aligned16(src.delta_s));
+                   : ld4_stream(src.delta_s, span_base + c * kSub + lane * 4, d);
     Ranges r = make_ranges(0, b0, b1);
     bool valid0 = false;
     u32x2 pr0 = {0u, 0u};
@@ -694,7 +693,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_pass1_server(ServerV src, float
 #pragma unroll
         for (int j = 0; j < 4; ++j) f[c][j] = (e + j < d) && (bits[c][j] & 0x7FFFFFFFu) >= lo_key;
         if (e < d)
-            st4_stream(buf, e, d, vec, f32x4{f[c][0] ? 0.f : v[c].x, f[c][1] ? 0.f : v[c].y, f[c][2] ? 0.f : v[c].z,
+            st4_stream(buf, e, d, f32x4{f[c][0] ? 0.f : v[c].x, f[c][1] ? 0.f : v[c].y, f[c][2] ? 0.f : v[c].z,
                                      f[c][3] ? 0.f : v[c].w});
         const uint64_t m0 = __ballot(f[c][0]), m1 = __ballot(f[c][1]), m2 = __ballot(f[c][2]), m3 = __ballot(f[c][3]);
         before[c] = lanes_below(m0) + lanes_below(m1) + lanes_below(m2) + lanes_below(m3);
@@ -733,11 +732,10 @@ __global__ __launch_bounds__(kBlock) void k_topk_fallback_hist(const float *buf,
     for (int i = threadIdx.x; i < kH1; i += kBlock) h[i] = 0u;
     __syncthreads();
     const float *brow = buf + row * stride;
-    const bool vec = aligned16(brow);
     for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
         const int64_t e = tile * kTile + threadIdx.x * 4;
         if (e >= d) continue;
-        const f32x4 v = ld4(brow, e, d, vec);
+        const f32x4 v = ld4(brow, e, d);
         if (e + 0 < d) atomicAdd(&h[key_of(v.x) >> 19], 1u);
         if (e + 1 < d) atomicAdd(&h[key_of(v.y) >> 19], 1u);
         if (e + 2 < d) atomicAdd(&h[key_of(v.z) >> 19], 1u);
@@ -1279,7 +1277,6 @@ __global__ __launch_bounds__(kBlock, 8) void k_topk_finish(FinishArgs a)
         __syncthreads();
         for (int i = threadIdx.x; i < kH1; i += kBlock) h[i] = 0u;
         __syncthreads();
-        const bool vec = aligned16(brow);
         for (int64_t tile = blockIdx.x; tile < a.n_reg; tile += G) {
             const uint32_t cnt = cnt_row[tile];
             const u32x2 *src = srow + tile * kReg;
@@ -1289,7 +1286,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_topk_finish(FinishArgs a)
             __syncthreads();
             const int64_t e = tile * kTile + threadIdx.x * 4;
             if (e < a.d) {
-                const f32x4 v = ld4(brow, e, a.d, vec);
+                const f32x4 v = ld4(brow, e, a.d);
                 if (e + 0 < a.d) atomicAdd(&h[key_of(v.x) >> 19], 1u);
                 if (e + 1 < a.d) atomicAdd(&h[key_of(v.y) >> 19], 1u);
                 if (e + 2 < a.d) atomicAdd(&h[key_of(v.z) >> 19], 1u);
