@@ -167,7 +167,11 @@ typedef struct {
     int32_t topk_spin_limit;  /* TOPK single launch: polls a workgroup spends on one wait before it
                                  gives up; 0 = the default (about 4 million, seconds); -1 = none
                                  (every wait that is not satisfied at once fails: a host-forced
-                                 failure for tests of the error path, every kernel still exits) */
+                                 failure for tests of the error path, every kernel still exits).
+                                 Where another compressor's workgroups wait for each other inside a
+                                 launch (a worker block with one value per vector), -1 makes them
+                                 give up at once too; the launch after it then completes the
+                                 work, with the same results */
 } ds_config_t;
 
 typedef struct ds_ctx ds_ctx_t;

@@ -240,9 +240,9 @@ __device__ __forceinline__ uint32_t wave_sign_word(bool n0, bool n1, bool n2, bo
     return w;
 }
 
-// Every wavefront deposits its eight words in `sw_lds` (64 words, 16-byte aligned) with stash_sign_words BEFORE a workgroup barrier; AFTER it, flush_sign_words writes
-// the tile's 256 bytes (tile_first = first element of the 2048-element tile) as one
-// non-temporal store of 16 x 16 bytes.  Only 128-bit groups whose first element is below
+// Every wavefront deposits its eight words in `sw_lds` (64 words, 16-byte aligned) with
+// stash_sign_words BEFORE a workgroup barrier; AFTER it, flush_sign_words writes the tile's 256
+// bytes (tile_first = first element of the 2048-element tile) as one store of 16 x 16 bytes.  Only 128-bit groups whose first element is below
 // `bit_lim` are written; bit_lim is a multiple of 64: the end of the caller's chunk, or
 // 64*ceil(d/64) at the end of the row so that the pad bits of the last word are written as zero.
 // Measured on the fused sign worker pass while the error buffer was still accessed with
@@ -256,11 +256,11 @@ __device__ __forceinline__ void stash_sign_words(uint32_t *sw_lds, uint32_t word
     if ((lane_id() & 7) == 0) sw_lds[wave_id() * 8 + (lane_id() >> 3)] = word;
 }
 
-__device__ __forceinline__ void flush_sign_words(const uint32_t *sw_lds, uint64_t *__restrict__ words_row,
-                                                 int64_t tile_first, int64_t bit_lim)
+// Thread t < 16 of the 16 that write one tile's words.
+__device__ __forceinline__ void flush_sign_words_at(const uint32_t *sw_lds, uint64_t *__restrict__ words_row,
+                                                    int64_t tile_first, int64_t bit_lim, int t)
 {
-    const int t = threadIdx.x;
-    if (t < 16 && tile_first + 128 * t < bit_lim) {
+    if (tile_first + 128 * t < bit_lim) {
         uint32_t *dst = reinterpret_cast<uint32_t *>(words_row) + (tile_first >> 5) + 4 * t;
         const u32x4 w4 = reinterpret_cast<const u32x4 *>(sw_lds)[t];
         if (tile_first + 128 * (t + 1) <= bit_lim) {
@@ -270,6 +270,12 @@ __device__ __forceinline__ void flush_sign_words(const uint32_t *sw_lds, uint64_
             dst[1] = w4.y;
         }
     }
+}
+
+__device__ __forceinline__ void flush_sign_words(const uint32_t *sw_lds, uint64_t *__restrict__ words_row,
+                                                 int64_t tile_first, int64_t bit_lim)
+{
+    if (threadIdx.x < 16) flush_sign_words_at(sw_lds, words_row, tile_first, bit_lim, threadIdx.x);
 }
 
 // The four sign bits of elements e..e+3 (e a multiple of 4) read from a sign plane.
@@ -319,6 +325,32 @@ __device__ __forceinline__ f32x4 fma4(float a, f32x4 b, f32x4 c)
 {
     return f32x4{__fmaf_rn(a, b.x, c.x), __fmaf_rn(a, b.y, c.y), __fmaf_rn(a, b.z, c.z), __fmaf_rn(a, b.w, c.w)};
 }
+
+// DevShared<T> is the type of every word that workgroups of ONE launch hand to each other
+// (histograms, group counts, arrival counters, published picks): it offers device-scope
+// operations only, so a plain load or store on that path does not compile.  The memory is
+// allocated and cleared as plain words by the host and by other launches (a launch boundary
+// makes those visible); `as_shared` is the one place where such a pointer becomes typed.
+template <class T>
+class DevShared {
+    T w_;
+
+public:
+    DevShared() = delete;
+    __device__ __forceinline__ T load() const { return __hip_atomic_load(&w_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void store(T v) { __hip_atomic_store(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ T fetch_add(T v) { return __hip_atomic_fetch_add(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void add(T v) { (void)__hip_atomic_fetch_add(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    // Plain store of zero, for the one case where the word is dead for the rest of this launch
+    // (nothing of it reads or adds to it any more) and the next launch expects it cleared.
+    __device__ __forceinline__ void clear_for_next_launch() { w_ = T(0); }
+};
+using DevWord = DevShared<uint32_t>;
+using DevWord64 = DevShared<uint64_t>;
+static_assert(sizeof(DevWord) == 4 && sizeof(DevWord64) == 8, "a shared word is just the word");
+
+template <class T>
+__host__ __device__ __forceinline__ DevShared<T> *as_shared(T *p) { return reinterpret_cast<DevShared<T> *>(p); }
 
 // Tail shared by every update kernel (Algorithm 1, last worker block), q = decoded
 // server message for elements e..e+3:

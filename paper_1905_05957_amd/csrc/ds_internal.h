@@ -57,6 +57,10 @@ struct ds_ctx {
     bool sign_s_deferred;  // the same for the server's buffer and sign_prev_s
     float *sign_prev_w;    // [n, S]
     float *sign_prev_s;    // [S]
+    int held_T;            // tiles per workgroup of the held route, 0 = not taken
+    void *held_rows;       // [n] synchronisation words (HeldRow in sign.hip)
+    uint32_t *held_gave_up; // [n, workgroups per row] written by every held launch
+    uint32_t held_patience; // ticks of the 100 MHz clock a workgroup waits at most
     // TOPK
     ds_topk_scratch *topk;
     // RSPARSE

@@ -231,32 +231,6 @@ struct ServerV {
 // write-back or invalidation is needed -- an agent-scope fence per workgroup costs a full L2
 // write-back on this GPU and tripled the step time when tried.
 //
-// DevShared<T> is the type of every word that workgroups of ONE launch hand to each other
-// (histograms, group counts, arrival counters, published picks): it offers device-scope
-// operations only, so a plain load or store on that path does not compile.  The memory is
-// allocated and cleared as plain words by the host and by other launches (a launch boundary
-// makes those visible); `as_shared` is the one place where such a pointer becomes typed.
-template <class T>
-class DevShared {
-    T w_;
-
-public:
-    DevShared() = delete;
-    __device__ __forceinline__ T load() const { return __hip_atomic_load(&w_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    __device__ __forceinline__ void store(T v) { __hip_atomic_store(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    __device__ __forceinline__ T fetch_add(T v) { return __hip_atomic_fetch_add(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    __device__ __forceinline__ void add(T v) { (void)__hip_atomic_fetch_add(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    // Plain store of zero, for the one case where the word is dead for the rest of this launch
-    // (nothing of it reads or adds to it any more) and the next launch expects it cleared.
-    __device__ __forceinline__ void clear_for_next_launch() { w_ = T(0); }
-};
-using DevWord = DevShared<uint32_t>;
-using DevWord64 = DevShared<uint64_t>;
-static_assert(sizeof(DevWord) == 4 && sizeof(DevWord64) == 8, "a shared word is just the word");
-
-template <class T>
-__host__ __device__ __forceinline__ DevShared<T> *as_shared(T *p) { return reinterpret_cast<DevShared<T> *>(p); }
-
 // True in exactly one workgroup of those that call it with the same counter: the last of
 // `expected` to arrive.  Every wavefront first waits until the memory system has acknowledged
 // its own outstanding atomics and stores (an explicit wait on the vector memory counter: a

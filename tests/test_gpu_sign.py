@@ -7,6 +7,7 @@ import torch
 
 import ds_workloads as W
 import oracle as O
+import paper_1905_05957_amd as P
 from parity_util import Pair, assert_close_rows
 
 pytestmark = pytest.mark.gpu
@@ -231,3 +232,41 @@ def test_sign_deferred_error_against_oracle(gpu_device):
         assert_close_rows(pair.x.cpu().numpy(), h_x, "deferred x")
     finally:
         pair.close()
+
+
+# One look at rows whose scale spans workgroups: rows that one workgroup holds (1, 2, 4, 8, 14, 24 tiles), the
+# sizes of several workgroups per row, the ends of tiles and rows (d mod 4), on rows that do not
+# start at 16-byte boundaries, with a sentinel behind every row.  The reference is the two-look
+# form of the same block, whose sums are taken in the same order: equal bit for bit.
+# `patience` -1 makes every workgroup that would have to wait give up, so that the finish launch
+# forms its errors.
+@pytest.mark.parametrize("patience", [0, -1])
+@pytest.mark.parametrize("n,d,dtype,rms", [
+    (3, 2047, torch.float32, False), (2, 2049, torch.float32, True), (2, 4 * 2048 - 3, torch.bfloat16, False),
+    (2, 8 * 2048 + 1, torch.float32, False), (2, 14 * 2048, torch.bfloat16, True), (2, 24 * 2048 - 2, torch.float32, False),
+    (2, 25 * 2048 + 3, torch.float32, False), (5, 300_001, torch.bfloat16, False), (8, 700_002, torch.float32, True),
+    (9, 1_800_003, torch.float32, False), (9, 2_600_001, torch.bfloat16, False), (3, 9_000_005, torch.float32, False),
+    (3, 9_000_006, torch.bfloat16, True)])
+def test_sign_whole_vector_in_one_look(gpu_device, n, d, dtype, rms, patience):
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(d)
+    stride = d + 5
+    flags = P.FLAG_SIGN_RMS if rms else 0
+    g = torch.randn((n, stride), device=gpu_device, generator=gen).mul_(1e-2).to(dtype)[:, :d]
+    ctx = P.Context("sign", n, d, grad_dtype="bf16" if dtype == torch.bfloat16 else "f32", scale_mode="whole",
+                    flags=flags, topk_spin_limit=patience)
+    try:
+        held = torch.randn((n, stride), device=gpu_device, generator=gen).mul_(1e-3)
+        held[:, d:] = 77.0
+        want = held.clone()
+        msg = ctx.alloc_payload(n, gpu_device)
+        words, scales = torch.zeros_like(msg.sign_words), torch.zeros_like(msg.scales)
+        for _ in range(3):                   # the second and third call see what the first left behind
+            ctx.worker_compress(0, g, held[:, :d], msg)
+            P.ds_worker_compress_sign_noalloc(g, want[:, :d], words, scales, flags=flags)
+            torch.cuda.synchronize()
+            assert torch.equal(msg.sign_words, words)
+            assert torch.equal(msg.scales, scales)
+            assert torch.equal(held, want)
+    finally:
+        ctx.close()
