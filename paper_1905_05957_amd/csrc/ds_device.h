@@ -229,15 +229,20 @@ __device__ __forceinline__ uint32_t spread4(uint32_t x)   // bit i of the low by
 // = bit j & 31 of word j >> 5), word q from lanes 8q .. 8q+7.  Every lane returns the word of
 // its own 8-lane group: the lane's four bits are shifted to their place and the eight lanes
 // are OR-ed together in three cross-lane steps.  Every lane of the wavefront must be active.
-__device__ __forceinline__ uint32_t wave_sign_word(bool n0, bool n1, bool n2, bool n3)
+__device__ __forceinline__ uint32_t wave_nibble_word(uint32_t nib)
 {
-    const uint32_t nib = static_cast<uint32_t>(n0) | (static_cast<uint32_t>(n1) << 1) |
-                         (static_cast<uint32_t>(n2) << 2) | (static_cast<uint32_t>(n3) << 3);
     uint32_t w = nib << (4 * (lane_id() & 7));
     w |= dpp_u32<kDppXor1>(w);
     w |= dpp_u32<kDppXor2>(w);
     w |= dpp_u32<kDppHalfMirror>(w);
     return w;
+}
+
+__device__ __forceinline__ uint32_t wave_sign_word(bool n0, bool n1, bool n2, bool n3)
+{
+    const uint32_t nib = static_cast<uint32_t>(n0) | (static_cast<uint32_t>(n1) << 1) |
+                         (static_cast<uint32_t>(n2) << 2) | (static_cast<uint32_t>(n3) << 3);
+    return wave_nibble_word(nib);
 }
 
 // Every wavefront deposits its eight words in `sw_lds` (64 words, 16-byte aligned) with
@@ -340,6 +345,7 @@ public:
     __device__ __forceinline__ T load() const { return __hip_atomic_load(&w_, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     __device__ __forceinline__ void store(T v) { __hip_atomic_store(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     __device__ __forceinline__ T fetch_add(T v) { return __hip_atomic_fetch_add(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void raise_to(T v) { (void)__hip_atomic_fetch_max(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     __device__ __forceinline__ void add(T v) { (void)__hip_atomic_fetch_add(&w_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
     // Plain store of zero, for the one case where the word is dead for the rest of this launch
     // (nothing of it reads or adds to it any more) and the next launch expects it cleared.

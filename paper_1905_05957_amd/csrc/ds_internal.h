@@ -31,6 +31,14 @@ struct ds_topk_scratch;  // defined in topk.hip
 struct ds_rs_scratch;    // defined in rsparse.hip
 struct ds_tern_scratch;  // defined in ternary.hip
 
+// What the workgroups of a launch that holds rows on chip share (held.h); T == 0: not taken.
+struct ds_held_sync {
+    int T, parts;          // tiles per workgroup, workgroups per row
+    void *rows;            // [n] synchronisation words (HeldRow)
+    uint32_t *gave_up;     // [n, parts] written by every such launch
+    uint32_t patience;     // ticks of the 100 MHz clock a workgroup waits at most
+};
+
 // What the update of Algorithm 1 needs when it rides along with a server kernel; x == nullptr:
 // no update.
 struct ds_update_args {
@@ -57,10 +65,7 @@ struct ds_ctx {
     bool sign_s_deferred;  // the same for the server's buffer and sign_prev_s
     float *sign_prev_w;    // [n, S]
     float *sign_prev_s;    // [S]
-    int held_T;            // tiles per workgroup of the held route, 0 = not taken
-    void *held_rows;       // [n] synchronisation words (HeldRow in sign.hip)
-    uint32_t *held_gave_up; // [n, workgroups per row] written by every held launch
-    uint32_t held_patience; // ticks of the 100 MHz clock a workgroup waits at most
+    ds_held_sync held, held_s;   // one look at rows with one scale: worker, server
     // TOPK
     ds_topk_scratch *topk;
     // RSPARSE

@@ -1,0 +1,194 @@
+// Held route: kernels that need one value per row (a scale, a maximum) before they can finish its
+// elements keep a row in registers and LDS across the workgroups of one launch instead of
+// reading it twice.  Shared pieces: the synchronisation words and the bounded wait, the addressing
+// of the held tiles, and the choice of how many tiles a workgroup holds.
+#pragma once
+#include "ds_device.h"
+#include "ds_internal.h"
+
+#include <type_traits>
+
+namespace ds {
+
+// Synchronisation words of one row; published word and counter on cache lines of their own.
+constexpr size_t kHeldRowBytes = 256;
+constexpr int kFinishParts = 64;             // workgroups of a held launch that one of the finish launch looks after
+struct HeldRow {
+    DevShared<uint64_t> pub;      // kHeldValue | bits of the row's value, 0 = not there yet
+    DevShared<uint32_t> quit;     // row 0 only: a workgroup of this call gave up, the others do not wait either
+    uint32_t pad0[29];
+    DevShared<uint32_t> arrived;
+    DevShared<uint32_t> most;     // ternary: largest |v| of the row so far, as bits
+    DevShared<uint64_t> kept;     // ternary: workgroups that have encoded << 40 | non-zero codes
+    DevShared<uint64_t> sum;      // ternary: sum of |v| over the row, fp64 bits
+    uint32_t pad1[26];
+
+    // after a launch, in the next one
+    __device__ __forceinline__ void clear_for_next_launch()
+    {
+        pub.clear_for_next_launch();
+        quit.clear_for_next_launch();
+        arrived.clear_for_next_launch();
+        most.clear_for_next_launch();
+    }
+};
+static_assert(sizeof(HeldRow) == kHeldRowBytes, "as allocated by the host");
+constexpr uint64_t kHeldValue = 1ull << 32;
+
+// The row's published value, false if it did not come in time.  Every thread of the workgroup calls.
+__device__ __forceinline__ bool held_wait(HeldRow *rows, int row, uint32_t patience, uint32_t *sh, float *s)
+{
+    if (threadIdx.x == 0) {
+        const long long t0 = wall_clock64();
+        uint64_t v;
+        for (uint32_t polls = 0;; ++polls) {
+            v = rows[row].pub.load();
+            if (v & kHeldValue) break;
+            if ((polls & 7u) == 0u) {
+                if (rows[0].quit.load() != 0u) break;
+                if (wall_clock64() - t0 >= static_cast<long long>(patience)) { rows[0].quit.store(1u); break; }
+            }
+            __builtin_amdgcn_s_sleep(8);
+        }
+        sh[0] = (v & kHeldValue) ? 1u : 0u;
+        sh[1] = static_cast<uint32_t>(v);
+    }
+    __syncthreads();
+    *s = __uint_as_float(sh[1]);
+    return sh[0] != 0u;
+}
+
+// Tile t of a workgroup's stretch of an fp32 row as a buffer: a descriptor in scalar registers and
+// one 32-bit offset per lane, the same for every tile, where 64-bit addresses would take the
+// registers that v needs.  Only the whole groups of four elements of the row lie inside the
+// buffer: a lane past them reads zero and stores nothing, and the one to three elements of a
+// last cut group are the caller's.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t held_tile(const float *first, int left, int t)
+{
+    const int whole = (left & ~3) - t * kTile;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(first + t * kTile), 0, (whole > 0 ? whole : 0) * 4, 0x00027000);
+}
+
+constexpr int kNonTemporal = 2;   // cache policy operand of the buffer instructions
+
+__device__ __forceinline__ f32x4 held_ld4(const float *first, int left, int t)
+{
+    const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, kNonTemporal);
+    return f32x4{__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
+}
+
+__device__ __forceinline__ void held_st4(float *first, int left, int t, f32x4 v)
+{
+    const u32x4 u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(u, held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, kNonTemporal);
+}
+
+// Four gradients of tile t, zero past the row's last whole group of four.
+template <bool BF16>
+__device__ __forceinline__ f32x4 held_g4(const void *grow, int64_t first, int left, int t)
+{
+    if constexpr (BF16) return ld4_bf16(static_cast<const uint16_t *>(grow), first + t * kTile + threadIdx.x * 4, first + (left & ~3));
+    else return held_ld4(static_cast<const float *>(grow) + first, left, t);
+}
+
+// Between the phases of a held kernel: the compiler must not carry what it derived from v in one
+// phase (sign masks, addresses) into the next in registers that v itself needs.
+template <int T>
+__device__ __forceinline__ void held_fence(f32x4 (&v)[T], int &left)
+{
+    asm volatile("" : "+s"(left));
+#pragma unroll
+    for (int t = 0; t < T; ++t) asm volatile("" : "+v"(v[t]));
+}
+
+// Elements of the row from the first one of the workgroup on, as far as they matter to it.
+template <int T>
+__device__ __forceinline__ int held_left(int64_t tile0, int64_t d)
+{
+    const int64_t left = d - tile0 * kTile;
+    return left < T * kTile ? static_cast<int>(left) : T * kTile;
+}
+
+// f(0), f(1), ... with the index as a compile-time constant
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (A < B) {
+        f(std::integral_constant<int, A>{});
+        static_for<A + 1, B>(f);
+    }
+}
+
+// wavefronts per SIMD that the register count of a kernel holding R tiles in registers allows
+constexpr int held_waves(int R) { return R <= 4 ? 8 : R <= 8 ? 6 : 4; }
+
+// The built sizes: calls f with the tiles that a workgroup keeps in registers and in LDS as
+// compile-time constants.  512 threads with up to 64, 80 and 128 registers leave room for 4, 3
+// and 2 workgroups per compute unit, and the LDS tiles fill that number's share of 160 KB.
+constexpr int kHeldT[] = {1, 2, 4, 8, 14, 24};
+
+template <class F>
+static void with_held(int T, F f)
+{
+    using std::integral_constant;
+    switch (T) {
+    case 1: f(integral_constant<int, 1>{}, integral_constant<int, 0>{}); break;
+    case 2: f(integral_constant<int, 2>{}, integral_constant<int, 0>{}); break;
+    case 4: f(integral_constant<int, 4>{}, integral_constant<int, 0>{}); break;
+    case 8: f(integral_constant<int, 4>{}, integral_constant<int, 4>{}); break;
+    case 14: f(integral_constant<int, 8>{}, integral_constant<int, 6>{}); break;
+    case 24: f(integral_constant<int, 15>{}, integral_constant<int, 9>{}); break;
+    }
+}
+
+// Tiles per workgroup for `rows` rows, 0 = the device cannot hold a row; per_cu(R, L): resident
+// workgroups of that kernel per compute unit, negative on failure.  Measured on the 1-bit worker block:
+//  * a row that fits one workgroup: the smallest size that holds it.  Nobody waits and the finish
+//    launch falls away (8 x 16,000: 10.4 us a call against 12.9 us with one tile per workgroup);
+//  * else the smallest size with which the device holds all rows at once: most workgroups, no row
+//    waits for room (7 x 2,345,679: 72, 42, 35, 38 us with 2, 4, 8, 14 tiles, of which 8 is the
+//    first that holds all);
+//  * else 14 tiles if that holds four rows (8 x 5,000,003: 88 us, 24 tiles 93 us), 24 otherwise
+//    (8 x 16,000,000: 302 us, 14 tiles 314 us, 399 us in two looks; 8 x 24,000,000: 451 us, 619 us
+//    in two looks).
+template <class F>
+static ds_status_t held_size(const ds_ctx *c, int64_t rows, F per_cu, int *T_out)
+{
+    int cus = 0;
+    DS_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+    const int64_t tiles = c->n_tiles;
+    const bool one = tiles <= kHeldT[5];
+    *T_out = 0;
+    for (int T : kHeldT) {
+        if (one && tiles > T) continue;
+        int held = 0;
+        with_held(T, [&](auto r, auto l) { held = per_cu(r, l); });
+        if (held < 0) return DS_ERR_DEVICE;
+        const int64_t slots = static_cast<int64_t>(held) * cus, parts = (tiles + T - 1) / T;
+        const int64_t at_once = one ? 1 : (T == 24) ? 1 : (T == 14 && rows > 4) ? 4 : rows;   // rows to be held
+        if (at_once * parts <= slots) { *T_out = T; return DS_OK; }
+    }
+    return DS_OK;
+}
+
+// The synchronisation words and flags of a context that takes the route with `sync->T` tiles.
+static ds_status_t held_alloc(const ds_ctx *c, int32_t rows, ds_held_sync *sync)
+{
+    const size_t n = static_cast<size_t>(rows);
+    // a wait: 20 us and four times what a row's bytes take, in ticks of the 100 MHz clock
+    sync->patience = (c->cfg.topk_spin_limit < 0) ? 0u : static_cast<uint32_t>(2000 + c->cfg.d / 1000);
+    sync->parts = static_cast<int>((c->n_tiles + sync->T - 1) / sync->T);
+    DS_HIP_TRY(hipMalloc(&sync->rows, kHeldRowBytes * n));
+    DS_HIP_TRY(hipMemset(sync->rows, 0, kHeldRowBytes * n));
+    DS_HIP_TRY(hipMalloc(&sync->gave_up, sizeof(uint32_t) * n * static_cast<size_t>(sync->parts)));
+    return DS_OK;
+}
+
+static void held_free(ds_held_sync *sync)
+{
+    if (sync->rows) (void)hipFree(sync->rows);
+    if (sync->gave_up) (void)hipFree(sync->gave_up);
+    *sync = ds_held_sync{};
+}
+
+}  // namespace ds

@@ -17,6 +17,7 @@
 // the shape, so results are bit-reproducible run to run.
 #include "ds_device.h"
 #include "ds_internal.h"
+#include "held.h"
 
 #include <mutex>
 #include <type_traits>
@@ -527,41 +528,6 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t strid
 // bytes).  With all errors of a workgroup loaded up front and the gradients in groups of three the
 // first took 220 us, with D = 4 and 6 tiles in flight instead of 3 213 and 214 us.
 //
-// Synchronisation words of one row; published word and counter on cache lines of their own.
-constexpr size_t kHeldRowBytes = 256;
-struct HeldRow {
-    DevShared<uint64_t> pub;      // kHeldScale | bits of the scale, 0 = not there yet
-    DevShared<uint32_t> quit;     // row 0 only: a workgroup of this call gave up, the others do not wait either
-    uint32_t pad0[29];
-    DevShared<uint32_t> arrived;
-    uint32_t pad1[31];
-};
-static_assert(sizeof(HeldRow) == kHeldRowBytes, "as allocated by the host");
-constexpr uint64_t kHeldScale = 1ull << 32;
-
-// The row's scale, false if it did not come in time.  Every thread of the workgroup calls.
-__device__ __forceinline__ bool held_wait(HeldRow *rows, int row, uint32_t patience, uint32_t *sh, float *s)
-{
-    if (threadIdx.x == 0) {
-        const long long t0 = wall_clock64();
-        uint64_t v;
-        for (uint32_t polls = 0;; ++polls) {
-            v = rows[row].pub.load();
-            if (v & kHeldScale) break;
-            if ((polls & 7u) == 0u) {
-                if (rows[0].quit.load() != 0u) break;
-                if (wall_clock64() - t0 >= static_cast<long long>(patience)) { rows[0].quit.store(1u); break; }
-            }
-            __builtin_amdgcn_s_sleep(8);
-        }
-        sh[0] = (v & kHeldScale) ? 1u : 0u;
-        sh[1] = static_cast<uint32_t>(v);
-    }
-    __syncthreads();
-    *s = __uint_as_float(sh[1]);
-    return sh[0] != 0u;
-}
-
 // What a workgroup of the held route shares: per tile the wavefronts' sums and the sign words.
 template <int T>
 struct HeldShared {
@@ -628,63 +594,10 @@ __device__ __forceinline__ bool held_scale(HeldShared<T> &m, int64_t tile0, int 
     const double total = block_sum(acc, m.red, false);
     *s = group_scale(total, len, RMS);
     if (threadIdx.x == 0) {
-        rows[row].pub.store(kHeldScale | __float_as_uint(*s));
+        rows[row].pub.store(kHeldValue | __float_as_uint(*s));
         *scale_out = *s;
     }
     return true;
-}
-
-// Tile t of a workgroup's stretch of an fp32 row as a buffer: a descriptor in scalar registers and
-// one 32-bit offset per lane, the same for every tile, where 64-bit addresses would take the
-// registers that v needs.  Only the whole groups of four elements of the row lie inside the
-// buffer: a lane past them reads zero and stores nothing, and the one to three elements of a
-// last cut group are the caller's.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t held_tile(const float *first, int left, int t)
-{
-    const int whole = (left & ~3) - t * kTile;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(first + t * kTile), 0, (whole > 0 ? whole : 0) * 4, 0x00027000);
-}
-
-constexpr int kNonTemporal = 2;   // cache policy operand of the buffer instructions
-
-__device__ __forceinline__ f32x4 held_ld4(const float *first, int left, int t)
-{
-    const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, kNonTemporal);
-    return f32x4{__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
-}
-
-__device__ __forceinline__ void held_st4(float *first, int left, int t, f32x4 v)
-{
-    const u32x4 u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-    __builtin_amdgcn_raw_buffer_store_b128(u, held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, kNonTemporal);
-}
-
-// Between the phases of a held kernel: the compiler must not carry what it derived from v in one
-// phase (sign masks, addresses) into the next in registers that v itself needs.
-template <int T>
-__device__ __forceinline__ void held_fence(f32x4 (&v)[T], int &left)
-{
-    asm volatile("" : "+s"(left));
-#pragma unroll
-    for (int t = 0; t < T; ++t) asm volatile("" : "+v"(v[t]));
-}
-
-// Elements of the row from the first one of the workgroup on, as far as they matter to it.
-template <int T>
-__device__ __forceinline__ int held_left(int64_t tile0, int64_t d)
-{
-    const int64_t left = d - tile0 * kTile;
-    return left < T * kTile ? static_cast<int>(left) : T * kTile;
-}
-
-// f(0), f(1), ... with the index as a compile-time constant
-template <int A, int B, class F>
-__device__ __forceinline__ void static_for(F f)
-{
-    if constexpr (A < B) {
-        f(std::integral_constant<int, A>{});
-        static_for<A + 1, B>(f);
-    }
 }
 
 // One lane's group of four that the end of the row cuts, and where it lies in the stretch (-1: nowhere).
@@ -706,13 +619,6 @@ __device__ __forceinline__ HeldCut held_cut(const void *grow, const float *drow,
 
 // v of tile t, zero past the end of the row.  The selects run in every workgroup: under a branch
 // the compiler copies all of the held values around it.
-template <bool BF16>
-__device__ __forceinline__ f32x4 held_g4(const void *grow, int64_t first, int left, int t)
-{
-    if constexpr (BF16) return ld4_bf16(static_cast<const uint16_t *>(grow), first + t * kTile + threadIdx.x * 4, first + (left & ~3));
-    else return held_ld4(static_cast<const float *>(grow) + first, left, t);
-}
-
 __device__ __forceinline__ f32x4 held_sum4(f32x4 g, f32x4 dl, const HeldCut &c, int t)
 {
     f32x4 v = g + dl;
@@ -735,10 +641,9 @@ __device__ __forceinline__ void held_store(f32x4 v, int t, float *out, int left,
 // R tiles of a workgroup are held in registers and L more in LDS (every thread reads back its own
 // elements).
 constexpr int kHeldDepth = 3;
-constexpr int held_waves(int R, int L) { return R <= 4 ? 8 : R <= 8 ? 6 : 4; }
 
 template <bool BF16, bool RMS, int R, int L>
-__global__ __launch_bounds__(kBlock, held_waves(R, L)) void k_sign_held_worker(WorkerSrc<BF16> src, float *delta, int64_t d,
+__global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(WorkerSrc<BF16> src, float *delta, int64_t d,
                                                                             uint64_t *words, int64_t W, ds_sign_tables tb,
                                                                             double *partials, float *scales, HeldRow *rows,
                                                                             uint32_t *gave_up, uint32_t patience)
@@ -791,7 +696,6 @@ __global__ __launch_bounds__(kBlock, held_waves(R, L)) void k_sign_held_worker(W
 
 // After a held launch: forms the error where a workgroup gave up (normally nowhere) and clears
 // the synchronisation words for the next call.  `parts` workgroups of T tiles per row.
-constexpr int kFinishParts = 64;
 __global__ __launch_bounds__(kBlock) void k_sign_held_finish(float *buf, int64_t stride, int64_t d, const float *__restrict__ scales,
                                                              int T, int parts, const uint32_t *__restrict__ gave_up, HeldRow *rows)
 {
@@ -800,9 +704,7 @@ __global__ __launch_bounds__(kBlock) void k_sign_held_finish(float *buf, int64_t
     const int mine = part0 + lane_id();
     uint64_t left = __ballot(mine < parts && gave_up[row * static_cast<int64_t>(parts) + mine] != 0u);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        rows[row].pub.clear_for_next_launch();
-        rows[row].arrived.clear_for_next_launch();
-        rows[row].quit.clear_for_next_launch();
+        rows[row].clear_for_next_launch();
     }
     if (left == 0) return;
     float *brow = buf + row * stride;
@@ -901,69 +803,6 @@ ds_status_t ds_sign_server_identity(ds_ctx *c, const ds_payload_t *in, float *de
     return ds_launch_status();
 }
 
-// The built sizes of the held route: calls f with the tiles that a workgroup keeps in registers and in
-// LDS as compile-time constants.  512 threads with up to 64, 80 and 128 registers leave room for
-// 4, 3 and 2 workgroups per compute unit, and the LDS tiles fill that number's share of 160 KB.
-constexpr int kHeldT[] = {1, 2, 4, 8, 14, 24};
-
-template <class F>
-static void with_held(int T, F f)
-{
-    using std::integral_constant;
-    switch (T) {
-    case 1: f(integral_constant<int, 1>{}, integral_constant<int, 0>{}); break;
-    case 2: f(integral_constant<int, 2>{}, integral_constant<int, 0>{}); break;
-    case 4: f(integral_constant<int, 4>{}, integral_constant<int, 0>{}); break;
-    case 8: f(integral_constant<int, 4>{}, integral_constant<int, 4>{}); break;
-    case 14: f(integral_constant<int, 8>{}, integral_constant<int, 6>{}); break;
-    case 24: f(integral_constant<int, 15>{}, integral_constant<int, 9>{}); break;
-    }
-}
-
-// Tiles per workgroup of the held route for `rows` rows, 0 = the device cannot hold a row.
-//  * a row that fits one workgroup: the smallest size that holds it.  Nobody waits and the finish
-//    launch falls away (8 x 16,000: 10.4 us a call against 12.9 us with one tile per workgroup);
-//  * else the smallest size with which the device holds all rows at once: most workgroups, no row
-//    waits for room (7 x 2,345,679: 72, 42, 35, 38 us with 2, 4, 8, 14 tiles, of which 8 is the
-//    first that holds all);
-//  * else 14 tiles if that holds four rows (8 x 5,000,003: 88 us, 24 tiles 93 us), 24 otherwise
-//    (8 x 16,000,000: 302 us, 14 tiles 314 us, 399 us in two looks; 8 x 24,000,000: 451 us, 619 us
-//    in two looks).
-static ds_status_t held_size(const ds_ctx *c, int64_t rows, int *T_out)
-{
-    int cus = 0;
-    DS_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    const int64_t tiles = c->n_tiles;
-    *T_out = 0;
-    for (int T : kHeldT) {
-        int per_cu = 0;
-        hipError_t e = hipSuccess;
-        with_held(T, [&](auto r, auto l) {
-            constexpr int R = decltype(r)::value, L = decltype(l)::value;
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sign_held_worker<false, false, R, L>, kBlock, 0);
-        });
-        if (e != hipSuccess) return DS_ERR_DEVICE;
-        const int64_t slots = static_cast<int64_t>(per_cu) * cus, parts = (tiles + T - 1) / T;
-        const bool one = tiles <= kHeldT[5];
-        const int64_t need = one ? (tiles <= T ? 0 : slots + 1) : (T == 24) ? parts : (T == 14 && rows > 4) ? 4 * parts : rows * parts;
-        if (need <= slots) { *T_out = T; return DS_OK; }
-    }
-    return DS_OK;
-}
-
-static ds_status_t held_init(ds_ctx *c)
-{
-    const size_t n = static_cast<size_t>(c->cfg.n);
-    const ds_status_t rc = held_size(c, c->cfg.n, &c->held_T);
-    if (rc != DS_OK || !c->held_T) return rc;
-    // a wait: 20 us and four times what a row's bytes take, in ticks of the 100 MHz clock
-    c->held_patience = (c->cfg.topk_spin_limit < 0) ? 0u : static_cast<uint32_t>(2000 + c->cfg.d / 1000);
-    DS_HIP_TRY(hipMalloc(&c->held_rows, kHeldRowBytes * n));
-    DS_HIP_TRY(hipMemset(c->held_rows, 0, kHeldRowBytes * n));
-    DS_HIP_TRY(hipMalloc(&c->held_gave_up, sizeof(uint32_t) * n * static_cast<size_t>((c->n_tiles + c->held_T - 1) / c->held_T)));
-    return DS_OK;
-}
-
 ds_status_t ds_sign_init(ds_ctx *c)
 {
     const ds_config_t &cfg = c->cfg;
@@ -973,9 +812,7 @@ ds_status_t ds_sign_init(ds_ctx *c)
     c->sign_prev_w = c->sign_prev_s = nullptr;
     c->sign_tb_mem = nullptr;
     c->sign_partials = nullptr;
-    c->held_T = 0;
-    c->held_rows = nullptr;
-    c->held_gave_up = nullptr;
+    c->held = ds_held_sync{};
     std::vector<int64_t> seg_off;
     if (cfg.scale_mode == DS_SCALE_WHOLE) {
         seg_off = {0, d};
@@ -1046,8 +883,17 @@ ds_status_t ds_sign_init(ds_ctx *c)
     if (hipGetLastError() != hipSuccess) return DS_ERR_DEVICE;
     DS_HIP_TRY(hipMalloc(&c->sign_partials, sizeof(double) * n_pieces * static_cast<size_t>(cfg.n)));
     if (S == 1 && !c->nofb && !(cfg.flags & DS_FLAG_DEFERRED_ERROR)) {
-        const ds_status_t rc = held_init(c);
+        const ds_status_t rc = held_size(c, cfg.n, [](auto r, auto l) {
+            constexpr int R = decltype(r)::value, L = decltype(l)::value;
+            int per_cu = 0;
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sign_held_worker<false, false, R, L>, kBlock, 0) ==
+                           hipSuccess ? per_cu : -1;
+        }, &c->held.T);
         if (rc != DS_OK) return rc;
+        if (c->held.T) {
+            const ds_status_t ra = held_alloc(c, cfg.n, &c->held);
+            if (ra != DS_OK) return ra;
+        }
     }
     if ((cfg.flags & DS_FLAG_DEFERRED_ERROR) && !c->nofb) {
         c->sign_defer = true;
@@ -1061,10 +907,7 @@ void ds_sign_fini(ds_ctx *c)
 {
     if (c->sign_tb_mem) (void)hipFree(c->sign_tb_mem);
     if (c->sign_partials) (void)hipFree(c->sign_partials);
-    if (c->held_rows) (void)hipFree(c->held_rows);
-    if (c->held_gave_up) (void)hipFree(c->held_gave_up);
-    c->held_rows = nullptr;
-    c->held_gave_up = nullptr;
+    held_free(&c->held);
     if (c->sign_prev_w) (void)hipFree(c->sign_prev_w);
     if (c->sign_prev_s) (void)hipFree(c->sign_prev_s);
     c->sign_prev_w = c->sign_prev_s = nullptr;
@@ -1098,23 +941,22 @@ ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, i
         });
         return ds_launch_status();
     }
-    if (c->held_T) {
-        const int parts = static_cast<int>((c->n_tiles + c->held_T - 1) / c->held_T);
-        const dim3 hgrid(static_cast<unsigned>(parts), static_cast<unsigned>(cfg.n));
-        HeldRow *rows = static_cast<HeldRow *>(c->held_rows);
-        with_held(c->held_T, [&](auto rr, auto ll) {
+    if (c->held.T) {
+        const ds_held_sync &h = c->held;
+        const unsigned rows_n = static_cast<unsigned>(cfg.n);
+        HeldRow *rows = static_cast<HeldRow *>(h.rows);
+        with_held(h.T, [&](auto rr, auto ll) {
             constexpr int R = decltype(rr)::value, L = decltype(ll)::value;
             with_flags(bf16, rms, false, [&](auto bf, auto rm, auto) {
                 constexpr bool BF = decltype(bf)::value, RM = decltype(rm)::value;
                 WorkerSrc<BF> src{g, gs, delta, dstr};
-                k_sign_held_worker<BF, RM, R, L><<<hgrid, kBlock, 0, st>>>(src, delta, cfg.d, out->sign_words, c->W, c->sign_tb,
-                                                                        c->sign_partials, out->scales, rows, c->held_gave_up,
-                                                                        c->held_patience);
+                k_sign_held_worker<BF, RM, R, L><<<dim3(static_cast<unsigned>(h.parts), rows_n), kBlock, 0, st>>>(
+                    src, delta, cfg.d, out->sign_words, c->W, c->sign_tb, c->sign_partials, out->scales, rows, h.gave_up, h.patience);
             });
         });
-        if (parts > 1)
-            k_sign_held_finish<<<dim3(static_cast<unsigned>((parts + kFinishParts - 1) / kFinishParts), static_cast<unsigned>(cfg.n)),
-                                 kBlock, 0, st>>>(delta, dstr, cfg.d, out->scales, c->held_T, parts, c->held_gave_up, rows);
+        if (h.parts > 1)
+            k_sign_held_finish<<<dim3(static_cast<unsigned>((h.parts + kFinishParts - 1) / kFinishParts), rows_n), kBlock, 0, st>>>(
+                delta, dstr, cfg.d, out->scales, h.T, h.parts, h.gave_up, rows);
         return ds_launch_status();
     }
     dim3 grid(static_cast<unsigned>(c->n_tiles), static_cast<unsigned>(cfg.n));

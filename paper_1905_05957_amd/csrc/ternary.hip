@@ -13,10 +13,13 @@
 //   rowstat  per row: the maximum, and the sum in a fixed order
 //   encode   codes from the second look: two bit planes packed like the sign words, kept count per tile
 //   scale    per row: sum / count, rounded once
+// Rows that the device can hold on chip (k_tern_held) are read once: the workgroups of a row keep
+// its elements until the maximum is known.
 // The message is 2 bits per element: plane `levels` (bit j = code_j is not 0), plane
 // `sign_words` (bit j = code_j is -1), one fp32 scale.
 #include "ds_device.h"
 #include "ds_internal.h"
+#include "held.h"
 
 #include <new>
 
@@ -28,6 +31,7 @@ struct ds_tern_scratch {
     uint32_t *pcnt;    // [n][n_tiles]
     float *rowmax;     // [n]
     double *rowsum;    // [n]
+    ds_held_sync held;
 };
 
 namespace {
@@ -68,8 +72,8 @@ __global__ __launch_bounds__(kBlock) void k_tern_stats(const void *g, int64_t gs
 __global__ __launch_bounds__(kBlock) void k_tern_rowstat(const float *pmax, const double *psum, int64_t n_tiles,
                                                          float *rowmax, double *rowsum)
 {
-    __shared__ double sm[kBlock];
-    __shared__ float mm[kBlock];
+    __shared__ double lds[kWaves];
+    __shared__ float mx[kWaves];
     const int row = blockIdx.x;
     double acc = 0.0;
     float m = 0.f;
@@ -77,17 +81,53 @@ __global__ __launch_bounds__(kBlock) void k_tern_rowstat(const float *pmax, cons
         acc += psum[row * n_tiles + t];
         m = fmaxf(m, pmax[row * n_tiles + t]);
     }
-    sm[threadIdx.x] = acc;
-    mm[threadIdx.x] = m;
-    __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            sm[threadIdx.x] += sm[threadIdx.x + o];
-            mm[threadIdx.x] = fmaxf(mm[threadIdx.x], mm[threadIdx.x + o]);
-        }
-        __syncthreads();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if (lane_id() == 0) mx[wave_id()] = m;
+    const double total = block_sum(acc, lds, false);          // its barrier also covers mx
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) m = fmaxf(m, mx[w]);
+        rowmax[row] = m;
+        rowsum[row] = total;
     }
-    if (threadIdx.x == 0) { rowmax[row] = mm[0]; rowsum[row] = sm[0]; }
+}
+
+struct TernKey {
+    uint32_t key0, key1, step_lo;
+};
+
+// Codes of elements e..e+3: bit c = code is not 0, bit 4 + c = code is -1.  The encoding is bound by
+// vector instructions, and four IEEE divisions were a third of them.  With U = 2^24 u a whole
+// number and q = |v| * fl(2^24 / m), which is within 2^-22 of 2^24 fl(|v| / m), U outside
+// q (1 -+ 2^-20) (and, for U = 0, q above 2^-20) decides u < fl(|v| / m) without the quotient; what
+// lies inside, NaN included, and rows whose maximum leaves the range of that product divide.
+__device__ __forceinline__ uint32_t tern_codes4(f32x4 v, float m, int64_t e, int64_t d, int row, TernKey K)
+{
+    const u32x4 rnd = philox4x32_10(u32x4{static_cast<uint32_t>(e >> 2), 0u, static_cast<uint32_t>(row), K.step_lo}, K.key0, K.key1);
+    const float vv[4] = {v.x, v.y, v.z, v.w};
+    const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+    const bool in_range = m >= 0x1p-100f && m <= 0x1p100f;      // uniform
+    const float r = __fdiv_rn(0x1p24f, m);
+    uint32_t nz = 0u, open = 0u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float U = static_cast<float>(rr[c] >> 8), q = fabsf(vv[c]) * r;
+        const bool below = U < __fmaf_rn(q, 1.f - 0x1p-20f, -0x1p-20f), above = U > q * (1.f + 0x1p-20f);
+        nz |= below ? 1u << c : 0u;
+        open |= (below || above) ? 0u : 1u << c;
+    }
+    if (!in_range) { nz = 0u; open = (m > 0.f) ? 15u : 0u; }
+    if (open) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool keep = static_cast<float>(rr[c] >> 8) * 0x1p-24f < __fdiv_rn(fabsf(vv[c]), m);
+            nz |= ((open >> c) & 1u) && keep ? 1u << c : 0u;
+        }
+    }
+    nz &= (e + 4 <= d) ? 15u : (e < d) ? (1u << (d - e)) - 1u : 0u;
+    const uint32_t neg = (vv[0] < 0.f ? 1u : 0u) | (vv[1] < 0.f ? 2u : 0u) | (vv[2] < 0.f ? 4u : 0u) | (vv[3] < 0.f ? 8u : 0u);
+    return nz | ((nz & neg) << 4);
 }
 
 template <bool BF16>
@@ -103,21 +143,10 @@ __global__ __launch_bounds__(kBlock) void k_tern_encode(const void *g, int64_t g
     const void *grow = grad_row<BF16>(g, gs, row);
     const f32x4 v = ld4_grad<BF16>(grow, e, d);
     const float m = rowmax[row];
-    bool keep[4] = {false, false, false, false};
-    if (e < d && m > 0.f) {
-        const u32x4 rnd = philox4x32_10(u32x4{static_cast<uint32_t>(e >> 2), 0u, static_cast<uint32_t>(row), step_lo}, key0, key1);
-        const float vv[4] = {v.x, v.y, v.z, v.w};
-        const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float p = __fdiv_rn(fabsf(vv[c]), m);
-            const float u = static_cast<float>(rr[c] >> 8) * 0x1p-24f;
-            keep[c] = (e + c < d) && (u < p);
-        }
-    }
-    stash_sign_words(sw_nz, wave_sign_word(keep[0], keep[1], keep[2], keep[3]));
-    stash_sign_words(sw_neg, wave_sign_word(keep[0] && v.x < 0.f, keep[1] && v.y < 0.f, keep[2] && v.z < 0.f, keep[3] && v.w < 0.f));
-    const uint32_t kept = wave_sum_u32(static_cast<uint32_t>(keep[0]) + keep[1] + keep[2] + keep[3]);
+    const uint32_t code = tern_codes4(v, m, e, d, row, TernKey{key0, key1, step_lo});
+    stash_sign_words(sw_nz, wave_nibble_word(code & 15u));
+    stash_sign_words(sw_neg, wave_nibble_word(code >> 4));
+    const uint32_t kept = wave_sum_u32(static_cast<uint32_t>(__popc(code & 15u)));
     if (lane_id() == 0) cnt[wave_id()] = kept;
     __syncthreads();
     flush_sign_words(sw_nz, nz + row * W, base, W * 64);
@@ -143,6 +172,203 @@ __global__ __launch_bounds__(kBlock) void k_tern_scale(const uint32_t *pcnt, con
         __syncthreads();
     }
     if (threadIdx.x == 0) scales[row] = sm[0] ? static_cast<float>(rowsum[row] / static_cast<double>(sm[0])) : 0.f;
+}
+
+// ---------------------------------------------------------------------------------------
+// held route: rows that are read once
+// ---------------------------------------------------------------------------------------
+// A workgroup keeps T consecutive tiles in registers and LDS, hands over their sums and maximum,
+// waits for the row's maximum, which the workgroup that arrives last publishes, and encodes what
+// it holds; the workgroup that encodes last writes the scale.  Waits are bounded, and what a
+// workgroup that gave up did not encode the finish launch does (held.h).  Worker call at
+// 8 x 11,173,962: 189 us in two looks with four divisions per thread, 169 us in two looks without
+// them, 153 us here (57 us for its bytes at the copy kernel's rate).
+template <int T>
+struct TernShared {
+    double sums[T][kWaves], red[kWaves];
+    float mx[kWaves];
+    uint32_t cnt[kWaves], sh[2];
+};
+
+// The wavefront's words of one tile to both planes.
+__device__ __forceinline__ void tern_put_words(uint32_t code, int64_t tile_first, uint64_t *neg_row, uint64_t *nz_row, int64_t bit_lim)
+{
+    const uint32_t a = wave_nibble_word(code & 15u), b = wave_nibble_word(code >> 4);
+    const int64_t bit = tile_first + threadIdx.x * 4;         // first element of this lane; word of an 8-lane group: its first lane
+    if ((lane_id() & 7) == 0 && bit < bit_lim) {
+        reinterpret_cast<uint32_t *>(nz_row)[bit >> 5] = a;
+        reinterpret_cast<uint32_t *>(neg_row)[bit >> 5] = b;
+    }
+}
+
+// Counts the workgroup's non-zero codes in; the workgroup that completes the row writes its scale.
+// `kept` is per thread; `sum` = sum |v| of a row that is one workgroup's.  Every thread calls.
+__device__ __forceinline__ void tern_count_in(uint32_t kept, uint32_t *cnt, HeldRow *row_sync, int parts, double sum, float *scale_out)
+{
+    kept = wave_sum_u32(kept);
+    if (lane_id() == 0) cnt[wave_id()] = kept;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint64_t total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) total += cnt[w];
+    if (parts > 1) {
+        const uint64_t before = row_sync->kept.fetch_add((1ull << 40) | total);
+        if ((before >> 40) + 1u != static_cast<uint64_t>(parts)) return;
+        total += before & ((1ull << 40) - 1u);
+        row_sync->kept.store(0u);                             // nobody counts in any more
+        sum = __longlong_as_double(static_cast<long long>(row_sync->sum.load()));
+    }
+    *scale_out = total ? static_cast<float>(sum / static_cast<double>(total)) : 0.f;
+}
+
+template <bool BF16, int R, int L>
+__global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void *g, int64_t gs, int64_t d, int32_t n_tiles, double *psum,
+                                                                     float *rowmax, TernKey K, uint64_t *neg, uint64_t *nz, int64_t W,
+                                                                     float *scales, HeldRow *rows, uint32_t *gave_up, uint32_t patience)
+{
+    constexpr int T = R + L;
+    __shared__ TernShared<T> sm;
+    __shared__ f32x4 far[L ? L : 1][kBlock];
+    const int row = blockIdx.y;
+    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * T, first = tile0 * kTile;
+    const void *grow = grad_row<BF16>(g, gs, row);
+    int left = held_left<T>(tile0, d);
+    f32x4 cut = {0.f, 0.f, 0.f, 0.f};
+    int cut_at = -1;
+    if (left & 3) {                                           // the row ends inside a group of four
+        cut_at = left & ~3;
+        cut = ld4_grad<BF16>(grow, first + cut_at, first + left);
+    }
+    constexpr int D = 6 < T ? 6 : T;                          // tiles in flight
+    f32x4 v[R], ring[L ? D : 1];
+    auto fetch = [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        if constexpr (q < L) ring[q % D] = held_g4<BF16>(grow, first, left, R + q);
+        else v[q - L] = held_g4<BF16>(grow, first, left, q - L);
+    };
+    float mx = 0.f;
+    static_for<0, D>(fetch);
+    static_for<0, T>([&](auto qc) {
+        constexpr int q = decltype(qc)::value, t = q < L ? R + q : q - L;
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 w;
+        if constexpr (q < L) w = ring[q % D];
+        else w = v[t];
+        const bool mine = static_cast<int>(threadIdx.x) * 4 + t * kTile == cut_at;
+        w.x = mine ? cut.x : w.x;
+        w.y = mine ? cut.y : w.y;
+        w.z = mine ? cut.z : w.z;
+        asm volatile("" : "+v"(w));
+        if constexpr (q + D < T) fetch(std::integral_constant<int, q + D>{});
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (q < L) far[q][threadIdx.x] = w;
+        else v[t] = w;
+        const float a0 = fabsf(w.x), a1 = fabsf(w.y), a2 = fabsf(w.z), a3 = fabsf(w.w);
+        mx = fmaxf(mx, fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)));
+        const double s = wave_sum(((static_cast<double>(a0) + static_cast<double>(a1)) + static_cast<double>(a2)) + static_cast<double>(a3));
+        if (lane_id() == 0) sm.sums[t][wave_id()] = s;
+    });
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane_id() == 0) sm.mx[wave_id()] = mx;
+    held_fence(v, left);
+    __syncthreads();
+    double tile_sum = 0.0;                                    // lane t < T of every wavefront: tile t
+    if (lane_id() < T) {
+        tile_sum = sm.sums[lane_id()][0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) tile_sum += sm.sums[lane_id()][w];
+    }
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, sm.mx[w]);
+    const bool alone = gridDim.x == 1;
+    double row_sum_alone = 0.0;
+    bool ok = true;
+    if (alone) {
+        row_sum_alone = wave_sum(tile_sum);
+    } else {
+        uint64_t *psum_row = reinterpret_cast<uint64_t *>(psum) + static_cast<int64_t>(row) * n_tiles;
+        if (wave_id() == 0) {
+            if (lane_id() < T && tile0 + lane_id() < n_tiles)
+                as_shared(psum_row)[tile0 + lane_id()].store(__double_as_longlong(tile_sum));
+            if (lane_id() == 0) rows[row].most.raise_to(__float_as_uint(mx));     // not negative: ordered like its bits
+            // both are in memory before the arrival is announced
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane_id() == 0) sm.sh[0] = (rows[row].arrived.fetch_add(1u) + 1u == gridDim.x) ? 1u : 0u;
+        }
+        __syncthreads();
+        const bool last = sm.sh[0] != 0u;
+        __syncthreads();
+        if (!last) {
+            ok = held_wait(rows, row, patience, sm.sh, &mx);
+        } else {
+            double acc = 0.0;
+            for (int32_t p = threadIdx.x; p < n_tiles; p += kBlock)
+                acc += __longlong_as_double(static_cast<long long>(as_shared(psum_row)[p].load()));
+            const double total = block_sum(acc, sm.red, false);
+            mx = __uint_as_float(rows[row].most.load());
+            if (threadIdx.x == 0) {
+                rowmax[row] = mx;                             // for the finish launch
+                rows[row].sum.store(__double_as_longlong(total));
+                // the sum is in memory before anyone can count in
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                rows[row].pub.store(kHeldValue | __float_as_uint(mx));
+            }
+        }
+        if (threadIdx.x == 0) gave_up[row * static_cast<int64_t>(gridDim.x) + blockIdx.x] = ok ? 0u : 1u;
+        if (!ok) return;                                      // uniform
+    }
+    held_fence(v, left);
+    const int64_t bit_lim = W * 64;
+    uint64_t *neg_row = neg + row * W, *nz_row = nz + row * W;
+    uint32_t kept = 0;
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        const int64_t e = first + t * kTile + threadIdx.x * 4;
+        const uint32_t code = tern_codes4(v[t], mx, e, d, row, K);
+        tern_put_words(code, first + t * kTile, neg_row, nz_row, bit_lim);
+        kept += __popc(code & 15u);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll 1
+    for (int t = R; t < T; ++t) {
+        const int64_t e = first + t * kTile + threadIdx.x * 4;
+        const uint32_t code = tern_codes4(far[t - R][threadIdx.x], mx, e, d, row, K);
+        tern_put_words(code, first + t * kTile, neg_row, nz_row, bit_lim);
+        kept += __popc(code & 15u);
+    }
+    tern_count_in(kept, sm.cnt, rows + row, gridDim.x, row_sum_alone, scales + row);
+}
+
+// After a held launch: encodes what a workgroup that gave up did not (normally nothing) and clears
+// the synchronisation words for the next call.
+template <bool BF16>
+__global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int64_t gs, int64_t d, const float *rowmax, TernKey K,
+                                                             uint64_t *neg, uint64_t *nz, int64_t W, float *scales, int T, int parts,
+                                                             const uint32_t *gave_up, HeldRow *rows)
+{
+    __shared__ uint32_t cnt[kWaves];
+    const int row = blockIdx.y;
+    const int part0 = blockIdx.x * kFinishParts, mine = part0 + lane_id();
+    uint64_t left = __ballot(mine < parts && gave_up[row * static_cast<int64_t>(parts) + mine] != 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) rows[row].clear_for_next_launch();
+    if (left == 0) return;
+    const void *grow = grad_row<BF16>(g, gs, row);
+    const float m = rowmax[row];
+    while (left) {
+        const int64_t tile0 = static_cast<int64_t>(part0 + __builtin_ctzll(left)) * T;
+        left &= left - 1;
+        uint32_t kept = 0;
+        for (int t = 0; t < T; ++t) {
+            const int64_t tile_first = (tile0 + t) * kTile, e = tile_first + threadIdx.x * 4;
+            const uint32_t code = tern_codes4(ld4_grad<BF16>(grow, e, d), m, e, d, row, K);
+            tern_put_words(code, tile_first, neg + row * W, nz + row * W, W * 64);
+            kept += __popc(code & 15u);
+        }
+        tern_count_in(kept, cnt, rows + row, parts, 0.0, scales + row);
+        __syncthreads();                                      // cnt is used again
+    }
 }
 
 // code * scale of elements e..e+3 of one message
@@ -193,7 +419,20 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     DS_HIP_TRY(hipMalloc(&t->pcnt, n * tiles * sizeof(uint32_t)));
     DS_HIP_TRY(hipMalloc(&t->rowmax, n * sizeof(float)));
     DS_HIP_TRY(hipMalloc(&t->rowsum, n * sizeof(double)));
-    return DS_OK;
+    const ds_status_t rc = held_size(c, c->cfg.n, [](auto r, auto l) {
+        constexpr int R = decltype(r)::value, L = decltype(l)::value;
+        int per_cu = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tern_held<false, R, L>, kBlock, 0) == hipSuccess ? per_cu : -1;
+    }, &t->held.T);
+    if (rc != DS_OK) return rc;
+    // Encoding is bound by vector instructions and wants wavefronts, of which the largest size
+    // leaves half; it pays only where the second look would come from memory.  8 x 11,173,962 fp32
+    // (358 MB): 153 us a call against 169 us in two looks; 3 x 16,000,001 (192 MB, the second look
+    // comes from the 256 MB memory-side cache): 111 against 96 us.  The smaller sizes always pay
+    // (4 x 5,000,000: 39 against 45 us, 4 x 60,000: 12.6 against 16.6 us).
+    const size_t grad_bytes = n * static_cast<size_t>(c->cfg.d) * (c->cfg.grad_dtype == DS_BF16 ? 2 : 4);
+    if (t->held.T == 24 && tiles > 24 && grad_bytes <= (static_cast<size_t>(256) << 20)) t->held.T = 0;
+    return t->held.T ? held_alloc(c, c->cfg.n, &t->held) : DS_OK;
 }
 
 void ds_ternary_fini(ds_ctx *c)
@@ -203,6 +442,7 @@ void ds_ternary_fini(ds_ctx *c)
     void *ptrs[5] = {t->pmax, t->psum, t->pcnt, t->rowmax, t->rowsum};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    held_free(&t->held);
     delete t;
     c->tern = nullptr;
 }
@@ -217,6 +457,25 @@ ds_status_t ds_ternary_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
     const uint32_t key1 = static_cast<uint32_t>(c->cfg.seed >> 32) ^ static_cast<uint32_t>(step >> 32);
     uint64_t *nz = reinterpret_cast<uint64_t *>(out->levels);
     const bool bf16 = c->cfg.grad_dtype == DS_BF16;
+    if (t->held.T) {
+        const ds_held_sync &h = t->held;
+        HeldRow *rows = static_cast<HeldRow *>(h.rows);
+        const TernKey K{key0, key1, static_cast<uint32_t>(step)};
+        const dim3 hgrid(static_cast<unsigned>(h.parts), n), fgrid(static_cast<unsigned>((h.parts + kFinishParts - 1) / kFinishParts), n);
+        auto go = [&](auto bf) {
+            constexpr bool BF = decltype(bf)::value;
+            with_held(h.T, [&](auto rr, auto ll) {
+                constexpr int R = decltype(rr)::value, L = decltype(ll)::value;
+                k_tern_held<BF, R, L><<<hgrid, kBlock, 0, st>>>(g, gs, d, static_cast<int32_t>(n_tiles), t->psum, t->rowmax, K,
+                                                                out->sign_words, nz, c->W, out->scales, rows, h.gave_up, h.patience);
+            });
+            if (h.parts > 1)
+                k_tern_held_finish<BF><<<fgrid, kBlock, 0, st>>>(g, gs, d, t->rowmax, K, out->sign_words, nz, c->W, out->scales, h.T,
+                                                                 h.parts, h.gave_up, rows);
+        };
+        if (bf16) go(std::true_type{}); else go(std::false_type{});
+        return ds_launch_status();
+    }
     if (bf16) k_tern_stats<true><<<grid, kBlock, 0, st>>>(g, gs, d, t->pmax, t->psum);
     else k_tern_stats<false><<<grid, kBlock, 0, st>>>(g, gs, d, t->pmax, t->psum);
     k_tern_rowstat<<<n, kBlock, 0, st>>>(t->pmax, t->psum, n_tiles, t->rowmax, t->rowsum);

@@ -127,3 +127,28 @@ def test_unsupported_combinations_are_refused_at_create(gpu_device):
     assert code(comp="topk", n=2, d=100, k=3, flags=NOFB | SID, grad_dtype="bf16") == 5
     assert code(comp="rsparse", n=2, d=100, keep_prob=0.6, flags=SID) == 5
     assert code(comp="identity", n=2, d=100, flags=NOFB) == 5
+
+
+# Ternary rows that are read once: rows that one workgroup holds, several workgroups per row of every
+# size, ends of tiles, words and rows (d mod 4).  `patience` -1: every workgroup that would have to
+# wait for the row's maximum gives up and the finish launch encodes what it held.
+@pytest.mark.parametrize("patience", [0, -1])
+@pytest.mark.parametrize("n,d,dtype", [(3, 2047, "f32"), (2, 4 * 2048 - 3, "bf16"), (2, 8 * 2048 + 1, "f32"), (2, 14 * 2048, "bf16"),
+                                       (2, 24 * 2048 - 2, "f32"), (2, 25 * 2048 + 3, "f32"), (5, 300_001, "bf16"),
+                                       (8, 700_002, "f32"), (9, 1_800_003, "f32"), (9, 2_600_001, "bf16"), (3, 9_000_005, "f32")])
+def test_ternary_rows_read_once(gpu_device, n, d, dtype, patience):
+    wl = W.Workload("ternary", "ternary", n=n, d=d, dist="normal", sigma=1e-3, gamma=0.05, grad_dtype=dtype, seed=7)
+    parity_util.CONTEXT_FLAGS, parity_util.CONTEXT_KW = NOFB | SID, {"topk_spin_limit": patience}
+    try:
+        pair = Pair(wl, gpu_device)
+    finally:
+        parity_util.CONTEXT_FLAGS, parity_util.CONTEXT_KW = 0, {}
+    try:
+        for t in range(2):
+            pair.compared_step(t, wl.gradients(t, gpu_device))
+        # an all-zero row has an all-zero message
+        g = wl.gradients(2, gpu_device)
+        g[n - 1].zero_()
+        pair.compared_step(2, g)
+    finally:
+        pair.close()
