@@ -375,7 +375,7 @@ ds_status_t ds_server_aggregate_compress_update(ds_ctx_t *c, uint64_t step, cons
         if (!guard.ok) return DS_ERR_DEVICE;
         return ds_rsparse_server_update(c, step, in, delta_s, out, x, m, gamma, beta, static_cast<hipStream_t>(hip_stream));
     }
-    if ((c->cfg.comp == DS_COMP_SIGN && c->sign_fused) || c->cfg.comp == DS_COMP_QSGD) {
+    if ((c->cfg.comp == DS_COMP_SIGN && (c->sign_fused || c->held_s.T)) || c->cfg.comp == DS_COMP_QSGD) {
         // one pass: x (and m) are updated from the registers that hold the server's message
         DeviceGuard guard(c->device);
         if (!guard.ok) return DS_ERR_DEVICE;

@@ -71,16 +71,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t held_tile(const float *first, 
 
 constexpr int kNonTemporal = 2;   // cache policy operand of the buffer instructions
 
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ f32x4 held_ld4(const float *first, int left, int t)
 {
-    const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, kNonTemporal);
+    const u32x4 u = __builtin_amdgcn_raw_buffer_load_b128(held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, POLICY);
     return f32x4{__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
 }
 
+template <int POLICY = kNonTemporal>
 __device__ __forceinline__ void held_st4(float *first, int left, int t, f32x4 v)
 {
     const u32x4 u = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
-    __builtin_amdgcn_raw_buffer_store_b128(u, held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, kNonTemporal);
+    __builtin_amdgcn_raw_buffer_store_b128(u, held_tile(first, left, t), static_cast<int>(threadIdx.x) * 16, 0, POLICY);
 }
 
 // Four gradients of tile t, zero past the row's last whole group of four.

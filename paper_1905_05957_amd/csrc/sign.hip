@@ -694,18 +694,190 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
     for (int t = R; t < T; ++t) held_store(far[t - R][threadIdx.x], t, drow + first, left, ok, s);
 }
 
-// After a held launch: forms the error where a workgroup gave up (normally nowhere) and clears
-// the synchronisation words for the next call.  `parts` workgroups of T tiles per row.
+// The parameter-server block the same way, and with UPD the model update of Algorithm 1 (2: through
+// the momentum buffer) from the values that the workgroup holds: the average is formed once, the
+// error is read and written once, the server's message is not read back.  Compressor, reduce,
+// second look and update as launches of their own took 59 us at 8 x 11,173,962, one launch and its
+// finish take 45 us (30 us for their bytes at the copy kernel's rate; the barrier is not hidden, there
+// is one row).  The buffers are read and written once, but ordinary accesses beat non-temporal
+// ones here at every size: 45 against 49 us, 2 x 24,000,000 78 against 93 us.  With 14 and 24
+// tiles per workgroup instead of the smallest size that holds the row, 58 and 60 us.
+struct HeldUpdate {
+    float *x, *m;
+    float gamma, beta;
+};
+
+// x (and m) of elements e..e+3 of the row from the held v: q = the decoded message.
+template <int UPD>
+__device__ __forceinline__ void held_update4(f32x4 v, f32x4 &x, f32x4 &m, float s, const HeldUpdate &u)
+{
+    f32x4 q = {(v.x < 0.f) ? -s : s, (v.y < 0.f) ? -s : s, (v.z < 0.f) ? -s : s, (v.w < 0.f) ? -s : s};
+    if constexpr (UPD == 2) q = m = fma4(u.beta, m, q);
+    x = fma4(-u.gamma, q, x);
+}
+
+// One tile's average: v = delta_s + (1/n) sum_i Q[v_i] by the chain over workers.  word0, sc0: sign
+// words and scales of the first eight workers (layout as in k_sign_pass1_server).
+__device__ __forceinline__ f32x4 held_chain(f32x4 v, uint32_t word0, float sc0, const ServerArgs &a, int64_t wave_first)
+{
+    const int lane = lane_id();
+    const int top_shift = 28 - 4 * (lane & 7);
+    for (int i0 = 0; i0 < a.n; i0 += 8) {
+        const int nb = (a.n - i0 < 8) ? a.n - i0 : 8;
+        uint32_t word = word0;
+        float sc = sc0;
+        if (i0 > 0) {
+            word = 0u;
+            if ((lane >> 3) < nb && wave_first + 32 * (lane & 7) < a.W * 64)
+                word = reinterpret_cast<const uint32_t *>(a.words_in + (i0 + (lane >> 3)) * a.W)[(wave_first >> 5) + (lane & 7)];
+            sc = (lane < nb) ? a.scales_in[i0 + lane] : 0.f;
+        }
+        if (nb == 8) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t w = __shfl(word, i * 8 + (lane >> 3), 64);
+                v = chain4_top(v, w << top_shift, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), i)), a.inv_n);
+            }
+        } else {
+            for (int i = 0; i < nb; ++i) {
+                const uint32_t w = __shfl(word, i * 8 + (lane >> 3), 64);
+                v = chain4_top(v, w << top_shift, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), i)), a.inv_n);
+            }
+        }
+    }
+    return v;
+}
+
+template <bool RMS, int UPD, int R, int L>
+__global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(ServerArgs a, float *delta_s, int64_t d, uint64_t *words_out,
+                                                                            ds_sign_tables tb, double *partials, float *scale_out,
+                                                                            HeldUpdate u, HeldRow *rows, uint32_t *gave_up,
+                                                                            uint32_t patience)
+{
+    constexpr int T = R + L;
+    __shared__ HeldShared<T> m;
+    __shared__ f32x4 far[L ? L : 1][kBlock];
+    const int lane = lane_id();
+    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * T, first = tile0 * kTile;
+    int left = held_left<T>(tile0, d);
+    f32x4 cut = {0.f, 0.f, 0.f, 0.f};
+    int cut_at = -1;
+    if (left & 3) {
+        cut_at = left & ~3;
+        cut = ld4_tail(delta_s, first + cut_at, first + left);
+    }
+    const float sc0 = (lane < a.n && lane < 8) ? a.scales_in[lane] : 0.f;
+    constexpr int D = 4 < T ? 4 : T;
+    f32x4 v[R], ring[L ? D : 1];
+    uint32_t word[D];
+    auto fetch = [&](auto qc) {
+        constexpr int q = decltype(qc)::value, t = q < L ? R + q : q - L;
+        if constexpr (q < L) ring[q % D] = held_ld4<0>(delta_s + first, left, t);
+        else v[t] = held_ld4<0>(delta_s + first, left, t);
+        const int64_t wave_first = first + t * kTile + wave_id() * 256;
+        word[q % D] = 0u;
+        if ((lane >> 3) < a.n && wave_first + 32 * (lane & 7) < a.W * 64)
+            word[q % D] = reinterpret_cast<const uint32_t *>(a.words_in + (lane >> 3) * a.W)[(wave_first >> 5) + (lane & 7)];
+    };
+    static_for<0, D>(fetch);
+    static_for<0, T>([&](auto qc) {
+        constexpr int q = decltype(qc)::value, t = q < L ? R + q : q - L;
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 w;
+        if constexpr (q < L) w = ring[q % D];
+        else w = v[t];
+        const int e = static_cast<int>(threadIdx.x) * 4 + t * kTile;
+        const bool mine = e == cut_at;
+        w.x = mine ? cut.x : w.x;
+        w.y = mine ? cut.y : w.y;
+        w.z = mine ? cut.z : w.z;
+        w = held_chain(w, word[q % D], sc0, a, first + t * kTile + wave_id() * 256);
+        w = zero_past(w, e, left);
+        asm volatile("" : "+v"(w));
+        cut.x = mine ? w.x : cut.x;
+        cut.y = mine ? w.y : cut.y;
+        cut.z = mine ? w.z : cut.z;
+        if constexpr (q + D < T) fetch(std::integral_constant<int, q + D>{});
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (q < L) far[q][threadIdx.x] = w;
+        else v[t] = w;
+        held_look<RMS, T>(w, t, m);
+    });
+    held_fence(v, left);
+    const bool mine_cut = cut_at >= 0 && (cut_at & (kTile - 1)) == static_cast<int>(threadIdx.x) * 4;   // `cut` holds its v
+    // the update's operands of the first tiles are asked for before the wait
+    constexpr int P = UPD == 0 ? 0 : R <= 2 ? R : R <= 4 ? (UPD == 2 ? 1 : 2) : 0;
+    f32x4 xv[P ? P : 1], mv[P ? P : 1];
+#pragma unroll
+    for (int t = 0; t < P; ++t) {
+        xv[t] = held_ld4<0>(u.x + first, left, t);
+        if constexpr (UPD == 2) mv[t] = held_ld4<0>(u.m + first, left, t);
+    }
+    float s;
+    const bool ok = held_scale<RMS, T>(m, tile0, 0, words_out, tb, partials, scale_out, rows, patience, &s);
+    if (threadIdx.x == 0 && gridDim.x != 1) gave_up[blockIdx.x] = ok ? 0u : 1u;
+    if (!ok) {                                                // uniform
+#pragma unroll
+        for (int t = 0; t < T; ++t) held_st4<0>(delta_s + first, left, t, t < R ? v[t < R ? t : 0] : far[t < R ? 0 : t - R][threadIdx.x]);
+        if (mine_cut) st4_tail(delta_s + first, cut_at, left, cut);
+        return;
+    }
+    // tiles in groups whose operands of the update are asked for together
+    constexpr int G = P ? P : 2;
+#pragma unroll
+    for (int t0 = 0; t0 < T; t0 += G) {
+        f32x4 xg[G], mg[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if constexpr (UPD != 0) {
+                if (t0 + j < P) {
+                    xg[j] = xv[j];
+                    if constexpr (UPD == 2) mg[j] = mv[j];
+                } else if (t0 + j < T) {
+                    xg[j] = held_ld4<0>(u.x + first, left, t0 + j);
+                    if constexpr (UPD == 2) mg[j] = held_ld4<0>(u.m + first, left, t0 + j);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int t = t0 + j;
+            if (t < T) {
+                const f32x4 w = t < R ? v[t < R ? t : 0] : far[(t < R || t >= T) ? 0 : t - R][threadIdx.x];
+                held_st4<0>(delta_s + first, left, t, sign_error4(w, s));
+                if constexpr (UPD != 0) {
+                    held_update4<UPD>(w, xg[j], mg[j], s, u);
+                    held_st4<0>(u.x + first, left, t, xg[j]);
+                    if constexpr (UPD == 2) held_st4<0>(u.m + first, left, t, mg[j]);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (mine_cut) {
+        st4_tail(delta_s + first, cut_at, left, sign_error4(cut, s));
+        if constexpr (UPD != 0) {
+            float *xr = u.x + first, *mr = UPD == 2 ? u.m + first : nullptr;
+            f32x4 xc = ld4_tail(xr, cut_at, left), mc = UPD == 2 ? ld4_tail(mr, cut_at, left) : xc;
+            held_update4<UPD>(cut, xc, mc, s, u);
+            st4_tail(xr, cut_at, left, xc);
+            if constexpr (UPD == 2) st4_tail(mr, cut_at, left, mc);
+        }
+    }
+}
+
+// After a held launch: forms the error (and, where u.x is set, the update) where a workgroup gave up,
+// normally nowhere, and clears the synchronisation words for the next call.  `parts` workgroups of
+// T tiles per row.
 __global__ __launch_bounds__(kBlock) void k_sign_held_finish(float *buf, int64_t stride, int64_t d, const float *__restrict__ scales,
-                                                             int T, int parts, const uint32_t *__restrict__ gave_up, HeldRow *rows)
+                                                             int T, int parts, const uint32_t *__restrict__ gave_up, HeldRow *rows,
+                                                             HeldUpdate u)
 {
     const int row = blockIdx.y;
     const int part0 = blockIdx.x * kFinishParts;
     const int mine = part0 + lane_id();
     uint64_t left = __ballot(mine < parts && gave_up[row * static_cast<int64_t>(parts) + mine] != 0u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        rows[row].clear_for_next_launch();
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) rows[row].clear_for_next_launch();
     if (left == 0) return;
     float *brow = buf + row * stride;
     const float s = scales[row];
@@ -714,7 +886,20 @@ __global__ __launch_bounds__(kBlock) void k_sign_held_finish(float *buf, int64_t
         left &= left - 1;
         for (int t = 0; t < T; ++t) {
             const int64_t e = (tile0 + t) * kTile + threadIdx.x * 4;
-            if (e < d) st4_stream(brow, e, d, sign_error4(ld4_stream(brow, e, d), s));
+            if (e >= d) continue;
+            const f32x4 v = ld4_stream(brow, e, d);
+            st4_stream(brow, e, d, sign_error4(v, s));
+            if (u.x) {
+                f32x4 x4 = ld4_stream(u.x, e, d), m4 = x4;
+                if (u.m) {
+                    m4 = ld4_stream(u.m, e, d);
+                    held_update4<2>(v, x4, m4, s, u);
+                    st4_stream(u.m, e, d, m4);
+                } else {
+                    held_update4<1>(v, x4, m4, s, u);
+                }
+                st4_stream(u.x, e, d, x4);
+            }
         }
     }
 }
@@ -812,7 +997,7 @@ ds_status_t ds_sign_init(ds_ctx *c)
     c->sign_prev_w = c->sign_prev_s = nullptr;
     c->sign_tb_mem = nullptr;
     c->sign_partials = nullptr;
-    c->held = ds_held_sync{};
+    c->held = c->held_s = ds_held_sync{};
     std::vector<int64_t> seg_off;
     if (cfg.scale_mode == DS_SCALE_WHOLE) {
         seg_off = {0, d};
@@ -894,6 +1079,18 @@ ds_status_t ds_sign_init(ds_ctx *c)
             const ds_status_t ra = held_alloc(c, cfg.n, &c->held);
             if (ra != DS_OK) return ra;
         }
+        // the server's block handles one row
+        const ds_status_t rs = c->sid ? DS_OK : held_size(c, 1, [](auto r, auto l) {
+            constexpr int R = decltype(r)::value, L = decltype(l)::value;
+            int per_cu = 0;
+            return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sign_held_server<false, 2, R, L>, kBlock, 0) ==
+                           hipSuccess ? per_cu : -1;
+        }, &c->held_s.T);
+        if (rs != DS_OK) return rs;
+        if (c->held_s.T) {
+            const ds_status_t ra = held_alloc(c, 1, &c->held_s);
+            if (ra != DS_OK) return ra;
+        }
     }
     if ((cfg.flags & DS_FLAG_DEFERRED_ERROR) && !c->nofb) {
         c->sign_defer = true;
@@ -908,6 +1105,7 @@ void ds_sign_fini(ds_ctx *c)
     if (c->sign_tb_mem) (void)hipFree(c->sign_tb_mem);
     if (c->sign_partials) (void)hipFree(c->sign_partials);
     held_free(&c->held);
+    held_free(&c->held_s);
     if (c->sign_prev_w) (void)hipFree(c->sign_prev_w);
     if (c->sign_prev_s) (void)hipFree(c->sign_prev_s);
     c->sign_prev_w = c->sign_prev_s = nullptr;
@@ -956,7 +1154,7 @@ ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, i
         });
         if (h.parts > 1)
             k_sign_held_finish<<<dim3(static_cast<unsigned>((h.parts + kFinishParts - 1) / kFinishParts), rows_n), kBlock, 0, st>>>(
-                delta, dstr, cfg.d, out->scales, h.T, h.parts, h.gave_up, rows);
+                delta, dstr, cfg.d, out->scales, h.T, h.parts, h.gave_up, rows, HeldUpdate{nullptr, nullptr, 0.f, 0.f});
         return ds_launch_status();
     }
     dim3 grid(static_cast<unsigned>(c->n_tiles), static_cast<unsigned>(cfg.n));
@@ -982,7 +1180,7 @@ ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, i
     return rc;
 }
 
-// x != nullptr (chunk route only): the model update for the same elements in the same kernel.
+// x != nullptr (chunk and held routes only): the model update for the same elements in the same kernel.
 ds_status_t ds_sign_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, const ds_payload_t *out,
                            hipStream_t st, float *x, float *m, float gamma, float beta)
 {
@@ -1007,7 +1205,25 @@ ds_status_t ds_sign_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
         if (rms) with_upd(std::true_type{}); else with_upd(std::false_type{});
         return ds_launch_status();
     }
-    if (x) return DS_ERR_UNSUPPORTED;   // the caller asks for the fused form on the chunk route only
+    if (c->held_s.T) {
+        const ds_held_sync &h = c->held_s;
+        HeldRow *rows = static_cast<HeldRow *>(h.rows);
+        const HeldUpdate u{x, m, gamma, beta};
+        with_held(h.T, [&](auto rr, auto ll) {
+            constexpr int R = decltype(rr)::value, L = decltype(ll)::value;
+            with_flags(rms, x != nullptr, m != nullptr, [&](auto rm, auto up, auto mo) {
+                constexpr bool RM = decltype(rm)::value;
+                constexpr int UPD = decltype(up)::value ? (decltype(mo)::value ? 2 : 1) : 0;
+                k_sign_held_server<RM, UPD, R, L><<<static_cast<unsigned>(h.parts), kBlock, 0, st>>>(
+                    a, delta_s, cfg.d, out->sign_words, c->sign_tb, c->sign_partials, out->scales, u, rows, h.gave_up, h.patience);
+            });
+        });
+        if (h.parts > 1)
+            k_sign_held_finish<<<static_cast<unsigned>((h.parts + kFinishParts - 1) / kFinishParts), kBlock, 0, st>>>(
+                delta_s, cfg.d, cfg.d, out->scales, h.T, h.parts, h.gave_up, rows, u);
+        return ds_launch_status();
+    }
+    if (x) return DS_ERR_UNSUPPORTED;   // the caller asks for the fused form on the routes that have it
     dim3 grid(static_cast<unsigned>(c->n_tiles));
     const bool deferred = c->sign_defer && c->sign_s_deferred && delta_s;
     // Deferred form: the buffer is looked at once per call, so it may stream past the caches.

@@ -270,3 +270,52 @@ def test_sign_whole_vector_in_one_look(gpu_device, n, d, dtype, rms, patience):
             assert torch.equal(held, want)
     finally:
         ctx.close()
+
+
+# The server block of the same route, alone and with the update.  The reference is the deferred error
+# form, whose server keeps its launches apart: the message, the materialised error, x and m are
+# equal bit for bit.
+@pytest.mark.parametrize("patience", [0, -1])
+@pytest.mark.parametrize("n,d,momentum,rms", [
+    (1, 3, True, False), (3, 2047, False, False), (9, 2 * 2048 - 1, True, False), (8, 4 * 2048 + 2, False, True), (16, 14 * 2048, True, False),
+    (5, 24 * 2048 - 3, True, False), (12, 25 * 2048 + 1, False, False), (8, 700_002, True, False), (3, 3_000_001, True, False),
+    (3, 5_000_003, False, True), (2, 9_000_002, True, False), (2, 17_000_001, True, False), (1, 23_000_003, False, False)])
+def test_sign_whole_vector_server_in_one_look(gpu_device, n, d, momentum, rms, patience):
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(d)
+    flags = P.FLAG_SIGN_RMS if rms else 0
+    ctxs = [P.Context("sign", n, d, scale_mode="whole", flags=flags | P.FLAG_DEFERRED_ERROR),
+            P.Context("sign", n, d, scale_mode="whole", flags=flags, topk_spin_limit=patience),
+            P.Context("sign", n, d, scale_mode="whole", flags=flags, topk_spin_limit=patience)]
+    try:
+        msg = ctxs[0].alloc_payload(n, gpu_device)
+        err0 = torch.randn(d, device=gpu_device, generator=gen).mul_(1e-3)
+        x0 = torch.randn(d, device=gpu_device, generator=gen)
+        m0 = torch.randn(d, device=gpu_device, generator=gen).mul_(1e-3) if momentum else None
+        beta = 0.9 if momentum else 0.0
+        # a sentinel behind every buffer that is written in place
+        def guarded(t):
+            out = torch.full((d + 8,), 77.0, device=gpu_device)
+            out[:d] = t
+            return out
+        state = [(guarded(err0), guarded(x0), None if m0 is None else guarded(m0), c.alloc_server_payload()) for c in ctxs]
+        for t in range(2):
+            msg.sign_words.copy_(torch.randint(-2 ** 62, 2 ** 62, msg.sign_words.shape, device=gpu_device, generator=gen))
+            msg.scales.copy_(torch.rand(msg.scales.shape, device=gpu_device, generator=gen).mul_(1e-2))
+            for i, (c, (e, x, m, out)) in enumerate(zip(ctxs, state)):
+                mv = None if m is None else m[:d]
+                if i == 1:
+                    c.server_aggregate_compress_update(t, msg, e[:d], out, x[:d], mv, 0.05, beta)
+                else:
+                    c.server_aggregate_compress(t, msg, e[:d], out)
+                    c.apply_update(out, x[:d], mv, 0.05, beta)
+            ctxs[0].materialize_error(None, state[0][0][:d])
+            torch.cuda.synchronize()
+            for i in (1, 2):
+                for name, a, b in zip(("error", "x", "m"), state[0], state[i]):
+                    assert (a is None and b is None) or torch.equal(a, b), (t, i, name)
+                assert torch.equal(state[0][3].sign_words, state[i][3].sign_words), (t, i)
+                assert torch.equal(state[0][3].scales, state[i][3].scales), (t, i)
+    finally:
+        for c in ctxs:
+            c.close()

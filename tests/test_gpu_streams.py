@@ -19,6 +19,7 @@ def _cases():
     return [
         ("sign_chunk", W.c5(d=2048 * 300 + 1280, n=4, n_seg=8), 0),
         ("sign_segments_deferred", W.c2(d=600_002, n=3, n_seg=12, lo=64), P.FLAG_DEFERRED_ERROR),
+        ("sign_whole_held", W.Workload("sign_whole", "sign", n=4, d=3_000_001, dist="normal", sigma=1e-2, gamma=0.05), 0),
         ("qsgd", W.c4(d=2048 * 200 + 40, n=5), 0),
         ("topk_chain", W.c3(d=700_007, n=4), P.FLAG_TOPK_MULTI_LAUNCH),
         ("topk_single_launch", W.c3(d=700_007, n=4), 0),
