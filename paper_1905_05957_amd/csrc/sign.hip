@@ -699,8 +699,8 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
 // error is read and written once, the server's message is not read back.  Compressor, reduce,
 // second look and update as launches of their own took 59 us at 8 x 11,173,962, one launch and its
 // finish take 45 us (30 us for their bytes at the copy kernel's rate; the barrier is not hidden, there
-// is one row).  The buffers are read and written once, but ordinary accesses beat non-temporal
-// ones here at every size: 45 against 49 us, 2 x 24,000,000 78 against 93 us.  With 14 and 24
+// is one row).  Ordinary accesses beat non-temporal ones where server calls follow each other
+// (45 against 49 us, 2 x 24,000,000 78 against 93 us); inside whole steps both take the same.  With 14 and 24
 // tiles per workgroup instead of the smallest size that holds the row, 58 and 60 us.
 struct HeldUpdate {
     float *x, *m;
