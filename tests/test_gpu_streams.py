@@ -61,3 +61,44 @@ def test_two_contexts_on_two_streams(gpu_device, name, wl, flags):
     finally:
         for p in (alone, a, b):
             p.close()
+
+
+def _cleared_cases():
+    """Contexts whose first call depends on words that ds_create clears."""
+    both = P.FLAG_SERVER_IDENTITY | P.FLAG_NO_ERROR_FEEDBACK
+    return [
+        ("sign_whole", W.Workload("sign_whole", "sign", n=4, d=3_000_001, dist="normal", sigma=1e-2, gamma=0.05), 0),
+        ("ternary", W.Workload("ternary", "ternary", n=4, d=3_000_001, dist="normal", sigma=1e-2, gamma=0.05), both),
+        ("topk", W.c3(d=700_007, n=4), 0),
+    ]
+
+
+@pytest.mark.parametrize("name,wl,flags", _cleared_cases(), ids=[c[0] for c in _cleared_cases()])
+def test_first_call_on_a_side_stream_right_after_create(gpu_device, name, wl, flags):
+    """The side stream does not wait for the default stream, which is busy while the context is
+    created; what ds_create clears has to be cleared when it returns."""
+    parity_util.CONTEXT_FLAGS = flags
+    try:
+        a, b = Pair(wl, gpu_device), Pair(wl, gpu_device)
+        g = wl.gradients(0, gpu_device)
+        side = torch.cuda.Stream()
+        a.gpu_step(0, g)
+        src, dst = (torch.zeros(1 << 26, device=gpu_device) for _ in range(2))
+        torch.cuda.synchronize()
+        b.ctx.close()
+        for _ in range(100):                       # some milliseconds of the default stream
+            dst.copy_(src)
+        b.ctx = parity_util.gpu_context(wl)
+        b.ctx.worker_compress(0, g, b.delta, b.pw, stream=side)
+        b.ctx.server_aggregate_compress(0, b.pw, b.delta_s, b.ps, stream=side)
+        b.ctx.apply_update(b.ps, b.x, b.m, wl.gamma, 0.0 if wl.beta is None else wl.beta, stream=side)
+        torch.cuda.synchronize()
+        for key, t in a.pw.tensors().items():
+            assert torch.equal(t, b.pw.tensors()[key]), f"{name} worker {key}"
+        for key, t in a.ps.tensors().items():
+            assert torch.equal(t, b.ps.tensors()[key]), f"{name} server {key}"
+        assert torch.equal(a.x, b.x)
+        a.close()
+        b.close()
+    finally:
+        parity_util.CONTEXT_FLAGS = 0
