@@ -34,6 +34,7 @@ struct ds_tern_scratch;  // defined in ternary.hip
 // What the workgroups of a launch that holds rows on chip share (held.h); T == 0: not taken.
 struct ds_held_sync {
     int T, parts;          // tiles per workgroup, workgroups per row
+    int64_t slots;         // workgroups that the device holds at once
     void *rows;            // [n] synchronisation words (HeldRow)
     uint32_t *gave_up;     // [n, parts] written by every such launch
     uint32_t patience;     // ticks of the 100 MHz clock a workgroup waits at most

@@ -12,24 +12,40 @@ namespace ds {
 
 // Synchronisation words of one row; published word and counter on cache lines of their own.
 constexpr size_t kHeldRowBytes = 256;
-constexpr int kFinishParts = 64;             // workgroups of a held launch that one of the finish launch looks after
+// A wait that was not answered in time (part of a row had no room beside another stream's workgroups) ends
+// all waits of its call, and nobody waits in the next one either.  If the wait after that is in vain
+// too, two calls go by without one, then four, up to kHeldShy, until a call has all its waits answered:
+// the price of waiting in vain is not paid over and over, and a single late call is soon forgotten.
+// 1-bit worker block at 8 x 11,173,962 with a matrix product running on another stream: 323 .. 338 us a call,
+// 478 .. 496 us when every late call was followed by kHeldShy calls without a wait.
+constexpr uint32_t kHeldShy = 256, kHeldLate = ~0u;
 struct HeldRow {
     DevShared<uint64_t> pub;      // kHeldValue | bits of the row's value, 0 = not there yet
-    DevShared<uint32_t> quit;     // row 0 only: a workgroup of this call gave up, the others do not wait either
-    uint32_t pad0[29];
+    DevShared<uint32_t> quit;     // row 0 only: nobody waits in this call: kHeldLate, or calls left for which that holds
+    uint32_t span;                // row 0 only: calls without a wait after the last late one
+    uint32_t pad0[28];
     DevShared<uint32_t> arrived;
     DevShared<uint32_t> most;     // ternary: largest |v| of the row so far, as bits
     DevShared<uint64_t> kept;     // ternary: workgroups that have encoded << 40 | non-zero codes
     DevShared<uint64_t> sum;      // ternary: sum of |v| over the row, fp64 bits
     uint32_t pad1[26];
 
-    // after a launch, in the next one
-    __device__ __forceinline__ void clear_for_next_launch()
+    // in the finish launch, by one thread per row
+    __device__ __forceinline__ void next_call(bool first_row)
     {
         pub.clear_for_next_launch();
-        quit.clear_for_next_launch();
         arrived.clear_for_next_launch();
         most.clear_for_next_launch();
+        if (!first_row) return;
+        const uint32_t q = quit.load();
+        if (q == kHeldLate) {
+            span = (span == 0u) ? 1u : (span < kHeldShy) ? 2u * span : kHeldShy;
+            quit.store(span);
+        } else if (q != 0u) {
+            quit.store(q - 1u);
+        } else {
+            span = 0u;
+        }
     }
 };
 static_assert(sizeof(HeldRow) == kHeldRowBytes, "as allocated by the host");
@@ -46,7 +62,7 @@ __device__ __forceinline__ bool held_wait(HeldRow *rows, int row, uint32_t patie
             if (v & kHeldValue) break;
             if ((polls & 7u) == 0u) {
                 if (rows[0].quit.load() != 0u) break;
-                if (wall_clock64() - t0 >= static_cast<long long>(patience)) { rows[0].quit.store(1u); break; }
+                if (wall_clock64() - t0 >= static_cast<long long>(patience)) { rows[0].quit.store(kHeldLate); break; }
             }
             __builtin_amdgcn_s_sleep(8);
         }
@@ -154,13 +170,13 @@ static void with_held(int T, F f)
 //    (8 x 16,000,000: 302 us, 14 tiles 314 us, 399 us in two looks; 8 x 24,000,000: 451 us, 619 us
 //    in two looks).
 template <class F>
-static ds_status_t held_size(const ds_ctx *c, int64_t rows, F per_cu, int *T_out)
+static ds_status_t held_size(const ds_ctx *c, int64_t rows, F per_cu, ds_held_sync *sync)
 {
     int cus = 0;
     DS_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
     const int64_t tiles = c->n_tiles;
     const bool one = tiles <= kHeldT[5];
-    *T_out = 0;
+    sync->T = 0;
     for (int T : kHeldT) {
         if (one && tiles > T) continue;
         int held = 0;
@@ -168,7 +184,7 @@ static ds_status_t held_size(const ds_ctx *c, int64_t rows, F per_cu, int *T_out
         if (held < 0) return DS_ERR_DEVICE;
         const int64_t slots = static_cast<int64_t>(held) * cus, parts = (tiles + T - 1) / T;
         const int64_t at_once = one ? 1 : (T == 24) ? 1 : (T == 14 && rows > 4) ? 4 : rows;   // rows to be held
-        if (at_once * parts <= slots) { *T_out = T; return DS_OK; }
+        if (at_once * parts <= slots) { sync->T = T; sync->slots = slots; return DS_OK; }
     }
     return DS_OK;
 }
@@ -177,9 +193,12 @@ static ds_status_t held_size(const ds_ctx *c, int64_t rows, F per_cu, int *T_out
 static ds_status_t held_alloc(const ds_ctx *c, int32_t rows, ds_held_sync *sync)
 {
     const size_t n = static_cast<size_t>(rows);
-    // a wait: 20 us and four times what a row's bytes take, in ticks of the 100 MHz clock
-    sync->patience = (c->cfg.topk_spin_limit < 0) ? 0u : static_cast<uint32_t>(2000 + c->cfg.d / 1000);
     sync->parts = static_cast<int>((c->n_tiles + sync->T - 1) / sync->T);
+    // A wait, in ticks of the 100 MHz clock: 20 us, and 10 ps (eight bytes at 0.8 TB/s) for every element of
+    // the rows that are loaded at the same time, which share the bandwidth: those that the device
+    // holds and the one whose workgroups come in as others leave.
+    const int64_t together = sync->slots / sync->parts + 1;
+    sync->patience = (c->cfg.topk_spin_limit < 0) ? 0u : static_cast<uint32_t>(2000 + (rows < together ? rows : together) * c->cfg.d / 1000);
     DS_HIP_TRY(hipMalloc(&sync->rows, kHeldRowBytes * n));
     DS_HIP_TRY(hipMemset(sync->rows, 0, kHeldRowBytes * n));
     DS_HIP_TRY(hipMalloc(&sync->gave_up, sizeof(uint32_t) * n * static_cast<size_t>(sync->parts)));

@@ -341,34 +341,31 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
     tern_count_in(kept, sm.cnt, rows + row, gridDim.x, row_sum_alone, scales + row);
 }
 
-// After a held launch: encodes what a workgroup that gave up did not (normally nothing) and clears
-// the synchronisation words for the next call.
+// After a held launch: encodes what a workgroup that gave up did not (normally nothing), one workgroup
+// for each of them, and readies the synchronisation words for the next call.  8 x 11,173,962 with all
+// waits given up: 172 us, 1259 us with one finishing workgroup for 64 of the held launch.
 template <bool BF16>
 __global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int64_t gs, int64_t d, const float *rowmax, TernKey K,
-                                                             uint64_t *neg, uint64_t *nz, int64_t W, float *scales, int T, int parts,
+                                                             uint64_t *neg, uint64_t *nz, int64_t W, float *scales, int T,
                                                              const uint32_t *gave_up, HeldRow *rows)
 {
     __shared__ uint32_t cnt[kWaves];
-    const int row = blockIdx.y;
-    const int part0 = blockIdx.x * kFinishParts, mine = part0 + lane_id();
-    uint64_t left = __ballot(mine < parts && gave_up[row * static_cast<int64_t>(parts) + mine] != 0u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) rows[row].clear_for_next_launch();
-    if (left == 0) return;
+    const int row = blockIdx.y, part = blockIdx.x;
+    if (part == 0 && threadIdx.x == 0) rows[row].next_call(row == 0);
+    if (gave_up[row * static_cast<int64_t>(gridDim.x) + part] == 0u) return;
     const void *grow = grad_row<BF16>(g, gs, row);
     const float m = rowmax[row];
-    while (left) {
-        const int64_t tile0 = static_cast<int64_t>(part0 + __builtin_ctzll(left)) * T;
-        left &= left - 1;
-        uint32_t kept = 0;
-        for (int t = 0; t < T; ++t) {
-            const int64_t tile_first = (tile0 + t) * kTile, e = tile_first + threadIdx.x * 4;
-            const uint32_t code = tern_codes4(ld4_grad<BF16>(grow, e, d), m, e, d, row, K);
-            tern_put_words(code, tile_first, neg + row * W, nz + row * W, W * 64);
-            kept += __popc(code & 15u);
-        }
-        tern_count_in(kept, cnt, rows + row, parts, 0.0, scales + row);
-        __syncthreads();                                      // cnt is used again
+    uint32_t kept = 0;
+    f32x4 next = ld4_grad<BF16>(grow, static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4, d);
+    for (int t = 0; t < T; ++t) {
+        const int64_t tile_first = (static_cast<int64_t>(part) * T + t) * kTile, e = tile_first + threadIdx.x * 4;
+        const f32x4 v = next;
+        if (t + 1 < T) next = ld4_grad<BF16>(grow, e + kTile, d);       // zero past the end of the row
+        const uint32_t code = tern_codes4(v, m, e, d, row, K);
+        tern_put_words(code, tile_first, neg + row * W, nz + row * W, W * 64);
+        kept += __popc(code & 15u);
     }
+    tern_count_in(kept, cnt, rows + row, gridDim.x, 0.0, scales + row);
 }
 
 // code * scale of elements e..e+3 of one message
@@ -423,7 +420,7 @@ ds_status_t ds_ternary_init(ds_ctx *c)
         constexpr int R = decltype(r)::value, L = decltype(l)::value;
         int per_cu = 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tern_held<false, R, L>, kBlock, 0) == hipSuccess ? per_cu : -1;
-    }, &t->held.T);
+    }, &t->held);
     if (rc != DS_OK) return rc;
     // Encoding is bound by vector instructions and wants wavefronts, of which the largest size
     // leaves half; it pays only where the second look would come from memory.  8 x 11,173,962 fp32
@@ -461,7 +458,7 @@ ds_status_t ds_ternary_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
         const ds_held_sync &h = t->held;
         HeldRow *rows = static_cast<HeldRow *>(h.rows);
         const TernKey K{key0, key1, static_cast<uint32_t>(step)};
-        const dim3 hgrid(static_cast<unsigned>(h.parts), n), fgrid(static_cast<unsigned>((h.parts + kFinishParts - 1) / kFinishParts), n);
+        const dim3 hgrid(static_cast<unsigned>(h.parts), n);
         auto go = [&](auto bf) {
             constexpr bool BF = decltype(bf)::value;
             with_held(h.T, [&](auto rr, auto ll) {
@@ -470,8 +467,8 @@ ds_status_t ds_ternary_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
                                                                 out->sign_words, nz, c->W, out->scales, rows, h.gave_up, h.patience);
             });
             if (h.parts > 1)
-                k_tern_held_finish<BF><<<fgrid, kBlock, 0, st>>>(g, gs, d, t->rowmax, K, out->sign_words, nz, c->W, out->scales, h.T,
-                                                                 h.parts, h.gave_up, rows);
+                k_tern_held_finish<BF><<<hgrid, kBlock, 0, st>>>(g, gs, d, t->rowmax, K, out->sign_words, nz, c->W, out->scales, h.T,
+                                                                 h.gave_up, rows);
         };
         if (bf16) go(std::true_type{}); else go(std::false_type{});
         return ds_launch_status();

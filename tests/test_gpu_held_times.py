@@ -1,0 +1,82 @@
+"""GPU: times of the route that holds rows on chip, against the launches that it stands for and in the
+forms that a working program does not normally reach.  The bounds leave a factor to the noise of a shared
+machine; what they catch is a fallback or a choice of size that costs several times the plain way."""
+import pytest
+import torch
+
+import paper_1905_05957_amd as P
+
+pytestmark = pytest.mark.gpu
+
+NOFB_SID = P.FLAG_NO_ERROR_FEEDBACK | P.FLAG_SERVER_IDENTITY
+
+
+def best_us(call, calls=10, runs=5):
+    """GPU time of one call of a captured run of calls, the best of `runs`."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        for _ in range(calls):
+            call()
+    best = float("inf")
+    for _ in range(runs):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+class Sign:
+    """Buffers and calls of one 1-bit context with one scale per vector."""
+
+    def __init__(self, dev, n, d, dtype="f32", **kw):
+        gen = torch.Generator(device=dev)
+        gen.manual_seed(d)
+        self.ctx = P.Context("sign", n, d, grad_dtype=dtype, scale_mode="whole", **kw)
+        self.g = torch.randn((n, d), device=dev, generator=gen).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        self.delta = torch.zeros((n, d), device=dev)
+        self.delta_s, self.x = torch.zeros(d, device=dev), torch.zeros(d, device=dev)
+        self.msg, self.out = self.ctx.alloc_payload(n, dev), self.ctx.alloc_server_payload(dev)
+        self.ctx.worker_compress(0, self.g, self.delta, self.msg)
+
+    def worker(self):
+        self.ctx.worker_compress(0, self.g, self.delta, self.msg)
+
+    def two_looks(self):
+        P.ds_worker_compress_sign_noalloc(self.g, self.delta, self.msg.sign_words, self.msg.scales)
+
+    def server(self):
+        self.ctx.server_aggregate_compress_update(0, self.msg, self.delta_s, self.out, self.x, None, 0.05)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_worker_call_that_gives_up_costs_what_two_looks_cost(gpu_device, dtype):
+    s = Sign(gpu_device, 8, 11_173_962, dtype, topk_spin_limit=-1)
+    gave_up, plain = best_us(s.worker), best_us(s.two_looks)
+    s.ctx.close()
+    assert gave_up < 2.0 * plain, (gave_up, plain)
+
+
+def test_a_server_call_that_gives_up_costs_what_separate_launches_cost(gpu_device):
+    s = Sign(gpu_device, 8, 11_173_962, topk_spin_limit=-1)
+    apart = Sign(gpu_device, 8, 11_173_962, flags=P.FLAG_DEFERRED_ERROR)
+    gave_up, plain = best_us(s.server), best_us(apart.server)
+    s.ctx.close()
+    apart.ctx.close()
+    assert gave_up < 2.5 * plain, (gave_up, plain)     # the separate launches look once at the error
+
+
+def test_a_ternary_call_that_gives_up(gpu_device):
+    n, d = 8, 11_173_962
+    g = torch.randn((n, d), device=gpu_device)
+    us = []
+    for patience in (0, -1):
+        ctx = P.Context("ternary", n, d, flags=NOFB_SID, topk_spin_limit=patience)
+        msg = ctx.alloc_payload(n, gpu_device)
+        us.append(best_us(lambda: ctx.worker_compress(0, g, None, msg)))
+        ctx.close()
+    assert us[1] < 2.5 * us[0], us                      # the gradients are read once more and encoded apart

@@ -272,6 +272,26 @@ def test_sign_whole_vector_in_one_look(gpu_device, n, d, dtype, rms, patience):
         ctx.close()
 
 
+def test_sign_whole_vector_over_many_calls_that_give_up(gpu_device):
+    """Late calls are followed by 1, 2, 4, ... calls in which nobody waits (patience -1: every call that
+    waits is late): 40 calls go through six such stretches and keep the bits of two looks."""
+    n, d = 3, 200_003
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(1)
+    g = torch.randn((n, d), device=gpu_device, generator=gen)
+    ctx = P.Context("sign", n, d, scale_mode="whole", topk_spin_limit=-1)
+    try:
+        msg = ctx.alloc_payload(n, gpu_device)
+        held, want = torch.zeros_like(g), torch.zeros_like(g)
+        words, scales = torch.zeros_like(msg.sign_words), torch.zeros_like(msg.scales)
+        for t in range(40):
+            ctx.worker_compress(t, g, held, msg)
+            P.ds_worker_compress_sign_noalloc(g, want, words, scales)
+            assert torch.equal(msg.sign_words, words) and torch.equal(msg.scales, scales) and torch.equal(held, want), t
+    finally:
+        ctx.close()
+
+
 # The server block of the same route, alone and with the update.  The reference is the deferred error
 # form, whose server keeps its launches apart: the message, the materialised error, x and m are
 # equal bit for bit.
