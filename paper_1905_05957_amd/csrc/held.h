@@ -159,32 +159,46 @@ static void with_held(int T, F f)
     }
 }
 
-// Tiles per workgroup for `rows` rows, 0 = the device cannot hold a row; per_cu(R, L): resident
-// workgroups of that kernel per compute unit, negative on failure.  Measured on the 1-bit worker block:
-//  * a row that fits one workgroup: the smallest size that holds it.  Nobody waits and the finish
-//    launch falls away (8 x 16,000: 10.4 us a call against 12.9 us with one tile per workgroup);
-//  * else the smallest size with which the device holds all rows at once: most workgroups, no row
-//    waits for room (7 x 2,345,679: 72, 42, 35, 38 us with 2, 4, 8, 14 tiles, of which 8 is the
-//    first that holds all);
-//  * else 14 tiles if that holds four rows (8 x 5,000,003: 88 us, 24 tiles 93 us), 24 otherwise
-//    (8 x 16,000,000: 302 us, 14 tiles 314 us, 399 us in two looks; 8 x 24,000,000: 451 us, 619 us
-//    in two looks).
-template <class F>
-static ds_status_t held_size(const ds_ctx *c, int64_t rows, F per_cu, ds_held_sync *sync)
+// One line of a kernel's choice of size: `T` tiles per workgroup if the device holds `rows` rows at once
+// (all, if they are fewer or 0 stands here) and a row is not more than `parts` workgroups (0: any number).
+struct HeldStep {
+    int T, rows, parts;
+};
+
+// Tiles per workgroup for `rows` rows, 0 = the kernel's way in separate launches; per_cu(R, L): resident
+// workgroups of that kernel per compute unit, negative on failure.  A row of at most `one` tiles is left to
+// one workgroup, of the smallest size that holds it: nobody waits and the finish launch falls away, but
+// the tiles come one after the other, and a size pays for all the tiles that it is built for.  For
+// longer rows the first step that holds is taken.  What speaks for a size:
+//  * more workgroups have more loads in flight, and a row that is on chip as a whole does not wait for
+//    room: the smallest size with which all rows are there at once, or else a few rows, so that one row's loads
+//    overlap another's barrier and stores;
+//  * the arrivals of a row's workgroups are additions to one word, which come one after the other (11 ns
+//    each), so short rows take fewer workgroups than the device would hold.
+// The lines lie where the kernels were measured to cross over; the figures stand with each kernel's steps.
+template <class F, int N>
+static ds_status_t held_size(const ds_ctx *c, int64_t rows, int one, const HeldStep (&steps)[N], F per_cu, ds_held_sync *sync)
 {
     int cus = 0;
     DS_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
     const int64_t tiles = c->n_tiles;
-    const bool one = tiles <= kHeldT[5];
     sync->T = 0;
-    for (int T : kHeldT) {
-        if (one && tiles > T) continue;
+    auto take = [&](int T, int64_t at_once, int64_t most) {
         int held = 0;
         with_held(T, [&](auto r, auto l) { held = per_cu(r, l); });
         if (held < 0) return DS_ERR_DEVICE;
         const int64_t slots = static_cast<int64_t>(held) * cus, parts = (tiles + T - 1) / T;
-        const int64_t at_once = one ? 1 : (T == 24) ? 1 : (T == 14 && rows > 4) ? 4 : rows;   // rows to be held
-        if (at_once * parts <= slots) { sync->T = T; sync->slots = slots; return DS_OK; }
+        if (at_once * parts <= slots && parts <= most) { sync->T = T; sync->slots = slots; }
+        return DS_OK;
+    };
+    if (tiles <= one) {
+        for (int T : kHeldT)
+            if (tiles <= T) return take(T, 1, 1);
+    }
+    for (const HeldStep &s : steps) {
+        if (s.T == 0) break;
+        const ds_status_t rc = take(s.T, (s.rows && s.rows < rows) ? s.rows : rows, s.parts ? s.parts : tiles);
+        if (rc != DS_OK || sync->T) return rc;
     }
     return DS_OK;
 }

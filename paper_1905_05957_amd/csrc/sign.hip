@@ -1072,7 +1072,18 @@ ds_status_t ds_sign_init(ds_ctx *c)
     if (hipGetLastError() != hipSuccess) return DS_ERR_DEVICE;
     DS_HIP_TRY(hipMalloc(&c->sign_partials, sizeof(double) * n_pieces * static_cast<size_t>(cfg.n)));
     if (S == 1 && !c->nofb && !(cfg.flags & DS_FLAG_DEFERRED_ERROR)) {
-        const ds_status_t rc = held_size(c, cfg.n, [](auto r, auto l) {
+        // Worker.  GPU time of a call, n = 1 .. 16, against two looks as separate launches and one tile per workgroup:
+        //  * one workgroup, fp32, 12 tiles in 14: 7.4 .. 8.2 us, 7.7 .. 9.5 and 6.7 .. 8.1 us, and a launch less for the
+        //    host (11 us a call in a stream of calls, 13 us with the finish launch); 16 to 24 tiles in 24: 11.1 .. 12.1 us,
+        //    7.3 .. 10.9 and 6.5 .. 8.3 us.  bf16, 8 tiles in 8: 6.3 .. 7.3 us, 7.3 .. 8.8 and 6.5 .. 7.8 us; 12 tiles in 14:
+        //    9.0 .. 9.9 us, 7.8 .. 9.5 and 6.8 .. 8.1 us;
+        //  * 1 x 1,000,003: 12.8, 10.3, 9.1 and 9.7 us with 1, 2, 4 and 8 tiles, 10.1 us in two looks; 4 x 300,001: 9.8, 8.8
+        //    and 9.2 us with 1, 2 and 4;
+        //  * 7 x 2,345,679: 72, 42, 35, 38 us with 2, 4, 8, 14 tiles, of which 8 is the first that holds all rows;
+        //  * 8 x 5,000,003: 88 us with 14, 93 us with 24 tiles; 8 x 16,000,000: 352 and 333 us, 541 us in two looks;
+        //    8 x 24,000,000: 454 us with 24, 619 us in two looks.
+        static constexpr HeldStep worker[] = {{1, 0, 128}, {2, 0, 128}, {4, 0, 0}, {8, 0, 0}, {14, 4, 0}, {24, 1, 0}};
+        const ds_status_t rc = held_size(c, cfg.n, cfg.grad_dtype == DS_BF16 ? 8 : 14, worker, [](auto r, auto l) {
             constexpr int R = decltype(r)::value, L = decltype(l)::value;
             int per_cu = 0;
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sign_held_worker<false, false, R, L>, kBlock, 0) ==
@@ -1083,8 +1094,24 @@ ds_status_t ds_sign_init(ds_ctx *c)
             const ds_status_t ra = held_alloc(c, cfg.n, &c->held);
             if (ra != DS_OK) return ra;
         }
-        // the server's block handles one row
-        const ds_status_t rs = c->sid ? DS_OK : held_size(c, 1, [](auto r, auto l) {
+        // The server's block handles one row, and the chain over the workers comes once per tile, so that the more
+        // workers there are, the more workgroups are wanted.  GPU time of server and update against
+        // separate launches:
+        //  * one workgroup: 4 tiles in 4, n = 1 .. 16: 5.7 .. 8.9 us, 9.2 .. 9.9 us (one tile per workgroup 6.6 .. 7.5 us, but
+        //    13 us instead of 11 us a call in a stream of calls); 8 tiles in 8: 8.7 .. 15.5 us, 9.0 .. 10.0 us; 24 tiles in
+        //    24: 22 .. 42 us, 9.1 .. 10.1 us; n = 64: 2 tiles in 2 12.0 us, 12.7 us, in two workgroups 10.3 us;
+        //  * d = 1,000,003, n = 1: 13.7, 11.4 and 11.4 us with 1, 2 and 4 tiles, 13.1 us; n = 16: 14.7, 13.2 and 14.7, 14.6 us;
+        //  * d = 8,000,002: 35 us with 4 tiles, 47 us (n = 8), 53 and 61 us (n = 32), 77.6 and 80.8 us (n = 64), 185 and 174 us
+        //    (n = 200); d = 16,000,001, 8 tiles: 57 and 80 us (n = 8), 95 and 107 us (n = 32); 11,173,962 and n = 64: 113 and
+        //    106 us; d = 2,500,001, 2 tiles: 35.0 and 35.6 us (n = 64), 77 and 68 us (n = 200).
+        static constexpr HeldStep few[] = {{1, 0, 256}, {2, 0, 256}, {4, 0, 0}, {8, 0, 0}, {14, 0, 0}, {24, 0, 0}};
+        static constexpr HeldStep upto16[] = {{1, 0, 256}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {14, 0, 0}, {24, 0, 0}};
+        static constexpr HeldStep upto32[] = {{1, 0, 256}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        static constexpr HeldStep upto64[] = {{1, 0, 0}, {2, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        static constexpr HeldStep many[] = {{1, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        const int n = cfg.n, one = n <= 16 ? 4 : n <= 32 ? 2 : 1;
+        const auto &server = n <= 8 ? few : n <= 16 ? upto16 : n <= 32 ? upto32 : n <= 64 ? upto64 : many;
+        const ds_status_t rs = c->sid ? DS_OK : held_size(c, 1, one, server, [](auto r, auto l) {
             constexpr int R = decltype(r)::value, L = decltype(l)::value;
             int per_cu = 0;
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sign_held_server<false, 2, R, L>, kBlock, 0) ==

@@ -416,7 +416,8 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     DS_HIP_TRY(hipMalloc(&t->pcnt, n * tiles * sizeof(uint32_t)));
     DS_HIP_TRY(hipMalloc(&t->rowmax, n * sizeof(float)));
     DS_HIP_TRY(hipMalloc(&t->rowsum, n * sizeof(double)));
-    const ds_status_t rc = held_size(c, c->cfg.n, [](auto r, auto l) {
+    static constexpr HeldStep steps[] = {{1, 0, 0}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {14, 4, 0}, {24, 1, 0}};
+    const ds_status_t rc = held_size(c, c->cfg.n, 24, steps, [](auto r, auto l) {
         constexpr int R = decltype(r)::value, L = decltype(l)::value;
         int per_cu = 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tern_held<false, R, L>, kBlock, 0) == hipSuccess ? per_cu : -1;

@@ -67,7 +67,37 @@ def test_a_server_call_that_gives_up_costs_what_separate_launches_cost(gpu_devic
     gave_up, plain = best_us(s.server), best_us(apart.server)
     s.ctx.close()
     apart.ctx.close()
-    assert gave_up < 2.5 * plain, (gave_up, plain)     # the separate launches look once at the error
+    assert gave_up < 2.5 * plain, (gave_up, plain)     # `plain` looks once at the error
+
+
+# Short rows and rows of few workers, where a launch costs as much as the work: the sizes that are taken may
+# not cost more than the launches that they stand for.
+@pytest.mark.parametrize("n", [1, 8, 16])
+@pytest.mark.parametrize("d,dtype", [(4 * 2048, "bf16"), (8 * 2048 - 2, "f32"), (12 * 2048, "bf16"), (14 * 2048 - 3, "f32"), (20 * 2048 + 1, "f32"),
+                                     (24 * 2048, "f32"), (24 * 2048 - 1, "bf16"), (30 * 2048, "f32"), (300_001, "f32"), (1_000_003, "f32")])
+def test_a_short_row_costs_no_more_than_two_looks(gpu_device, n, d, dtype):
+    s = Sign(gpu_device, n, d, dtype)
+    held, plain = best_us(s.worker, 30), best_us(s.two_looks, 30)
+    s.ctx.close()
+    assert held < 1.25 * plain, (held, plain)
+
+
+@pytest.mark.parametrize("n,d", [(1, 4 * 2048), (8, 4 * 2048), (16, 4 * 2048), (64, 2 * 2048), (1, 8 * 2048), (8, 12 * 2048), (16, 16 * 2048),
+                                 (4, 24 * 2048), (16, 24 * 2048), (4, 1_000_003), (200, 2_500_001), (64, 11_173_962)])
+def test_a_server_call_costs_no_more_than_separate_launches(gpu_device, n, d):
+    us = []
+    for flags in (0, P.FLAG_DEFERRED_ERROR):
+        ctx = P.Context("sign", n, d, scale_mode="whole", flags=flags)
+        msg, out = ctx.alloc_payload(n, gpu_device), ctx.alloc_server_payload(gpu_device)
+        delta_s, x = torch.zeros(d, device=gpu_device), torch.zeros(d, device=gpu_device)
+
+        def call():     # the deferred form and its second look: the launches of the plain form, apart
+            ctx.server_aggregate_compress_update(0, msg, delta_s, out, x, None, 0.05)
+            ctx.materialize_error(None, delta_s)
+
+        us.append(best_us(call, 30))
+        ctx.close()
+    assert us[0] < 1.15 * us[1], us
 
 
 def test_a_ternary_call_that_gives_up(gpu_device):
