@@ -25,17 +25,17 @@ struct HeldRow {
     uint32_t span;                // row 0 only: calls without a wait after the last late one
     uint32_t pad0[28];
     DevShared<uint32_t> arrived;
-    DevShared<uint32_t> most;     // ternary: largest |v| of the row so far, as bits
-    DevShared<uint64_t> kept;     // ternary: workgroups that have encoded << 40 | non-zero codes
-    DevShared<uint64_t> sum;      // ternary: sum of |v| over the row, fp64 bits
-    uint32_t pad1[26];
+    DevShared<uint32_t> late;     // ternary: a workgroup of the row gave up
+    DevShared<uint32_t> done;     // ternary: workgroups of the finish launch that are through with the row
+    uint32_t pad1[29];
 
     // in the finish launch, by one thread per row
     __device__ __forceinline__ void next_call(bool first_row)
     {
         pub.clear_for_next_launch();
         arrived.clear_for_next_launch();
-        most.clear_for_next_launch();
+        late.clear_for_next_launch();
+        done.clear_for_next_launch();
         if (!first_row) return;
         const uint32_t q = quit.load();
         if (q == kHeldLate) {

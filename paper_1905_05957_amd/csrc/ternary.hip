@@ -97,14 +97,15 @@ struct TernKey {
     uint32_t key0, key1, step_lo;
 };
 
-// Codes of elements e..e+3: bit c = code is not 0, bit 4 + c = code is -1.  The encoding is bound by
+// Codes of the four elements of group `quad` of the row (elements 4 quad ..), of which `left` (at most 4) belong
+// to it: bit c = code is not 0, bit 4 + c = code is -1.  The encoding is bound by
 // vector instructions, and four IEEE divisions were a third of them.  With U = 2^24 u a whole
 // number and q = |v| * fl(2^24 / m), which is within 2^-22 of 2^24 fl(|v| / m), U outside
 // q (1 -+ 2^-20) (and, for U = 0, q above 2^-20) decides u < fl(|v| / m) without the quotient; what
 // lies inside, NaN included, and rows whose maximum leaves the range of that product divide.
-__device__ __forceinline__ uint32_t tern_codes4(f32x4 v, float m, int64_t e, int64_t d, int row, TernKey K)
+__device__ __forceinline__ uint32_t tern_codes4(f32x4 v, float m, uint32_t quad, int left, int row, TernKey K)
 {
-    const u32x4 rnd = philox4x32_10(u32x4{static_cast<uint32_t>(e >> 2), 0u, static_cast<uint32_t>(row), K.step_lo}, K.key0, K.key1);
+    const u32x4 rnd = philox4x32_10(u32x4{quad, 0u, static_cast<uint32_t>(row), K.step_lo}, K.key0, K.key1);
     const float vv[4] = {v.x, v.y, v.z, v.w};
     const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
     const bool in_range = m >= 0x1p-100f && m <= 0x1p100f;      // uniform
@@ -125,7 +126,7 @@ __device__ __forceinline__ uint32_t tern_codes4(f32x4 v, float m, int64_t e, int
             nz |= ((open >> c) & 1u) && keep ? 1u << c : 0u;
         }
     }
-    nz &= (e + 4 <= d) ? 15u : (e < d) ? (1u << (d - e)) - 1u : 0u;
+    nz &= (left >= 4) ? 15u : (left > 0) ? (1u << left) - 1u : 0u;
     const uint32_t neg = (vv[0] < 0.f ? 1u : 0u) | (vv[1] < 0.f ? 2u : 0u) | (vv[2] < 0.f ? 4u : 0u) | (vv[3] < 0.f ? 8u : 0u);
     return nz | ((nz & neg) << 4);
 }
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(kBlock) void k_tern_encode(const void *g, int64_t g
     const void *grow = grad_row<BF16>(g, gs, row);
     const f32x4 v = ld4_grad<BF16>(grow, e, d);
     const float m = rowmax[row];
-    const uint32_t code = tern_codes4(v, m, e, d, row, TernKey{key0, key1, step_lo});
+    const uint32_t code = tern_codes4(v, m, static_cast<uint32_t>(e >> 2), static_cast<int>(d - e), row, TernKey{key0, key1, step_lo});
     stash_sign_words(sw_nz, wave_nibble_word(code & 15u));
     stash_sign_words(sw_neg, wave_nibble_word(code >> 4));
     const uint32_t kept = wave_sum_u32(static_cast<uint32_t>(__popc(code & 15u)));
@@ -179,10 +180,18 @@ __global__ __launch_bounds__(kBlock) void k_tern_scale(const uint32_t *pcnt, con
 // ---------------------------------------------------------------------------------------
 // A workgroup keeps T consecutive tiles in registers and LDS, hands over their sums and maximum,
 // waits for the row's maximum, which the workgroup that arrives last publishes, and encodes what
-// it holds; the workgroup that encodes last writes the scale.  Waits are bounded, and what a
-// workgroup that gave up did not encode the finish launch does (held.h).  Worker call at
-// 8 x 11,173,962: 189 us in two looks with four divisions per thread, 169 us in two looks without
-// them, 153 us here (57 us for its bytes at the copy kernel's rate).
+// it holds and leaves its count of kept codes for the finish launch, which writes the scale.  Waits are
+// bounded, and what a workgroup that gave up did not encode the finish launch does (held.h).  The arrival
+// is the only word that all workgroups of a row add to: such additions come one after the other, about
+// 11 ns each, and with the maximum and the count as two more of them a call at 1 x 1,000,003 took 24.9, 16.9 and
+// 13.8 us with 1, 2 and 4 tiles per workgroup.  Worker call at
+// 8 x 11,173,962: 189 us in two looks with four divisions per thread, 164 us in two looks without
+// them, 149 us here (57 us for its bytes at the copy kernel's rate).
+__device__ __forceinline__ float tern_scale(double sum, uint32_t kept)
+{
+    return kept ? static_cast<float>(sum / static_cast<double>(kept)) : 0.f;
+}
+
 template <int T>
 struct TernShared {
     double sums[T][kWaves], red[kWaves];
@@ -190,41 +199,33 @@ struct TernShared {
     uint32_t cnt[kWaves], sh[2];
 };
 
-// The wavefront's words of one tile to both planes.
-__device__ __forceinline__ void tern_put_words(uint32_t code, int64_t tile_first, uint64_t *neg_row, uint64_t *nz_row, int64_t bit_lim)
+// The wavefront's words of one tile to both planes: word of an 8-lane group, by its first lane.  Rows have
+// fewer than 2^31 elements and a stretch reaches less than 2^31 past their end: 32 bits number the groups of
+// four and their bits.
+__device__ __forceinline__ void tern_put_words(uint32_t code, uint32_t quad, uint64_t *neg_row, uint64_t *nz_row, uint32_t words)
 {
-    const uint32_t a = wave_nibble_word(code & 15u), b = wave_nibble_word(code >> 4);
-    const int64_t bit = tile_first + threadIdx.x * 4;         // first element of this lane; word of an 8-lane group: its first lane
-    if ((lane_id() & 7) == 0 && bit < bit_lim) {
-        reinterpret_cast<uint32_t *>(nz_row)[bit >> 5] = a;
-        reinterpret_cast<uint32_t *>(neg_row)[bit >> 5] = b;
+    const uint32_t a = wave_nibble_word(code & 15u), b = wave_nibble_word(code >> 4), w = quad >> 3;
+    if ((lane_id() & 7) == 0 && w < words) {
+        reinterpret_cast<uint32_t *>(nz_row)[w] = a;
+        reinterpret_cast<uint32_t *>(neg_row)[w] = b;
     }
 }
 
-// Counts the workgroup's non-zero codes in; the workgroup that completes the row writes its scale.
-// `kept` is per thread; `sum` = sum |v| of a row that is one workgroup's.  Every thread calls.
-__device__ __forceinline__ void tern_count_in(uint32_t kept, uint32_t *cnt, HeldRow *row_sync, int parts, double sum, float *scale_out)
+// Non-zero codes of the workgroup, in thread 0.  Every thread calls, with its own.
+__device__ __forceinline__ uint32_t tern_kept(uint32_t kept, uint32_t *cnt)
 {
     kept = wave_sum_u32(kept);
     if (lane_id() == 0) cnt[wave_id()] = kept;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    uint64_t total = 0;
+    uint32_t total = cnt[0];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) total += cnt[w];
-    if (parts > 1) {
-        const uint64_t before = row_sync->kept.fetch_add((1ull << 40) | total);
-        if ((before >> 40) + 1u != static_cast<uint64_t>(parts)) return;
-        total += before & ((1ull << 40) - 1u);
-        row_sync->kept.store(0u);                             // nobody counts in any more
-        sum = __longlong_as_double(static_cast<long long>(row_sync->sum.load()));
-    }
-    *scale_out = total ? static_cast<float>(sum / static_cast<double>(total)) : 0.f;
+    for (int w = 1; w < kWaves; ++w) total += cnt[w];
+    return total;
 }
 
 template <bool BF16, int R, int L>
 __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void *g, int64_t gs, int64_t d, int32_t n_tiles, double *psum,
-                                                                     float *rowmax, TernKey K, uint64_t *neg, uint64_t *nz, int64_t W,
+                                                                     float *pmax, uint32_t *pcnt, float *rowmax, double *rowsum, TernKey K, uint64_t *neg, uint64_t *nz, int64_t W,
                                                                      float *scales, HeldRow *rows, uint32_t *gave_up, uint32_t patience)
 {
     constexpr int T = R + L;
@@ -266,6 +267,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
         else v[t] = w;
         const float a0 = fabsf(w.x), a1 = fabsf(w.y), a2 = fabsf(w.z), a3 = fabsf(w.w);
         mx = fmaxf(mx, fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)));
+        asm volatile("" : "+v"(mx));      // now: put off to the end, the maximum keeps |v| of all tiles in registers
         const double s = wave_sum(((static_cast<double>(a0) + static_cast<double>(a1)) + static_cast<double>(a2)) + static_cast<double>(a3));
         if (lane_id() == 0) sm.sums[t][wave_id()] = s;
     });
@@ -289,10 +291,11 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
         row_sum_alone = wave_sum(tile_sum);
     } else {
         uint64_t *psum_row = reinterpret_cast<uint64_t *>(psum) + static_cast<int64_t>(row) * n_tiles;
+        uint32_t *pmax_row = reinterpret_cast<uint32_t *>(pmax) + static_cast<int64_t>(row) * n_tiles;   // one per workgroup
         if (wave_id() == 0) {
             if (lane_id() < T && tile0 + lane_id() < n_tiles)
                 as_shared(psum_row)[tile0 + lane_id()].store(__double_as_longlong(tile_sum));
-            if (lane_id() == 0) rows[row].most.raise_to(__float_as_uint(mx));     // not negative: ordered like its bits
+            if (lane_id() == 0) as_shared(pmax_row)[blockIdx.x].store(__float_as_uint(mx));
             // both are in memory before the arrival is announced
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane_id() == 0) sm.sh[0] = (rows[row].arrived.fetch_add(1u) + 1u == gridDim.x) ? 1u : 0u;
@@ -307,65 +310,98 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
             for (int32_t p = threadIdx.x; p < n_tiles; p += kBlock)
                 acc += __longlong_as_double(static_cast<long long>(as_shared(psum_row)[p].load()));
             const double total = block_sum(acc, sm.red, false);
-            mx = __uint_as_float(rows[row].most.load());
-            if (threadIdx.x == 0) {
-                rowmax[row] = mx;                             // for the finish launch
-                rows[row].sum.store(__double_as_longlong(total));
-                // the sum is in memory before anyone can count in
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                rows[row].pub.store(kHeldValue | __float_as_uint(mx));
+            if (wave_id() == 0) {
+                for (uint32_t p = lane_id(); p < gridDim.x; p += 64) mx = fmaxf(mx, __uint_as_float(as_shared(pmax_row)[p].load()));
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+                if (lane_id() == 0) {
+                    rowmax[row] = mx;                         // for the finish launch
+                    rowsum[row] = total;
+                    rows[row].pub.store(kHeldValue | __float_as_uint(mx));
+                    sm.sh[1] = __float_as_uint(mx);
+                }
             }
+            __syncthreads();
+            mx = __uint_as_float(sm.sh[1]);
         }
-        if (threadIdx.x == 0) gave_up[row * static_cast<int64_t>(gridDim.x) + blockIdx.x] = ok ? 0u : 1u;
+        if (threadIdx.x == 0) {
+            gave_up[row * static_cast<int64_t>(gridDim.x) + blockIdx.x] = ok ? 0u : 1u;
+            if (!ok) rows[row].late.store(1u);
+        }
         if (!ok) return;                                      // uniform
     }
     held_fence(v, left);
-    const int64_t bit_lim = W * 64;
+    const uint32_t words = static_cast<uint32_t>(W) * 2u, quad0 = static_cast<uint32_t>(first >> 2) + threadIdx.x;
     uint64_t *neg_row = neg + row * W, *nz_row = nz + row * W;
     uint32_t kept = 0;
+    auto encode = [&](f32x4 w, int t) {
+        const uint32_t quad = quad0 + t * (kTile / 4);
+        const uint32_t code = tern_codes4(w, mx, quad, left - t * kTile - static_cast<int>(threadIdx.x) * 4, row, K);
+        tern_put_words(code, quad, neg_row, nz_row, words);
+        kept += __popc(code & 15u);
+    };
 #pragma unroll
     for (int t = 0; t < R; ++t) {
-        const int64_t e = first + t * kTile + threadIdx.x * 4;
-        const uint32_t code = tern_codes4(v[t], mx, e, d, row, K);
-        tern_put_words(code, first + t * kTile, neg_row, nz_row, bit_lim);
-        kept += __popc(code & 15u);
+        encode(v[t], t);
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll 1
-    for (int t = R; t < T; ++t) {
-        const int64_t e = first + t * kTile + threadIdx.x * 4;
-        const uint32_t code = tern_codes4(far[t - R][threadIdx.x], mx, e, d, row, K);
-        tern_put_words(code, first + t * kTile, neg_row, nz_row, bit_lim);
-        kept += __popc(code & 15u);
-    }
-    tern_count_in(kept, sm.cnt, rows + row, gridDim.x, row_sum_alone, scales + row);
+    for (int t = R; t < T; ++t) encode(far[t - R][threadIdx.x], t);
+    kept = tern_kept(kept, sm.cnt);
+    if (threadIdx.x != 0) return;
+    if (alone) scales[row] = tern_scale(row_sum_alone, kept);
+    else pcnt[static_cast<int64_t>(row) * n_tiles + blockIdx.x] = kept;    // added up by the finish launch
 }
 
-// After a held launch: encodes what a workgroup that gave up did not (normally nothing), one workgroup
-// for each of them, and readies the synchronisation words for the next call.  8 x 11,173,962 with all
-// waits given up: 172 us, 1259 us with one finishing workgroup for 64 of the held launch.
+// After a held launch: writes the scale of every row from the counts of its workgroups and readies the
+// synchronisation words for the next call.  In a row in which a workgroup gave up (normally none) one
+// workgroup for each of them encodes what it held, and the one that is through last adds up.
+// 8 x 11,173,962 with all waits given up: 172 us, 1259 us with one finishing workgroup for 64 of
+// the held launch.
 template <bool BF16>
-__global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int64_t gs, int64_t d, const float *rowmax, TernKey K,
-                                                             uint64_t *neg, uint64_t *nz, int64_t W, float *scales, int T,
+__global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int64_t gs, int64_t d, int32_t n_tiles, uint32_t *pcnt,
+                                                             const float *rowmax, const double *rowsum, TernKey K, uint64_t *neg,
+                                                             uint64_t *nz, int64_t W, float *scales, int T,
                                                              const uint32_t *gave_up, HeldRow *rows)
 {
-    __shared__ uint32_t cnt[kWaves];
+    __shared__ uint32_t cnt[kWaves], last;
     const int row = blockIdx.y, part = blockIdx.x;
-    if (part == 0 && threadIdx.x == 0) rows[row].next_call(row == 0);
-    if (gave_up[row * static_cast<int64_t>(gridDim.x) + part] == 0u) return;
-    const void *grow = grad_row<BF16>(g, gs, row);
-    const float m = rowmax[row];
-    uint32_t kept = 0;
-    f32x4 next = ld4_grad<BF16>(grow, static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4, d);
-    for (int t = 0; t < T; ++t) {
-        const int64_t tile_first = (static_cast<int64_t>(part) * T + t) * kTile, e = tile_first + threadIdx.x * 4;
-        const f32x4 v = next;
-        if (t + 1 < T) next = ld4_grad<BF16>(grow, e + kTile, d);       // zero past the end of the row
-        const uint32_t code = tern_codes4(v, m, e, d, row, K);
-        tern_put_words(code, tile_first, neg + row * W, nz + row * W, W * 64);
-        kept += __popc(code & 15u);
+    DevWord *cnt_row = as_shared(pcnt + static_cast<int64_t>(row) * n_tiles);
+    const bool late = rows[row].late.load() != 0u;            // uniform: nobody clears it before all have come by here
+    if (!late && part != 0) return;
+    if (late) {
+        uint32_t kept = 0;
+        const bool mine = gave_up[row * static_cast<int64_t>(gridDim.x) + part] != 0u;
+        if (mine) {
+            const void *grow = grad_row<BF16>(g, gs, row);
+            const float m = rowmax[row];
+            f32x4 next = ld4_grad<BF16>(grow, static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4, d);
+            for (int t = 0; t < T; ++t) {
+                const int64_t e = (static_cast<int64_t>(part) * T + t) * kTile + threadIdx.x * 4;
+                const uint32_t quad = static_cast<uint32_t>(e >> 2);
+                const f32x4 v = next;
+                if (t + 1 < T) next = ld4_grad<BF16>(grow, e + kTile, d);       // zero past the end of the row
+                const uint32_t code = tern_codes4(v, m, quad, static_cast<int>(d - e), row, K);
+                tern_put_words(code, quad, neg + row * W, nz + row * W, static_cast<uint32_t>(W) * 2u);
+                kept += __popc(code & 15u);
+            }
+        }
+        kept = tern_kept(kept, cnt);
+        if (threadIdx.x == 0) {
+            if (mine) cnt_row[part].store(kept);
+            // the count is in memory before it is announced
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            last = (rows[row].done.fetch_add(1u) + 1u == gridDim.x) ? 1u : 0u;
+        }
+        __syncthreads();
+        if (last == 0u) return;                               // uniform
     }
-    tern_count_in(kept, cnt, rows + row, gridDim.x, 0.0, scales + row);
+    uint32_t kept = 0;
+    for (uint32_t p = threadIdx.x; p < gridDim.x; p += kBlock) kept += cnt_row[p].load();
+    kept = tern_kept(kept, cnt);                              // not more than d: 32 bits hold it
+    if (threadIdx.x != 0) return;
+    scales[row] = tern_scale(rowsum[row], kept);
+    rows[row].next_call(row == 0);
 }
 
 // code * scale of elements e..e+3 of one message
@@ -416,20 +452,28 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     DS_HIP_TRY(hipMalloc(&t->pcnt, n * tiles * sizeof(uint32_t)));
     DS_HIP_TRY(hipMalloc(&t->rowmax, n * sizeof(float)));
     DS_HIP_TRY(hipMalloc(&t->rowsum, n * sizeof(double)));
-    static constexpr HeldStep steps[] = {{1, 0, 0}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {14, 4, 0}, {24, 1, 0}};
-    const ds_status_t rc = held_size(c, c->cfg.n, 24, steps, [](auto r, auto l) {
+    // GPU time of a worker call, two looks as separate launches against sizes of the held route.  In a stream of
+    // calls the four launches of two looks also cost the host 17 us, the two of this route 12 us, and the one of a
+    // row that one workgroup holds 10 us.
+    //  * one workgroup, 8 tiles in 8: 7.8 .. 8.1 us (bf16 8.9 .. 9.4), two looks 8.9 .. 10.6 us; 12 tiles in 14: 11.5 .. 11.9 us
+    //    (bf16 13.1 .. 13.5), 9.0 .. 10.6 us;
+    //  * one row gains on the host's side only: d = 300,001 9.1 us, with 2 tiles 10.1 us; 1,000,003 10.1 us, with 1, 2, 4
+    //    and 8 tiles 16.0, 12.9, 12.1 and 13.7 us; 2,500,001 13.3 us, with 4 and 8 tiles 16.6 and 16.2 us;
+    //  * n = 8: 300,001 13.1 us, 1, 2 and 4 tiles 18.7, 12.2 and 12.7 us; 1,000,003 23.3 us, 4 and 8 tiles 18.0 and 17.9 us;
+    //    2,500,001 44 us, 8, 14 and 24 tiles 39, 35 and 37 us; 5,000,003 78, 69, 63 and 69 us;
+    //  * 8,000,002, two and more rows on chip: n = 8 121 us, 8 and 24 tiles 113 and 109 us; bf16 125, 119 and 133 us;
+    //    8 x 11,173,962 164 us, 24 tiles (two rows) 149 us, 8 tiles (a row and a half) 197 us; bf16 171 and 173 us;
+    //    8 x 16,000,001, not two rows with any size: 231 us, 24 tiles 273 us.
+    static constexpr HeldStep one_row[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+    static constexpr HeldStep f32[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {24, 2, 0}};
+    static constexpr HeldStep bf16[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {8, 2, 0}};
+    const auto &steps = c->cfg.n == 1 ? one_row : c->cfg.grad_dtype == DS_BF16 ? bf16 : f32;
+    const ds_status_t rc = held_size(c, c->cfg.n, 8, steps, [](auto r, auto l) {
         constexpr int R = decltype(r)::value, L = decltype(l)::value;
         int per_cu = 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tern_held<false, R, L>, kBlock, 0) == hipSuccess ? per_cu : -1;
     }, &t->held);
     if (rc != DS_OK) return rc;
-    // Encoding is bound by vector instructions and wants wavefronts, of which the largest size
-    // leaves half; it pays only where the second look would come from memory.  8 x 11,173,962 fp32
-    // (358 MB): 153 us a call against 169 us in two looks; 3 x 16,000,001 (192 MB, the second look
-    // comes from the 256 MB memory-side cache): 111 against 96 us.  The smaller sizes always pay
-    // (4 x 5,000,000: 39 against 45 us, 4 x 60,000: 12.6 against 16.6 us).
-    const size_t grad_bytes = n * static_cast<size_t>(c->cfg.d) * (c->cfg.grad_dtype == DS_BF16 ? 2 : 4);
-    if (t->held.T == 24 && tiles > 24 && grad_bytes <= (static_cast<size_t>(256) << 20)) t->held.T = 0;
     return t->held.T ? held_alloc(c, c->cfg.n, &t->held) : DS_OK;
 }
 
@@ -464,12 +508,13 @@ ds_status_t ds_ternary_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
             constexpr bool BF = decltype(bf)::value;
             with_held(h.T, [&](auto rr, auto ll) {
                 constexpr int R = decltype(rr)::value, L = decltype(ll)::value;
-                k_tern_held<BF, R, L><<<hgrid, kBlock, 0, st>>>(g, gs, d, static_cast<int32_t>(n_tiles), t->psum, t->rowmax, K,
+                k_tern_held<BF, R, L><<<hgrid, kBlock, 0, st>>>(g, gs, d, static_cast<int32_t>(n_tiles), t->psum, t->pmax, t->pcnt, t->rowmax,
+                                                                t->rowsum, K,
                                                                 out->sign_words, nz, c->W, out->scales, rows, h.gave_up, h.patience);
             });
             if (h.parts > 1)
-                k_tern_held_finish<BF><<<hgrid, kBlock, 0, st>>>(g, gs, d, t->rowmax, K, out->sign_words, nz, c->W, out->scales, h.T,
-                                                                 h.gave_up, rows);
+                k_tern_held_finish<BF><<<hgrid, kBlock, 0, st>>>(g, gs, d, static_cast<int32_t>(n_tiles), t->pcnt, t->rowmax, t->rowsum, K,
+                                                                 out->sign_words, nz, c->W, out->scales, h.T, h.gave_up, rows);
         };
         if (bf16) go(std::true_type{}); else go(std::false_type{});
         return ds_launch_status();
