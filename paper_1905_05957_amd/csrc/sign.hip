@@ -1103,14 +1103,16 @@ ds_status_t ds_sign_init(ds_ctx *c)
         //  * d = 1,000,003, n = 1: 13.7, 11.4 and 11.4 us with 1, 2 and 4 tiles, 13.1 us; n = 16: 14.7, 13.2 and 14.7, 14.6 us;
         //  * d = 8,000,002: 35 us with 4 tiles, 47 us (n = 8), 53 and 61 us (n = 32), 77.6 and 80.8 us (n = 64), 185 and 174 us
         //    (n = 200); d = 16,000,001, 8 tiles: 57 and 80 us (n = 8), 95 and 107 us (n = 32); 11,173,962 and n = 64: 113 and
-        //    106 us; d = 2,500,001, 2 tiles: 35.0 and 35.6 us (n = 64), 77 and 68 us (n = 200).
+        //    106 us; d = 2,500,001, 2 tiles: 35.0 and 35.6 us (n = 64), 77 and 68 us (n = 200);
+        //  * d = 18,000,001 with momentum, 14 tiles: 132 and 134 us (n = 20), 155 and 147 us (n = 32); d = 24,000,000, 24 tiles:
+        //    171 and 172 us (n = 20), 200 and 188 us (n = 32).
         static constexpr HeldStep few[] = {{1, 0, 256}, {2, 0, 256}, {4, 0, 0}, {8, 0, 0}, {14, 0, 0}, {24, 0, 0}};
-        static constexpr HeldStep upto16[] = {{1, 0, 256}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {14, 0, 0}, {24, 0, 0}};
+        static constexpr HeldStep upto24[] = {{1, 0, 256}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {14, 0, 0}, {24, 0, 0}};
         static constexpr HeldStep upto32[] = {{1, 0, 256}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {0, 0, 0}, {0, 0, 0}};
         static constexpr HeldStep upto64[] = {{1, 0, 0}, {2, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
         static constexpr HeldStep many[] = {{1, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
         const int n = cfg.n, one = n <= 16 ? 4 : n <= 32 ? 2 : 1;
-        const auto &server = n <= 8 ? few : n <= 16 ? upto16 : n <= 32 ? upto32 : n <= 64 ? upto64 : many;
+        const auto &server = n <= 8 ? few : n <= 24 ? upto24 : n <= 32 ? upto32 : n <= 64 ? upto64 : many;
         const ds_status_t rs = c->sid ? DS_OK : held_size(c, 1, one, server, [](auto r, auto l) {
             constexpr int R = decltype(r)::value, L = decltype(l)::value;
             int per_cu = 0;
