@@ -172,9 +172,8 @@ ds_status_t ds_create(const ds_config_t *cfg, ds_ctx_t **out)
     // The words that kernels expect cleared were cleared on the default stream.  The clear may be
     // asynchronous to the host, and a stream that does not wait for the default stream would not
     // wait for it either: the first call on such a stream could meet what the memory held before.
-    if (rc == DS_OK && (cfg->comp == DS_COMP_SIGN || cfg->comp == DS_COMP_TOPK || cfg->comp == DS_COMP_TERNARY) &&
-        hipStreamSynchronize(nullptr) != hipSuccess)
-        rc = DS_ERR_DEVICE;
+    const bool cleared = cfg->comp == DS_COMP_TOPK || cfg->comp == DS_COMP_TERNARY || c->held.T || c->held_s.T;
+    if (rc == DS_OK && cleared && hipStreamSynchronize(nullptr) != hipSuccess) rc = DS_ERR_DEVICE;
     if (rc != DS_OK) {
         ds_destroy(c);
         return rc;

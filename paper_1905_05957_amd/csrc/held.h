@@ -213,16 +213,15 @@ static ds_status_t held_alloc(const ds_ctx *c, int32_t rows, ds_held_sync *sync)
     // holds and the one whose workgroups come in as others leave.
     const int64_t together = sync->slots / sync->parts + 1;
     sync->patience = (c->cfg.topk_spin_limit < 0) ? 0u : static_cast<uint32_t>(2000 + (rows < together ? rows : together) * c->cfg.d / 1000);
-    DS_HIP_TRY(hipMalloc(&sync->rows, kHeldRowBytes * n));
+    DS_HIP_TRY(hipMalloc(&sync->rows, kHeldRowBytes * n + sizeof(uint32_t) * n * static_cast<size_t>(sync->parts)));
     DS_HIP_TRY(hipMemset(sync->rows, 0, kHeldRowBytes * n));
-    DS_HIP_TRY(hipMalloc(&sync->gave_up, sizeof(uint32_t) * n * static_cast<size_t>(sync->parts)));
+    sync->gave_up = reinterpret_cast<uint32_t *>(static_cast<char *>(sync->rows) + kHeldRowBytes * n);
     return DS_OK;
 }
 
 static void held_free(ds_held_sync *sync)
 {
     if (sync->rows) (void)hipFree(sync->rows);
-    if (sync->gave_up) (void)hipFree(sync->gave_up);
     *sync = ds_held_sync{};
 }
 

@@ -1019,52 +1019,57 @@ ds_status_t ds_sign_init(ds_ctx *c)
     const int64_t S = static_cast<int64_t>(seg_off.size()) - 1;
     c->S = S;
     const int64_t n_tiles = c->n_tiles;
-    std::vector<int32_t> tile_piece_first(n_tiles + 1), piece_seg, seg_piece_first(S + 1);
-    std::vector<int2> tile_info(n_tiles);
-    std::vector<int64_t> piece_start;
-    int64_t s = 0;
-    for (int64_t t = 0; t < n_tiles; ++t) {
-        const int64_t lo = t * kTile, hi = (lo + kTile < d) ? lo + kTile : d;
-        tile_piece_first[t] = static_cast<int32_t>(piece_start.size());
-        int64_t pos = lo;
-        while (pos < hi) {
-            while (seg_off[s + 1] <= pos) ++s;
-            if (pos == seg_off[s]) seg_piece_first[s] = static_cast<int32_t>(piece_start.size());
-            piece_start.push_back(pos);
-            piece_seg.push_back(static_cast<int32_t>(s));
-            pos = (seg_off[s + 1] < hi) ? seg_off[s + 1] : hi;
+    // One group for the whole vector: a piece is a tile, and the kernels read none of the tables.  Uploading them
+    // was most of the time to create such a context.
+    int64_t n_pieces = n_tiles;
+    if (S > 1) {
+        std::vector<int32_t> tile_piece_first(n_tiles + 1), piece_seg, seg_piece_first(S + 1);
+        std::vector<int2> tile_info(n_tiles);
+        std::vector<int64_t> piece_start;
+        int64_t s = 0;
+        for (int64_t t = 0; t < n_tiles; ++t) {
+            const int64_t lo = t * kTile, hi = (lo + kTile < d) ? lo + kTile : d;
+            tile_piece_first[t] = static_cast<int32_t>(piece_start.size());
+            int64_t pos = lo;
+            while (pos < hi) {
+                while (seg_off[s + 1] <= pos) ++s;
+                if (pos == seg_off[s]) seg_piece_first[s] = static_cast<int32_t>(piece_start.size());
+                piece_start.push_back(pos);
+                piece_seg.push_back(static_cast<int32_t>(s));
+                pos = (seg_off[s + 1] < hi) ? seg_off[s + 1] : hi;
+            }
         }
-    }
-    const int64_t n_pieces = static_cast<int64_t>(piece_seg.size());
-    if (n_pieces > 0x7FFFFFFF) return DS_ERR_SHAPE;
-    tile_piece_first[n_tiles] = static_cast<int32_t>(n_pieces);
-    seg_piece_first[S] = static_cast<int32_t>(n_pieces);
-    piece_start.push_back(d);
-    for (int64_t t = 0; t < n_tiles; ++t) {
-        const int32_t p0 = tile_piece_first[t], cnt = tile_piece_first[t + 1] - p0;
-        tile_info[t] = int2{p0, cnt == 1 ? piece_seg[p0] : -cnt};
-    }
+        n_pieces = static_cast<int64_t>(piece_seg.size());
+        if (n_pieces > 0x7FFFFFFF) return DS_ERR_SHAPE;
+        tile_piece_first[n_tiles] = static_cast<int32_t>(n_pieces);
+        seg_piece_first[S] = static_cast<int32_t>(n_pieces);
+        piece_start.push_back(d);
+        for (int64_t t = 0; t < n_tiles; ++t) {
+            const int32_t p0 = tile_piece_first[t], cnt = tile_piece_first[t + 1] - p0;
+            tile_info[t] = int2{p0, cnt == 1 ? piece_seg[p0] : -cnt};
+        }
 
-    // one allocation: int64 arrays first (8-byte aligned), then the int32 arrays
-    const size_t b_ps = sizeof(int64_t) * (n_pieces + 1), b_so = sizeof(int64_t) * (S + 1);
-    const size_t b_tpf = sizeof(int32_t) * (n_tiles + 1), b_pseg = sizeof(int32_t) * n_pieces;
-    const size_t b_spf = sizeof(int32_t) * (S + 1), b_ti = sizeof(int2) * n_tiles;
-    char *mem = nullptr;
-    DS_HIP_TRY(hipMalloc(&mem, b_ps + b_so + b_ti + b_tpf + b_pseg + b_spf));
-    c->sign_tb_mem = mem;
-    char *p = mem;
-    auto put = [&](const void *src, size_t bytes) -> const void * {
-        const void *at = p;
-        if (bytes) (void)hipMemcpy(p, src, bytes, hipMemcpyHostToDevice);
-        p += bytes;
-        return at;
-    };
-    c->sign_tb.piece_start = static_cast<const int64_t *>(put(piece_start.data(), b_ps));
-    c->sign_tb.seg_off = static_cast<const int64_t *>(put(seg_off.data(), b_so));
-    c->sign_tb.tile_info = static_cast<const int2 *>(put(tile_info.data(), b_ti));
-    c->sign_tb.tile_piece_first = static_cast<const int32_t *>(put(tile_piece_first.data(), b_tpf));
-    c->sign_tb.piece_seg = static_cast<const int32_t *>(put(piece_seg.data(), b_pseg));
-    c->sign_tb.seg_piece_first = static_cast<const int32_t *>(put(seg_piece_first.data(), b_spf));
+        // one allocation: int64 arrays first (8-byte aligned), then the int32 arrays
+        const size_t b_ps = sizeof(int64_t) * (n_pieces + 1), b_so = sizeof(int64_t) * (S + 1);
+        const size_t b_tpf = sizeof(int32_t) * (n_tiles + 1), b_pseg = sizeof(int32_t) * n_pieces;
+        const size_t b_spf = sizeof(int32_t) * (S + 1), b_ti = sizeof(int2) * n_tiles;
+        char *mem = nullptr;
+        DS_HIP_TRY(hipMalloc(&mem, b_ps + b_so + b_ti + b_tpf + b_pseg + b_spf));
+        c->sign_tb_mem = mem;
+        char *p = mem;
+        auto put = [&](const void *src, size_t bytes) -> const void * {
+            const void *at = p;
+            if (bytes) (void)hipMemcpy(p, src, bytes, hipMemcpyHostToDevice);
+            p += bytes;
+            return at;
+        };
+        c->sign_tb.piece_start = static_cast<const int64_t *>(put(piece_start.data(), b_ps));
+        c->sign_tb.seg_off = static_cast<const int64_t *>(put(seg_off.data(), b_so));
+        c->sign_tb.tile_info = static_cast<const int2 *>(put(tile_info.data(), b_ti));
+        c->sign_tb.tile_piece_first = static_cast<const int32_t *>(put(tile_piece_first.data(), b_tpf));
+        c->sign_tb.piece_seg = static_cast<const int32_t *>(put(piece_seg.data(), b_pseg));
+        c->sign_tb.seg_piece_first = static_cast<const int32_t *>(put(seg_piece_first.data(), b_spf));
+    }
     c->sign_tb.n_pieces = static_cast<int32_t>(n_pieces);
     c->sign_tb.n_seg = static_cast<int32_t>(S);
     c->sign_tb.rms = (cfg.flags & DS_FLAG_SIGN_RMS) != 0;

@@ -16,7 +16,7 @@ struct Clear {
     size_t bytes;
 };
 std::vector<Clear> pending;
-int queries, allocations, live;
+int allocations, clears, copies, live;
 
 void carry_out()
 {
@@ -44,15 +44,15 @@ int hipFree(void *p)
 }
 int hipHostMalloc(void **p, size_t bytes, unsigned) { return hipMalloc(p, bytes); }
 int hipHostFree(void *p) { return hipFree(p); }
-int hipMemset(void *at, int value, size_t bytes) { pending.push_back({at, value, bytes}); return 0; }
-int hipMemcpy(void *dst, const void *src, size_t bytes, int) { carry_out(); memcpy(dst, src, bytes); return 0; }
+int hipMemset(void *at, int value, size_t bytes) { ++clears; pending.push_back({at, value, bytes}); return 0; }
+int hipMemcpy(void *dst, const void *src, size_t bytes, int) { ++copies; carry_out(); memcpy(dst, src, bytes); return 0; }
 int hipStreamSynchronize(void *) { carry_out(); return 0; }
 int hipDeviceSynchronize() { carry_out(); return 0; }
 int hipGetLastError() { return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipSetDevice(int) { return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *, int, size_t) { ++queries; *v = 4; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *, int, size_t) { *v = 4; return 0; }
 }
 
 namespace {
@@ -83,6 +83,16 @@ void cleared_before_the_first_call(const char *name, const ds_config_t &cfg)
     ds_destroy(c);
     expect(live == 0, "everything is given back", name);
 }
+// what creating a context asks of the runtime: allocations, and transfers that the host waits for
+void creation_cost(const char *name, const ds_config_t &cfg, int most_allocations, int most_transfers)
+{
+    allocations = clears = copies = 0;
+    ds_ctx_t *c = nullptr;
+    expect(ds_create(&cfg, &c) == DS_OK, "is created", name);
+    expect(allocations <= most_allocations, "allocations", name);
+    expect(clears + copies <= most_transfers, "clears and copies", name);
+    ds_destroy(c);
+}
 }  // namespace
 
 int main()
@@ -94,5 +104,12 @@ int main()
     cleared_before_the_first_call("top-k", config(DS_COMP_TOPK, 4, 300001));
     cleared_before_the_first_call("qsgd", config(DS_COMP_QSGD, 4, 300001));
     cleared_before_the_first_call("rsparse", config(DS_COMP_RSPARSE, 4, 300001));
+
+    // before the 1-bit context with one scale held rows on chip it made 2 allocations and 6 copies, the ternary one
+    // 5 allocations
+    creation_cost("sign, one scale, one workgroup", config(DS_COMP_SIGN, 4, 1024), 3, 2);
+    creation_cost("sign, one scale, many workgroups", config(DS_COMP_SIGN, 8, 11173962), 3, 2);
+    creation_cost("sign, one scale, rows beyond the device", config(DS_COMP_SIGN, 2, 60000000), 1, 0);
+    creation_cost("ternary", config(DS_COMP_TERNARY, 8, 11173962, nofb_sid), 6, 1);
     return bad ? 1 : 0;
 }
