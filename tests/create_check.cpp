@@ -1,12 +1,17 @@
-// ds_create and ds_destroy against a stand-in for the HIP runtime, without a GPU: the functions below
+// The library's host side against a stand-in for the HIP runtime, without a GPU: the functions below
 // take the place of the runtime's (an executable's symbols come first), device memory is host
-// memory, and a clear is carried out when something waits for the default stream, as late as the
-// runtime may do it.  Called by test_create_cpu.py; exit status 0 and one line per check.
+// memory, a clear is carried out when something waits for the default stream, as late as the
+// runtime may do it, and a launch is written down instead of carried out.  Called by test_create_cpu.py:
+//   create_check           ds_create and ds_destroy; one line per check, exit status 0 if all hold
+//   create_check launches  reads "block comp n d dtype flags" lines (block w: worker, s: server and update in one
+//                          call) and prints the launches of that call: name and grid, one line each, then a dot
 #include "../include/ds.h"
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
+#include <string>
 #include <vector>
 
 namespace {
@@ -17,6 +22,28 @@ struct Clear {
 };
 std::vector<Clear> pending;
 int allocations, clears, copies, live;
+
+struct Grid {
+    unsigned x, y, z;
+};
+// functions by their address in the host program, filled in while the library is loaded
+std::map<const void *, std::string> &kernels()
+{
+    static std::map<const void *, std::string> k;
+    return k;
+}
+
+// Workgroups of 512 threads per compute unit: those that hold R tiles in registers and L in LDS are built for
+// 64, 80 and 128 registers.
+int resident(const void *f)
+{
+    const std::string &name = kernels()[f];
+    const size_t at = name.find("_held"), end = name.find("EEEv", at == std::string::npos ? 0 : at);
+    if (at == std::string::npos || end == std::string::npos) return 4;
+    const size_t l = name.rfind("Li", end), r = name.rfind("Li", l - 1);
+    const int in_registers = atoi(name.c_str() + r + 2);
+    return in_registers <= 4 ? 4 : in_registers <= 8 ? 3 : 2;
+}
 
 void carry_out()
 {
@@ -52,7 +79,40 @@ int hipGetLastError() { return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipSetDevice(int) { return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *, int, size_t) { *v = 4; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *f, int, size_t) { *v = resident(f); return 0; }
+
+void **__hipRegisterFatBinary(const void *)
+{
+    static void *module;
+    return &module;
+}
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipRegisterFunction(void **, const void *f, char *, const char *name, unsigned, void *, void *, void *, void *, int *)
+{
+    kernels()[f] = name;
+}
+int hipGetSymbolAddress(void **, const void *) { return 1; }
+static Grid pushed[2];
+int __hipPushCallConfiguration(Grid grid, Grid block, size_t, void *)
+{
+    pushed[0] = grid;
+    pushed[1] = block;
+    return 0;
+}
+int __hipPopCallConfiguration(Grid *grid, Grid *block, size_t *lds, void **stream)
+{
+    *grid = pushed[0];
+    *block = pushed[1];
+    *lds = 0;
+    *stream = nullptr;
+    return 0;
+}
+int hipLaunchKernel(const void *f, Grid grid, Grid, void **, size_t, void *)
+{
+    printf("%s %u %u\n", kernels()[f].c_str(), grid.x, grid.y);
+    return 0;
+}
 }
 
 namespace {
@@ -93,10 +153,38 @@ void creation_cost(const char *name, const ds_config_t &cfg, int most_allocation
     expect(clears + copies <= most_transfers, "clears and copies", name);
     ds_destroy(c);
 }
+int launches()
+{
+    char block;
+    int comp, n, dtype, flags;
+    long long d;
+    while (scanf(" %c %d %d %lld %d %d", &block, &comp, &n, &d, &dtype, &flags) == 6) {
+        ds_config_t cfg = config(comp, n, d, flags);
+        cfg.grad_dtype = dtype;
+        ds_ctx_t *c = nullptr;
+        if (ds_create(&cfg, &c) != DS_OK) return 1;
+        // never read or written: no launch is carried out
+        alignas(16) static char any[16];
+        ds_payload_t p;
+        p.sign_words = reinterpret_cast<uint64_t *>(any);
+        p.scales = reinterpret_cast<float *>(any);
+        p.levels = reinterpret_cast<uint8_t *>(any);
+        p.pairs = reinterpret_cast<ds_pair_t *>(any);
+        p.dense = reinterpret_cast<float *>(any);
+        float *f = reinterpret_cast<float *>(any);
+        const ds_status_t rc = block == 'w' ? ds_worker_compress(c, 0, any, d, f, d, &p, nullptr)
+                                            : ds_server_aggregate_compress_update(c, 0, &p, f, &p, f, f, 0.1f, 0.9f, nullptr);
+        printf(rc == DS_OK ? ".\n" : "failed\n");
+        ds_destroy(c);
+    }
+    return 0;
+}
+
 }  // namespace
 
-int main()
+int main(int argc, char **)
 {
+    if (argc > 1) return launches();
     const int nofb_sid = DS_FLAG_NO_ERROR_FEEDBACK | DS_FLAG_SERVER_IDENTITY;
     cleared_before_the_first_call("sign, one scale", config(DS_COMP_SIGN, 4, 300001));
     cleared_before_the_first_call("sign, one scale, deferred", config(DS_COMP_SIGN, 4, 300001, DS_FLAG_DEFERRED_ERROR));

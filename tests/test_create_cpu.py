@@ -1,24 +1,89 @@
-"""Contexts are created and destroyed against a stand-in for the HIP runtime (create_check.cpp), so
-what ds_create leaves behind is checked without a GPU."""
+"""The library's host side against a stand-in for the HIP runtime (create_check.cpp): what ds_create leaves
+behind, and what is launched for a shape, checked without a GPU."""
 import os
+import re
 import shutil
 import subprocess
 
 import pytest
 
+import held_shapes as H
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.join(os.path.dirname(HERE), "paper_1905_05957_amd")
+SIGN, TERNARY = 1, 6
+RMS, NOFB_SID = 4, 8 | 16
 
 
-def test_create_against_a_stand_in_runtime(tmp_path):
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
-    binary = str(tmp_path / "create_check")
+    binary = str(tmp_path_factory.mktemp("create") / "create_check")
     # -rdynamic: the program's own functions answer for the runtime's
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", os.path.join(HERE, "create_check.cpp"), "-o", binary,
                     "-rdynamic", "-L" + PKG, "-lds_hip", "-Wl,--unresolved-symbols=ignore-in-shared-libs",
                     f"-Wl,-rpath,{PKG}:{rocm}/lib"], check=True)
-    r = subprocess.run([binary], capture_output=True, text=True, timeout=120)
+    return binary
+
+
+def test_create_against_a_stand_in_runtime(program):
+    r = subprocess.run([program], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "FAILED" not in r.stdout and "ok: ternary" in r.stdout, r.stdout + r.stderr
+
+
+def _launches(program, calls):
+    """Per call the list of (kernel, grid x, grid y)."""
+    text = "".join(" ".join(str(v) for v in c) + "\n" for c in calls)
+    r = subprocess.run([program, "launches"], input=text, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "failed" not in r.stdout, r.stdout + r.stderr
+    out = [[(n, int(x), int(y)) for n, x, y in (line.split() for line in block.splitlines())] for block in r.stdout.split("\n.\n")[:-1]]
+    assert len(out) == len(calls)
+    return out
+
+
+def _check(launched, kernel, tiles, workgroups, rows, shape):
+    first, x, y = launched[0]
+    if tiles == 0:
+        assert not any("_held" in n for n, _, _ in launched) and (x, y) == (workgroups, rows), (shape, launched)
+        return
+    r, l = H.REGISTERS_AND_LDS[tiles]
+    assert kernel in first and re.search(f"Li{r}ELi{l}EEEv", first) and (x, y) == (workgroups, rows), (shape, launched)
+    assert len(launched) == (1 if workgroups == 1 else 2), (shape, launched)
+    if workgroups > 1:
+        assert "_held_finish" in launched[1][0] and launched[1][1:] == (workgroups, rows), (shape, launched)
+
+
+def test_worker_shapes_are_launched_as_listed(program):
+    calls = [("w", SIGN, n, d, int(dtype == "bf16"), RMS * rms) for n, d, dtype, rms, _, _ in H.SIGN_WORKER]
+    for shape, launched in zip(H.SIGN_WORKER, _launches(program, calls)):
+        n, d, dtype, rms, tiles, workgroups = shape
+        kernel = "k_sign_held_worker" + f"ILb{int(dtype == 'bf16')}ELb{int(rms)}E"
+        _check(launched, kernel, tiles, workgroups, n, shape)
+
+
+def test_server_shapes_are_launched_as_listed(program):
+    calls = [("s", SIGN, n, d, 0, RMS * rms) for n, d, _, rms, _, _ in H.SIGN_SERVER]
+    for shape, launched in zip(H.SIGN_SERVER, _launches(program, calls)):
+        n, d, _, rms, tiles, workgroups = shape
+        _check(launched, f"k_sign_held_serverILb{int(rms)}E", tiles, workgroups, 1, shape)
+
+
+def test_ternary_shapes_are_launched_as_listed(program):
+    calls = [("w", TERNARY, n, d, int(dtype == "bf16"), NOFB_SID) for n, d, dtype, _, _ in H.TERNARY]
+    for shape, launched in zip(H.TERNARY, _launches(program, calls)):
+        n, d, dtype, tiles, workgroups = shape
+        _check(launched, f"k_tern_heldILb{int(dtype == 'bf16')}E", tiles, workgroups, n, shape)
+
+
+def test_every_size_is_listed(program):
+    """Several workgroups of every size, one workgroup of every size that is left to one, both types, and separate
+    launches stand in the lists."""
+    assert {t for *_, t, w in H.SIGN_WORKER if w > 1} == {0, 1, 2, 4, 8, 14, 24}
+    assert {t for *_, t, w in H.SIGN_SERVER if w > 1} == {0, 1, 2, 4, 8, 14, 24}
+    assert {t for *_, t, w in H.TERNARY if w > 1} == {0, 1, 2, 4, 8, 14, 24}
+    assert {t for *_, t, w in H.SIGN_WORKER if w == 1} == {1, 2, 4, 8, 14}
+    assert {t for *_, t, w in H.SIGN_SERVER if w == 1} == {1, 2, 4}
+    assert {t for *_, t, w in H.TERNARY if w == 1} == {1, 4, 8}

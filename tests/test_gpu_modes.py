@@ -10,6 +10,8 @@ import pytest
 import torch
 
 import ds_workloads as W
+import held_shapes
+import oracle as O
 import paper_1905_05957_amd as P
 import parity_util
 from parity_util import Pair
@@ -129,13 +131,10 @@ def test_unsupported_combinations_are_refused_at_create(gpu_device):
     assert code(comp="identity", n=2, d=100, flags=NOFB) == 5
 
 
-# Ternary rows that are read once: rows that one workgroup holds, several workgroups per row of every
-# size, ends of tiles, words and rows (d mod 4).  `patience` -1: every workgroup that would have to
-# wait for the row's maximum gives up and the finish launch encodes what it held.
+# Ternary rows that are read once.  `patience` -1: every workgroup that would have to wait for the row's
+# maximum gives up and the finish launch encodes what it held.
 @pytest.mark.parametrize("patience", [0, -1])
-@pytest.mark.parametrize("n,d,dtype", [(3, 2047, "f32"), (2, 4 * 2048 - 3, "bf16"), (2, 8 * 2048 + 1, "f32"), (2, 14 * 2048, "bf16"),
-                                       (2, 24 * 2048 - 2, "f32"), (2, 25 * 2048 + 3, "f32"), (5, 300_001, "bf16"),
-                                       (8, 700_002, "f32"), (9, 1_800_003, "f32"), (9, 2_600_001, "bf16"), (3, 9_000_005, "f32")])
+@pytest.mark.parametrize("n,d,dtype", [shape[:3] for shape in held_shapes.TERNARY])
 def test_ternary_rows_read_once(gpu_device, n, d, dtype, patience):
     wl = W.Workload("ternary", "ternary", n=n, d=d, dist="normal", sigma=1e-3, gamma=0.05, grad_dtype=dtype, seed=7)
     parity_util.CONTEXT_FLAGS, parity_util.CONTEXT_KW = NOFB | SID, {"topk_spin_limit": patience}
@@ -152,3 +151,76 @@ def test_ternary_rows_read_once(gpu_device, n, d, dtype, patience):
         pair.compared_step(2, g)
     finally:
         pair.close()
+
+
+def _ternary_against_oracle(gpu_device, g, patience, seed=7, step=0):
+    n, d = g.shape
+    ctx = P.Context("ternary", n, d, flags=NOFB | SID, seed=seed, topk_spin_limit=patience)
+    try:
+        msg = ctx.alloc_payload(n, gpu_device)
+        for _ in range(2):                   # the second call sees what the first left behind
+            ctx.worker_compress(step, torch.from_numpy(g).to(gpu_device), None, msg)
+            got = msg.to_numpy()
+        with np.errstate(all="ignore"):
+            want = O.worker_compress(O.Config(O.TERNARY, n=n, d=d, seed=seed), step, g, np.zeros((n, d), np.float32))
+        return got, want
+    finally:
+        ctx.close()
+
+
+# Maxima beyond the range in which the product test decides (every element divides), at its edges, and rows
+# of subnormals only; one workgroup per row, several, and rows that are looked at twice.
+@pytest.mark.parametrize("n,d,power,patience", [(n, d, p, patience) for n, d in ((2, 5001), (2, 60_003)) for patience in (0, -1)
+                                                for p in (-140, -126, -101, -100, 99, 100, 110, 120)] +
+                         [(1, 5_000_003, -126, 0), (1, 5_000_003, 110, 0)])
+def test_ternary_maxima_over_the_whole_range(gpu_device, n, d, power, patience):
+    scale = 2.0 ** power
+    rng = np.random.default_rng(3)
+    g = rng.uniform(-1.0, 1.0, (n, d)).astype(np.float32)
+    g[:, 7] = [1.0, -1.0][:n]                                   # the maximum is the scale itself
+    g = (g.astype(np.float64) * scale).astype(np.float32)
+    got, want = _ternary_against_oracle(gpu_device, g, patience)
+    assert np.array_equal(got["levels"], want["levels"]) and np.array_equal(got["sign_words"], want["sign_words"])
+    assert np.all(np.abs(got["scales"].astype(np.float64) - want["scales"]) <= 1e-6 * want["scales"])
+
+
+# Elements whose |v| / m lies at the element's uniform, and one and two steps of fp32 to both sides: the
+# product test must leave them to the division.
+@pytest.mark.parametrize("m", [1.0, 0.7, 3.0e-20])
+def test_ternary_decisions_at_the_uniform(gpu_device, m):
+    seed, step, n, d = 7, 3, 2, 20_003
+    m = np.float32(m)
+    g = np.zeros((n, d), np.float32)
+    for i in range(n):
+        u = np.array([O.uniform24(seed, step, i, j) for j in range(d)], np.float64)
+        v = (u * np.float64(m)).astype(np.float32)
+        for c, steps in enumerate((0, 1, 2, -1, -2)):
+            part = v[c::5]
+            for _ in range(abs(steps)):
+                part = np.nextafter(part, np.float32(np.inf) if steps > 0 else np.float32(0.0), dtype=np.float32)
+            v[c::5] = part
+        v = np.minimum(v, m)
+        v[1::2] *= -1
+        v[11] = m
+        g[i] = v
+    got, want = _ternary_against_oracle(gpu_device, g, 0, seed, step)
+    assert np.array_equal(got["levels"], want["levels"]) and np.array_equal(got["sign_words"], want["sign_words"])
+    kept = np.unpackbits(want["levels"][0].view(np.uint8)).sum()
+    assert 0.2 * d < kept < 0.8 * d                             # both outcomes are there in number
+
+
+@pytest.mark.parametrize("patience", [0, -1])
+@pytest.mark.parametrize("n,d", [(3, 5001), (3, 60_003), (1, 5_000_003)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_ternary_rows_that_are_not_finite(gpu_device, n, d, bad, patience):
+    rng = np.random.default_rng(5)
+    g = rng.standard_normal((n, d)).astype(np.float32)
+    g[0, 3] = g[0, d - 1] = bad
+    if n > 1:
+        g[1, :] = bad                                           # the last row stays as it is
+    got, want = _ternary_against_oracle(gpu_device, g, patience)
+    assert np.array_equal(got["levels"], want["levels"]) and np.array_equal(got["sign_words"], want["sign_words"])
+    a, b = got["scales"].astype(np.float64), want["scales"].astype(np.float64)
+    finite = np.isfinite(b)
+    assert np.array_equal(finite, np.isfinite(a)) and np.array_equal(np.isnan(a), np.isnan(b))
+    assert np.all(np.abs(a[finite] - b[finite]) <= 1e-6 * np.abs(b[finite]))

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import ds_workloads as W
+import held_shapes
 import oracle as O
 import paper_1905_05957_amd as P
 from parity_util import Pair, assert_close_rows
@@ -234,20 +235,14 @@ def test_sign_deferred_error_against_oracle(gpu_device):
         pair.close()
 
 
-# One look at rows whose scale spans workgroups: rows that one workgroup holds (1, 2, 4, 8, 14, 24 tiles), the
-# sizes of several workgroups per row, the ends of tiles and rows (d mod 4), on rows that do not
-# start at 16-byte boundaries, with a sentinel behind every row.  The reference is the two-look
-# form of the same block, whose sums are taken in the same order: equal bit for bit.
-# `patience` -1 makes every workgroup that would have to wait give up, so that the finish launch
-# forms its errors.
+# One look at rows whose scale spans workgroups, on rows that do not start at 16-byte boundaries, with a
+# sentinel behind every row.  The reference is the two-look form of the same block, whose sums are
+# taken in the same order: equal bit for bit.  `patience` -1 makes every workgroup that would have to
+# wait give up, so that the finish launch forms its errors.
 @pytest.mark.parametrize("patience", [0, -1])
-@pytest.mark.parametrize("n,d,dtype,rms", [
-    (3, 2047, torch.float32, False), (2, 2049, torch.float32, True), (2, 4 * 2048 - 3, torch.bfloat16, False),
-    (2, 8 * 2048 + 1, torch.float32, False), (2, 14 * 2048, torch.bfloat16, True), (2, 24 * 2048 - 2, torch.float32, False),
-    (2, 25 * 2048 + 3, torch.float32, False), (5, 300_001, torch.bfloat16, False), (8, 700_002, torch.float32, True),
-    (9, 1_800_003, torch.float32, False), (9, 2_600_001, torch.bfloat16, False), (3, 9_000_005, torch.float32, False),
-    (3, 9_000_006, torch.bfloat16, True)])
+@pytest.mark.parametrize("n,d,dtype,rms", [shape[:4] for shape in held_shapes.SIGN_WORKER])
 def test_sign_whole_vector_in_one_look(gpu_device, n, d, dtype, rms, patience):
+    dtype = torch.bfloat16 if dtype == "bf16" else torch.float32
     gen = torch.Generator(device=gpu_device)
     gen.manual_seed(d)
     stride = d + 5
@@ -296,10 +291,7 @@ def test_sign_whole_vector_over_many_calls_that_give_up(gpu_device):
 # form, whose server keeps its launches apart: the message, the materialised error, x and m are
 # equal bit for bit.
 @pytest.mark.parametrize("patience", [0, -1])
-@pytest.mark.parametrize("n,d,momentum,rms", [
-    (1, 3, True, False), (3, 2047, False, False), (9, 2 * 2048 - 1, True, False), (8, 4 * 2048 + 2, False, True), (16, 14 * 2048, True, False),
-    (5, 24 * 2048 - 3, True, False), (12, 25 * 2048 + 1, False, False), (8, 700_002, True, False), (3, 3_000_001, True, False),
-    (3, 5_000_003, False, True), (2, 9_000_002, True, False), (2, 17_000_001, True, False), (1, 23_000_003, False, False)])
+@pytest.mark.parametrize("n,d,momentum,rms", [shape[:4] for shape in held_shapes.SIGN_SERVER])
 def test_sign_whole_vector_server_in_one_look(gpu_device, n, d, momentum, rms, patience):
     gen = torch.Generator(device=gpu_device)
     gen.manual_seed(d)
@@ -339,3 +331,47 @@ def test_sign_whole_vector_server_in_one_look(gpu_device, n, d, momentum, rms, p
     finally:
         for c in ctxs:
             c.close()
+
+
+def _same_bits_or_nan(a, b):
+    return torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.nan_to_num(a, 0.0, 1e38, -1e38).view(torch.int32),
+                                                                       torch.nan_to_num(b, 0.0, 1e38, -1e38).view(torch.int32))
+
+
+# Not finite, zero of either sign and subnormal: one workgroup, several, and the last group of four that the
+# end of the row cuts.
+@pytest.mark.parametrize("patience", [0, -1])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf"), -0.0, 1e-41])
+@pytest.mark.parametrize("n,d", [(2, 8191), (3, 300_003)])
+def test_sign_whole_vector_with_values_that_are_not_normal(gpu_device, n, d, bad, patience):
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(d)
+    g = torch.randn((n, d), device=gpu_device, generator=gen)
+    g[0, 5], g[0, d - 1], g[1, d // 2: d // 2 + 7] = bad, bad, bad          # the last row stays as it is
+    g[1, ::3] = 0.0
+    plain = P.Context("sign", n, d, scale_mode="whole", flags=P.FLAG_DEFERRED_ERROR)
+    ctx = P.Context("sign", n, d, scale_mode="whole", topk_spin_limit=patience)
+    try:
+        msg = ctx.alloc_payload(n, gpu_device)
+        held = torch.zeros((n, d), device=gpu_device)
+        held[:, ::5] = bad
+        want = held.clone()
+        words, scales = torch.zeros_like(msg.sign_words), torch.zeros_like(msg.scales)
+        ctx.worker_compress(0, g, held, msg)
+        P.ds_worker_compress_sign_noalloc(g, want, words, scales)
+        assert torch.equal(msg.sign_words, words)
+        assert _same_bits_or_nan(msg.scales, scales) and _same_bits_or_nan(held, want)
+        outs = []
+        for c in (plain, ctx):
+            delta_s, x, m = (torch.full((d,), v, device=gpu_device) for v in (bad, 1.0, 0.5))
+            delta_s[1::2] = 1e-3
+            out = c.alloc_server_payload(gpu_device)
+            c.server_aggregate_compress_update(0, msg, delta_s, out, x, m, 0.05, 0.9)
+            c.materialize_error(None, delta_s)
+            outs.append((out.sign_words, out.scales, delta_s, x, m))
+        assert torch.equal(outs[0][0], outs[1][0])
+        for a, b in zip(outs[0][1:], outs[1][1:]):
+            assert _same_bits_or_nan(a, b)
+    finally:
+        ctx.close()
+        plain.close()
