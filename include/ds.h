@@ -98,7 +98,8 @@ typedef enum {
  *
  * DS_FLAG_DEFERRED_ERROR: SIGN with scale groups that span workgroups (whole vector,
  * arbitrary segments, chunks that are no multiple of 128 or exceed 2048) needs the group
- * scale before it can store delta = v - Q[v], i.e. a second look at v.  With this flag the
+ * scale before it can store delta = v - Q[v], i.e. a second look at v (or, what whole vectors of up to
+ * about 25 million elements get without this flag, all of v on chip until then).  With this flag the
  * second look is folded into the next call's load: after a call the error buffers hold v, the
  * context holds that call's scales, and the next ds_worker_compress /
  * ds_server_aggregate_compress forms delta = v - Q[v] while it reads the buffer (the same

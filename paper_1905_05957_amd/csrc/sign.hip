@@ -4,11 +4,13 @@
 // A message is a sign plane (bit = v < 0) plus one scale per group, scale = mean |v| of
 // the group, so that the decoded group has the l1 magnitude of v.
 //
-// Two routes:
+// Three routes:
 //  * fused (groups are chunks of 512..2048 elements, a multiple of 128): one workgroup holds
 //    a whole chunk in registers, so v = g + delta, sum |v|, the sign bits and
 //    delta' = v - Q[v] happen in ONE pass over HBM.
-//  * general (whole vector, arbitrary segments, other chunk sizes): the scale needs a sum
+//  * held (one group, the whole vector, where the device holds a row on chip; held.h): the workgroups
+//    of a row keep v until the row's scale is known, so this is ONE pass over HBM too.
+//  * general (whole vectors beyond that, arbitrary segments, other chunk sizes): the scale needs a sum
 //    over more than one workgroup, so pass 1 writes v into the delta buffer together with
 //    the sign bits and fp64 partial sums, a small kernel reduces them in a fixed order,
 //    and pass 2 turns v into delta' = v - Q[v].
@@ -525,7 +527,7 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t strid
 // the worker call at 8 x 11,173,962 took 243 us with 1.5 rows resident (T = 8), 222 us with 2.0
 // (T = 14), 213 us with 2.25 (T = 24), at 171 us for its bytes at the copy kernel's rate and 286 us
 // in two looks.  7 x 2,345,679, all rows resident: 35 us against 62 us in two looks (31 us for its
-// bytes).  With all errors of a workgroup loaded up front and the gradients in groups of three the
+// bytes; both with the finish launch, 4.8 us).  With all errors of a workgroup loaded up front and the gradients in groups of three the
 // first took 220 us, with D = 4 and 6 tiles in flight instead of 3 213 and 214 us.
 //
 // What a workgroup of the held route shares: per tile the wavefronts' sums and the sign words.
@@ -699,9 +701,10 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
 // error is read and written once, the server's message is not read back.  Compressor, reduce,
 // second look and update as launches of their own took 59 us at 8 x 11,173,962, one launch and its
 // finish take 45 us (30 us for their bytes at the copy kernel's rate; the barrier is not hidden, there
-// is one row).  Ordinary accesses beat non-temporal ones where server calls follow each other
-// (45 against 49 us, 2 x 24,000,000 78 against 93 us); inside whole steps both take the same.  With 14 and 24
-// tiles per workgroup instead of the smallest size that holds the row, 58 and 60 us.
+// is one row).  Ordinary accesses beat non-temporal ones at every size that is held, above 64 MB too: whole
+// steps at 8 x 11,173,962 260 against 265 us, with momentum 271 and 282 us; 2 x 24,000,000 189 and 204 us, with
+// momentum 225 and 240 us; 1 x 5,000,003 with momentum 50 and 52 us.  With 14 and 24 tiles per workgroup instead of
+// the smallest size that holds the row, server and update take 58 and 60 us.
 struct HeldUpdate {
     float *x, *m;
     float gamma, beta;

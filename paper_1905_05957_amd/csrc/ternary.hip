@@ -8,13 +8,13 @@
 //
 // The comparison system runs without compensation and with a server that does not compress,
 // and that is the mode built here: v = g, no error buffer.  The row-wide maximum has to be
-// known before the first code, so the worker call looks at g twice:
+// known before the first code.  Rows that the device can hold on chip are read once (k_tern_held, where
+// that was measured to pay): the workgroups of a row keep its elements until the maximum is known.
+// Other worker calls look at g twice:
 //   stats    per 2048-element tile: max |v| and sum |v| (fp64)
 //   rowstat  per row: the maximum, and the sum in a fixed order
 //   encode   codes from the second look: two bit planes packed like the sign words, kept count per tile
 //   scale    per row: sum / count, rounded once
-// Rows that the device can hold on chip (k_tern_held) are read once: the workgroups of a row keep
-// its elements until the maximum is known.
 // The message is 2 bits per element: plane `levels` (bit j = code_j is not 0), plane
 // `sign_words` (bit j = code_j is -1), one fp32 scale.
 #include "ds_device.h"
@@ -179,14 +179,16 @@ __global__ __launch_bounds__(kBlock) void k_tern_scale(const uint32_t *pcnt, con
 // held route: rows that are read once
 // ---------------------------------------------------------------------------------------
 // A workgroup keeps T consecutive tiles in registers and LDS, hands over their sums and maximum,
-// waits for the row's maximum, which the workgroup that arrives last publishes, and encodes what
-// it holds and leaves its count of kept codes for the finish launch, which writes the scale.  Waits are
-// bounded, and what a workgroup that gave up did not encode the finish launch does (held.h).  The arrival
-// is the only word that all workgroups of a row add to: such additions come one after the other, about
-// 11 ns each, and with the maximum and the count as two more of them a call at 1 x 1,000,003 took 24.9, 16.9 and
-// 13.8 us with 1, 2 and 4 tiles per workgroup.  Worker call at
+// waits for the row's maximum, which the workgroup that arrives last publishes, encodes what it holds
+// and leaves its count of kept codes for the finish launch, which writes the scale.  Waits are bounded,
+// and what a workgroup that gave up did not encode the finish launch does (held.h).  The arrival is the
+// only word that all workgroups of a row add to: such additions come one after the other, about 11 ns
+// each, and with the maximum and the count as two more of them a call at 1 x 1,000,003 took 24.9, 16.9 and
+// 13.8 us with 1, 2 and 4 tiles per workgroup (16.0, 12.9 and 12.1 us without).
+//
+// What bounds it is the encoding: vector instructions, most of them Philox.  Worker call at
 // 8 x 11,173,962: 189 us in two looks with four divisions per thread, 164 us in two looks without
-// them, 149 us here (57 us for its bytes at the copy kernel's rate).
+// them, 149 .. 154 us here with the finish launch (57 us for its bytes at the copy kernel's rate).
 __device__ __forceinline__ float tern_scale(double sum, uint32_t kept)
 {
     return kept ? static_cast<float>(sum / static_cast<double>(kept)) : 0.f;
