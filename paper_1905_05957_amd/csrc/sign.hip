@@ -490,7 +490,8 @@ __global__ __launch_bounds__(kBlock) void k_sign_reduce(const double *__restrict
     }
 }
 
-// Pass 2: the buffer holds v; overwrite with delta' = v - Q[v].
+// Pass 2: the buffer holds v; overwrite with delta' = v - Q[v].  STREAM: non-temporal stores.
+template <bool STREAM>
 __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t stride, int64_t d,
                                                        const float *__restrict__ scales, int64_t S,
                                                        ds_sign_tables tb)
@@ -506,7 +507,9 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t strid
     const int64_t e = tile * kTile + threadIdx.x * 4;
     if (e >= d) return;
     const f32x4 v = ld4_stream(brow, e, d);
-    st4_stream(brow, e, d, sign_error_tile(v, e, d, srow, tb, tp.p0, tp.p1, tp.seg0));
+    const f32x4 o = sign_error_tile(v, e, d, srow, tb, tp.p0, tp.p1, tp.seg0);
+    if constexpr (STREAM) st4_stream(brow, e, d, o);
+    else st4(brow, e, d, o);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1163,6 +1166,20 @@ static void with_flags(bool a, bool b, bool c, F f)
     if (a) l1(std::true_type{}); else l1(std::false_type{});
 }
 
+// Pass 2 over `rows` rows.  Its stores are ordinary ones where the buffer is more than what the eight L2s take in
+// beside the rest and fits the 256 MB memory-side cache, which then still holds it for the next call.  Whole
+// steps with groups of 16,384, ordinary against non-temporal: 8 x 800,000 (26 MB) 43.5 and 48.0 us, 8 x 1,000,002
+// 48.8 and 52.4 us, 8 x 4,000,002 137 and 143 us, 1 x 25,557,032 (102 MB) 193 and 202 us, 16 x 3,900,002 (250 MB) 229
+// and 234 us; but 16 x 200,002 (13 MB) 38 and 33 us, 8 x 25,557,030 (818 MB) 870 and 839 us, and, where the worker's and
+// the server's buffer do not fit together, 1 x 60,000,002 431 and 418 us.
+static void sign_pass2(float *buf, int64_t stride, int64_t d, int64_t rows, const float *scales, int64_t S, const ds_sign_tables &tb, hipStream_t st)
+{
+    const dim3 grid(static_cast<unsigned>((d + kTile - 1) / kTile), static_cast<unsigned>(rows));
+    const int64_t mb = (rows * d * 4) >> 20;
+    if (mb >= 20 && mb < 256 && (d * 4) >> 20 < 192) k_sign_pass2<false><<<grid, kBlock, 0, st>>>(buf, stride, d, scales, S, tb);
+    else k_sign_pass2<true><<<grid, kBlock, 0, st>>>(buf, stride, d, scales, S, tb);
+}
+
 ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, int64_t dstr,
                            const ds_payload_t *out, hipStream_t st)
 {
@@ -1215,7 +1232,7 @@ ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, i
     });
     k_sign_reduce<<<dim3(static_cast<unsigned>(c->S), static_cast<unsigned>(cfg.n)), kBlock, 0, st>>>(
         c->sign_partials, c->sign_tb, out->scales, c->S, c->sign_defer ? c->sign_prev_w : nullptr);
-    if (!c->sign_defer && delta) k_sign_pass2<<<grid, kBlock, 0, st>>>(delta, dstr, cfg.d, out->scales, c->S, c->sign_tb);
+    if (!c->sign_defer && delta) sign_pass2(delta, dstr, cfg.d, cfg.n, out->scales, c->S, c->sign_tb, st);
     const ds_status_t rc = ds_launch_status();
     if (rc == DS_OK && c->sign_defer) c->sign_w_deferred = true;   // the buffer now holds v; delta = v - Q[v] is applied by the next load
     return rc;
@@ -1279,7 +1296,7 @@ ds_status_t ds_sign_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
     });
     k_sign_reduce<<<dim3(static_cast<unsigned>(c->S), 1), kBlock, 0, st>>>(c->sign_partials, c->sign_tb, out->scales, c->S,
                                                                           c->sign_defer ? c->sign_prev_s : nullptr);
-    if (!c->sign_defer && delta_s) k_sign_pass2<<<grid, kBlock, 0, st>>>(delta_s, cfg.d, cfg.d, out->scales, c->S, c->sign_tb);
+    if (!c->sign_defer && delta_s) sign_pass2(delta_s, cfg.d, cfg.d, 1, out->scales, c->S, c->sign_tb, st);
     const ds_status_t rc = ds_launch_status();
     if (rc == DS_OK && c->sign_defer) c->sign_s_deferred = true;
     return rc;
@@ -1291,13 +1308,11 @@ ds_status_t ds_sign_materialize(ds_ctx *c, float *delta, int64_t dstr, float *de
     const ds_config_t &cfg = c->cfg;
     if (!c->sign_defer) return DS_OK;
     if (delta && c->sign_w_deferred) {
-        k_sign_pass2<<<dim3(static_cast<unsigned>(c->n_tiles), static_cast<unsigned>(cfg.n)), kBlock, 0, st>>>(
-            delta, dstr, cfg.d, c->sign_prev_w, c->S, c->sign_tb);
+        sign_pass2(delta, dstr, cfg.d, cfg.n, c->sign_prev_w, c->S, c->sign_tb, st);
         c->sign_w_deferred = false;
     }
     if (delta_s && c->sign_s_deferred) {
-        k_sign_pass2<<<dim3(static_cast<unsigned>(c->n_tiles)), kBlock, 0, st>>>(delta_s, cfg.d, cfg.d, c->sign_prev_s, c->S,
-                                                                                c->sign_tb);
+        sign_pass2(delta_s, cfg.d, cfg.d, 1, c->sign_prev_s, c->S, c->sign_tb, st);
         c->sign_s_deferred = false;
     }
     return ds_launch_status();
@@ -1397,6 +1412,6 @@ extern "C" ds_status_t ds_worker_compress_sign_noalloc(int32_t n, int64_t d, int
         k_sign_pass1_worker<BF, 0, RM><<<grid, kBlock, 0, st>>>(src, delta, d, sign_words, W, tb, partials, nullptr, 1);
     });
     k_sign_reduce<<<dim3(1, static_cast<unsigned>(n)), kBlock, 0, st>>>(partials, tb, scales, 1, nullptr);
-    k_sign_pass2<<<grid, kBlock, 0, st>>>(delta, delta_row_stride, d, scales, 1, tb);
+    sign_pass2(delta, delta_row_stride, d, n, scales, 1, tb, st);
     return ds_launch_status();
 }

@@ -375,3 +375,14 @@ def test_sign_whole_vector_with_values_that_are_not_normal(gpu_device, n, d, bad
     finally:
         ctx.close()
         plain.close()
+
+
+# Error buffers that the second look stores with ordinary accesses (20 to 256 MB) and with non-temporal ones.
+@pytest.mark.parametrize("n,d", [(8, 700_002), (3, 300_001), (2, 3_000_003)])
+def test_sign_second_look_at_buffers_of_different_size(gpu_device, n, d):
+    pair = Pair(W.c2(d=d, n=n, n_seg=12, lo=64), gpu_device)
+    try:
+        for t in range(2):
+            pair.compared_step(t, pair.wl.gradients(t, gpu_device))
+    finally:
+        pair.close()
