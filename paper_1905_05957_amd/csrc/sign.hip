@@ -118,12 +118,13 @@ __device__ __forceinline__ f32x4 sign_error4(f32x4 v, float s)
 // ---------------------------------------------------------------------------------------
 // fused route: one workgroup per chunk
 // ---------------------------------------------------------------------------------------
-// Common tail: scale from the held values, sign plane, error, stores.
+// Common tail: scale from the held values, sign plane, error, stores.  keep: the error is stored with ordinary
+// accesses.
 template <bool RMS>
 __device__ __forceinline__ float fused_finish(f32x4 v, int64_t base, int64_t lim,
                                              float *__restrict__ err_row,
                                              uint64_t *__restrict__ words_row, int64_t bit_lim,
-                                             float *__restrict__ scale_out, double *lds, uint32_t *sw_lds)
+                                             float *__restrict__ scale_out, double *lds, uint32_t *sw_lds, bool keep = false)
 {
     // sign words: gathered in LDS, one store per workgroup after the barrier of the reduction
     stash_sign_words(sw_lds, wave_sign_word(v.x < 0.f, v.y < 0.f, v.z < 0.f, v.w < 0.f));
@@ -132,20 +133,24 @@ __device__ __forceinline__ float fused_finish(f32x4 v, int64_t base, int64_t lim
     if (threadIdx.x == 0) *scale_out = scale;
     flush_sign_words(sw_lds, words_row, base, bit_lim);
     const int64_t e = base + threadIdx.x * 4;
-    if (err_row && e < lim) st4_stream(err_row, e, lim, sign_error4(v, scale));   // no buffer: no compensation
+    if (err_row && e < lim) {                                   // no buffer: no compensation
+        if (keep) st4(err_row, e, lim, sign_error4(v, scale));  // uniform
+        else st4_stream(err_row, e, lim, sign_error4(v, scale));
+    }
     return scale;
 }
 
 // NOFB: Algorithm 1 without compensation, v = g; no error buffer is touched.
-// CPW chunks per workgroup, all loads issued before the first is used.  With compensation one
-// chunk per workgroup is fastest; without it a chunk is only 4 to 8 KiB of traffic and a
-// workgroup per chunk is bound by the rate at which workgroups can be dispatched (486 k
-// workgroups took 0.88 ms for 2.1 GB on the 124 M-element workload), so that variant takes four.
+// CPW chunks per workgroup, all loads issued before the first is used: two with compensation; without
+// it a chunk is only 4 to 8 KiB of traffic and a workgroup per chunk is bound by the rate at which
+// workgroups can be dispatched (486 k workgroups took 0.88 ms for 2.1 GB on the 124 M-element
+// workload), so that variant takes four.
+// keep_odd: every other row's error is stored with ordinary accesses.
 template <bool BF16, bool RMS, bool NOFB, int CPW>
 __global__ __launch_bounds__(kBlock) void k_sign_chunk_worker(WorkerSrc<BF16> src, float *delta,
                                                               int64_t d, int64_t chunk,
                                                               uint64_t *words, int64_t W,
-                                                              float *scales, int64_t S)
+                                                              float *scales, int64_t S, bool keep_odd)
 {
     __shared__ double lds[CPW][kWaves];
     __shared__ __attribute__((aligned(16))) uint32_t sw_lds[CPW][kWaves * 8];
@@ -168,7 +173,7 @@ __global__ __launch_bounds__(kBlock) void k_sign_chunk_worker(WorkerSrc<BF16> sr
         const int64_t ci = static_cast<int64_t>(blockIdx.x) * CPW + c;
         if (base[c] < d)    // uniform over the workgroup
             fused_finish<RMS>(v[c], base[c], lim[c], drow, words + row * W, (lim[c] == d) ? W * 64 : lim[c],
-                              scales + row * S + ci, lds[c], sw_lds[c]);
+                              scales + row * S + ci, lds[c], sw_lds[c], keep_odd && (row & 1));
     }
 }
 
@@ -1187,13 +1192,23 @@ ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, i
     const bool bf16 = cfg.grad_dtype == DS_BF16;
     const bool rms = (cfg.flags & DS_FLAG_SIGN_RMS) != 0;
     if (c->sign_fused) {
+        // With every other row's errors stored with ordinary accesses the next call finds those rows in a cache,
+        // where the buffer as a whole would not stay: half of it in the eight L2s (32 MB) or, beside the gradients, in
+        // the 256 MB memory-side cache.  Whole steps, chunks of 2048, ordinary accesses for no, every other and every row:
+        //  * fp32: 8 x 400,000 (13 MB) 14.6, 13.4 and 13.9 us; 16 x 2,000,000 (128 MB) 73.8, 72.0 and 73.5 us; 16 x 3,900,000
+        //    (250 MB) 139, 131 and 135 us; 8 x 11,173,960 (357 MB) 212, 200 and 235 us; 2 x 60,000,002 (480 MB) 400, 382 and
+        //    437 us; in between 4 x 4,000,000 (64 MB) 46.2, 47.1 and 47.1 us; beyond, 8 x 25,557,032 (818 MB) 490 and 516 us;
+        //  * bf16: 8 x 11,173,960 183 and 180 us, 8 x 16,000,002 259 and 254 us, but 16 x 1,000,002 36.8 and 38.0 us;
+        //  * chunks of 512, 4 x 11,173,962: 209 and 216 us.
+        const int64_t mb = (cfg.n * cfg.d * 4) >> 20, half_mb = ((cfg.n / 2) * cfg.d * 4) >> 20;
+        const bool keep_odd = cfg.chunk == kTile && half_mb < 256 && (bf16 ? mb >= 256 : mb <= 32 || mb >= 96);
         with_flags(bf16, rms, c->nofb, [&](auto bf, auto rm, auto nf) {
             constexpr bool BF = decltype(bf)::value, RM = decltype(rm)::value, NF = decltype(nf)::value;
             constexpr int CPW = NF ? 4 : 2;
             const dim3 grid(static_cast<unsigned>((c->S + CPW - 1) / CPW), static_cast<unsigned>(cfg.n));
             WorkerSrc<BF> src{g, gs, delta, dstr};
             k_sign_chunk_worker<BF, RM, NF, CPW><<<grid, kBlock, 0, st>>>(src, delta, cfg.d, cfg.chunk, out->sign_words, c->W,
-                                                                          out->scales, c->S);
+                                                                          out->scales, c->S, keep_odd);
         });
         return ds_launch_status();
     }

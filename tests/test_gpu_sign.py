@@ -386,3 +386,18 @@ def test_sign_second_look_at_buffers_of_different_size(gpu_device, n, d):
             pair.compared_step(t, pair.wl.gradients(t, gpu_device))
     finally:
         pair.close()
+
+
+# Chunks of 2048 with fp32 gradients: every other row's error takes ordinary accesses up to 32 MB and from 96 MB on; other
+# buffers here do not.
+@pytest.mark.parametrize("n,d,chunk,dtype", [(3, 50_003, 2048, "f32"), (3, 3_000_001, 2048, "f32"), (2, 13_000_002, 2048, "f32"),
+                                             (2, 34_000_002, 2048, "bf16"), (4, 50_002, 2048, "f32"), (4, 50_002, 2048, "bf16"), (5, 20_481, 1024, "f32"),
+                                             (1, 4_097, 2048, "f32")])
+def test_sign_chunk_rows_of_every_alignment(gpu_device, n, d, chunk, dtype):
+    wl = W.Workload("sign_chunk", "sign", n=n, d=d, dist="normal", sigma=1e-2, gamma=0.05, scale_mode="chunk", chunk=chunk, grad_dtype=dtype)
+    pair = Pair(wl, gpu_device)
+    try:
+        for t in range(3 if d < 1_000_000 else 1):
+            pair.compared_step(t, wl.gradients(t, gpu_device))
+    finally:
+        pair.close()
