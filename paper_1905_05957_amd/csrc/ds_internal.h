@@ -35,6 +35,7 @@ struct ds_tern_scratch;  // defined in ternary.hip
 struct ds_held_sync {
     int T, parts;          // tiles per workgroup, workgroups per row
     int64_t slots;         // workgroups that the device holds at once
+    bool self;             // several workgroups per row and no finish launch
     void *rows;            // [n] synchronisation words (HeldRow)
     uint32_t *gave_up;     // [n, parts] written by every such launch
     uint32_t patience;     // ticks of the 100 MHz clock a workgroup waits at most

@@ -648,6 +648,66 @@ __device__ __forceinline__ void held_store(f32x4 v, int t, float *out, int left,
     if ((left & 3) && e == (left & ~3)) st4_tail(out, e, left, o);
 }
 
+struct HeldUpdate {
+    float *x, *m;
+    float gamma, beta;
+};
+
+// x (and m) of elements e..e+3 of the row from the held v: q = the decoded message.
+template <int UPD>
+__device__ __forceinline__ void held_update4(f32x4 v, f32x4 &x, f32x4 &m, float s, const HeldUpdate &u)
+{
+    f32x4 q = {(v.x < 0.f) ? -s : s, (v.y < 0.f) ? -s : s, (v.z < 0.f) ? -s : s, (v.w < 0.f) ? -s : s};
+    if constexpr (UPD == 2) q = m = fma4(u.beta, m, q);
+    x = fma4(-u.gamma, q, x);
+}
+
+// What a workgroup that gave up left: its error, and where u.x is set the update, from the stored v.
+__device__ __forceinline__ void held_finish_part(float *brow, int64_t d, int part, int T, float s, const HeldUpdate &u)
+{
+    const int64_t e0 = static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4;
+    constexpr int D = 4;                                      // loads in flight
+    for (int t0 = 0; t0 < T; t0 += D) {
+        f32x4 v[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            v[j] = (t0 + j < T) ? ld4_stream(brow, e0 + (t0 + j) * kTile, d) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            const int64_t e = e0 + (t0 + j) * kTile;
+            if (t0 + j >= T || e >= d) continue;
+            st4_stream(brow, e, d, sign_error4(v[j], s));
+            if (u.x) {
+                f32x4 x4 = ld4_stream(u.x, e, d), m4 = x4;
+                if (u.m) {
+                    m4 = ld4_stream(u.m, e, d);
+                    held_update4<2>(v[j], x4, m4, s, u);
+                    st4_stream(u.m, e, d, m4);
+                } else {
+                    held_update4<1>(v[j], x4, m4, s, u);
+                }
+                st4_stream(u.x, e, d, x4);
+            }
+        }
+    }
+}
+
+// The end of a workgroup in a row that finishes itself.
+__device__ __forceinline__ void held_self_finish(float *brow, int64_t d, int T, bool ok, uint32_t *gave_up_row, HeldRow *rows, int row,
+                                                 uint32_t *sh, const HeldUpdate &u)
+{
+    uint32_t unused;
+    if (!held_depart(rows + row, gridDim.x, ok, 0u, sh, &unused)) return;
+    if (rows[row].late.load() != 0u) {                        // uniform: all have departed
+        __threadfence();
+        const float s = __uint_as_float(static_cast<uint32_t>(rows[row].pub.load()));
+        for (uint32_t p = 0; p < gridDim.x; ++p)
+            if (as_shared(gave_up_row)[p].load() != 0u) held_finish_part(brow, d, static_cast<int>(p), T, s, u);
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) rows[row].next_call(row == 0);
+}
+
 // R tiles of a workgroup are held in registers and L more in LDS (every thread reads back its own
 // elements).
 constexpr int kHeldDepth = 3;
@@ -656,7 +716,7 @@ template <bool BF16, bool RMS, int R, int L>
 __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(WorkerSrc<BF16> src, float *delta, int64_t d,
                                                                             uint64_t *words, int64_t W, ds_sign_tables tb,
                                                                             double *partials, float *scales, HeldRow *rows,
-                                                                            uint32_t *gave_up, uint32_t patience)
+                                                                            uint32_t *gave_up, uint32_t patience, bool self)
 {
     constexpr int T = R + L;
     __shared__ HeldShared<T> m;
@@ -694,7 +754,8 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
     float s;
     const bool ok = held_scale<RMS, T>(m, tile0, row, words + row * W, tb, partials + static_cast<int64_t>(row) * tb.n_pieces,
                                        scales + row, rows, patience, &s);
-    if (threadIdx.x == 0 && gridDim.x != 1) gave_up[row * static_cast<int64_t>(gridDim.x) + blockIdx.x] = ok ? 0u : 1u;
+    uint32_t *gave_up_row = gave_up + row * static_cast<int64_t>(gridDim.x);
+    if (threadIdx.x == 0 && gridDim.x != 1) as_shared(gave_up_row)[blockIdx.x].store(ok ? 0u : 1u);
 #pragma unroll
     for (int t = 0; t < R; ++t) {
         held_store(v[t], t, drow + first, left, ok, s);
@@ -702,6 +763,8 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
     }
 #pragma unroll
     for (int t = R; t < T; ++t) held_store(far[t - R][threadIdx.x], t, drow + first, left, ok, s);
+    if constexpr (kHeldSelf<R, L>)
+        if (self) held_self_finish(drow, d, T, ok, gave_up_row, rows, row, m.sh, HeldUpdate{nullptr, nullptr, 0.f, 0.f});
 }
 
 // The parameter-server block the same way, and with UPD the model update of Algorithm 1 (2: through
@@ -713,20 +776,6 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
 // steps at 8 x 11,173,962 260 against 265 us, with momentum 271 and 282 us; 2 x 24,000,000 189 and 204 us, with
 // momentum 225 and 240 us; 1 x 5,000,003 with momentum 50 and 52 us.  With 14 and 24 tiles per workgroup instead of
 // the smallest size that holds the row, server and update take 58 and 60 us.
-struct HeldUpdate {
-    float *x, *m;
-    float gamma, beta;
-};
-
-// x (and m) of elements e..e+3 of the row from the held v: q = the decoded message.
-template <int UPD>
-__device__ __forceinline__ void held_update4(f32x4 v, f32x4 &x, f32x4 &m, float s, const HeldUpdate &u)
-{
-    f32x4 q = {(v.x < 0.f) ? -s : s, (v.y < 0.f) ? -s : s, (v.z < 0.f) ? -s : s, (v.w < 0.f) ? -s : s};
-    if constexpr (UPD == 2) q = m = fma4(u.beta, m, q);
-    x = fma4(-u.gamma, q, x);
-}
-
 // One tile's average: v = delta_s + (1/n) sum_i Q[v_i] by the chain over workers.  word0, sc0: sign
 // words and scales of the first eight workers (layout as in k_sign_pass1_server).
 __device__ __forceinline__ f32x4 held_chain(f32x4 v, uint32_t word0, float sc0, const ServerArgs &a, int64_t wave_first)
@@ -763,7 +812,7 @@ template <bool RMS, int UPD, int R, int L>
 __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(ServerArgs a, float *delta_s, int64_t d, uint64_t *words_out,
                                                                             ds_sign_tables tb, double *partials, float *scale_out,
                                                                             HeldUpdate u, HeldRow *rows, uint32_t *gave_up,
-                                                                            uint32_t patience)
+                                                                            uint32_t patience, bool self)
 {
     constexpr int T = R + L;
     __shared__ HeldShared<T> m;
@@ -826,11 +875,13 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(Serv
     }
     float s;
     const bool ok = held_scale<RMS, T>(m, tile0, 0, words_out, tb, partials, scale_out, rows, patience, &s);
-    if (threadIdx.x == 0 && gridDim.x != 1) gave_up[blockIdx.x] = ok ? 0u : 1u;
+    if (threadIdx.x == 0 && gridDim.x != 1) as_shared(gave_up)[blockIdx.x].store(ok ? 0u : 1u);
     if (!ok) {                                                // uniform
 #pragma unroll
         for (int t = 0; t < T; ++t) held_st4<0>(delta_s + first, left, t, t < R ? v[t < R ? t : 0] : far[t < R ? 0 : t - R][threadIdx.x]);
         if (mine_cut) st4_tail(delta_s + first, cut_at, left, cut);
+        if constexpr (kHeldSelf<R, L>)
+            if (self) held_self_finish(delta_s, d, T, false, gave_up, rows, 0, m.sh, u);
         return;
     }
     // tiles in groups whose operands of the update are asked for together
@@ -875,9 +926,12 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(Serv
             if constexpr (UPD == 2) st4_tail(mr, cut_at, left, mc);
         }
     }
+    if constexpr (kHeldSelf<R, L>)
+        if (self) held_self_finish(delta_s, d, T, true, gave_up, rows, 0, m.sh, u);
 }
 
-// After a held launch: forms the error (and, where u.x is set, the update) where a workgroup gave up,
+// After a held launch (rows that finish themselves go without): forms the error (and, where u.x is set, the
+// update) where a workgroup gave up,
 // normally nowhere, and readies the synchronisation words for the next call.  One workgroup for every
 // workgroup of the held launch.  Calls in which all waits are given up, 8 x 11,173,962: worker 375 us
 // (two looks 289 us, held 213 us), server and update 66 us; 1203 and 521 us with one finishing workgroup for
@@ -890,33 +944,7 @@ __global__ __launch_bounds__(kBlock) void k_sign_held_finish(float *buf, int64_t
     const int row = gridDim.y - 1 - blockIdx.y, part = gridDim.x - 1 - blockIdx.x;
     if (part == 0 && threadIdx.x == 0) rows[row].next_call(row == 0);
     if (gave_up[row * static_cast<int64_t>(gridDim.x) + part] == 0u) return;
-    float *brow = buf + row * stride;
-    const float s = scales[row];
-    const int64_t e0 = static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4;
-    constexpr int D = 4;                                      // loads in flight
-    for (int t0 = 0; t0 < T; t0 += D) {
-        f32x4 v[D];
-#pragma unroll
-        for (int j = 0; j < D; ++j)
-            v[j] = (t0 + j < T) ? ld4_stream(brow, e0 + (t0 + j) * kTile, d) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < D; ++j) {
-            const int64_t e = e0 + (t0 + j) * kTile;
-            if (t0 + j >= T || e >= d) continue;
-            st4_stream(brow, e, d, sign_error4(v[j], s));
-            if (u.x) {
-                f32x4 x4 = ld4_stream(u.x, e, d), m4 = x4;
-                if (u.m) {
-                    m4 = ld4_stream(u.m, e, d);
-                    held_update4<2>(v[j], x4, m4, s, u);
-                    st4_stream(u.m, e, d, m4);
-                } else {
-                    held_update4<1>(v[j], x4, m4, s, u);
-                }
-                st4_stream(u.x, e, d, x4);
-            }
-        }
-    }
+    held_finish_part(buf + row * stride, d, part, T, scales[row], u);
 }
 
 template <bool MOM, bool DECODE_ONLY, bool STREAM>
@@ -1089,17 +1117,16 @@ ds_status_t ds_sign_init(ds_ctx *c)
     DS_HIP_TRY(hipMalloc(&c->sign_partials, sizeof(double) * n_pieces * static_cast<size_t>(cfg.n)));
     if (S == 1 && !c->nofb && !(cfg.flags & DS_FLAG_DEFERRED_ERROR)) {
         // Worker.  GPU time of a call, n = 1 .. 16, against two looks as separate launches and one tile per workgroup:
-        //  * one workgroup, fp32, 12 tiles in 14: 7.4 .. 8.2 us, 7.7 .. 9.5 and 6.7 .. 8.1 us, and a launch less for the
-        //    host (11 us a call in a stream of calls, 13 us with the finish launch); 16 to 24 tiles in 24: 11.1 .. 12.1 us,
-        //    7.3 .. 10.9 and 6.5 .. 8.3 us.  bf16, 8 tiles in 8: 6.3 .. 7.3 us, 7.3 .. 8.8 and 6.5 .. 7.8 us; 12 tiles in 14:
-        //    9.0 .. 9.9 us, 7.8 .. 9.5 and 6.8 .. 8.1 us;
+        //  * one workgroup, 8 tiles in 8: 5.5 .. 6.1 us (bf16 6.3 .. 7.3), 7.1 .. 9.0 and 6.4 .. 7.8 us; 12 tiles in 14: 7.4 .. 8.2 us
+        //    (bf16 9.0 .. 9.9), 7.7 .. 9.5 and 6.6 .. 7.4 us; 24 tiles in 24: 11.3 .. 12.1 us (bf16 13.9 .. 15.2), 7.3 .. 11.2 and
+        //    6.5 .. 8.3 us;
         //  * 1 x 1,000,003: 12.8, 10.3, 9.1 and 9.7 us with 1, 2, 4 and 8 tiles, 10.1 us in two looks; 4 x 300,001: 9.8, 8.8
         //    and 9.2 us with 1, 2 and 4;
         //  * 7 x 2,345,679: 72, 42, 35, 38 us with 2, 4, 8, 14 tiles, of which 8 is the first that holds all rows;
         //  * 8 x 5,000,003: 88 us with 14, 93 us with 24 tiles; 8 x 16,000,000: 352 and 333 us, 541 us in two looks;
         //    8 x 24,000,000: 454 us with 24, 619 us in two looks.
         static constexpr HeldStep worker[] = {{1, 0, 128}, {2, 0, 128}, {4, 0, 0}, {8, 0, 0}, {14, 4, 0}, {24, 1, 0}};
-        const ds_status_t rc = held_size(c, cfg.n, cfg.grad_dtype == DS_BF16 ? 8 : 14, worker, [](auto r, auto l) {
+        const ds_status_t rc = held_size(c, cfg.n, 8, worker, [](auto r, auto l) {
             constexpr int R = decltype(r)::value, L = decltype(l)::value;
             int per_cu = 0;
             return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_sign_held_worker<false, false, R, L>, kBlock, 0) ==
@@ -1113,9 +1140,9 @@ ds_status_t ds_sign_init(ds_ctx *c)
         // The server's block handles one row, and the chain over the workers comes once per tile, so that the more
         // workers there are, the more workgroups are wanted.  GPU time of server and update against
         // separate launches:
-        //  * one workgroup: 4 tiles in 4, n = 1 .. 16: 5.7 .. 8.9 us, 9.2 .. 9.9 us (one tile per workgroup 6.6 .. 7.5 us, but
-        //    13 us instead of 11 us a call in a stream of calls); 8 tiles in 8: 8.7 .. 15.5 us, 9.0 .. 10.0 us; 24 tiles in
-        //    24: 22 .. 42 us, 9.1 .. 10.1 us; n = 64: 2 tiles in 2 12.0 us, 12.7 us, in two workgroups 10.3 us;
+        //  * one workgroup: 4 tiles in 4: 5.7 us (n = 1), 6.8 us (n = 8), 8.9 us (n = 16), 9.2 .. 9.9 us, one tile per
+        //    workgroup 6.6 .. 7.5 us; 8 tiles in 8: 8.7 .. 15.5 us, 9.0 .. 10.0 us; 24 tiles in 24: 22 .. 42 us, 9.1 .. 10.1 us,
+        //    one tile per workgroup 6.9 .. 7.8 us; n = 64: 2 tiles in 2 12.0 us, 12.7 us, in two workgroups 10.3 us;
         //  * d = 1,000,003, n = 1: 13.7, 11.4 and 11.4 us with 1, 2 and 4 tiles, 13.1 us; n = 16: 14.7, 13.2 and 14.7, 14.6 us;
         //  * d = 8,000,002: 35 us with 4 tiles, 47 us (n = 8), 53 and 61 us (n = 32), 77.6 and 80.8 us (n = 64), 185 and 174 us
         //    (n = 200); d = 16,000,001, 8 tiles: 57 and 80 us (n = 8), 95 and 107 us (n = 32); 11,173,962 and n = 64: 113 and
@@ -1127,7 +1154,7 @@ ds_status_t ds_sign_init(ds_ctx *c)
         static constexpr HeldStep upto32[] = {{1, 0, 256}, {2, 0, 0}, {4, 0, 0}, {8, 0, 0}, {0, 0, 0}, {0, 0, 0}};
         static constexpr HeldStep upto64[] = {{1, 0, 0}, {2, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
         static constexpr HeldStep many[] = {{1, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-        const int n = cfg.n, one = n <= 16 ? 4 : n <= 32 ? 2 : 1;
+        const int n = cfg.n, one = n <= 8 ? 4 : n <= 32 ? 2 : 1;
         const auto &server = n <= 8 ? few : n <= 24 ? upto24 : n <= 32 ? upto32 : n <= 64 ? upto64 : many;
         const ds_status_t rs = c->sid ? DS_OK : held_size(c, 1, one, server, [](auto r, auto l) {
             constexpr int R = decltype(r)::value, L = decltype(l)::value;
@@ -1222,10 +1249,10 @@ ds_status_t ds_sign_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, i
                 constexpr bool BF = decltype(bf)::value, RM = decltype(rm)::value;
                 WorkerSrc<BF> src{g, gs, delta, dstr};
                 k_sign_held_worker<BF, RM, R, L><<<dim3(static_cast<unsigned>(h.parts), rows_n), kBlock, 0, st>>>(
-                    src, delta, cfg.d, out->sign_words, c->W, c->sign_tb, c->sign_partials, out->scales, rows, h.gave_up, h.patience);
+                    src, delta, cfg.d, out->sign_words, c->W, c->sign_tb, c->sign_partials, out->scales, rows, h.gave_up, h.patience, h.self);
             });
         });
-        if (h.parts > 1)
+        if (h.parts > 1 && !h.self)
             k_sign_held_finish<<<dim3(static_cast<unsigned>(h.parts), rows_n), kBlock, 0, st>>>(
                 delta, dstr, cfg.d, out->scales, h.T, h.gave_up, rows, HeldUpdate{nullptr, nullptr, 0.f, 0.f});
         return ds_launch_status();
@@ -1288,10 +1315,10 @@ ds_status_t ds_sign_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
                 constexpr bool RM = decltype(rm)::value;
                 constexpr int UPD = decltype(up)::value ? (decltype(mo)::value ? 2 : 1) : 0;
                 k_sign_held_server<RM, UPD, R, L><<<static_cast<unsigned>(h.parts), kBlock, 0, st>>>(
-                    a, delta_s, cfg.d, out->sign_words, c->sign_tb, c->sign_partials, out->scales, u, rows, h.gave_up, h.patience);
+                    a, delta_s, cfg.d, out->sign_words, c->sign_tb, c->sign_partials, out->scales, u, rows, h.gave_up, h.patience, h.self);
             });
         });
-        if (h.parts > 1)
+        if (h.parts > 1 && !h.self)
             k_sign_held_finish<<<static_cast<unsigned>(h.parts), kBlock, 0, st>>>(
                 delta_s, cfg.d, cfg.d, out->scales, h.T, h.gave_up, rows, u);
         return ds_launch_status();

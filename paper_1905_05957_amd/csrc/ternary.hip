@@ -225,10 +225,30 @@ __device__ __forceinline__ uint32_t tern_kept(uint32_t kept, uint32_t *cnt)
     return total;
 }
 
+// Encodes what a workgroup that gave up did not; the thread's non-zero codes.
+template <bool BF16>
+__device__ __forceinline__ uint32_t tern_finish_part(const void *grow, int64_t d, int part, int T, float m, int row, TernKey K,
+                                                     uint64_t *neg_row, uint64_t *nz_row, uint32_t words)
+{
+    uint32_t kept = 0;
+    f32x4 next = ld4_grad<BF16>(grow, static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4, d);
+    for (int t = 0; t < T; ++t) {
+        const int64_t e = (static_cast<int64_t>(part) * T + t) * kTile + threadIdx.x * 4;
+        const uint32_t quad = static_cast<uint32_t>(e >> 2);
+        const f32x4 v = next;
+        if (t + 1 < T) next = ld4_grad<BF16>(grow, e + kTile, d);       // zero past the end of the row
+        const uint32_t code = tern_codes4(v, m, quad, static_cast<int>(d - e), row, K);
+        tern_put_words(code, quad, neg_row, nz_row, words);
+        kept += __popc(code & 15u);
+    }
+    return kept;
+}
+
 template <bool BF16, int R, int L>
 __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void *g, int64_t gs, int64_t d, int32_t n_tiles, double *psum,
-                                                                     float *pmax, uint32_t *pcnt, float *rowmax, double *rowsum, TernKey K, uint64_t *neg, uint64_t *nz, int64_t W,
-                                                                     float *scales, HeldRow *rows, uint32_t *gave_up, uint32_t patience)
+                                                                     float *pmax, uint32_t *pcnt, float *rowmax, double *rowsum, TernKey K,
+                                                                     uint64_t *neg, uint64_t *nz, int64_t W, float *scales, HeldRow *rows,
+                                                                     uint32_t *gave_up, uint32_t patience, bool self)
 {
     constexpr int T = R + L;
     __shared__ TernShared<T> sm;
@@ -318,7 +338,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
                 for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
                 if (lane_id() == 0) {
                     rowmax[row] = mx;                         // for the finish launch
-                    rowsum[row] = total;
+                    as_shared(reinterpret_cast<uint64_t *>(rowsum))[row].store(__double_as_longlong(total));
                     rows[row].pub.store(kHeldValue | __float_as_uint(mx));
                     sm.sh[1] = __float_as_uint(mx);
                 }
@@ -327,10 +347,10 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
             mx = __uint_as_float(sm.sh[1]);
         }
         if (threadIdx.x == 0) {
-            gave_up[row * static_cast<int64_t>(gridDim.x) + blockIdx.x] = ok ? 0u : 1u;
+            as_shared(gave_up + row * static_cast<int64_t>(gridDim.x))[blockIdx.x].store(ok ? 0u : 1u);
             if (!ok) rows[row].late.store(1u);
         }
-        if (!ok) return;                                      // uniform
+        if (!ok && !(kHeldSelf<R, L> && self)) return;        // uniform
     }
     held_fence(v, left);
     const uint32_t words = static_cast<uint32_t>(W) * 2u, quad0 = static_cast<uint32_t>(first >> 2) + threadIdx.x;
@@ -342,14 +362,34 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
         tern_put_words(code, quad, neg_row, nz_row, words);
         kept += __popc(code & 15u);
     };
+    if (!kHeldSelf<R, L> || ok) {                             // uniform
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-        encode(v[t], t);
-        __builtin_amdgcn_sched_barrier(0);
-    }
+        for (int t = 0; t < R; ++t) {
+            encode(v[t], t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll 1
-    for (int t = R; t < T; ++t) encode(far[t - R][threadIdx.x], t);
+        for (int t = R; t < T; ++t) encode(far[t - R][threadIdx.x], t);
+    }
     kept = tern_kept(kept, sm.cnt);
+    if constexpr (kHeldSelf<R, L>)
+        if (self) {
+            uint32_t all;
+            if (!held_depart(rows + row, gridDim.x, ok, kept, sm.sh, &all)) return;
+            if (rows[row].late.load() != 0u) {                // uniform: all have departed
+                const float m = __uint_as_float(static_cast<uint32_t>(rows[row].pub.load()));
+                uint32_t more = 0;
+                for (uint32_t p = 0; p < gridDim.x; ++p)
+                    if (as_shared(gave_up + row * static_cast<int64_t>(gridDim.x))[p].load() != 0u)
+                        more += tern_finish_part<BF16>(grow, d, static_cast<int>(p), T, m, row, K, neg_row, nz_row, words);
+                __syncthreads();                              // sm.cnt is used again
+                all += tern_kept(more, sm.cnt);
+            }
+            if (threadIdx.x != 0) return;
+            scales[row] = tern_scale(__longlong_as_double(static_cast<long long>(as_shared(reinterpret_cast<uint64_t *>(rowsum))[row].load())), all);
+            rows[row].next_call(row == 0);
+            return;
+        }
     if (threadIdx.x != 0) return;
     if (alone) scales[row] = tern_scale(row_sum_alone, kept);
     else pcnt[static_cast<int64_t>(row) * n_tiles + blockIdx.x] = kept;    // added up by the finish launch
@@ -374,20 +414,9 @@ __global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int6
     if (late) {
         uint32_t kept = 0;
         const bool mine = gave_up[row * static_cast<int64_t>(gridDim.x) + part] != 0u;
-        if (mine) {
-            const void *grow = grad_row<BF16>(g, gs, row);
-            const float m = rowmax[row];
-            f32x4 next = ld4_grad<BF16>(grow, static_cast<int64_t>(part) * T * kTile + threadIdx.x * 4, d);
-            for (int t = 0; t < T; ++t) {
-                const int64_t e = (static_cast<int64_t>(part) * T + t) * kTile + threadIdx.x * 4;
-                const uint32_t quad = static_cast<uint32_t>(e >> 2);
-                const f32x4 v = next;
-                if (t + 1 < T) next = ld4_grad<BF16>(grow, e + kTile, d);       // zero past the end of the row
-                const uint32_t code = tern_codes4(v, m, quad, static_cast<int>(d - e), row, K);
-                tern_put_words(code, quad, neg + row * W, nz + row * W, static_cast<uint32_t>(W) * 2u);
-                kept += __popc(code & 15u);
-            }
-        }
+        if (mine)
+            kept = tern_finish_part<BF16>(grad_row<BF16>(g, gs, row), d, part, T, rowmax[row], row, K, neg + row * W, nz + row * W,
+                                          static_cast<uint32_t>(W) * 2u);
         kept = tern_kept(kept, cnt);
         if (threadIdx.x == 0) {
             if (mine) cnt_row[part].store(kept);
@@ -456,9 +485,10 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     DS_HIP_TRY(hipMalloc(&t->rowsum, n * sizeof(double)));
     // GPU time of a worker call, two looks as separate launches against sizes of the held route.  In a stream of
     // calls the four launches of two looks also cost the host 17 us, the two of this route 12 us, and the one of a
-    // row that one workgroup holds 10 us.
-    //  * one workgroup, 8 tiles in 8: 7.8 .. 8.1 us (bf16 8.9 .. 9.4), two looks 8.9 .. 10.6 us; 12 tiles in 14: 11.5 .. 11.9 us
-    //    (bf16 13.1 .. 13.5), 9.0 .. 10.6 us;
+    // row that finishes itself or that one workgroup holds 10 us.
+    //  * one workgroup, 4 tiles in 4: 5.2 .. 5.5 us (bf16 5.8 .. 6.2), two looks 8.8 .. 10.3 us; 8 tiles in 8: 7.8 .. 8.1 us (bf16
+    //    8.9 .. 9.4), 8.9 .. 10.6 us; 12 tiles in 14: 11.5 .. 11.9 us (bf16 13.1 .. 13.5), 9.0 .. 10.6 us; one tile per workgroup
+    //    5 to 24 tiles 7.7 .. 8.6 us;
     //  * one row gains on the host's side only: d = 300,001 9.1 us, with 2 tiles 10.1 us; 1,000,003 10.1 us, with 1, 2, 4
     //    and 8 tiles 16.0, 12.9, 12.1 and 13.7 us; 2,500,001 13.3 us, with 4 and 8 tiles 16.6 and 16.2 us;
     //  * n = 8: 300,001 13.1 us, 1, 2 and 4 tiles 18.7, 12.2 and 12.7 us; 1,000,003 23.3 us, 4 and 8 tiles 18.0 and 17.9 us;
@@ -470,7 +500,7 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     static constexpr HeldStep f32[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {24, 2, 0}};
     static constexpr HeldStep bf16[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {8, 2, 0}};
     const auto &steps = c->cfg.n == 1 ? one_row : c->cfg.grad_dtype == DS_BF16 ? bf16 : f32;
-    const ds_status_t rc = held_size(c, c->cfg.n, 8, steps, [](auto r, auto l) {
+    const ds_status_t rc = held_size(c, c->cfg.n, 4, steps, [](auto r, auto l) {
         constexpr int R = decltype(r)::value, L = decltype(l)::value;
         int per_cu = 0;
         return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_tern_held<false, R, L>, kBlock, 0) == hipSuccess ? per_cu : -1;
@@ -512,9 +542,9 @@ ds_status_t ds_ternary_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
                 constexpr int R = decltype(rr)::value, L = decltype(ll)::value;
                 k_tern_held<BF, R, L><<<hgrid, kBlock, 0, st>>>(g, gs, d, static_cast<int32_t>(n_tiles), t->psum, t->pmax, t->pcnt, t->rowmax,
                                                                 t->rowsum, K,
-                                                                out->sign_words, nz, c->W, out->scales, rows, h.gave_up, h.patience);
+                                                                out->sign_words, nz, c->W, out->scales, rows, h.gave_up, h.patience, h.self);
             });
-            if (h.parts > 1)
+            if (h.parts > 1 && !h.self)
                 k_tern_held_finish<BF><<<hgrid, kBlock, 0, st>>>(g, gs, d, static_cast<int32_t>(n_tiles), t->pcnt, t->rowmax, t->rowsum, K,
                                                                  out->sign_words, nz, c->W, out->scales, h.T, h.gave_up, rows);
         };

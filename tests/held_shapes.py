@@ -8,7 +8,8 @@ rules that moves a shape to another way does not go unnoticed."""
 SIGN_WORKER = [
     (3, 2047, "f32", False, 1, 1), (2, 2049, "f32", True, 2, 1), (2, 4 * 2048 - 3, "bf16", False, 4, 1),
     (2, 5 * 2048 + 2, "f32", False, 8, 1), (2, 8 * 2048 - 1, "bf16", True, 8, 1),
-    (2, 8 * 2048 + 1, "f32", False, 14, 1), (2, 14 * 2048 - 2, "f32", True, 14, 1), (1100, 12 * 2048 - 1, "bf16", False, 14, 1),
+    (2, 8 * 2048 + 1, "f32", False, 1, 9), (2, 14 * 2048 - 2, "f32", True, 1, 14), (2, 32 * 2048 - 1, "bf16", False, 1, 32),
+    (2, 32 * 2048 + 1, "f32", False, 1, 33), (60, 30 * 2048 + 5, "f32", False, 2, 16), (1100, 12 * 2048 - 1, "bf16", False, 14, 1),
     (2, 14 * 2048, "bf16", True, 1, 14), (2, 24 * 2048 - 2, "f32", False, 1, 24), (2, 25 * 2048 + 3, "f32", False, 1, 26),
     (5, 300_001, "bf16", False, 2, 74), (8, 700_002, "f32", True, 4, 86), (9, 1_800_003, "f32", False, 8, 110),
     (9, 2_600_001, "bf16", False, 14, 91), (9, 2_600_003, "f32", True, 14, 91),
@@ -19,7 +20,7 @@ SIGN_WORKER = [
 # n, d, momentum, rms, tiles, workgroups
 SIGN_SERVER = [
     (1, 3, True, False, 1, 1), (3, 2047, False, False, 1, 1), (70, 2047, True, False, 1, 1), (9, 2 * 2048 - 1, True, False, 2, 1),
-    (28, 2 * 2048 - 1, False, True, 2, 1), (8, 3 * 2048 + 2, True, False, 4, 1), (16, 4 * 2048, False, True, 4, 1),
+    (28, 2 * 2048 - 1, False, True, 2, 1), (8, 3 * 2048 + 2, True, False, 4, 1), (16, 4 * 2048, False, True, 1, 4),
     (70, 2 * 2048 - 1, True, False, 1, 2), (8, 4 * 2048 + 2, False, True, 1, 5), (16, 14 * 2048, True, False, 1, 14),
     (5, 24 * 2048 - 3, True, False, 1, 24), (12, 25 * 2048 + 1, False, False, 1, 26), (40, 700_002, True, False, 1, 342),
     (8, 700_002, True, False, 2, 171), (12, 700_003, False, False, 2, 171), (40, 3_000_001, False, True, 2, 733),
@@ -30,7 +31,8 @@ SIGN_SERVER = [
 
 # n, d, dtype, tiles, workgroups
 TERNARY = [
-    (3, 2047, "f32", 1, 1), (2, 4 * 2048 - 3, "bf16", 4, 1), (2, 5 * 2048 + 1, "f32", 8, 1), (2, 8 * 2048 - 2, "bf16", 8, 1),
+    (3, 2047, "f32", 1, 1), (2, 4 * 2048 - 3, "bf16", 4, 1), (2, 2 * 2048 - 1, "f32", 2, 1), (2, 5 * 2048 + 1, "f32", 1, 6), (2, 8 * 2048 - 2, "bf16", 1, 8),
+    (2, 32 * 2048 - 3, "bf16", 1, 32), (2, 32 * 2048 + 1, "f32", 1, 33), (60, 30 * 2048 + 5, "f32", 2, 16),
     (2, 8 * 2048 + 1, "f32", 1, 9), (2, 14 * 2048, "bf16", 1, 14), (2, 24 * 2048 - 2, "f32", 1, 24), (2, 25 * 2048 + 3, "f32", 1, 26),
     (5, 300_001, "bf16", 2, 74), (1, 300_003, "f32", 2, 74), (8, 700_002, "f32", 4, 86), (1, 1_000_003, "bf16", 4, 123),
     (9, 1_800_003, "f32", 8, 110), (4, 8_000_002, "bf16", 8, 489), (9, 2_600_001, "bf16", 14, 91), (9, 2_600_002, "f32", 14, 91),

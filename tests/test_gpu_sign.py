@@ -267,10 +267,11 @@ def test_sign_whole_vector_in_one_look(gpu_device, n, d, dtype, rms, patience):
         ctx.close()
 
 
-def test_sign_whole_vector_over_many_calls_that_give_up(gpu_device):
+@pytest.mark.parametrize("d", [200_003, 40_001])
+def test_sign_whole_vector_over_many_calls_that_give_up(gpu_device, d):
     """Late calls are followed by 1, 2, 4, ... calls in which nobody waits (patience -1: every call that
     waits is late): 40 calls go through six such stretches and keep the bits of two looks."""
-    n, d = 3, 200_003
+    n = 3
     gen = torch.Generator(device=gpu_device)
     gen.manual_seed(1)
     g = torch.randn((n, d), device=gpu_device, generator=gen)
