@@ -191,9 +191,10 @@ static void with_held(int T, F f)
 }
 
 // One line of a kernel's choice of size: `T` tiles per workgroup if the device holds `rows` rows at once
-// (all, if they are fewer or 0 stands here) and a row is not more than `parts` workgroups (0: any number).
+// (all, if they are fewer or 0 stands here), a row is not more than `parts` workgroups (0: any number) and
+// rounds of whole rows keep at least `full` per cent of the device's workgroups busy.
 struct HeldStep {
-    int T, rows, parts;
+    int T, rows, parts, full = 0;
 };
 
 // Tiles per workgroup for `rows` rows, 0 = the kernel's way in separate launches; per_cu(R, L): resident
@@ -205,7 +206,9 @@ struct HeldStep {
 //    room: the smallest size with which all rows are there at once, or else a few rows, so that one row's loads
 //    overlap another's barrier and stores;
 //  * the arrivals of a row's workgroups are additions to one word, which come one after the other (11 ns
-//    each), so short rows take fewer workgroups than the device would hold.
+//    each), so short rows take fewer workgroups than the device would hold;
+//  * rows that are not all there at once go in rounds: what the last round leaves free, and the room that one more row
+//    would not fit into, is idle.
 // The lines lie where the kernels were measured to cross over; the figures stand with each kernel's steps.
 template <class F, int N>
 static ds_status_t held_size(const ds_ctx *c, int64_t rows, int one, const HeldStep (&steps)[N], F per_cu, ds_held_sync *sync)
@@ -214,21 +217,23 @@ static ds_status_t held_size(const ds_ctx *c, int64_t rows, int one, const HeldS
     DS_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
     const int64_t tiles = c->n_tiles;
     sync->T = 0;
-    auto take = [&](int T, int64_t at_once, int64_t most) {
+    auto take = [&](int T, int64_t at_once, int64_t most, int full) {
         int held = 0;
         with_held(T, [&](auto r, auto l) { held = per_cu(r, l); });
         if (held < 0) return DS_ERR_DEVICE;
         const int64_t slots = static_cast<int64_t>(held) * cus, parts = (tiles + T - 1) / T;
-        if (at_once * parts <= slots && parts <= most) { sync->T = T; sync->slots = slots; }
+        if (at_once * parts > slots || parts > most) return DS_OK;
+        const int64_t together = slots / parts, rounds = (rows + together - 1) / together;
+        if (100 * rows * parts >= full * rounds * slots) { sync->T = T; sync->slots = slots; }
         return DS_OK;
     };
     if (tiles <= one) {
         for (int T : kHeldT)
-            if (tiles <= T) return take(T, 1, 1);
+            if (tiles <= T) return take(T, 1, 1, 0);
     }
     for (const HeldStep &s : steps) {
         if (s.T == 0) break;
-        const ds_status_t rc = take(s.T, (s.rows && s.rows < rows) ? s.rows : rows, s.parts ? s.parts : tiles);
+        const ds_status_t rc = take(s.T, (s.rows && s.rows < rows) ? s.rows : rows, s.parts ? s.parts : tiles, s.full);
         if (rc != DS_OK || sync->T) return rc;
     }
     return DS_OK;

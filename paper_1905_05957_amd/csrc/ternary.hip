@@ -213,7 +213,7 @@ __device__ __forceinline__ void tern_put_words(uint32_t code, uint32_t quad, uin
     }
 }
 
-// Non-zero codes of the workgroup, in thread 0.  Every thread calls, with its own.
+// Non-zero codes of the workgroup.  Every thread calls, with its own.
 __device__ __forceinline__ uint32_t tern_kept(uint32_t kept, uint32_t *cnt)
 {
     kept = wave_sum_u32(kept);
@@ -495,10 +495,13 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     //    2,500,001 44 us, 8, 14 and 24 tiles 39, 35 and 37 us; 5,000,003 78, 69, 63 and 69 us;
     //  * 8,000,002, two and more rows on chip: n = 8 121 us, 8 and 24 tiles 113 and 109 us; bf16 125, 119 and 133 us;
     //    8 x 11,173,962 164 us, 24 tiles (two rows) 149 us, 8 tiles (a row and a half) 197 us; bf16 171 and 173 us;
-    //    8 x 16,000,001, not two rows with any size: 231 us, 24 tiles 273 us.
+    //    8 x 16,000,001, not two rows with any size: 231 us, 24 tiles 273 us;
+    //  * rounds of two rows, n = 3 .. 16, two looks : held by how much of the device the rounds keep busy.  24 tiles: 0.87 at 54 %
+    //    (3 x 9,000,001, 57.6 and 66.3 us), 0.91 .. 0.98 at 60 .. 68 %, 0.98 .. 1.04 at 70 .. 75 %, 1.05 .. 1.14 above.  8 tiles of
+    //    bf16: 0.91 .. 0.98 at 60 .. 70 %, 0.98 .. 1.01 at 72 .. 80 %, 1.00 .. 1.06 above.
     static constexpr HeldStep one_row[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-    static constexpr HeldStep f32[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {24, 2, 0}};
-    static constexpr HeldStep bf16[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {8, 2, 0}};
+    static constexpr HeldStep f32[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {24, 2, 0, 70}};
+    static constexpr HeldStep bf16[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {8, 2, 0, 80}};
     const auto &steps = c->cfg.n == 1 ? one_row : c->cfg.grad_dtype == DS_BF16 ? bf16 : f32;
     const ds_status_t rc = held_size(c, c->cfg.n, 4, steps, [](auto r, auto l) {
         constexpr int R = decltype(r)::value, L = decltype(l)::value;

@@ -115,7 +115,8 @@ def test_a_ternary_call_that_gives_up(gpu_device):
 # The first shape has a fraction of the second one's work, or the same work on narrower gradients.
 @pytest.mark.parametrize("less,more,factor", [((1, 1_000_003, "f32"), (8, 1_000_003, "f32"), 1.0), ((1, 5_000_003, "bf16"), (4, 5_000_003, "bf16"), 0.8),
                                               ((8, 24 * 2048, "f32"), (8, 100_001, "f32"), 1.3), ((4, 14 * 2048, "bf16"), (4, 100_001, "bf16"), 1.3),
-                                              ((16, 11_173_962, "bf16"), (16, 11_173_962, "f32"), 1.25), ((8, 24_000_000, "bf16"), (8, 24_000_000, "f32"), 1.2)])
+                                              ((16, 11_173_962, "bf16"), (16, 11_173_962, "f32"), 1.25), ((3, 9_000_001, "f32"), (4, 9_000_001, "f32"), 0.9),
+                                              ((5, 6_000_000, "bf16"), (6, 6_000_000, "bf16"), 0.9), ((8, 24_000_000, "bf16"), (8, 24_000_000, "f32"), 1.2)])
 def test_ternary_times_follow_the_work(gpu_device, less, more, factor):
     us = []
     for n, d, dtype in (less, more):
