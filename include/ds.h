@@ -171,8 +171,9 @@ typedef struct {
                                  failure for tests of the error path, every kernel still exits).
                                  Where another compressor's workgroups wait for each other inside a
                                  launch (a worker block with one value per vector), -1 makes them
-                                 give up at once too; the launch after it then completes the
-                                 work, with the same results */
+                                 give up at once too; the launch after it, or for a row of up to
+                                 32 tiles of 2048 elements the row's last workgroup, then completes
+                                 the work, with the same results */
 } ds_config_t;
 
 typedef struct ds_ctx ds_ctx_t;
