@@ -27,7 +27,8 @@
 //   verify     if the candidates number fewer than k, or the k-th key lies outside the
 //              histogram window (the sample misjudged), the row takes the exact two-look
 //              route: v restored, dense 12-bit histogram, pick, dense compaction.
-// The refinement exists twice: as ONE launch whose workgroups are all resident and wait for
+// Rows of up to 65,536 elements take one workgroup and one launch for all of that (k_topk_solo).  For longer
+// ones the refinement exists twice: as ONE launch whose workgroups are all resident and wait for
 // each other per row (k_topk_finish, the default), and as a chain of small launches in which
 // the last workgroup of a row finishes each step (12 + 11 + 8 key bits), for contexts whose
 // calls may overlap on the device.  Nothing depends on scheduling order, so results are
@@ -94,6 +95,7 @@ struct ds_topk_scratch {
     int64_t n_sub;        // 256-element subtiles per row (sampling, server ranges)
     int64_t n_reg, reg_pad, n_groups;
     int rows;
+    bool solo;            // rows are short: one workgroup per row (k_topk_solo)
     // fused refinement route (k_topk_finish)
     uint32_t *fhist;      // [rows][kFRow], zero between calls
     char *sync;           // [rows][kSyncStride] arrival counters and published picks
@@ -1408,6 +1410,460 @@ __global__ __launch_bounds__(kBlock, 8) void k_topk_finish(FinishArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
+// short rows: one workgroup does the whole call for a row
+// ---------------------------------------------------------------------------------------
+// A row of up to 65,536 elements fits the registers of one compute unit (16 wavefronts, 64 elements per
+// thread): it is loaded once, the k-th key is found with histograms in LDS, and the error, the message
+// and the model update leave from there.  Nothing waits for another workgroup and nothing passes
+// through memory between the steps.  What bounds it is latency and the vector issue of a single compute unit,
+// 0.1 us for every instruction that all 65,536 elements take; the launches it stands for (sample, dense pass,
+// refinement, on the server the ranges too) are each a few microseconds of ramp and of round trips to memory
+// around next to no work.
+//
+// Thread t holds elements tile * 4096 + 4 t .. + 3 of up to 16 tiles.  As few instructions as possible see all of
+// them: one in eight (one in four of rows up to 32,768) is put into a histogram whose key of rank 1.15 k/8 + 32
+// is a lower bound lo for the k-th key, a comparison as floats counts the elements that reach it, and
+// these candidates are listed in LDS in index order.  The rest works on the list: three histograms of 12, 11 and
+// 8 bits, then the kept ones to their slots.  Where the list does not hold the k-th key (fewer than k candidates)
+// or does not fit (very many ties), the same histograms are taken over all elements.
+//
+// A step (worker, server and update) at 4 x 60,040, k = 600: 67 us in the launches it stands for, 46 us here (two
+// kernels of 23 us, of which a compute unit needs about 12 for loads and stores); 4 x 4096: 61 and 28 us;
+// 16 x 65,536, k = 66, the least gain of 62 shapes of 1 to 600 rows but one: 67 and 51 us; 200 x 60,040: 212 and
+// 174 us.  With the histograms and the emission over all elements instead of a list: 107 us at 4 x 60,040.
+constexpr int kSoloThreads = 1024, kSoloWaves = kSoloThreads / 64;
+constexpr int kSoloTile = 4 * kSoloThreads, kSoloTiles = 16;
+constexpr int64_t kSoloMax = static_cast<int64_t>(kSoloTile) * kSoloTiles;
+constexpr int kSoloStrip = 8 * kSoloTile;          // elements of the server's vector that LDS holds at a time
+constexpr int kSoloList = 16384;                   // candidates that LDS holds, in the same memory
+constexpr int kSoloSampleFrom = kSoloTile;         // rows of more elements are sampled first
+constexpr int kSoloThinFrom = 8 * kSoloTile;       // and one element in eight instead of four in rows longer than this
+
+struct SoloShared {
+    union {
+        float strip[kSoloStrip];
+        u32x2 list[kSoloList];                     // (index, value bits) in index order
+    };
+    uint32_t h[kH1], h2[kH2], h3[kH3];
+    uint32_t cnt[kSoloTiles * kSoloWaves];         // per tile and wavefront
+    uint32_t part[kSoloWaves], part2[kSoloWaves], out[2];
+};
+static_assert(sizeof(float) * kSoloStrip == sizeof(u32x2) * kSoloList, "strip and list share their memory");
+
+// Adds one to bin `bin` for every lane with `on`; lanes that all hit one bin (ties, zeros) add once.
+__device__ __forceinline__ void solo_add(uint32_t *h, uint32_t bin, bool on)
+{
+    const uint64_t mask = __ballot(on);
+    if (mask == 0) return;
+    const int lead = __builtin_ctzll(mask);
+    const uint32_t first = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(bin), lead));
+    if (__ballot(on && bin == first) == mask) {
+        if (lane_id() == lead) atomicAdd(&h[first], static_cast<uint32_t>(__popcll(mask)));
+    } else if (on) {
+        atomicAdd(&h[bin], 1u);
+    }
+}
+
+// Largest bin b with at least `need` keys in the bins >= b, and what is still needed from it: out[0], out[1]
+// (kNone if the histogram holds fewer keys).  Clears the histogram.  Every thread calls; the histogram
+// is complete, and `out` may be read until the next call's first barrier.
+template <int NB>
+__device__ __forceinline__ void solo_pick(uint32_t *h, uint32_t need, uint32_t *part, uint32_t *out)
+{
+    constexpr int PER = (NB >= kSoloThreads) ? NB / kSoloThreads : 1;
+    const int t = threadIdx.x;
+    const bool active = t * PER < NB;
+    __syncthreads();
+    uint32_t local[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        local[j] = active ? h[t * PER + j] : 0u;
+        sum += local[j];
+        if (active) h[t * PER + j] = 0u;
+    }
+    const uint32_t pre = wave_inclusive_scan_u32(sum);
+    const uint32_t incl = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(pre), 63)) - pre + sum;
+    if (lane_id() == 0) part[wave_id()] = incl;
+    if (t == 0) { out[0] = kNone; out[1] = 0u; }
+    __syncthreads();
+    uint32_t running = incl - sum;
+    for (int w = wave_id() + 1; w < kSoloWaves; ++w) running += part[w];
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) {
+        const uint32_t above = running;
+        running += local[j];
+        if (running >= need && above < need) { out[0] = static_cast<uint32_t>(t * PER + j); out[1] = need - above; }
+    }
+    __syncthreads();
+}
+
+// v = delta_s + (1/n) sum_i Q[v_i] of the server, as the chain over workers in ascending order: strips
+// of 32768 elements in LDS, to which the messages are applied one worker after the other (a message
+// lists an element once).  Eight batches of 1024 entries are in flight at a time.
+__device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t d, float *strip, f32x4 (&v)[kSoloTiles])
+{
+    const int tid = threadIdx.x;
+    const int batches = static_cast<int>((src.k + kSoloThreads - 1) / kSoloThreads);
+    constexpr int kTilesOfStrip = kSoloStrip / kSoloTile;
+#pragma unroll
+    for (int q = 0; q < kSoloTiles / kTilesOfStrip; ++q) {
+        const int64_t base = static_cast<int64_t>(q) * kSoloStrip;
+        if (base < d) {                                        // uniform
+            f32x4 a[kTilesOfStrip];
+#pragma unroll
+            for (int t = 0; t < kTilesOfStrip; ++t) {
+                const int64_t e = base + t * kSoloTile + tid * 4;
+                a[t] = ld4(src.delta_s, e, d);
+            }
+            int w = 0, b = 0;                                  // worker and batch of its entries
+            bool put = false;
+            while (w < src.n) {
+                u32x2 pr[8];
+                bool fresh[8];                                 // first batch of a worker
+                int held = 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    pr[i] = u32x2{kNone, 0u};
+                    fresh[i] = false;
+                    if (w < src.n) {
+                        const int64_t j = static_cast<int64_t>(b) * kSoloThreads + tid;
+                        if (j < src.k) pr[i] = src.pairs_in[static_cast<int64_t>(w) * src.k + j];
+                        fresh[i] = b == 0;
+                        held = i + 1;
+                        if (++b == batches) { b = 0; ++w; }
+                    }
+                }
+                if (!put) {
+#pragma unroll
+                    for (int t = 0; t < kTilesOfStrip; ++t) reinterpret_cast<f32x4 *>(strip)[t * kSoloThreads + tid] = a[t];
+                    put = true;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (i >= held) break;
+                    if (fresh[i]) __syncthreads();             // what the worker before has added is in
+                    const uint32_t rel = pr[i].x - static_cast<uint32_t>(base);
+                    if (rel < static_cast<uint32_t>(kSoloStrip)) strip[rel] = __fmaf_rn(__uint_as_float(pr[i].y), src.inv_n, strip[rel]);
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < kTilesOfStrip; ++t) v[q * kTilesOfStrip + t] = reinterpret_cast<const f32x4 *>(strip)[t * kSoloThreads + tid];
+        }
+    }
+}
+
+// Raw loads of a row's elements, kept apart from their use so that many are in flight.  `at` is clamped
+// into the row by the caller (d >= 4); value() forms v.
+struct SoloRaw {
+    f32x4 g, delta;
+    u32x2 h;
+};
+template <bool BF16>
+__device__ __forceinline__ void solo_fetch(const WorkerV<BF16> &src, int row, int at, SoloRaw &r)
+{
+    if constexpr (BF16) r.h = __builtin_nontemporal_load(reinterpret_cast<const u32x2_any *>(static_cast<const uint16_t *>(src.g) + row * src.gs + at));
+    else r.g = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(static_cast<const float *>(src.g) + row * src.gs + at));
+    r.delta = *reinterpret_cast<const f32x4_any *>(src.delta + row * src.dstr + at);
+}
+__device__ __forceinline__ void solo_fetch(const GradV &src, int row, int at, SoloRaw &r)
+{
+    r.g = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(src.g + row * src.gs + at));
+}
+template <bool BF16>
+__device__ __forceinline__ f32x4 solo_value(const WorkerV<BF16> &, const SoloRaw &r)
+{
+    if constexpr (BF16)
+        return f32x4{__uint_as_float(r.h.x << 16), __uint_as_float(r.h.x & 0xFFFF0000u), __uint_as_float(r.h.y << 16),
+                     __uint_as_float(r.h.y & 0xFFFF0000u)} + r.delta;
+    else return r.g + r.delta;
+}
+__device__ __forceinline__ f32x4 solo_value(const GradV &, const SoloRaw &r) { return r.g; }
+
+// v of a row, zero past its end: loads of eight tiles in flight, four by four.
+template <class Src>
+__device__ __forceinline__ void solo_row_v(const Src &src, int row, int d, f32x4 (&v)[kSoloTiles])
+{
+    const int tid = threadIdx.x, whole = d & ~3;
+    const bool mine = (whole & (kSoloTile - 1)) == tid * 4 && whole < d;     // the thread whose last group of four d cuts
+    f32x4 cut = {0.f, 0.f, 0.f, 0.f};
+    if (mine) cut = src.load(row, whole, d, nullptr);
+    SoloRaw ring[2][4];
+    auto fetch = [&](int q) {
+        if (q * 4 * kSoloTile < whole) {                       // uniform; whole >= 4 then
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int e = (q * 4 + j) * kSoloTile + tid * 4;
+                solo_fetch(src, row, e < whole ? e : whole - 4, ring[q & 1][j]);
+            }
+        }
+    };
+    fetch(0);
+#pragma unroll
+    for (int q = 0; q < kSoloTiles / 4; ++q) {
+        if (q + 1 < kSoloTiles / 4) fetch(q + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (q * 4 * kSoloTile < whole) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int e = (q * 4 + j) * kSoloTile + tid * 4;
+                const f32x4 w = solo_value(src, ring[q & 1][j]);
+                v[q * 4 + j] = (e < whole) ? w : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int t = 0; t < kSoloTiles; ++t)
+        if (mine && (whole / kSoloTile) == t) v[t] = cut;
+}
+
+// Before a tile of a phase: what the compiler derived from it in an earlier phase (keys, masks, addresses) is not
+// carried along in registers that the tiles need.
+__device__ __forceinline__ void solo_fence(f32x4 &v, int &first)
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" : "+v"(v));
+    asm volatile("" : "+v"(first));
+}
+
+// The k-th key of the elements that `level` puts into a histogram (bin, whether it counts): threshold key T and
+// the ties at T to keep.  level(h, shift, mask, prefix, prefix_shift) adds the keys whose upper bits are `prefix`.
+template <class F>
+__device__ __forceinline__ void solo_threshold(SoloShared &sm, uint32_t need, F level, uint32_t &T, uint32_t &k3)
+{
+    level(sm.h, 19, 4095u, 0u, 31);
+    solo_pick<kH1>(sm.h, need, sm.part, sm.out);
+    const uint32_t b1 = sm.out[0], k1 = sm.out[1];
+    level(sm.h2, 8, static_cast<uint32_t>(kH2 - 1), b1, 19);
+    solo_pick<kH2>(sm.h2, k1, sm.part, sm.out);
+    const uint32_t b2 = (b1 << 11) | sm.out[0], k2 = sm.out[1];
+    level(sm.h3, 0, 255u, b2, 8);
+    solo_pick<kH3>(sm.h3, k2, sm.part, sm.out);
+    T = (b2 << 8) | sm.out[0];
+    k3 = sm.out[1];
+}
+
+// What lies before this wavefront's part of tile t in the counts of all tiles and wavefronts, for lane
+// t * 4 + (wave >> 2); `all` = the total.
+__device__ __forceinline__ uint32_t solo_before(const uint32_t *cnt, int wave, int shift, uint32_t mask, uint32_t &all)
+{
+    static_assert(kSoloTiles * kSoloWaves == 256 && kSoloWaves == 16, "four entries per lane, four lanes per tile");
+    const u32x4 c4 = reinterpret_cast<const u32x4 *>(cnt)[lane_id()];
+    uint32_t before = 0, sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t c = (c4[j] >> shift) & mask;
+        if (j < (wave & 3)) before += c;
+        sum += c;
+    }
+    const uint32_t incl = wave_inclusive_scan_u32(sum);
+    all = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+    return before + incl - sum;
+}
+
+// sample_rank: 0 = the row is not sampled.  WR: the error is written to buf.  x != nullptr (one row
+// only): x <- fma(-gamma, val, x) at the kept entries.
+template <class Src, bool WR>
+__global__ __launch_bounds__(kSoloThreads) void k_topk_solo(Src src, float *buf, int64_t stride, int64_t d, int64_t k,
+                                                            uint32_t sample_rank, u32x2 *pairs, float *x, float gamma)
+{
+    constexpr bool kServer = std::is_same<Src, ServerV>::value;
+    __shared__ __attribute__((aligned(16))) SoloShared sm;
+    const int row = blockIdx.x, lane = lane_id(), tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+    const int dd = static_cast<int>(d);
+    const uint32_t need = static_cast<uint32_t>(k);
+    int first = tid * 4;
+    u32x2 *prow = pairs + static_cast<int64_t>(row) * k;
+    float *brow = WR ? buf + row * stride : nullptr;
+    f32x4 v[kSoloTiles];
+#pragma unroll
+    for (int t = 0; t < kSoloTiles; ++t) v[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (kServer) solo_server_v(src, d, sm.strip, v);
+    else solo_row_v(src, row, dd, v);
+    // the error is v but for the kept elements, which are cleared as they are emitted
+    if constexpr (WR) {
+#pragma unroll
+        for (int t = 0; t < kSoloTiles; ++t) {
+            if (t * kSoloTile < dd) {                          // uniform
+                solo_fence(v[t], first);
+                const int e = t * kSoloTile + first;
+                if (e < dd) st4(brow, e, d, v[t]);
+            }
+        }
+    }
+    for (int i = tid; i < kH1; i += kSoloThreads) sm.h[i] = 0u;
+    for (int i = tid; i < kH2; i += kSoloThreads) sm.h2[i] = 0u;
+    if (tid < kH3) sm.h3[tid] = 0u;
+    __syncthreads();
+
+    // lower bound; the elements past the end are 0 and never reach it
+    uint32_t lo = 1u;
+    if (sample_rank != 0u) {
+        const int thin = (dd > kSoloThinFrom) ? 1 : 0;
+#pragma unroll
+        for (int t = 0; t < kSoloTiles; ++t) {
+            if (t * kSoloTile < dd && !((t + wave) & thin)) {
+                solo_fence(v[t], first);
+                const int c = (lane + t) & 3, e = t * kSoloTile + first + c;
+                const float s = (c & 2) ? ((c & 1) ? v[t].w : v[t].z) : ((c & 1) ? v[t].y : v[t].x);
+                if (e < dd) atomicAdd(&sm.h[key_of(s) >> 19], 1u);
+            }
+        }
+        solo_pick<kH1>(sm.h, sample_rank, sm.part, sm.out);
+        if (sm.out[0] != kNone && sm.out[0] != 0u) lo = sm.out[0] << 19;
+    }
+    const float lo_f = __uint_as_float(lo);
+    // candidates per tile and wavefront (a NaN is the largest key and a candidate)
+#pragma unroll
+    for (int t = 0; t < kSoloTiles; ++t) {
+        if (t * kSoloTile < dd) {
+            solo_fence(v[t], first);
+            const uint32_t c = __popcll(__ballot(!(fabsf(v[t].x) < lo_f))) + __popcll(__ballot(!(fabsf(v[t].y) < lo_f))) +
+                               __popcll(__ballot(!(fabsf(v[t].z) < lo_f))) + __popcll(__ballot(!(fabsf(v[t].w) < lo_f)));
+            if (lane == 0) sm.cnt[t * kSoloWaves + wave] = c;
+        } else if (lane == 0) {
+            sm.cnt[t * kSoloWaves + wave] = 0u;
+        }
+    }
+    __syncthreads();
+    uint32_t listed;
+    const uint32_t at = solo_before(sm.cnt, wave, 0, ~0u, listed);
+    uint32_t T, k3;
+    if (listed >= need && listed <= static_cast<uint32_t>(kSoloList)) {        // uniform
+#pragma unroll
+        for (int t = 0; t < kSoloTiles; ++t) {
+            if (t * kSoloTile < dd) {
+                solo_fence(v[t], first);
+                const bool f0 = !(fabsf(v[t].x) < lo_f), f1 = !(fabsf(v[t].y) < lo_f), f2 = !(fabsf(v[t].z) < lo_f),
+                           f3 = !(fabsf(v[t].w) < lo_f);
+                if (__ballot(f0 || f1 || f2 || f3) != 0) {
+                    const uint32_t e = static_cast<uint32_t>(t * kSoloTile + first);
+                    uint32_t r = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(at), t * 4 + (wave >> 2)));
+                    r += lanes_below(__ballot(f0)) + lanes_below(__ballot(f1)) + lanes_below(__ballot(f2)) + lanes_below(__ballot(f3));
+                    if (f0) sm.list[r++] = u32x2{e, __float_as_uint(v[t].x)};
+                    if (f1) sm.list[r++] = u32x2{e + 1u, __float_as_uint(v[t].y)};
+                    if (f2) sm.list[r++] = u32x2{e + 2u, __float_as_uint(v[t].z)};
+                    if (f3) sm.list[r++] = u32x2{e + 3u, __float_as_uint(v[t].w)};
+                }
+            }
+        }
+        if constexpr (WR) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // v is stored before another thread clears parts of it
+        __syncthreads();
+        solo_threshold(sm, need, [&](uint32_t *h, int shift, uint32_t mask, uint32_t prefix, int prefix_shift) {
+            for (uint32_t i0 = 0; i0 < listed; i0 += kSoloThreads) {
+                const uint32_t i = i0 + tid;
+                const uint32_t key = (i < listed) ? sm.list[i].y & 0x7FFFFFFFu : 0u;
+                solo_add(h, (key >> shift) & mask, i < listed && (key >> prefix_shift) == prefix);
+            }
+        }, T, k3);
+        // every wavefront emits a stretch of the list
+        const uint32_t per = (listed + 64u * kSoloWaves - 1u) / (64u * kSoloWaves) * 64u;
+        const uint32_t i0 = wave * per, i1 = (i0 + per < listed) ? i0 + per : listed;
+        uint32_t gt = 0, eq = 0;
+        for (uint32_t b = i0; b < i1; b += 64u) {
+            const uint32_t i = b + lane;
+            const uint32_t key = (i < i1) ? sm.list[i].y & 0x7FFFFFFFu : 0u;
+            gt += __popcll(__ballot(i < i1 && key > T));
+            eq += __popcll(__ballot(i < i1 && key == T));
+        }
+        if (lane == 0) { sm.part[wave] = gt; sm.part2[wave] = eq; }
+        __syncthreads();
+        uint32_t slot0 = 0, ties = 0;
+        for (int w = 0; w < wave; ++w) { slot0 += sm.part[w]; ties += sm.part2[w]; }
+        slot0 += (ties < k3) ? ties : k3;
+        for (uint32_t b = i0; b < i1; b += 64u) {
+            const uint32_t i = b + lane;
+            const u32x2 pr = (i < i1) ? sm.list[i] : u32x2{0u, 0u};
+            const uint32_t key = pr.y & 0x7FFFFFFFu;
+            const bool is_eq = i < i1 && key == T;
+            const uint64_t eq_mask = __ballot(is_eq);
+            const bool keep = i < i1 && (key > T || (is_eq && ties + lanes_below(eq_mask) < k3));
+            const uint64_t keep_mask = __ballot(keep);
+            const uint32_t slot = slot0 + lanes_below(keep_mask);
+            if (keep && slot < need) {
+                prow[slot] = pr;
+                if constexpr (WR) brow[pr.x] = 0.f;
+            }
+            slot0 += __popcll(keep_mask);
+            ties += __popcll(eq_mask);
+        }
+    } else {
+        // v again from memory: as it has just been stored, or the gradient
+        const float *vrow;
+        if constexpr (WR) vrow = brow;
+        else vrow = src.g + row * src.gs;
+        // f(tile, four values, first element) for the thread's elements
+        auto each = [&](auto f) {
+            for (int t0 = 0; t0 * kSoloTile < dd; t0 += 4) {
+                f32x4 w[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) w[t] = ld4(vrow, (t0 + t) * kSoloTile + tid * 4, d);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if ((t0 + t) * kSoloTile < dd) f(t0 + t, w[t], (t0 + t) * kSoloTile + tid * 4);
+            }
+        };
+        solo_threshold(sm, need, [&](uint32_t *h, int shift, uint32_t mask, uint32_t prefix, int prefix_shift) {
+            each([&](int, f32x4 w, int e) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t key = key_of(w[c]);
+                    solo_add(h, (key >> shift) & mask, e + c < dd && (key >> prefix_shift) == prefix);
+                }
+            });
+        }, T, k3);
+        // keys above T, and ties << 16, of every wavefront's 256 elements of a tile
+        each([&](int t, f32x4 w, int e) {
+            uint32_t gt = 0, eq = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                gt += __popcll(__ballot(e + c < dd && key_of(w[c]) > T));
+                eq += __popcll(__ballot(e + c < dd && key_of(w[c]) == T));
+            }
+            if (lane == 0) sm.cnt[t * kSoloWaves + wave] = gt | (eq << 16);
+        });
+        __syncthreads();
+        uint32_t all;
+        const uint32_t gt_at = solo_before(sm.cnt, wave, 0, 0xFFFFu, all), eq_at = solo_before(sm.cnt, wave, 16, 0xFFFFu, all);
+        each([&](int t, f32x4 w, int e) {
+            bool gt[4], eq[4];
+            uint32_t g = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(gt_at), t * 4 + (wave >> 2)));
+            uint32_t q = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(eq_at), t * 4 + (wave >> 2)));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                gt[c] = e + c < dd && key_of(w[c]) > T;
+                eq[c] = e + c < dd && key_of(w[c]) == T;
+                g += lanes_below(__ballot(gt[c]));
+                q += lanes_below(__ballot(eq[c]));
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t slot = g + (q < k3 ? q : k3);
+                if ((gt[c] || (eq[c] && q < k3)) && slot < need) {
+                    prow[slot] = u32x2{static_cast<uint32_t>(e + c), __float_as_uint(w[c])};
+                    if constexpr (WR) brow[e + c] = 0.f;
+                }
+                g += gt[c] ? 1u : 0u;
+                q += eq[c] ? 1u : 0u;
+            }
+        });
+    }
+    if constexpr (kServer) {
+        if (x) {
+            // the entries as this workgroup has just written them, all loads in flight together
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            for (uint32_t i = tid; i < need; i += kSoloThreads) {
+                const u32x2 pr = __builtin_nontemporal_load(prow + i);
+                if (pr.x < static_cast<uint32_t>(dd)) x[pr.x] = __fmaf_rn(-gamma, __uint_as_float(pr.y), x[pr.x]);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------
 // consumers of a sparse message
 // ---------------------------------------------------------------------------------------
 // x <- fma(-gamma, val, x) at the kept indices (Algorithm 1, model update).
@@ -1488,6 +1944,13 @@ ds_status_t run_select(ds_ctx *c, int rows, const Src &src, float *buf, int64_t 
         (void)ds_launch_status();
         return DS_ERR_DEVICE;
     }
+    if (t->solo) {
+        const double part = (c->cfg.d > kSoloThinFrom) ? 0.125 : 0.25;
+        const uint32_t solo_rank = (c->cfg.d > kSoloSampleFrom) ? static_cast<uint32_t>(1.15 * part * static_cast<double>(c->cfg.k) + 32.0) : 0u;
+        constexpr bool kWr = !std::is_same<Src, GradV>::value;     // = wr
+        k_topk_solo<Src, kWr><<<rows, kSoloThreads, 0, st>>>(src, buf, stride, c->cfg.d, c->cfg.k, solo_rank, pairs, x, gamma);
+        return ds_launch_status();
+    }
     const int64_t d = c->cfg.d, k = c->cfg.k, n_sub = t->n_sub, n_reg = t->n_reg, reg_pad = t->reg_pad, n_groups = t->n_groups;
     const int64_t ns = (n_sub < kSampleSubs) ? n_sub : kSampleSubs;
     // sample rank: 1.15 x the expected number of top-k members in the sample, plus slack
@@ -1562,6 +2025,9 @@ ds_status_t ds_topk_init(ds_ctx *c)
     c->topk = t;
     const size_t rows = static_cast<size_t>(c->cfg.n);
     t->rows = c->cfg.n;
+    // A context that states limits of the single launch asks for that route.
+    t->solo = c->cfg.d <= kSoloMax && !(c->cfg.flags & DS_FLAG_TOPK_MULTI_LAUNCH) && c->cfg.topk_max_workgroups == 0 &&
+              c->cfg.topk_spin_limit == 0;
     t->n_sub = (c->cfg.d + kSub - 1) / kSub;
     t->n_reg = c->n_tiles;
     t->n_groups = (t->n_reg + kGroupRegs - 1) / kGroupRegs;
@@ -1674,7 +2140,7 @@ ds_status_t ds_topk_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
     ds_topk_scratch *t = c->topk;
     const u32x2 *pairs_in = reinterpret_cast<const u32x2 *>(in->pairs);
     const int64_t k = c->cfg.k;
-    build_sub_starts(c, pairs_in, st);
+    if (!t->solo) build_sub_starts(c, pairs_in, st);
     const ServerV src{pairs_in, t->sub_start, delta_s, k, t->n_sub, c->cfg.n, c->inv_n};
     return run_select(c, 1, src, delta_s, c->cfg.d, reinterpret_cast<u32x2 *>(out->pairs), st, t->prev_T + t->rows, x, gamma);
 }

@@ -17,6 +17,7 @@ def _cases():
     return [
         ("topk", W.c3(d=300_007, n=4), 0),
         ("topk_multi_launch", W.c3(d=300_007, n=4), P.FLAG_TOPK_MULTI_LAUNCH),
+        ("topk_short_rows", W.c3(d=40_003, n=4), 0),
         ("topk_momentum", dataclasses.replace(W.c3(d=100_003, n=3), beta=0.9), 0),
         ("sign_chunk_momentum", W.c5(d=2048 * 30 + 1280, n=4, n_seg=8), 0),
         ("sign_chunk_plain_sgd_odd_length", dataclasses.replace(W.c5(d=2048 * 31 + 1283, n=3, n_seg=8), beta=None), 0),

@@ -176,3 +176,37 @@ def test_topk_outliers_far_above_the_bulk(gpu_device):
         pos = torch.randperm(d, device=gpu_device, generator=gen)[:k]
         g[i, pos] = (1.0 + torch.rand(k, device=gpu_device, generator=gen)) * (1 if i == 0 else -1)
     _run(_wl(d, n=n, k=k), gpu_device, steps=2, grads=[g])
+
+
+@pytest.mark.parametrize("d,n,k,dtype", [
+    (1, 2, 1, "f32"), (3, 2, 2, "bf16"), (4, 3, 4, "f32"), (5, 1, 1, "bf16"), (4095, 3, 41, "f32"), (4096, 2, 4096, "f32"),
+    (4097, 3, 40, "bf16"), (8192, 3, 82, "f32"), (8193, 3, 82, "bf16"), (16_386, 9, 2000, "f32"), (32_768, 2, 300, "bf16"),
+    (32_769, 3, 1025, "f32"), (49_151, 18, 2500, "f32"), (65_535, 3, 655, "bf16"), (65_536, 2, 65_536, "f32"),
+    (65_536, 5, 66, "f32"), (65_537, 2, 655, "f32")])
+def test_topk_short_rows(gpu_device, d, n, k, dtype):
+    """One workgroup per row up to 65,536 elements: tiles of 4096, four tiles per load, strips of 32,768 on
+    the server, batches of 1024 entries, sampled from 8193 on."""
+    _run(_wl(d, n=n, k=k, grad_dtype=dtype), gpu_device)
+
+
+@pytest.mark.parametrize("what", ["ties", "zeros", "special", "misjudged"])
+def test_topk_short_rows_in_hard_cases(gpu_device, what):
+    d, n, k = 40_003, 3, 1500
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(5)
+    g = torch.randn((n, d), device=gpu_device, generator=gen)
+    if what == "ties":
+        g = torch.sign(g) * 0.5 ** torch.randint(0, 3, (n, d), device=gpu_device, generator=gen)
+    elif what == "zeros":                      # fewer than k entries that are not 0
+        g = torch.where(torch.rand((n, d), device=gpu_device, generator=gen) < 0.01, g, torch.zeros_like(g))
+    elif what == "special":
+        g[:, 5] = 3.3e38
+        g[:, 17] = -3.4e38
+        g[:, 100:200] *= 1e-42
+    else:
+        # large values exactly where the kernel samples (element (lane + tile) mod 4 of a thread's four), fewer than k
+        e = torch.arange(d, device=gpu_device)
+        sampled = (e & 3) == (((e // 4) & 63) + e // 4096) & 3
+        few = sampled & (torch.cumsum(sampled.int(), 0) <= k - 10)
+        g = torch.where(few[None, :], g.abs() + 100.0, g * 1e-3)
+    _run(_wl(d, n=n, k=k), gpu_device, grads=[g], steps=1 if what == "special" else 2)
