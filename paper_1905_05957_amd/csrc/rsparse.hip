@@ -23,6 +23,8 @@
 // the dense pass needs the offsets inside that pass; a chained scan with decoupled look-back
 // over the 2048-element tiles was tried and took 1250 us: a tile is too little work, the
 // look-back of a workgroup runs over most of the thousand workgroups that are resident with it.
+// Running it inside the dense pass of other rows (launches over 1/7, 2/7 and 4/7 of the rows, each generating for the
+// next) took 120 us more, not 75 us less: the pass needs every wavefront slot for its loads in flight.
 #include "ds_device.h"
 #include "ds_internal.h"
 
@@ -113,21 +115,16 @@ __device__ __forceinline__ uint32_t count_subtile(int64_t s, int lane, int64_t d
     return c;
 }
 
-// tot64 [row][ceil(n_sub / 64)]: kept elements per 64 consecutive subtiles (= per workgroup
-// here), which spares the scan a launch.
-__global__ __launch_bounds__(kBlock) void k_rs_counts(uint64_t *words, int64_t W, uint32_t *cnt, uint32_t *tot64, int64_t n_sub,
-                                                      int64_t n_t64, int64_t d, bool server, RsParams P)
+// 64 subtiles (workgroup x) of one row: tot64 [ceil(n_sub / 64)] takes their kept elements, which spares the scan a
+// launch.
+__device__ __forceinline__ void count_row_part(uint32_t x, uint32_t stream, uint32_t *wrow, int64_t W, uint32_t *cnt_row, uint32_t *tot_row,
+                                               int64_t n_sub, int64_t d, const RsParams &P, uint32_t *wsum)
 {
     static_assert(kWaves * kCountSubs == 64, "one workgroup = one entry of tot64");
-    __shared__ uint32_t wsum[kWaves];
-    const int row = blockIdx.y;
     const int lane = lane_id();
-    const uint32_t stream = server ? 0xFFFFFFFFu : static_cast<uint32_t>(row);
     const uint32_t thr = static_cast<uint32_t>((static_cast<uint64_t>(P.p24) << 8) - 1u);
-    uint32_t *wrow = reinterpret_cast<uint32_t *>(words + row * W);
-    uint32_t *cnt_row = cnt + row * (n_sub + 1);
     const int wave = __builtin_amdgcn_readfirstlane(wave_id());               // the loop bounds are scalars
-    const int64_t s0 = (static_cast<int64_t>(blockIdx.x) * kWaves + wave) * kCountSubs;
+    const int64_t s0 = (static_cast<int64_t>(x) * kWaves + wave) * kCountSubs;
     const int64_t s1 = (s0 + kCountSubs < n_sub) ? s0 + kCountSubs : n_sub;
     const int64_t full = d / kSub;                                            // subtiles before this one are whole
     uint32_t total = 0;
@@ -146,30 +143,62 @@ __global__ __launch_bounds__(kBlock) void k_rs_counts(uint64_t *words, int64_t W
         uint32_t t = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) t += wsum[w];
-        tot64[row * n_t64 + blockIdx.x] = t;
+        tot_row[x] = t;
     }
+}
+
+__global__ __launch_bounds__(kBlock) void k_rs_counts(uint64_t *words, int64_t W, uint32_t *cnt, uint32_t *tot64, int64_t n_sub,
+                                                      int64_t n_t64, int64_t d, RsParams P)
+{
+    __shared__ uint32_t wsum[kWaves];
+    const int row = blockIdx.y;
+    count_row_part(blockIdx.x, static_cast<uint32_t>(row), reinterpret_cast<uint32_t *>(words + row * W), W, cnt + row * (n_sub + 1),
+                   tot64 + row * n_t64, n_sub, d, P, wsum);
 }
 
 // Reader side: the same counts from the kept-bit plane.  One thread per subtile, so one
 // wavefront per entry of tot64.
-__global__ __launch_bounds__(kBlock) void k_rs_popcounts(const uint64_t *__restrict__ words, int64_t W, uint32_t *cnt,
-                                                         uint32_t *tot64, int64_t n_sub, int64_t n_t64, int64_t d)
+__device__ __forceinline__ void popcount_subtile(const uint64_t *__restrict__ words_row, int64_t s, uint32_t *cnt_row, uint32_t *tot_row,
+                                                 int64_t n_sub, int64_t n_t64, int64_t d)
 {
-    const int row = blockIdx.y;
-    const int64_t s = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     uint32_t c = 0;
     if (s < n_sub) {
-        const uint64_t *w = words + row * W + s * 4;
+        const uint64_t *w = words_row + s * 4;
         for (int q = 0; q < 4; ++q) {
             const int64_t first = (s * 4 + q) * 64;         // bits at or past d do not count, whatever they hold
             if (first >= d) break;
             const uint64_t valid = (d - first >= 64) ? ~0ull : ((1ull << (d - first)) - 1ull);
             c += __popcll(w[q] & valid);
         }
-        cnt[row * (n_sub + 1) + s] = c;
+        cnt_row[s] = c;
     }
     const uint32_t t = wave_sum_u32(c);
-    if (lane_id() == 0 && (s >> 6) < n_t64) tot64[row * n_t64 + (s >> 6)] = t;
+    if (lane_id() == 0 && (s >> 6) < n_t64) tot_row[s >> 6] = t;
+}
+
+__global__ __launch_bounds__(kBlock) void k_rs_popcounts(const uint64_t *__restrict__ words, uint32_t *cnt, uint32_t *tot64,
+                                                         int64_t n_sub, int64_t n_t64, int64_t d)
+{
+    popcount_subtile(words, static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x, cnt, tot64, n_sub, n_t64, d);
+}
+
+// Everything the server's pass wants to know beforehand, in one launch: row n of the tables is the server's
+// own message, from the generator (n_t64 workgroups, first, for they take longest), rows 0 .. n - 1 are the workers'
+// messages, from their planes (`per_row` workgroups each).  The generator is bound by integer ALU, the rest by memory:
+// 21 us at 8 x 25.6 M, 15 + 10 us as two launches, each of which had a scan behind it.
+__global__ __launch_bounds__(kBlock) void k_rs_server_counts(const uint64_t *__restrict__ words_in, uint64_t *words_out, int64_t W,
+                                                             uint32_t *cnt, uint32_t *tot64, int n, int64_t n_sub, int64_t n_t64,
+                                                             uint32_t per_row, int64_t d, RsParams P)
+{
+    __shared__ uint32_t wsum[kWaves];
+    if (blockIdx.x < n_t64) {
+        count_row_part(blockIdx.x, 0xFFFFFFFFu, reinterpret_cast<uint32_t *>(words_out), W, cnt + n * (n_sub + 1), tot64 + n * n_t64,
+                       n_sub, d, P, wsum);
+        return;
+    }
+    const uint32_t b = blockIdx.x - static_cast<uint32_t>(n_t64), row = b / per_row, x = b - row * per_row;
+    popcount_subtile(words_in + row * W, static_cast<int64_t>(x) * kBlock + threadIdx.x, cnt + row * (n_sub + 1), tot64 + row * n_t64,
+                     n_sub, n_t64, d);
 }
 
 // Counts [row][0 .. n_sub) -> exclusive offsets [row][0 .. n_sub], the last one the row's
@@ -225,8 +254,8 @@ __device__ __forceinline__ f32x4 place_kept4(float p0, float p1, float p2, float
     return f32x4{k0 ? p0 : 0.f, k1 ? a1 : 0.f, k2 ? b1 : 0.f, k3 ? (k2 ? b2 : b1) : 0.f};
 }
 
-// Q[v] of the four elements of a thread, the message and the error.
-__device__ __forceinline__ void rs_store4(f32x4 v, uint32_t nib, const Ranks &rk, uint32_t base, int64_t e, int64_t d,
+// Q[v] of the four elements of a thread, which it returns, the message and the error.
+__device__ __forceinline__ f32x4 rs_store4(f32x4 v, uint32_t nib, const Ranks &rk, uint32_t base, int64_t e, int64_t d,
                                           float *__restrict__ vals_row, float *__restrict__ err_row, float p)
 {
     const f32x4 q = {(nib & 1u) ? v.x / p : 0.f, (nib & 2u) ? v.y / p : 0.f, (nib & 4u) ? v.z / p : 0.f,
@@ -238,6 +267,7 @@ __device__ __forceinline__ void rs_store4(f32x4 v, uint32_t nib, const Ranks &rk
     if (nib & 4u) out[r++] = q.z;
     if (nib & 8u) out[r++] = q.w;
     if (e < d) st4_stream(err_row, e, d, v - q);
+    return q;
 }
 
 // Algorithm 1, worker block.
@@ -262,10 +292,17 @@ __global__ __launch_bounds__(kBlock) void k_rs_worker(const void *g, int64_t gs,
 // Parameter-server block: v = delta_s + (1/n) sum_i Q[v_i] as the chain acc = fma(q_i, 1/n, acc)
 // over workers in ascending order (elements a worker did not keep add nothing), then the same
 // compressor on the server's stream.
-__global__ __launch_bounds__(kBlock) void k_rs_server(const uint64_t *words_in, const float *vals_in, const uint32_t *off_in,
-                                                      int n, float inv_n, float *delta_s, int64_t d, int64_t W,
-                                                      const uint64_t *words_out, float *vals_out, const uint32_t *off_out,
-                                                      int64_t n_sub, float p)
+// UPD: 0 = that block alone; 1, 2 = followed by the model update for the same elements (2: through the momentum
+// buffer) from the registers that hold the message.
+// Bound by HBM over many streams (each worker's plane and values, 990 MB with the update at 8 x 25.6 M in 202 us);
+// the update as a launch of its own, which reads the message back, made it 168 + 48 us.  Batches of fewer than eight
+// workers take the same way: 4 x 25.6 M 515 -> 436 us a step, 12 x 8 M 375 -> 345 us.  Workgroups of 256 threads, of which
+// one more wavefront per SIMD fits, changed nothing.
+template <int UPD>
+__global__ __launch_bounds__(kBlock, 6) void k_rs_server(const uint64_t *words_in, const float *vals_in, const uint32_t *off_in,
+                                                         int n, float inv_n, float *delta_s, int64_t d, int64_t W,
+                                                         const uint64_t *words_out, float *vals_out, const uint32_t *off_out,
+                                                         int64_t n_sub, float p, float *x, float *m, float gamma, float beta)
 {
     const int64_t base = static_cast<int64_t>(blockIdx.x) * kTile;
     const int64_t e = base + threadIdx.x * 4;
@@ -274,54 +311,78 @@ __global__ __launch_bounds__(kBlock) void k_rs_server(const uint64_t *words_in, 
     const int64_t sub = wave_first >> 8;
     if (sub >= n_sub) return;                               // whole wavefronts
     f32x4 a = ld4_stream(delta_s, e, d);
-    {
-        for (int i0 = 0; i0 < n; i0 += 8) {
-            const int nb = (n - i0 < 8) ? n - i0 : 8;
-            // lane L: 32-bit word L & 7 of the plane of worker i0 + (L >> 3); lane i: offset of worker i0 + i
-            uint32_t word = 0u;
-            if ((lane >> 3) < nb && wave_first + 32 * (lane & 7) < W * 64)
-                word = reinterpret_cast<const uint32_t *>(words_in + (i0 + (lane >> 3)) * W)[(wave_first >> 5) + (lane & 7)];
-            const uint32_t o = (lane < nb) ? off_in[(i0 + lane) * (n_sub + 1) + sub] : 0u;
-            const uint32_t vn = valid_nibble(e, d);
-            if (nb == 8 && (sub + 1) * kSub + 4 <= d) {
-                // A full batch away from the end of the rows: a lane's kept values start at most
-                // at float (sub + 1) * 256 of a row, so four floats from there stay inside it.
-                // All eight fetches are issued before the first is used.
-                typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
-                f32x4_unaligned pk[8];
-                uint32_t nibs[8];
+    f32x4 xv = {0.f, 0.f, 0.f, 0.f}, mv = {0.f, 0.f, 0.f, 0.f};       // fetched up front, beside the error
+    if constexpr (UPD != 0) xv = ld4_stream(x, e, d);
+    if constexpr (UPD == 2) mv = ld4_stream(m, e, d);
+    const uint32_t vn = valid_nibble(e, d);
+    for (int i0 = 0; i0 < n; i0 += 8) {
+        const int nb = (n - i0 < 8) ? n - i0 : 8;
+        // lane L: 32-bit word L & 7 of the plane of worker i0 + (L >> 3); lane i: offset of worker i0 + i
+        uint32_t word = 0u;
+        if ((lane >> 3) < nb && wave_first + 32 * (lane & 7) < W * 64)
+            word = reinterpret_cast<const uint32_t *>(words_in + (i0 + (lane >> 3)) * W)[(wave_first >> 5) + (lane & 7)];
+        const uint32_t o = (lane < nb) ? off_in[(i0 + lane) * (n_sub + 1) + sub] : 0u;
+        if ((sub + 1) * kSub + 4 <= d) {
+            // Away from the end of the rows: a lane's kept values start at most at float
+            // (sub + 1) * 256 of a row, so four floats from there stay inside it.
+            // All fetches are issued before the first is used.
+            // Ranks of all eight messages together: where the values of each word start (population counts, summed
+            // over the words before in the worker's eight lanes), then the bits below a lane's four in its word.
+            uint32_t at = __popc(word);
+            const uint32_t own = at;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint32_t w = __shfl(word, i * 8 + (lane >> 3), 64);
-                    nibs[i] = (w >> (4 * (lane & 7))) & vn;
-                    const Ranks rk = subtile_ranks(nibs[i]);
-                    const int64_t at = static_cast<int64_t>(i0 + i) * d +
-                                       static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(o), i)) + rk.before;
-                    pk[i] = *reinterpret_cast<const f32x4_unaligned *>(vals_in + at);
-                }
+            for (int s = 1; s < 8; s <<= 1) {
+                const uint32_t y = static_cast<uint32_t>((s == 1) ? dpp_u32<0x111>(at) : (s == 2) ? dpp_u32<0x112>(at) : dpp_u32<0x114>(at));
+                at += ((lane & 7) >= s) ? y : 0u;
+            }
+            at = at - own + __shfl(o, lane >> 3, 64);
+            const int sh = 4 * (lane & 7);
+            const uint32_t below = (1u << sh) - 1u;
+            typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+            f32x4_unaligned pk[8];
+            uint32_t nibs = 0u;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) a = fma4(inv_n, place_kept4(pk[i].x, pk[i].y, pk[i].z, pk[i].w, nibs[i]), a);
-            } else {
-                for (int i = 0; i < nb; ++i) {
-                    const uint32_t w = __shfl(word, i * 8 + (lane >> 3), 64);
-                    const uint32_t nib = (w >> (4 * (lane & 7))) & vn;
-                    const Ranks rk = subtile_ranks(nib);
-                    const float *src = vals_in + static_cast<int64_t>(i0 + i) * d +
-                                       static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(o), i)) + rk.before;
-                    f32x4 q = {0.f, 0.f, 0.f, 0.f};
-                    uint32_t r = 0;
-                    if (nib & 1u) q.x = src[r++];
-                    if (nib & 2u) q.y = src[r++];
-                    if (nib & 4u) q.z = src[r++];
-                    if (nib & 8u) q.w = src[r++];
-                    a = fma4(inv_n, q, a);                  // an element that was not kept adds nothing: fma(0, 1/n, a) = a
-                }
+            for (int i = 0; i < 8; ++i) {
+                if (i >= nb) break;                     // uniform
+                const uint32_t w = __shfl(word, i * 8 + (lane >> 3), 64);
+                const uint32_t r = __shfl(at, i * 8 + (lane >> 3), 64) + __popc(w & below);
+                nibs |= ((w >> sh) & 15u) << (4 * i);
+                pk[i] = *reinterpret_cast<const f32x4_unaligned *>(vals_in + static_cast<int64_t>(i0 + i) * d + r);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (i >= nb) break;
+                a = fma4(inv_n, place_kept4(pk[i].x, pk[i].y, pk[i].z, pk[i].w, nibs >> (4 * i)), a);
+            }
+        } else {
+            for (int i = 0; i < nb; ++i) {
+                const uint32_t w = __shfl(word, i * 8 + (lane >> 3), 64);
+                const uint32_t nib = (w >> (4 * (lane & 7))) & vn;
+                const Ranks rk = subtile_ranks(nib);
+                const float *src = vals_in + static_cast<int64_t>(i0 + i) * d +
+                                   static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(o), i)) + rk.before;
+                f32x4 q = {0.f, 0.f, 0.f, 0.f};
+                uint32_t r = 0;
+                if (nib & 1u) q.x = src[r++];
+                if (nib & 2u) q.y = src[r++];
+                if (nib & 4u) q.z = src[r++];
+                if (nib & 8u) q.w = src[r++];
+                a = fma4(inv_n, q, a);                  // an element that was not kept adds nothing: fma(0, 1/n, a) = a
             }
         }
     }
-    const uint32_t nib = (e < d) ? load_sign_nibble(words_out, e) : 0u;         // written by k_rs_counts
+    const uint32_t nib = (e < d) ? load_sign_nibble(words_out, e) : 0u;         // written by k_rs_server_counts
     const Ranks rk = subtile_ranks(nib);
-    rs_store4(a, nib, rk, off_out[sub], e, d, vals_out, delta_s, p);
+    f32x4 q = rs_store4(a, nib, rk, off_out[sub], e, d, vals_out, delta_s, p);
+    if constexpr (UPD != 0) {
+        if (e < d) {
+            if constexpr (UPD == 2) {
+                q = fma4(beta, mv, q);
+                st4_stream(m, e, d, q);
+            }
+            st4_stream(x, e, d, fma4(-gamma, q, xv));
+        }
+    }
 }
 
 // Model update / decoder from one message.  SPARSE (plain update, small p): only the kept
@@ -373,10 +434,9 @@ RsParams make_params(const ds_ctx *c, uint64_t step)
 struct ds_rs_scratch {
     int64_t n_sub;
     uint32_t *off_w;    // [n][n_sub + 1]  worker messages, writer side
-    uint32_t *off_in;   // [n][n_sub + 1]  worker messages, as read by the server
-    uint32_t *off_s;    // [n_sub + 1]     server message, writer side
+    uint32_t *off_s;    // [n + 1][n_sub + 1]  worker messages as read by the server; last row: the server's, writer side
     uint32_t *off_r;    // [n_sub + 1]     a message as read by the update / decoder
-    uint32_t *tot64;    // [n][n_t64]      kept elements per 64 subtiles, from the count kernels for the scan
+    uint32_t *tot64;    // [n + 1][n_t64]  kept elements per 64 subtiles, from the count kernels for the scan
     int64_t n_t64;
 };
 
@@ -395,11 +455,10 @@ ds_status_t ds_rsparse_init(ds_ctx *c)
     t->n_sub = (c->cfg.d + kSub - 1) / kSub;
     const size_t row = static_cast<size_t>(t->n_sub + 1) * sizeof(uint32_t), n = static_cast<size_t>(c->cfg.n);
     DS_HIP_TRY(hipMalloc(&t->off_w, n * row));
-    DS_HIP_TRY(hipMalloc(&t->off_in, n * row));
-    DS_HIP_TRY(hipMalloc(&t->off_s, row));
+    DS_HIP_TRY(hipMalloc(&t->off_s, (n + 1) * row));
     DS_HIP_TRY(hipMalloc(&t->off_r, row));
     t->n_t64 = (t->n_sub + 63) / 64;
-    DS_HIP_TRY(hipMalloc(&t->tot64, n * static_cast<size_t>(t->n_t64) * sizeof(uint32_t)));
+    DS_HIP_TRY(hipMalloc(&t->tot64, (n + 1) * static_cast<size_t>(t->n_t64) * sizeof(uint32_t)));
     return DS_OK;
 }
 
@@ -407,7 +466,7 @@ void ds_rsparse_fini(ds_ctx *c)
 {
     ds_rs_scratch *t = c->rs;
     if (!t) return;
-    void *ptrs[5] = {t->off_w, t->off_in, t->off_s, t->off_r, t->tot64};
+    void *ptrs[4] = {t->off_w, t->off_s, t->off_r, t->tot64};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete t;
@@ -421,7 +480,7 @@ ds_status_t ds_rsparse_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
     const RsParams P = make_params(c, step);
     const unsigned n = static_cast<unsigned>(c->cfg.n);
     k_rs_counts<<<dim3(static_cast<unsigned>((t->n_sub + kWaves * kCountSubs - 1) / (kWaves * kCountSubs)), n), kBlock, 0, st>>>(
-        out->sign_words, c->W, t->off_w, t->tot64, t->n_sub, t->n_t64, c->cfg.d, false, P);
+        out->sign_words, c->W, t->off_w, t->tot64, t->n_sub, t->n_t64, c->cfg.d, P);
     scan_rows(t, t->off_w, n, st);
     const dim3 grid(static_cast<unsigned>(c->n_tiles), n);
     if (c->cfg.grad_dtype == DS_BF16)
@@ -433,23 +492,38 @@ ds_status_t ds_rsparse_worker(ds_ctx *c, uint64_t step, const void *g, int64_t g
     return ds_launch_status();
 }
 
-ds_status_t ds_rsparse_server(ds_ctx *c, uint64_t step, const ds_payload_t *in, float *delta_s, const ds_payload_t *out,
-                              hipStream_t st)
+// x != nullptr: the model update for the same elements in the same kernel.
+static ds_status_t rs_server(ds_ctx *c, uint64_t step, const ds_payload_t *in, float *delta_s, const ds_payload_t *out, float *x,
+                             float *m, float gamma, float beta, hipStream_t st)
 {
     ds_rs_scratch *t = c->rs;
     const RsParams P = make_params(c, step);
-    const unsigned n = static_cast<unsigned>(c->cfg.n);
-    k_rs_popcounts<<<dim3(static_cast<unsigned>((t->n_sub + kBlock - 1) / kBlock), n), kBlock, 0, st>>>(
-        in->sign_words, c->W, t->off_in, t->tot64, t->n_sub, t->n_t64, c->cfg.d);
-    scan_rows(t, t->off_in, n, st);
-    k_rs_counts<<<dim3(static_cast<unsigned>((t->n_sub + kWaves * kCountSubs - 1) / (kWaves * kCountSubs)), 1), kBlock, 0, st>>>(
-        out->sign_words, c->W, t->off_s, t->tot64, t->n_sub, t->n_t64, c->cfg.d, true, P);
-    scan_rows(t, t->off_s, 1, st);
-    k_rs_server<<<static_cast<unsigned>(c->n_tiles), kBlock, 0, st>>>(in->sign_words, in->dense, t->off_in, c->cfg.n, c->inv_n,
-                                                                    delta_s, c->cfg.d, c->W, out->sign_words, out->dense,
-                                                                    t->off_s, t->n_sub, P.p);
+    const unsigned n = static_cast<unsigned>(c->cfg.n), per_row = static_cast<unsigned>((t->n_sub + kBlock - 1) / kBlock);
+    k_rs_server_counts<<<static_cast<unsigned>(t->n_t64) + n * per_row, kBlock, 0, st>>>(
+        in->sign_words, out->sign_words, c->W, t->off_s, t->tot64, c->cfg.n, t->n_sub, t->n_t64, per_row, c->cfg.d, P);
+    scan_rows(t, t->off_s, n + 1, st);
+    const uint32_t *off_s = t->off_s + static_cast<int64_t>(n) * (t->n_sub + 1);
+    const unsigned grid = static_cast<unsigned>(c->n_tiles);
+    if (!x)
+        k_rs_server<0><<<grid, kBlock, 0, st>>>(in->sign_words, in->dense, t->off_s, c->cfg.n, c->inv_n, delta_s, c->cfg.d, c->W,
+                                                out->sign_words, out->dense, off_s, t->n_sub, P.p, x, m, gamma, beta);
+    else if (!m)
+        k_rs_server<1><<<grid, kBlock, 0, st>>>(in->sign_words, in->dense, t->off_s, c->cfg.n, c->inv_n, delta_s, c->cfg.d, c->W,
+                                                out->sign_words, out->dense, off_s, t->n_sub, P.p, x, m, gamma, beta);
+    else
+        k_rs_server<2><<<grid, kBlock, 0, st>>>(in->sign_words, in->dense, t->off_s, c->cfg.n, c->inv_n, delta_s, c->cfg.d, c->W,
+                                                out->sign_words, out->dense, off_s, t->n_sub, P.p, x, m, gamma, beta);
     return ds_launch_status();
 }
+
+ds_status_t ds_rsparse_server(ds_ctx *c, uint64_t step, const ds_payload_t *in, float *delta_s, const ds_payload_t *out,
+                              hipStream_t st)
+{
+    return rs_server(c, step, in, delta_s, out, nullptr, nullptr, 0.f, 0.f, st);
+}
+
+// p < 1/16: most 64-byte lines of x hold no kept element, and a plain update touches only those that do
+static bool sparse_update(const ds_ctx *c, const float *m) { return !m && c->cfg.k < (1 << 20); }
 
 // off == nullptr: the offsets of the packed values are derived from the message's own plane.
 template <bool DECODE_ONLY>
@@ -458,8 +532,8 @@ static ds_status_t rs_apply(ds_ctx *c, const uint64_t *words, const float *vals,
 {
     ds_rs_scratch *t = c->rs;
     if (!off) {
-        k_rs_popcounts<<<dim3(static_cast<unsigned>((t->n_sub + kBlock - 1) / kBlock), 1), kBlock, 0, st>>>(
-            words, c->W, t->off_r, t->tot64, t->n_sub, t->n_t64, c->cfg.d);
+        k_rs_popcounts<<<static_cast<unsigned>((t->n_sub + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+            words, t->off_r, t->tot64, t->n_sub, t->n_t64, c->cfg.d);
         scan_rows(t, t->off_r, 1, st);
         off = t->off_r;
     }
@@ -468,21 +542,23 @@ static ds_status_t rs_apply(ds_ctx *c, const uint64_t *words, const float *vals,
         k_rs_apply<false, true, false><<<blocks, kBlock, 0, st>>>(words, vals, off, x, nullptr, c->cfg.d, c->W, t->n_sub, 0.f, 0.f);
     else if (m)
         k_rs_apply<true, false, false><<<blocks, kBlock, 0, st>>>(words, vals, off, x, m, c->cfg.d, c->W, t->n_sub, gamma, beta);
-    else if (c->cfg.k < (1 << 20))      // p < 1/16: most 64-byte lines of x hold no kept element
+    else if (sparse_update(c, m))
         k_rs_apply<false, false, true><<<blocks, kBlock, 0, st>>>(words, vals, off, x, m, c->cfg.d, c->W, t->n_sub, gamma, beta);
     else
         k_rs_apply<false, false, false><<<blocks, kBlock, 0, st>>>(words, vals, off, x, m, c->cfg.d, c->W, t->n_sub, gamma, beta);
     return ds_launch_status();
 }
 
-// The server block followed by the model update: the update reads the server's message with
-// the offsets the server has just written it with, instead of deriving them from the plane again.
+// The server block followed by the model update: in one pass, or, where the update touches few elements, from the
+// server's message with the offsets the server has just written it with.
 ds_status_t ds_rsparse_server_update(ds_ctx *c, uint64_t step, const ds_payload_t *in, float *delta_s, const ds_payload_t *out,
                                      float *x, float *m, float gamma, float beta, hipStream_t st)
 {
+    if (!sparse_update(c, m)) return rs_server(c, step, in, delta_s, out, x, m, gamma, beta, st);
     const ds_status_t rc = ds_rsparse_server(c, step, in, delta_s, out, st);
     if (rc != DS_OK) return rc;
-    return rs_apply<false>(c, out->sign_words, out->dense, x, m, gamma, beta, st, c->rs->off_s);
+    return rs_apply<false>(c, out->sign_words, out->dense, x, m, gamma, beta, st,
+                           c->rs->off_s + static_cast<int64_t>(c->cfg.n) * (c->rs->n_sub + 1));
 }
 
 ds_status_t ds_rsparse_update(ds_ctx *c, const ds_payload_t *srv, float *x, float *m, float gamma, float beta, hipStream_t st)

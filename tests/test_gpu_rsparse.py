@@ -58,3 +58,23 @@ def test_rsparse_reads_only_the_kept_bits_below_d(gpu_device):
         assert torch.equal(clean, dirty)
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("beta", [None, 0.9])
+def test_rsparse_batches_of_workers_and_the_update_in_one_call(gpu_device, n, beta):
+    """Partial and full batches of eight messages away from and at the end of the rows, and the model updated in
+    the server's pass: bit for bit what the two calls give, which are compared with the oracle here."""
+    wl = _wl(5 * 2048 + 259, 0.6, n=n, beta=beta)
+    two, one = Pair(wl, gpu_device), Pair(wl, gpu_device)
+    try:
+        for t in range(2):
+            g = wl.gradients(t, gpu_device)
+            two.compared_step(t, g)
+            one.ctx.worker_compress(t, g, one.delta, one.pw)
+            one.ctx.server_aggregate_compress_update(t, one.pw, one.delta_s, one.ps, one.x, one.m, wl.gamma, beta or 0.0)
+            assert torch.equal(one.x, two.x) and torch.equal(one.delta_s, two.delta_s)
+            assert one.m is None or torch.equal(one.m, two.m)
+    finally:
+        two.close()
+        one.close()
