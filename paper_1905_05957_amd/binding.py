@@ -1,6 +1,7 @@
-"""ctypes binding of libds_hip.so -- same names as the C-ABI in include/ds.h.
+"""Binding of libds_hip.so -- same names as the C-ABI in include/ds.h.
 
-Marshalling only: tensors' device pointers and the current HIP stream are handed to the
+The step calls go through an extension module (csrc/fastcall.cpp) where every argument is plainly as the
+library assumes it, else, and for everything else, through ctypes and the checks here.  Marshalling only: tensors' device pointers and the current HIP stream are handed to the
 library; nothing here computes.  There is no CPU fallback: if the library is missing the
 import of a symbol fails loudly.
 """
@@ -96,6 +97,15 @@ def load_library():
     L.ds_version.restype = C.c_char_p
     _lib = L
     return L
+
+
+def _load_fastcall():
+    try:
+        from . import _fastcall
+    except ImportError as e:
+        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not fit this torch: build it with "
+                          "`python -m paper_1905_05957_amd.build`") from e
+    return _fastcall
 
 
 def _status_string(code: int) -> str:
@@ -243,8 +253,15 @@ class Context:
         self.S = sizes[1] // 4
         self.no_error_feedback = bool(int(flags) & FLAG_NO_ERROR_FEEDBACK)
         self.server_identity = bool(int(flags) & FLAG_SERVER_IDENTITY)
+        address = [C.cast(f, C.c_void_p).value for f in (L.ds_worker_compress, L.ds_server_aggregate_compress, L.ds_apply_update,
+                                                         L.ds_decompress, L.ds_server_aggregate_compress_update)]
+        self._calls = _load_fastcall().Calls(self._h.value, self.n, self.d, self.k, self.comp, self.grad_dtype == BF16,
+                                             self.no_error_feedback, self.server_identity, Payload, torch._C._cuda_getDevice,
+                                             torch._C._cuda_getCurrentRawStream, *address)
 
     def close(self):
+        if getattr(self, "_calls", None) is not None:
+            self._calls.close()
         if getattr(self, "_h", None) is not None and self._h.value:
             torch.cuda.synchronize()
             load_library().ds_destroy(self._h)
@@ -276,6 +293,9 @@ class Context:
 
     def worker_compress(self, step: int, g: torch.Tensor, delta: torch.Tensor, out: Payload,
                         stream=None):
+        rc = self._calls.worker(step, g, delta, out, stream)     # the status, or -1: the checks below decide
+        if rc >= 0:
+            return _check(rc, "ds_worker_compress")
         _need(g, "g", torch.bfloat16 if self.grad_dtype == BF16 else torch.float32, (self.n, self.d))
         if delta is not None or not self.no_error_feedback:
             _need(delta, "delta", torch.float32, (self.n, self.d))
@@ -289,6 +309,9 @@ class Context:
 
     def server_aggregate_compress(self, step: int, inp: Payload, delta_s: torch.Tensor,
                                   out: Payload, stream=None):
+        rc = self._calls.server(step, inp, delta_s, out, stream)
+        if rc >= 0:
+            return _check(rc, "ds_server_aggregate_compress")
         if delta_s is not None or not (self.no_error_feedback or self.server_identity):
             _need(delta_s, "delta_s", torch.float32, (self.d,))
         a, b = inp.check(self, self.n, "in").c_struct(), out.check(self, 1, "out", server=True).c_struct()
@@ -300,6 +323,9 @@ class Context:
     def server_aggregate_compress_update(self, step: int, inp: Payload, delta_s: torch.Tensor, out: Payload,
                                          x: torch.Tensor, m: Optional[torch.Tensor], gamma: float,
                                          beta: float = 0.0, stream=None):
+        rc = self._calls.server_update(step, inp, delta_s, out, x, m, gamma, beta, stream)
+        if rc >= 0:
+            return _check(rc, "ds_server_aggregate_compress_update")
         if delta_s is not None or not (self.no_error_feedback or self.server_identity):
             _need(delta_s, "delta_s", torch.float32, (self.d,))
         _need(x, "x", torch.float32, (self.d,))
@@ -314,6 +340,9 @@ class Context:
 
     def apply_update(self, srv: Payload, x: torch.Tensor, m: Optional[torch.Tensor], gamma: float,
                      beta: float = 0.0, stream=None):
+        rc = self._calls.update(srv, x, m, gamma, beta, stream)
+        if rc >= 0:
+            return _check(rc, "ds_apply_update")
         _need(x, "x", torch.float32, (self.d,))
         if m is not None:
             _need(m, "m", torch.float32, (self.d,))
@@ -335,6 +364,9 @@ class Context:
             "ds_materialize_error")
 
     def decompress(self, p: Payload, row: int, out: torch.Tensor, stream=None):
+        rc = self._calls.decode(p, row, out, stream)
+        if rc >= 0:
+            return _check(rc, "ds_decompress")
         _need(out, "dense_out", torch.float32, (self.d,))
         s = p.check(self, p.rows, "p", server=(self.server_identity and p.comp == COMP_IDENTITY)).c_struct()
         _check(load_library().ds_decompress(self._h, C.byref(s), p.rows, row, out.data_ptr(),

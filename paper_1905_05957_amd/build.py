@@ -1,4 +1,5 @@
-"""Builds libds_hip.so (the C-ABI library of HIP kernels) for gfx950 with hipcc, in tree."""
+"""Builds, in tree, libds_hip.so (the C-ABI library of HIP kernels, for gfx950 with hipcc) and _fastcall.so (the
+Python binding's step calls, host code only)."""
 from __future__ import annotations
 
 import os
@@ -9,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libds_hip.so")
+FASTCALL, FASTCALL_SRC = os.path.join(HERE, "_fastcall.so"), os.path.join(CSRC, "fastcall.cpp")
 SOURCES = ["ds_api.hip", "identity.hip", "sign.hip", "qsgd.hip", "topk.hip", "clip.hip", "rsparse.hip", "ternary.hip"]
 HEADERS = ["ds_device.h", "held.h", "ds_internal.h", os.path.join("..", "..", "include", "ds.h")]
 
@@ -30,8 +32,38 @@ def _hipcc() -> str:
     return "hipcc"
 
 
+def build_fastcall(force: bool = True) -> str:
+    """Compile the binding's extension module against this interpreter and its torch."""
+    deps = [FASTCALL_SRC, os.path.normpath(os.path.join(CSRC, "..", "..", "include", "ds.h"))]
+    if not force and os.path.exists(FASTCALL) and all(os.path.getmtime(FASTCALL) >= os.path.getmtime(p) for p in deps):
+        return FASTCALL
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    tmp = FASTCALL + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", os.path.join(base, "include"),
+           "-isystem", sysconfig.get_paths()["include"], FASTCALL_SRC, "-o", tmp, "-L" + os.path.join(base, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("compilation of _fastcall.so failed")
+    os.replace(tmp, FASTCALL)
+    return FASTCALL
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every source and link the shared library.  Always recompiles when force."""
+    """Compile every source, link the shared library and build the extension module.  Always recompiles when force."""
+    with ThreadPoolExecutor(max_workers=1) as ex:
+        fastcall = ex.submit(build_fastcall, force)
+        lib = build_library(force, verbose)
+        fastcall.result()
+    return lib
+
+
+def build_library(force: bool = True, verbose: bool = False) -> str:
+    """Compile the HIP sources and link libds_hip.so."""
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     deps = srcs + [os.path.normpath(os.path.join(CSRC, h)) for h in HEADERS]
     if not force and os.path.exists(LIB) and all(os.path.getmtime(LIB) >= os.path.getmtime(p) for p in deps):

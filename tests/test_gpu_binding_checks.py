@@ -124,3 +124,49 @@ def test_status_of_contexts_that_cannot_fail_asynchronously(gpu_device):
             assert ctx.status() == 0
         finally:
             ctx.close()
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("comp,kw,flags", [
+    ("sign", dict(scale_mode="chunk", chunk=1024), 0), ("topk", dict(k=50), 0), ("qsgd", dict(bucket=64), 0),
+    ("sign", {}, P.FLAG_SERVER_IDENTITY), ("ternary", {}, P.FLAG_SERVER_IDENTITY | P.FLAG_NO_ERROR_FEEDBACK)])
+def test_extension_and_python_route_agree(gpu_device, comp, kw, flags):
+    """Plain arguments go through the extension module; a tensor subclass goes through the checks in Python and
+    ctypes.  Both give the same bytes, on a side stream and for rows with a stride, too."""
+    dev, n, d = gpu_device, 3, 5000
+    side = torch.cuda.Stream()
+    outs = []
+    for plain in (True, False):
+        wrap = (lambda t: t) if plain else (lambda t: None if t is None else t.as_subclass(_Sub))
+        gen = torch.Generator(device=dev)
+        gen.manual_seed(3)
+        g = torch.randn(n, d + 12, device=dev, generator=gen)[:, :d]
+        nofb = bool(flags & P.FLAG_NO_ERROR_FEEDBACK)
+        delta = None if nofb else torch.zeros(n, d, device=dev)
+        delta_s = torch.zeros(d, device=dev) if not flags else None
+        x, m, dense = torch.ones(d, device=dev), torch.zeros(d, device=dev), torch.empty(d, device=dev)
+        ctx = P.Context(comp, n, d, flags=flags, **kw)
+        try:
+            pw, ps = ctx.alloc_payload(n, dev), ctx.alloc_server_payload(dev)
+            torch.cuda.synchronize()
+            if plain:
+                assert ctx._calls.worker(0, g, delta, pw, None) == 0
+            else:
+                assert ctx._calls.worker(0, wrap(g), wrap(delta), pw, None) == -1
+                ctx.worker_compress(0, wrap(g), wrap(delta), pw)
+            ctx.server_aggregate_compress(0, pw, wrap(delta_s), ps)
+            ctx.apply_update(ps, wrap(x), wrap(m), 0.1, 0.9)
+            ctx.decompress(ps, 0, wrap(dense))
+            torch.cuda.synchronize()
+            ctx.worker_compress(1, wrap(g), wrap(delta), pw, stream=side)
+            ctx.server_aggregate_compress_update(1, pw, wrap(delta_s), ps, wrap(x), wrap(m), 1, 0, side)
+            torch.cuda.synchronize()
+            outs.append([t.clone() for t in (x, m, dense, *pw.tensors().values(), *ps.tensors().values())])
+        finally:
+            ctx.close()
+        assert ctx._calls.worker(0, g, delta, pw, None) == -1               # closed
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
