@@ -97,38 +97,65 @@ struct TernKey {
     uint32_t key0, key1, step_lo;
 };
 
-// Codes of the four elements of group `quad` of the row (elements 4 quad ..), of which `left` (at most 4) belong
-// to it: bit c = code is not 0, bit 4 + c = code is -1.  The encoding is bound by
-// vector instructions, and four IEEE divisions were a third of them.  With U = 2^24 u a whole
-// number and q = |v| * fl(2^24 / m), which is within 2^-22 of 2^24 fl(|v| / m), U outside
-// q (1 -+ 2^-20) (and, for U = 0, q above 2^-20) decides u < fl(|v| / m) without the quotient; what
-// lies inside, NaN included, and rows whose maximum leaves the range of that product divide.
-__device__ __forceinline__ uint32_t tern_codes4(f32x4 v, float m, uint32_t quad, int left, int row, TernKey K)
+// What the encoding of a row needs to know of its maximum m: r = fl(2^32 / m), 0 where m leaves the range of the
+// products below.
+struct TernMax {
+    float m, r;
+};
+__device__ __forceinline__ TernMax tern_max(float m)
+{
+    return TernMax{m, (m >= 0x1p-90f && m <= 0x1p90f) ? __fdiv_rn(0x1p32f, m) : 0.f};
+}
+
+// acc * 2 + the sign bit of x, in one instruction
+__device__ __forceinline__ uint32_t push_sign(uint32_t acc, float x)
+{
+    return __builtin_amdgcn_alignbit(acc, __float_as_uint(x), 31);
+}
+
+// Codes of the four elements of group `quad` of the row (elements 4 quad .., zero past its end): bits of the codes
+// that are not 0, and << 16 of those that are -1.  The encoding is bound by vector instructions.  Element |v| is kept
+// iff U < 2^24 fl(|v| / m) for the upper 24 bits U of its random word R.  F = fl(R) is within 256 + 2^-24 R of 2^8 U, and
+// D = F - |v| r, one rounding, within (2^-20 |v| r + 512) of 2^8 U - 2^32 fl(|v| / m): outside of that its sign is the decision,
+// without the quotient, a shift or a comparison per bit.  Where one of the four lies inside, or is a NaN, and in rows whose
+// maximum leaves the range, the quotients decide.
+__device__ __forceinline__ uint32_t tern_codes4(f32x4 v, TernMax M, uint32_t quad, int row, TernKey K)
 {
     const u32x4 rnd = philox4x32_10(u32x4{quad, 0u, static_cast<uint32_t>(row), K.step_lo}, K.key0, K.key1);
-    const float vv[4] = {v.x, v.y, v.z, v.w};
-    const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
-    const bool in_range = m >= 0x1p-100f && m <= 0x1p100f;      // uniform
-    const float r = __fdiv_rn(0x1p24f, m);
-    uint32_t nz = 0u, open = 0u;
+    const float tol = M.r * 0x1p-20f;
+    uint32_t nz = 0u, neg = 0u;
+    bool open = !(M.r > 0.f);                                   // uniform
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const float U = static_cast<float>(rr[c] >> 8), q = fabsf(vv[c]) * r;
-        const bool below = U < __fmaf_rn(q, 1.f - 0x1p-20f, -0x1p-20f), above = U > q * (1.f + 0x1p-20f);
-        nz |= below ? 1u << c : 0u;
-        open |= (below || above) ? 0u : 1u << c;
+    for (int c = 3; c >= 0; --c) {
+        const float a = fabsf(v[c]);
+        const float D = __fmaf_rn(a, -M.r, static_cast<float>(rnd[c]));
+        open = open || !(fabsf(D) > __fmaf_rn(a, tol, 512.f));
+        nz = push_sign(nz, D);
+        neg = push_sign(neg, v[c]);
     }
-    if (!in_range) { nz = 0u; open = (m > 0.f) ? 15u : 0u; }
     if (open) {
+        nz = 0u;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const bool keep = static_cast<float>(rr[c] >> 8) * 0x1p-24f < __fdiv_rn(fabsf(vv[c]), m);
-            nz |= ((open >> c) & 1u) && keep ? 1u << c : 0u;
+            // not where m = 0: the quotient is a NaN
+            const bool keep = static_cast<float>(rnd[c] >> 8) * 0x1p-24f < __fdiv_rn(fabsf(v[c]), M.m);
+            nz |= keep ? 1u << c : 0u;
         }
     }
-    nz &= (left >= 4) ? 15u : (left > 0) ? (1u << left) - 1u : 0u;
-    const uint32_t neg = (vv[0] < 0.f ? 1u : 0u) | (vv[1] < 0.f ? 2u : 0u) | (vv[2] < 0.f ? 4u : 0u) | (vv[3] < 0.f ? 8u : 0u);
-    return nz | ((nz & neg) << 4);
+    return nz | ((nz & neg) << 16);                             // what is kept is not 0
+}
+
+// The 32-bit words that lane's group of eight lanes contributes to the two planes, from the codes of its lanes.
+__device__ __forceinline__ void tern_words(uint32_t code, uint32_t &nz, uint32_t &neg)
+{
+    uint32_t w = code << (4 * (lane_id() & 3));                 // four lanes: 16 bits of either plane
+    w |= dpp_u32<kDppXor1>(w);
+    w |= dpp_u32<kDppXor2>(w);
+    const uint32_t o = dpp_u32<kDppHalfMirror>(w);              // of the other four
+    const bool upper = (lane_id() & 4) != 0;
+    const uint32_t lo = upper ? o : w, hi = upper ? w : o;
+    nz = (lo & 0xFFFFu) | (hi << 16);
+    neg = (lo >> 16) | (hi & 0xFFFF0000u);
 }
 
 template <bool BF16>
@@ -143,11 +170,12 @@ __global__ __launch_bounds__(kBlock) void k_tern_encode(const void *g, int64_t g
     const int64_t e = base + threadIdx.x * 4;
     const void *grow = grad_row<BF16>(g, gs, row);
     const f32x4 v = ld4_grad<BF16>(grow, e, d);
-    const float m = rowmax[row];
-    const uint32_t code = tern_codes4(v, m, static_cast<uint32_t>(e >> 2), static_cast<int>(d - e), row, TernKey{key0, key1, step_lo});
-    stash_sign_words(sw_nz, wave_nibble_word(code & 15u));
-    stash_sign_words(sw_neg, wave_nibble_word(code >> 4));
-    const uint32_t kept = wave_sum_u32(static_cast<uint32_t>(__popc(code & 15u)));
+    const uint32_t code = tern_codes4(v, tern_max(rowmax[row]), static_cast<uint32_t>(e >> 2), row, TernKey{key0, key1, step_lo});
+    uint32_t w_nz, w_neg;
+    tern_words(code, w_nz, w_neg);
+    stash_sign_words(sw_nz, w_nz);
+    stash_sign_words(sw_neg, w_neg);
+    const uint32_t kept = wave_sum_u32(static_cast<uint32_t>(__popc(code & 0xFFFFu)));
     if (lane_id() == 0) cnt[wave_id()] = kept;
     __syncthreads();
     flush_sign_words(sw_nz, nz + row * W, base, W * 64);
@@ -186,17 +214,19 @@ __global__ __launch_bounds__(kBlock) void k_tern_scale(const uint32_t *pcnt, con
 // each, and with the maximum and the count as two more of them a call at 1 x 1,000,003 took 24.9, 16.9 and
 // 13.8 us with 1, 2 and 4 tiles per workgroup (16.0, 12.9 and 12.1 us without).
 //
-// What bounds it is the encoding: vector instructions, most of them Philox.  Worker call at
-// 8 x 11,173,962: 189 us in two looks with four divisions per thread, 164 us in two looks without
-// them, 149 .. 154 us here with the finish launch (57 us for its bytes at the copy kernel's rate).
+// What bounds it is vector instructions, 38 of Philox among about 150 per four elements (57 us for its bytes at the copy
+// kernel's rate).  Worker call at 8 x 11,173,962: 159 us in two looks; 149 .. 154 us here with three comparisons per
+// element in the encoding and a sum over the wavefront for every tile, 139 us with the encoding as it is (tern_codes4), 124 us
+// with sums that stay with their thread until the end.  Tried without effect: drawing while the tiles are loaded and keeping
+// |v| / U (145 us), and starting the second row later by a row's load, so that one would load while the other is
+// encoded (138 .. 141 us for 0 .. 1.5 loads).
 __device__ __forceinline__ float tern_scale(double sum, uint32_t kept)
 {
     return kept ? static_cast<float>(sum / static_cast<double>(kept)) : 0.f;
 }
 
-template <int T>
 struct TernShared {
-    double sums[T][kWaves], red[kWaves];
+    double sums[kWaves], red[kWaves];
     float mx[kWaves];
     uint32_t cnt[kWaves], sh[2];
 };
@@ -206,7 +236,9 @@ struct TernShared {
 // four and their bits.
 __device__ __forceinline__ void tern_put_words(uint32_t code, uint32_t quad, uint64_t *neg_row, uint64_t *nz_row, uint32_t words)
 {
-    const uint32_t a = wave_nibble_word(code & 15u), b = wave_nibble_word(code >> 4), w = quad >> 3;
+    const uint32_t w = quad >> 3;
+    uint32_t a, b;
+    tern_words(code, a, b);
     if ((lane_id() & 7) == 0 && w < words) {
         reinterpret_cast<uint32_t *>(nz_row)[w] = a;
         reinterpret_cast<uint32_t *>(neg_row)[w] = b;
@@ -227,7 +259,7 @@ __device__ __forceinline__ uint32_t tern_kept(uint32_t kept, uint32_t *cnt)
 
 // Encodes what a workgroup that gave up did not; the thread's non-zero codes.
 template <bool BF16>
-__device__ __forceinline__ uint32_t tern_finish_part(const void *grow, int64_t d, int part, int T, float m, int row, TernKey K,
+__device__ __forceinline__ uint32_t tern_finish_part(const void *grow, int64_t d, int part, int T, TernMax M, int row, TernKey K,
                                                      uint64_t *neg_row, uint64_t *nz_row, uint32_t words)
 {
     uint32_t kept = 0;
@@ -237,9 +269,9 @@ __device__ __forceinline__ uint32_t tern_finish_part(const void *grow, int64_t d
         const uint32_t quad = static_cast<uint32_t>(e >> 2);
         const f32x4 v = next;
         if (t + 1 < T) next = ld4_grad<BF16>(grow, e + kTile, d);       // zero past the end of the row
-        const uint32_t code = tern_codes4(v, m, quad, static_cast<int>(d - e), row, K);
+        const uint32_t code = tern_codes4(v, M, quad, row, K);
         tern_put_words(code, quad, neg_row, nz_row, words);
-        kept += __popc(code & 15u);
+        kept += __popc(code & 0xFFFFu);
     }
     return kept;
 }
@@ -251,7 +283,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
                                                                      uint32_t *gave_up, uint32_t patience, bool self)
 {
     constexpr int T = R + L;
-    __shared__ TernShared<T> sm;
+    __shared__ TernShared sm;
     __shared__ f32x4 far[L ? L : 1][kBlock];
     const int row = blockIdx.y;
     const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * T, first = tile0 * kTile;
@@ -271,6 +303,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
         else v[q - L] = held_g4<BF16>(grow, first, left, q - L);
     };
     float mx = 0.f;
+    double sum = 0.0;                                         // of the thread's elements
     static_for<0, D>(fetch);
     static_for<0, T>([&](auto qc) {
         constexpr int q = decltype(qc)::value, t = q < L ? R + q : q - L;
@@ -290,34 +323,30 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
         const float a0 = fabsf(w.x), a1 = fabsf(w.y), a2 = fabsf(w.z), a3 = fabsf(w.w);
         mx = fmaxf(mx, fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)));
         asm volatile("" : "+v"(mx));      // now: put off to the end, the maximum keeps |v| of all tiles in registers
-        const double s = wave_sum(((static_cast<double>(a0) + static_cast<double>(a1)) + static_cast<double>(a2)) + static_cast<double>(a3));
-        if (lane_id() == 0) sm.sums[t][wave_id()] = s;
+        sum += ((static_cast<double>(a0) + static_cast<double>(a1)) + static_cast<double>(a2)) + static_cast<double>(a3);
+        asm volatile("" : "+v"(sum));
     });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if (lane_id() == 0) sm.mx[wave_id()] = mx;
+    sum = wave_sum(sum);
+    if (lane_id() == 0) { sm.mx[wave_id()] = mx; sm.sums[wave_id()] = sum; }
     held_fence(v, left);
     __syncthreads();
-    double tile_sum = 0.0;                                    // lane t < T of every wavefront: tile t
-    if (lane_id() < T) {
-        tile_sum = sm.sums[lane_id()][0];
+    sum = sm.sums[0];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) tile_sum += sm.sums[lane_id()][w];
-    }
+    for (int w = 1; w < kWaves; ++w) sum += sm.sums[w];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, sm.mx[w]);
     const bool alone = gridDim.x == 1;
-    double row_sum_alone = 0.0;
     bool ok = true;
-    if (alone) {
-        row_sum_alone = wave_sum(tile_sum);
-    } else {
+    if (!alone) {
         uint64_t *psum_row = reinterpret_cast<uint64_t *>(psum) + static_cast<int64_t>(row) * n_tiles;
-        uint32_t *pmax_row = reinterpret_cast<uint32_t *>(pmax) + static_cast<int64_t>(row) * n_tiles;   // one per workgroup
+        uint32_t *pmax_row = reinterpret_cast<uint32_t *>(pmax) + static_cast<int64_t>(row) * n_tiles;   // both one per workgroup
         if (wave_id() == 0) {
-            if (lane_id() < T && tile0 + lane_id() < n_tiles)
-                as_shared(psum_row)[tile0 + lane_id()].store(__double_as_longlong(tile_sum));
-            if (lane_id() == 0) as_shared(pmax_row)[blockIdx.x].store(__float_as_uint(mx));
+            if (lane_id() == 0) {
+                as_shared(psum_row)[blockIdx.x].store(__double_as_longlong(sum));
+                as_shared(pmax_row)[blockIdx.x].store(__float_as_uint(mx));
+            }
             // both are in memory before the arrival is announced
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane_id() == 0) sm.sh[0] = (rows[row].arrived.fetch_add(1u) + 1u == gridDim.x) ? 1u : 0u;
@@ -329,7 +358,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
             ok = held_wait(rows, row, patience, sm.sh, &mx);
         } else {
             double acc = 0.0;
-            for (int32_t p = threadIdx.x; p < n_tiles; p += kBlock)
+            for (uint32_t p = threadIdx.x; p < gridDim.x; p += kBlock)
                 acc += __longlong_as_double(static_cast<long long>(as_shared(psum_row)[p].load()));
             const double total = block_sum(acc, sm.red, false);
             if (wave_id() == 0) {
@@ -356,11 +385,12 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
     const uint32_t words = static_cast<uint32_t>(W) * 2u, quad0 = static_cast<uint32_t>(first >> 2) + threadIdx.x;
     uint64_t *neg_row = neg + row * W, *nz_row = nz + row * W;
     uint32_t kept = 0;
+    const TernMax M = tern_max(mx);
     auto encode = [&](f32x4 w, int t) {
         const uint32_t quad = quad0 + t * (kTile / 4);
-        const uint32_t code = tern_codes4(w, mx, quad, left - t * kTile - static_cast<int>(threadIdx.x) * 4, row, K);
+        const uint32_t code = tern_codes4(w, M, quad, row, K);
         tern_put_words(code, quad, neg_row, nz_row, words);
-        kept += __popc(code & 15u);
+        kept += __popc(code & 0xFFFFu);
     };
     if (!kHeldSelf<R, L> || ok) {                             // uniform
 #pragma unroll
@@ -381,7 +411,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
                 uint32_t more = 0;
                 for (uint32_t p = 0; p < gridDim.x; ++p)
                     if (as_shared(gave_up + row * static_cast<int64_t>(gridDim.x))[p].load() != 0u)
-                        more += tern_finish_part<BF16>(grow, d, static_cast<int>(p), T, m, row, K, neg_row, nz_row, words);
+                        more += tern_finish_part<BF16>(grow, d, static_cast<int>(p), T, tern_max(m), row, K, neg_row, nz_row, words);
                 __syncthreads();                              // sm.cnt is used again
                 all += tern_kept(more, sm.cnt);
             }
@@ -391,7 +421,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
             return;
         }
     if (threadIdx.x != 0) return;
-    if (alone) scales[row] = tern_scale(row_sum_alone, kept);
+    if (alone) scales[row] = tern_scale(sum, kept);
     else pcnt[static_cast<int64_t>(row) * n_tiles + blockIdx.x] = kept;    // added up by the finish launch
 }
 
@@ -415,7 +445,7 @@ __global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int6
         uint32_t kept = 0;
         const bool mine = gave_up[row * static_cast<int64_t>(gridDim.x) + part] != 0u;
         if (mine)
-            kept = tern_finish_part<BF16>(grad_row<BF16>(g, gs, row), d, part, T, rowmax[row], row, K, neg + row * W, nz + row * W,
+            kept = tern_finish_part<BF16>(grad_row<BF16>(g, gs, row), d, part, T, tern_max(rowmax[row]), row, K, neg + row * W, nz + row * W,
                                           static_cast<uint32_t>(W) * 2u);
         kept = tern_kept(kept, cnt);
         if (threadIdx.x == 0) {
@@ -435,19 +465,20 @@ __global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int6
     rows[row].next_call(row == 0);
 }
 
-// code * scale of elements e..e+3 of one message
-__device__ __forceinline__ f32x4 tern_decode4(const uint64_t *neg_row, const uint64_t *nz_row, float s, int64_t e)
+// code * scale of four elements of one message from their bits of the planes
+__device__ __forceinline__ f32x4 tern_decode4(uint32_t nz, uint32_t neg, float s)
 {
-    const uint32_t kb = load_sign_nibble(nz_row, e), nb = load_sign_nibble(neg_row, e);
     f32x4 q;
-    q.x = (kb & 1u) ? ((nb & 1u) ? -s : s) : 0.f;
-    q.y = (kb & 2u) ? ((nb & 2u) ? -s : s) : 0.f;
-    q.z = (kb & 4u) ? ((nb & 4u) ? -s : s) : 0.f;
-    q.w = (kb & 8u) ? ((nb & 8u) ? -s : s) : 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t keep = static_cast<uint32_t>(static_cast<int32_t>(nz << (31 - c)) >> 31);
+        q[c] = __uint_as_float((__float_as_uint(s) ^ ((neg << (31 - c)) & 0x80000000u)) & keep);
+    }
     return q;
 }
 
-// Server that does not compress: a = (1/n) sum_i Q[v_i] by the chain from +0.
+// Server that does not compress: a = (1/n) sum_i Q[v_i] by the chain from +0.  The bits of eight messages are asked
+// for before the first is used: one message after the other was a chain of memory latencies.
 __global__ __launch_bounds__(kBlock) void k_tern_server_identity(const uint64_t *neg, const uint64_t *nz, const float *scales,
                                                                  int n, float inv_n, int64_t d, int64_t W, float *dense_out,
                                                                  ds_update_args u)
@@ -455,7 +486,20 @@ __global__ __launch_bounds__(kBlock) void k_tern_server_identity(const uint64_t 
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    for (int i = 0; i < n; ++i) a = fma4(inv_n, tern_decode4(neg + i * W, nz + i * W, scales[i], e), a);
+    for (int i0 = 0; i0 < n; i0 += 8) {
+        uint32_t kb[8], nb[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            kb[i] = nb[i] = 0u;
+            if (i0 + i < n) {                                   // uniform
+                kb[i] = load_sign_nibble(nz + (i0 + i) * W, e);
+                nb[i] = load_sign_nibble(neg + (i0 + i) * W, e);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i0 + i < n) a = fma4(inv_n, tern_decode4(kb[i], nb[i], scales[i0 + i]), a);
+    }
     put_average4(zero_past(a, e, d), e, d, dense_out, u.x, u.m, u.gamma, u.beta);
 }
 
@@ -464,7 +508,7 @@ __global__ __launch_bounds__(kBlock) void k_tern_decode(const uint64_t *neg_row,
 {
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
-    st4(out, e, d, tern_decode4(neg_row, nz_row, scale[0], e));
+    st4(out, e, d, tern_decode4(load_sign_nibble(nz_row, e), load_sign_nibble(neg_row, e), scale[0]));
 }
 
 unsigned blocks4(int64_t d) { return static_cast<unsigned>((d + kBlock * 4 - 1) / (kBlock * 4)); }
@@ -483,25 +527,28 @@ ds_status_t ds_ternary_init(ds_ctx *c)
     DS_HIP_TRY(hipMalloc(&t->pcnt, n * tiles * sizeof(uint32_t)));
     DS_HIP_TRY(hipMalloc(&t->rowmax, n * sizeof(float)));
     DS_HIP_TRY(hipMalloc(&t->rowsum, n * sizeof(double)));
-    // GPU time of a worker call, two looks as separate launches against sizes of the held route.  In a stream of
-    // calls the four launches of two looks also cost the host 17 us, the two of this route 12 us, and the one of a
-    // row that finishes itself or that one workgroup holds 10 us.
-    //  * one workgroup, 4 tiles in 4: 5.2 .. 5.5 us (bf16 5.8 .. 6.2), two looks 8.8 .. 10.3 us; 8 tiles in 8: 7.8 .. 8.1 us (bf16
-    //    8.9 .. 9.4), 8.9 .. 10.6 us; 12 tiles in 14: 11.5 .. 11.9 us (bf16 13.1 .. 13.5), 9.0 .. 10.6 us; one tile per workgroup
-    //    5 to 24 tiles 7.7 .. 8.6 us;
-    //  * one row gains on the host's side only: d = 300,001 9.1 us, with 2 tiles 10.1 us; 1,000,003 10.1 us, with 1, 2, 4
-    //    and 8 tiles 16.0, 12.9, 12.1 and 13.7 us; 2,500,001 13.3 us, with 4 and 8 tiles 16.6 and 16.2 us;
-    //  * n = 8: 300,001 13.1 us, 1, 2 and 4 tiles 18.7, 12.2 and 12.7 us; 1,000,003 23.3 us, 4 and 8 tiles 18.0 and 17.9 us;
-    //    2,500,001 44 us, 8, 14 and 24 tiles 39, 35 and 37 us; 5,000,003 78, 69, 63 and 69 us;
-    //  * 8,000,002, two and more rows on chip: n = 8 121 us, 8 and 24 tiles 113 and 109 us; bf16 125, 119 and 133 us;
-    //    8 x 11,173,962 164 us, 24 tiles (two rows) 149 us, 8 tiles (a row and a half) 197 us; bf16 171 and 173 us;
-    //    8 x 16,000,001, not two rows with any size: 231 us, 24 tiles 273 us;
-    //  * rounds of two rows, n = 3 .. 16, two looks : held by how much of the device the rounds keep busy.  24 tiles: 0.87 at 54 %
-    //    (3 x 9,000,001, 57.6 and 66.3 us), 0.91 .. 0.98 at 60 .. 68 %, 0.98 .. 1.04 at 70 .. 75 %, 1.05 .. 1.14 above.  8 tiles of
-    //    bf16: 0.91 .. 0.98 at 60 .. 70 %, 0.98 .. 1.01 at 72 .. 80 %, 1.00 .. 1.06 above.
-    static constexpr HeldStep one_row[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-    static constexpr HeldStep f32[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {24, 2, 0, 70}};
-    static constexpr HeldStep bf16[] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {8, 2, 0, 80}};
+    // GPU time of a worker call, two looks as separate launches against sizes of the held route (two looks are four
+    // launches, this route is two, and one for a row that finishes itself or that one workgroup holds, which counts for
+    // the host).
+    //  * one workgroup, 4 tiles in 4: 5.2 .. 5.5 us (bf16 5.8 .. 6.2), two looks 8.8 .. 10.3 us; one tile per workgroup 5 to 24
+    //    tiles 7.8 .. 8.4 us, two looks 9.1 .. 10.6 us;
+    //  * one row gains on the host's side only up to 5 M elements: d = 300,001 9.9 us, two looks 9.6 us; 1,000,003 11.4 and
+    //    10.6 us; 2,500,001 8 tiles 14.6 us, 13.0 us; 5,000,003 14 tiles 18.0 us, 17.5 us; 11,173,962 14 and 24 tiles 25.8 and
+    //    24.7 us, 30.9 us; 20,000,000 37.5 and 35.7 us, 49.5 us;
+    //  * n = 8: 300,001 13.4 us, 1, 2 and 4 tiles 19.2, 12.2 and 12.2 us; 1,000,003 22.7 us, 4 and 8 tiles 17.0 and 16.6 us;
+    //    2,500,001 44 us, 8, 14 and 24 tiles 34.5, 30.6 and 33.5 us; 5,000,003 80 us, 62, 55 and 59 us;
+    //  * rounds of fewer rows, two looks : 14 : 24 tiles, and how much of the device the rounds keep busy with 14 : 24:
+    //    8 x 8,000,002 115 : 94 : 91 us (73 : 85 %); 8 x 11,173,962 159 : 153 : 123 us (51 : 89 %); 3 x 9,000,001 56 : 47 : 55 us
+    //    (61 : 54 %); 5 x 9,000,001 86 : 73 : 79 us (68 : 60 %); 3 x 11,173,962 67 : 64 : 58 us (51 : 67 %); 8 x 16,000,001
+    //    225 : 199 : 214 us (73 : 64 %); 8 x 20,000,000 287 : 236 : 242 us (91 : 79 %); 8 x 24,000,000 24 tiles only, 326 : 265 us;
+    //  * bf16 the same, with 24 tiles a little behind: 8 x 8,000,002 120 : 101 : 109 us; 8 x 11,173,962 164 : 171 : 144 us; 5 x
+    //    9,000,001 89 : 78 : 93 us; 8 x 20,000,000 285 : 257 : 292 us; 8 x 24,000,000 340 : 304 us.  Rounds of two rows with 8 tiles:
+    //    8 x 8,000,002 104 us, 6 x 6,000,000 62 us (two looks 72 us);
+    //  * below: a step at 13 M elements with 24 tiles, 52 % busy, two rows 87 us (bf16 97), two looks 85 us (87); one row of
+    //    8,000,001, 36 % busy with 14 tiles, 43.1 us (45.6), 42.6 us (42.3).
+    static constexpr HeldStep one_row[8] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {14, 1, 0, 50}, {24, 1, 0, 50}};
+    static constexpr HeldStep f32[8] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {24, 1, 0, 85}, {14, 1, 0, 58}, {24, 1, 0, 65}};
+    static constexpr HeldStep bf16[8] = {{1, 0, 64}, {2, 0, 128}, {4, 0, 256}, {8, 0, 0}, {14, 4, 0}, {8, 2, 0, 70}, {14, 1, 0, 58}, {24, 1, 0, 65}};
     const auto &steps = c->cfg.n == 1 ? one_row : c->cfg.grad_dtype == DS_BF16 ? bf16 : f32;
     const ds_status_t rc = held_size(c, c->cfg.n, 4, steps, [](auto r, auto l) {
         constexpr int R = decltype(r)::value, L = decltype(l)::value;

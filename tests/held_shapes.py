@@ -36,9 +36,9 @@ TERNARY = [
     (2, 8 * 2048 + 1, "f32", 1, 9), (2, 14 * 2048, "bf16", 1, 14), (2, 24 * 2048 - 2, "f32", 1, 24), (2, 25 * 2048 + 3, "f32", 1, 26),
     (5, 300_001, "bf16", 2, 74), (1, 300_003, "f32", 2, 74), (8, 700_002, "f32", 4, 86), (1, 1_000_003, "bf16", 4, 123),
     (9, 1_800_003, "f32", 8, 110), (4, 8_000_002, "bf16", 8, 489), (9, 2_600_001, "bf16", 14, 91), (9, 2_600_002, "f32", 14, 91),
-    (4, 9_000_005, "f32", 24, 184), (2, 11_173_962, "f32", 24, 228), (5, 11_173_963, "f32", 24, 228), (7, 7_826_509, "bf16", 8, 478),
-    (3, 9_000_005, "f32", 0, 4395), (5, 6_000_002, "bf16", 0, 2930), (3, 7_826_508, "bf16", 0, 3822),
-    (1, 5_000_003, "f32", 0, 2442), (2, 13_000_001, "bf16", 0, 6348),
+    (4, 9_000_005, "f32", 14, 314), (2, 11_173_962, "f32", 24, 228), (5, 11_173_963, "f32", 24, 228), (7, 7_826_509, "bf16", 8, 478),
+    (3, 9_000_005, "f32", 14, 314), (5, 6_000_002, "bf16", 14, 210), (3, 7_826_508, "bf16", 8, 478),
+    (1, 5_000_003, "f32", 0, 2442), (2, 13_000_001, "bf16", 14, 454),
 ]
 
 # tiles -> tiles in registers and in LDS, the last template arguments of the kernels
