@@ -183,6 +183,18 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_worker(const void *g, int64_t g
     }
 }
 
+// Codes and sign bits (in the low bits) of four elements of a message added to the average: five instructions per element.
+// The codes become bytes in three operations; conversion from a byte, product, sign bit (two), fused multiply-add.
+__device__ __forceinline__ f32x4 chain4(f32x4 a, uint32_t codes, uint32_t bits, float unit, float inv_n)
+{
+    const uint32_t even = codes & 0x0F0Fu, odd = (codes >> 4) & 0x0F0Fu;
+    auto one = [&](float acc, uint32_t bytes, int at, int bit) {
+        const float mag = static_cast<float>((bytes >> (8 * at)) & 255u) * unit;
+        return __fmaf_rn(inv_n, __uint_as_float(__float_as_uint(mag) ^ ((bits << (31 - bit)) & 0x80000000u)), acc);
+    };
+    return f32x4{one(a.x, even, 0, 0), one(a.y, odd, 0, 1), one(a.z, even, 1, 2), one(a.w, odd, 1, 3)};
+}
+
 // Parameter-server block: v = delta_s + (1/n) sum_i decode(msg_i) as the fma chain over
 // workers in ascending order, then the same quantiser on the server's stream.
 // UPD: 0 = that block alone; 1, 2 = followed by the model update of Algorithm 1 for the same
@@ -190,12 +202,18 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_worker(const void *g, int64_t g
 // delta_s == nullptr: no server error (chain from +0, nothing stored back).
 // SID: the server does not compress: the average is written to dense_out (if not null) and / or
 // applied to x, m (if x is not null), and nothing else happens.
+//
+// Every thread loads its own 16 bits of codes and its byte of sign bits, of eight workers at a time.  (Fetched for several
+// workers by one instruction and handed out by lane exchanges, as it was before, their index arithmetic cost more than
+// the decoding: 190 and 147 us at 16 x 25.6 M, bound by vector issue, and whole steps of 17 shapes 1.00 to 1.07 times as
+// fast but for 16 x 1,000,003, 47.0 and 48.4 us.  Eight elements per thread, which halves the loads but has the
+// average change hands through LDS before it is quantised: 148 us, and slower below 5 M elements.)
 template <int UPD, bool SID>
-__global__ __launch_bounds__(kBlock) void k_qsgd_server(const uint8_t *levels_in, const uint64_t *words_in,
-                                                        const float *norms_in, int n, float inv_n, float *delta_s,
-                                                        QParams P, uint8_t *levels_out, uint64_t *words_out,
-                                                        float *norms_out, float *x, float *m, float gamma, float beta,
-                                                        float *dense_out)
+__global__ __launch_bounds__(kBlock, 8) void k_qsgd_server(const uint8_t *levels_in, const uint64_t *words_in,
+                                                           const float *norms_in, int n, float inv_n, float *delta_s,
+                                                           QParams P, uint8_t *levels_out, uint64_t *words_out,
+                                                           float *norms_out, float *x, float *m, float gamma, float beta,
+                                                           float *dense_out)
 {
     __shared__ double lds[kWaves];
     __shared__ __attribute__((aligned(16))) uint32_t sw_lds[kWaves * 8];
@@ -208,58 +226,44 @@ __global__ __launch_bounds__(kBlock) void k_qsgd_server(const uint8_t *levels_in
     const int64_t lev_stride = (P.d + 1) / 2;
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
     if (delta_s) a = ld4_stream(delta_s, e, P.d);
+    // messages of eight workers at a time, the first of them on their way while the decode units are staged
+    const uint8_t *lev = levels_in + (e >> 1);
+    const uint8_t *sgn = reinterpret_cast<const uint8_t *>(words_in) + (e >> 3);
+    const int nib = static_cast<int>(e & 4);                // either half of a byte
+    const bool whole = e + 4 <= P.d;
+    uint32_t codes[8], bits[8];
+    auto fetch = [&](int w0, int cnt) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (j < cnt) {                                   // uniform
+                codes[j] = *reinterpret_cast<const u16_byte *>(lev + (w0 + j) * lev_stride);
+                bits[j] = sgn[(w0 + j) * P.W * 8];
+            }
+        }
+    };
+    if (whole) fetch(0, n);
     f32x4 xv = {0.f, 0.f, 0.f, 0.f}, mv = {0.f, 0.f, 0.f, 0.f};      // fetched up front, beside the error
     if constexpr (UPD != 0) xv = ld4_stream(x, e, P.d);
     if constexpr (UPD == 2) mv = ld4_stream(m, e, P.d);
     for (int i0 = 0; i0 < n; i0 += kUnitGroup) {
         const int cnt = (n - i0 < kUnitGroup) ? n - i0 : kUnitGroup;
-        __syncthreads();
+        if (i0 > 0) __syncthreads();
         for (int t = threadIdx.x; t < cnt * bpt; t += kBlock) {
             const int i = t / bpt, b = t - i * bpt;
             const int64_t B = b0 + b;
             units[t] = (B < P.Bq) ? __fdiv_rn(norms_in[(i0 + i) * P.Bq + B], static_cast<float>(P.s)) : 0.f;
         }
         __syncthreads();
-        // Messages of the wavefront's 256 elements: 128 bytes of codes and 32 bytes of sign
-        // bits per worker.  Fast route (whole wavefront in range):
-        // eight workers at a time, one 32-bit load fetches the sign words of all eight
-        // (lane L: word L & 7 of worker L >> 3) and four 32-bit loads fetch the codes of two
-        // workers each (lane L: word L & 31 of worker L >> 5); ds_bpermute then hands every
-        // lane its own nibble and 16-bit code group.  Other wavefronts load per lane.
-        const int lane = lane_id();
-        const int64_t wave_first = tile_base + wave_id() * 256;
-        const bool fast = wave_first + 256 <= P.d;
-        if (fast) {
+        if (whole) {
             for (int j0 = 0; j0 < cnt; j0 += 8) {
-                const int nb = (cnt - j0 < 8) ? cnt - j0 : 8;
-                uint32_t sw = 0u;
-                if ((lane >> 3) < nb)
-                    sw = reinterpret_cast<const uint32_t *>(words_in + (i0 + j0 + (lane >> 3)) * P.W)[(wave_first >> 5) + (lane & 7)];
-                uint32_t cw[4];
+                if (i0 + j0 > 0) fetch(i0 + j0, cnt - j0);
 #pragma unroll
-                for (int p2 = 0; p2 < 4; ++p2) {
-                    const int wk = 2 * p2 + (lane >> 5);
-                    cw[p2] = 0u;
-                    if (wk < nb)
-                        cw[p2] = reinterpret_cast<const u32_byte *>(levels_in + (i0 + j0 + wk) * lev_stride + (wave_first >> 1))[lane & 31];
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    if (j >= nb) break;                      // uniform
-                    const uint32_t nib = (__shfl(sw, j * 8 + (lane >> 3), 64) >> (4 * (lane & 7))) & 15u;
-                    const uint32_t c32 = __shfl(cw[j >> 1], (j & 1) * 32 + (lane >> 1), 64);
-                    const uint32_t codes = (c32 >> (16 * (lane & 1))) & 0xFFFFu;
-                    a = fma4(inv_n, decode4(codes, nib, units[(j0 + j) * bpt + my_b]), a);
-                }
+                for (int j = 0; j < 8; ++j)
+                    if (j0 + j < cnt) a = chain4(a, codes[j], bits[j] >> nib, units[(j0 + j) * bpt + my_b], inv_n);
             }
         } else if (e < P.d) {
-            for (int i = 0; i < cnt; ++i) {
-                const int64_t w = i0 + i;
-                const uint32_t codes = load_codes4(levels_in + w * lev_stride, e, P.d);
-                const uint32_t nib = load_sign_nibble(words_in + w * P.W, e);
-                const f32x4 q = decode4(codes, nib, units[i * bpt + my_b]);
-                a = fma4(inv_n, q, a);   // fma(q, 1/n, acc): the product commutes
-            }
+            for (int j = 0; j < cnt; ++j)
+                a = chain4(a, load_codes4(lev + (i0 + j) * lev_stride, 0, P.d - e), sgn[(i0 + j) * P.W * 8] >> nib, units[j * bpt + my_b], inv_n);
         }
     }
     a = zero_past(a, e, P.d);
