@@ -27,7 +27,7 @@
 //   verify     if the candidates number fewer than k, or the k-th key lies outside the
 //              histogram window (the sample misjudged), the row takes the exact two-look
 //              route: v restored, dense 12-bit histogram, pick, dense compaction.
-// Rows of up to 65,536 elements take one workgroup and one launch for all of that (k_topk_solo).  For longer
+// Rows of up to 65,536 elements take one launch for all of that (k_topk_slices, k_topk_solo).  For longer
 // ones the refinement exists twice: as ONE launch whose workgroups are all resident and wait for
 // each other per row (k_topk_finish, the default), and as a chain of small launches in which
 // the last workgroup of a row finishes each step (12 + 11 + 8 key bits), for contexts whose
@@ -35,6 +35,7 @@
 // bit-reproducible and the two routes agree bit for bit.
 #include "ds_device.h"
 #include "ds_internal.h"
+#include "held.h"
 
 #include <new>
 #include <type_traits>
@@ -95,7 +96,7 @@ struct ds_topk_scratch {
     int64_t n_sub;        // 256-element subtiles per row (sampling, server ranges)
     int64_t n_reg, reg_pad, n_groups;
     int rows;
-    bool solo;            // rows are short: one workgroup per row (k_topk_solo)
+    bool solo;            // rows are short: one launch (k_topk_slices, k_topk_solo)
     // fused refinement route (k_topk_finish)
     uint32_t *fhist;      // [rows][kFRow], zero between calls
     char *sync;           // [rows][kSyncStride] arrival counters and published picks
@@ -1427,10 +1428,9 @@ __global__ __launch_bounds__(kBlock, 8) void k_topk_finish(FinishArgs a)
 // 8 bits, then the kept ones to their slots.  Where the list does not hold the k-th key (fewer than k candidates)
 // or does not fit (very many ties), the same histograms are taken over all elements.
 //
-// A step (worker, server and update) at 4 x 60,040, k = 600: 67 us in the launches it stands for, 46 us here (two
-// kernels of 23 us, of which a compute unit needs about 12 for loads and stores); 4 x 4096: 61 and 28 us;
-// 16 x 65,536, k = 66, the least gain of 62 shapes of 1 to 600 rows but one: 67 and 51 us; 200 x 60,040: 212 and
-// 174 us.  With the histograms and the emission over all elements instead of a list: 107 us at 4 x 60,040.
+// This kernel takes the rows of more than 16,384 elements that k_topk_slices leaves it (many rows, or large k).  Steps (worker,
+// server and update): 4 x 60,040, k = 30,000, which takes the histograms over all elements, 892 us in the launches it
+// stands for and 216 us here; 200 x 60,040, k = 600, 211 and 174 us; 8 x 65,536, k = 3276, 151 and 78 us.
 constexpr int kSoloThreads = 1024, kSoloWaves = kSoloThreads / 64;
 constexpr int kSoloTile = 4 * kSoloThreads, kSoloTiles = 16;
 constexpr int64_t kSoloMax = static_cast<int64_t>(kSoloTile) * kSoloTiles;
@@ -1497,17 +1497,18 @@ __device__ __forceinline__ void solo_pick(uint32_t *h, uint32_t need, uint32_t *
     __syncthreads();
 }
 
-// v = delta_s + (1/n) sum_i Q[v_i] of the server, as the chain over workers in ascending order: strips
-// of 32768 elements in LDS, to which the messages are applied one worker after the other (a message
+// v = delta_s + (1/n) sum_i Q[v_i] of the server for TILES tiles from element `first` on, as the chain over workers in
+// ascending order: strips of STRIP tiles in LDS, to which the messages are applied one worker after the other (a message
 // lists an element once).  Eight batches of 1024 entries are in flight at a time.
-__device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t d, float *strip, f32x4 (&v)[kSoloTiles])
+template <int TILES, int STRIP>
+__device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t first, int64_t d, float *strip, f32x4 (&v)[TILES])
 {
     const int tid = threadIdx.x;
     const int batches = static_cast<int>((src.k + kSoloThreads - 1) / kSoloThreads);
-    constexpr int kTilesOfStrip = kSoloStrip / kSoloTile;
+    constexpr int kTilesOfStrip = STRIP;
 #pragma unroll
-    for (int q = 0; q < kSoloTiles / kTilesOfStrip; ++q) {
-        const int64_t base = static_cast<int64_t>(q) * kSoloStrip;
+    for (int q = 0; q < TILES / kTilesOfStrip; ++q) {
+        const int64_t base = first + static_cast<int64_t>(q) * STRIP * kSoloTile;
         if (base < d) {                                        // uniform
             f32x4 a[kTilesOfStrip];
 #pragma unroll
@@ -1543,7 +1544,7 @@ __device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t d, flo
                     if (i >= held) break;
                     if (fresh[i]) __syncthreads();             // what the worker before has added is in
                     const uint32_t rel = pr[i].x - static_cast<uint32_t>(base);
-                    if (rel < static_cast<uint32_t>(kSoloStrip)) strip[rel] = __fmaf_rn(__uint_as_float(pr[i].y), src.inv_n, strip[rel]);
+                    if (rel < static_cast<uint32_t>(STRIP * kSoloTile)) strip[rel] = __fmaf_rn(__uint_as_float(pr[i].y), src.inv_n, strip[rel]);
                 }
             }
             __syncthreads();
@@ -1580,33 +1581,34 @@ __device__ __forceinline__ f32x4 solo_value(const WorkerV<BF16> &, const SoloRaw
 }
 __device__ __forceinline__ f32x4 solo_value(const GradV &, const SoloRaw &r) { return r.g; }
 
-// v of a row, zero past its end: loads of eight tiles in flight, four by four.
-template <class Src>
-__device__ __forceinline__ void solo_row_v(const Src &src, int row, int d, f32x4 (&v)[kSoloTiles])
+// v of TILES tiles of a row from element `first` on, zero past its end: loads of eight tiles in flight, four by four.
+template <int TILES, class Src>
+__device__ __forceinline__ void solo_row_v(const Src &src, int row, int first, int d, f32x4 (&v)[TILES])
 {
-    const int tid = threadIdx.x, whole = d & ~3;
-    const bool mine = (whole & (kSoloTile - 1)) == tid * 4 && whole < d;     // the thread whose last group of four d cuts
+    const int tid = threadIdx.x, whole = d & ~3, cut_at = whole - first;
+    // the thread whose last group of four d cuts
+    const bool mine = cut_at >= 0 && cut_at < TILES * kSoloTile && (cut_at & (kSoloTile - 1)) == tid * 4 && whole < d;
     f32x4 cut = {0.f, 0.f, 0.f, 0.f};
     if (mine) cut = src.load(row, whole, d, nullptr);
     SoloRaw ring[2][4];
     auto fetch = [&](int q) {
-        if (q * 4 * kSoloTile < whole) {                       // uniform; whole >= 4 then
+        if (first + q * 4 * kSoloTile < whole) {               // uniform; whole >= 4 then
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int e = (q * 4 + j) * kSoloTile + tid * 4;
+                const int e = first + (q * 4 + j) * kSoloTile + tid * 4;
                 solo_fetch(src, row, e < whole ? e : whole - 4, ring[q & 1][j]);
             }
         }
     };
     fetch(0);
 #pragma unroll
-    for (int q = 0; q < kSoloTiles / 4; ++q) {
-        if (q + 1 < kSoloTiles / 4) fetch(q + 1);
+    for (int q = 0; q < TILES / 4; ++q) {
+        if (q + 1 < TILES / 4) fetch(q + 1);
         __builtin_amdgcn_sched_barrier(0);
-        if (q * 4 * kSoloTile < whole) {
+        if (first + q * 4 * kSoloTile < whole) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int e = (q * 4 + j) * kSoloTile + tid * 4;
+                const int e = first + (q * 4 + j) * kSoloTile + tid * 4;
                 const f32x4 w = solo_value(src, ring[q & 1][j]);
                 v[q * 4 + j] = (e < whole) ? w : f32x4{0.f, 0.f, 0.f, 0.f};
             }
@@ -1614,8 +1616,8 @@ __device__ __forceinline__ void solo_row_v(const Src &src, int row, int d, f32x4
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int t = 0; t < kSoloTiles; ++t)
-        if (mine && (whole / kSoloTile) == t) v[t] = cut;
+    for (int t = 0; t < TILES; ++t)
+        if (mine && (cut_at / kSoloTile) == t) v[t] = cut;
 }
 
 // Before a tile of a phase: what the compiler derived from it in an earlier phase (keys, masks, addresses) is not
@@ -1662,6 +1664,161 @@ __device__ __forceinline__ uint32_t solo_before(const uint32_t *cnt, int wave, i
     return before + incl - sum;
 }
 
+// The whole selection and emission by histograms over all elements of a row of up to 16 tiles, for what the list does not
+// hold: load(e) gives v of elements e .. e + 3 (anything past the row's end).  brow: the error, cleared where an element is
+// kept (null: there is none).
+template <class L>
+__device__ __forceinline__ void solo_exact(SoloShared &sm, int wave, int dd, uint32_t need, L load, u32x2 *prow, float *brow)
+{
+    const int tid = threadIdx.x, lane = lane_id();
+    uint32_t T, k3;
+    __syncthreads();                                          // cnt may still be read
+    for (int i = tid; i < kSoloTiles * kSoloWaves; i += kSoloThreads) sm.cnt[i] = 0u;
+    __syncthreads();
+    // f(tile, four values, first element) for the thread's elements
+    auto each = [&](auto f) {
+        for (int t0 = 0; t0 * kSoloTile < dd; t0 += 4) {
+            f32x4 w[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) w[t] = load((t0 + t) * kSoloTile + tid * 4);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if ((t0 + t) * kSoloTile < dd) f(t0 + t, w[t], (t0 + t) * kSoloTile + tid * 4);
+        }
+    };
+    solo_threshold(sm, need, [&](uint32_t *h, int shift, uint32_t mask, uint32_t prefix, int prefix_shift) {
+        each([&](int, f32x4 w, int e) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t key = key_of(w[c]);
+                solo_add(h, (key >> shift) & mask, e + c < dd && (key >> prefix_shift) == prefix);
+            }
+        });
+    }, T, k3);
+    // keys above T, and ties << 16, of every wavefront's 256 elements of a tile
+    each([&](int t, f32x4 w, int e) {
+        uint32_t gt = 0, eq = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            gt += __popcll(__ballot(e + c < dd && key_of(w[c]) > T));
+            eq += __popcll(__ballot(e + c < dd && key_of(w[c]) == T));
+        }
+        if (lane == 0) sm.cnt[t * kSoloWaves + wave] = gt | (eq << 16);
+    });
+    __syncthreads();
+    uint32_t all;
+    const uint32_t gt_at = solo_before(sm.cnt, wave, 0, 0xFFFFu, all), eq_at = solo_before(sm.cnt, wave, 16, 0xFFFFu, all);
+    each([&](int t, f32x4 w, int e) {
+        bool gt[4], eq[4];
+        uint32_t g = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(gt_at), t * 4 + (wave >> 2)));
+        uint32_t q = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(eq_at), t * 4 + (wave >> 2)));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            gt[c] = e + c < dd && key_of(w[c]) > T;
+            eq[c] = e + c < dd && key_of(w[c]) == T;
+            g += lanes_below(__ballot(gt[c]));
+            q += lanes_below(__ballot(eq[c]));
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t slot = g + (q < k3 ? q : k3);
+            if ((gt[c] || (eq[c] && q < k3)) && slot < need) {
+                prow[slot] = u32x2{static_cast<uint32_t>(e + c), __float_as_uint(w[c])};
+                if (brow) brow[e + c] = 0.f;
+            }
+            g += gt[c] ? 1u : 0u;
+            q += eq[c] ? 1u : 0u;
+        }
+    });
+}
+
+// The threshold of the list, whose keys are lo or more.  They crowd just above lo, where the 12-bit bins would be hit by all
+// lanes at once, so the first histogram counts in steps of 2^11 from lo (the last bin takes what is an octave and more above)
+// and the second resolves the step.  Where the k-th key is an octave above lo, or there was no bound, the levels of
+// solo_threshold decide.  Step at 4 x 60,040: 51 us with those alone.
+__device__ __forceinline__ void solo_list_threshold(SoloShared &sm, uint32_t listed, uint32_t lo, uint32_t need, uint32_t &T, uint32_t &k3)
+{
+    auto keys = [&](auto f) {                                  // f(key, whether there is one), by whole wavefronts
+        for (uint32_t i0 = 0; i0 < listed; i0 += kSoloThreads) {
+            const uint32_t i = i0 + threadIdx.x;
+            f((i < listed) ? sm.list[i].y & 0x7FFFFFFFu : 0u, i < listed);
+        }
+    };
+    if (lo > 1u) {                                             // uniform
+        keys([&](uint32_t key, bool on) {
+            const uint32_t step = (key - lo) >> 11;
+            if (on) atomicAdd(&sm.h[step < kH1 ? step : kH1 - 1], 1u);
+        });
+        solo_pick<kH1>(sm.h, need, sm.part, sm.out);
+        const uint32_t step = sm.out[0], left = sm.out[1];
+        if (step != kH1 - 1) {                                 // uniform
+            keys([&](uint32_t key, bool on) {
+                if (on && ((key - lo) >> 11) == step) atomicAdd(&sm.h2[(key - lo) & (kH2 - 1)], 1u);
+            });
+            solo_pick<kH2>(sm.h2, left, sm.part, sm.out);
+            T = lo + (step << 11) + sm.out[0];
+            k3 = sm.out[1];
+            return;
+        }
+    }
+    solo_threshold(sm, need, [&](uint32_t *h, int shift, uint32_t mask, uint32_t prefix, int prefix_shift) {
+        keys([&](uint32_t key, bool on) { solo_add(h, (key >> shift) & mask, on && (key >> prefix_shift) == prefix); });
+    }, T, k3);
+}
+
+// The model update at the entries as this workgroup has just written them, all loads in flight together.
+__device__ __forceinline__ void solo_update(const u32x2 *prow, uint32_t need, int dd, float *x, float gamma)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < need; i += kSoloThreads) {
+        const u32x2 pr = __builtin_nontemporal_load(prow + i);
+        if (pr.x < static_cast<uint32_t>(dd)) x[pr.x] = __fmaf_rn(-gamma, __uint_as_float(pr.y), x[pr.x]);
+    }
+}
+
+// The kept ones of the list's `listed` candidates to their slots, in index order; their error is 0, and with BACK that of
+// the others is v.
+template <bool BACK>
+__device__ __forceinline__ void solo_emit(SoloShared &sm, int wave, uint32_t listed, uint32_t need, uint32_t T, uint32_t k3, u32x2 *prow,
+                                          float *brow)
+{
+    const int lane = lane_id();
+    // every wavefront emits a stretch of the list
+    const uint32_t per = (listed + 64u * kSoloWaves - 1u) / (64u * kSoloWaves) * 64u;
+    const uint32_t i0 = wave * per, i1 = (i0 + per < listed) ? i0 + per : listed;
+    uint32_t gt = 0, eq = 0;
+    for (uint32_t b = i0; b < i1; b += 64u) {
+        const uint32_t i = b + lane;
+        const uint32_t key = (i < i1) ? sm.list[i].y & 0x7FFFFFFFu : 0u;
+        gt += __popcll(__ballot(i < i1 && key > T));
+        eq += __popcll(__ballot(i < i1 && key == T));
+    }
+    if (lane == 0) { sm.part[wave] = gt; sm.part2[wave] = eq; }
+    __syncthreads();
+    uint32_t slot0 = 0, ties = 0;
+    for (int w = 0; w < wave; ++w) { slot0 += sm.part[w]; ties += sm.part2[w]; }
+    slot0 += (ties < k3) ? ties : k3;
+    for (uint32_t b = i0; b < i1; b += 64u) {
+        const uint32_t i = b + lane;
+        const u32x2 pr = (i < i1) ? sm.list[i] : u32x2{0u, 0u};
+        const uint32_t key = pr.y & 0x7FFFFFFFu;
+        const bool is_eq = i < i1 && key == T;
+        const uint64_t eq_mask = __ballot(is_eq);
+        const bool keep = i < i1 && (key > T || (is_eq && ties + lanes_below(eq_mask) < k3));
+        const uint64_t keep_mask = __ballot(keep);
+        const uint32_t slot = slot0 + lanes_below(keep_mask);
+        if (keep && slot < need) {
+            prow[slot] = pr;
+            if (brow) brow[pr.x] = 0.f;
+        } else if (BACK && i < i1 && brow) {
+            brow[pr.x] = __uint_as_float(pr.y);
+        }
+        slot0 += __popcll(keep_mask);
+        ties += __popcll(eq_mask);
+    }
+}
+
 // sample_rank: 0 = the row is not sampled.  WR: the error is written to buf.  x != nullptr (one row
 // only): x <- fma(-gamma, val, x) at the kept entries.
 template <class Src, bool WR>
@@ -1680,8 +1837,8 @@ __global__ __launch_bounds__(kSoloThreads) void k_topk_solo(Src src, float *buf,
     f32x4 v[kSoloTiles];
 #pragma unroll
     for (int t = 0; t < kSoloTiles; ++t) v[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (kServer) solo_server_v(src, d, sm.strip, v);
-    else solo_row_v(src, row, dd, v);
+    if constexpr (kServer) solo_server_v<kSoloTiles, kSoloStrip / kSoloTile>(src, 0, d, sm.strip, v);
+    else solo_row_v<kSoloTiles>(src, row, 0, dd, v);
     // the error is v but for the kept elements, which are cleared as they are emitted
     if constexpr (WR) {
 #pragma unroll
@@ -1765,115 +1922,199 @@ __global__ __launch_bounds__(kSoloThreads) void k_topk_solo(Src src, float *buf,
         }
         if constexpr (WR) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // v is stored before another thread clears parts of it
         __syncthreads();
-        solo_threshold(sm, need, [&](uint32_t *h, int shift, uint32_t mask, uint32_t prefix, int prefix_shift) {
-            for (uint32_t i0 = 0; i0 < listed; i0 += kSoloThreads) {
-                const uint32_t i = i0 + tid;
-                const uint32_t key = (i < listed) ? sm.list[i].y & 0x7FFFFFFFu : 0u;
-                solo_add(h, (key >> shift) & mask, i < listed && (key >> prefix_shift) == prefix);
-            }
-        }, T, k3);
-        // every wavefront emits a stretch of the list
-        const uint32_t per = (listed + 64u * kSoloWaves - 1u) / (64u * kSoloWaves) * 64u;
-        const uint32_t i0 = wave * per, i1 = (i0 + per < listed) ? i0 + per : listed;
-        uint32_t gt = 0, eq = 0;
-        for (uint32_t b = i0; b < i1; b += 64u) {
-            const uint32_t i = b + lane;
-            const uint32_t key = (i < i1) ? sm.list[i].y & 0x7FFFFFFFu : 0u;
-            gt += __popcll(__ballot(i < i1 && key > T));
-            eq += __popcll(__ballot(i < i1 && key == T));
-        }
-        if (lane == 0) { sm.part[wave] = gt; sm.part2[wave] = eq; }
-        __syncthreads();
-        uint32_t slot0 = 0, ties = 0;
-        for (int w = 0; w < wave; ++w) { slot0 += sm.part[w]; ties += sm.part2[w]; }
-        slot0 += (ties < k3) ? ties : k3;
-        for (uint32_t b = i0; b < i1; b += 64u) {
-            const uint32_t i = b + lane;
-            const u32x2 pr = (i < i1) ? sm.list[i] : u32x2{0u, 0u};
-            const uint32_t key = pr.y & 0x7FFFFFFFu;
-            const bool is_eq = i < i1 && key == T;
-            const uint64_t eq_mask = __ballot(is_eq);
-            const bool keep = i < i1 && (key > T || (is_eq && ties + lanes_below(eq_mask) < k3));
-            const uint64_t keep_mask = __ballot(keep);
-            const uint32_t slot = slot0 + lanes_below(keep_mask);
-            if (keep && slot < need) {
-                prow[slot] = pr;
-                if constexpr (WR) brow[pr.x] = 0.f;
-            }
-            slot0 += __popcll(keep_mask);
-            ties += __popcll(eq_mask);
-        }
+        solo_list_threshold(sm, listed, lo, need, T, k3);
+        solo_emit<false>(sm, wave, listed, need, T, k3, prow, brow);
     } else {
         // v again from memory: as it has just been stored, or the gradient
         const float *vrow;
         if constexpr (WR) vrow = brow;
         else vrow = src.g + row * src.gs;
-        // f(tile, four values, first element) for the thread's elements
-        auto each = [&](auto f) {
-            for (int t0 = 0; t0 * kSoloTile < dd; t0 += 4) {
-                f32x4 w[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) w[t] = ld4(vrow, (t0 + t) * kSoloTile + tid * 4, d);
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if ((t0 + t) * kSoloTile < dd) f(t0 + t, w[t], (t0 + t) * kSoloTile + tid * 4);
-            }
-        };
-        solo_threshold(sm, need, [&](uint32_t *h, int shift, uint32_t mask, uint32_t prefix, int prefix_shift) {
-            each([&](int, f32x4 w, int e) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t key = key_of(w[c]);
-                    solo_add(h, (key >> shift) & mask, e + c < dd && (key >> prefix_shift) == prefix);
-                }
-            });
-        }, T, k3);
-        // keys above T, and ties << 16, of every wavefront's 256 elements of a tile
-        each([&](int t, f32x4 w, int e) {
-            uint32_t gt = 0, eq = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                gt += __popcll(__ballot(e + c < dd && key_of(w[c]) > T));
-                eq += __popcll(__ballot(e + c < dd && key_of(w[c]) == T));
-            }
-            if (lane == 0) sm.cnt[t * kSoloWaves + wave] = gt | (eq << 16);
-        });
-        __syncthreads();
-        uint32_t all;
-        const uint32_t gt_at = solo_before(sm.cnt, wave, 0, 0xFFFFu, all), eq_at = solo_before(sm.cnt, wave, 16, 0xFFFFu, all);
-        each([&](int t, f32x4 w, int e) {
-            bool gt[4], eq[4];
-            uint32_t g = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(gt_at), t * 4 + (wave >> 2)));
-            uint32_t q = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(eq_at), t * 4 + (wave >> 2)));
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                gt[c] = e + c < dd && key_of(w[c]) > T;
-                eq[c] = e + c < dd && key_of(w[c]) == T;
-                g += lanes_below(__ballot(gt[c]));
-                q += lanes_below(__ballot(eq[c]));
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t slot = g + (q < k3 ? q : k3);
-                if ((gt[c] || (eq[c] && q < k3)) && slot < need) {
-                    prow[slot] = u32x2{static_cast<uint32_t>(e + c), __float_as_uint(w[c])};
-                    if constexpr (WR) brow[e + c] = 0.f;
-                }
-                g += gt[c] ? 1u : 0u;
-                q += eq[c] ? 1u : 0u;
-            }
-        });
+        solo_exact(sm, wave, dd, need, [&](int e) { return ld4(vrow, e, d); }, prow, brow);
     }
     if constexpr (kServer) {
-        if (x) {
-            // the entries as this workgroup has just written them, all loads in flight together
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            for (uint32_t i = tid; i < need; i += kSoloThreads) {
-                const u32x2 pr = __builtin_nontemporal_load(prow + i);
-                if (pr.x < static_cast<uint32_t>(dd)) x[pr.x] = __fmaf_rn(-gamma, __uint_as_float(pr.y), x[pr.x]);
+        if (x) solo_update(prow, need, dd, x, gamma);
+    }
+}
+
+// The same in slices of 16,384 elements, one workgroup each: a single compute unit takes about 50 GB/s, so the loads and
+// stores of a long row in one workgroup are most of its time.  Up to 16,384 elements there is one slice and the row stays
+// with its workgroup.  Otherwise every slice lists what reaches its own lower bound, chosen so that its own k largest
+// are among it, and the workgroup that arrives last takes all lists (k / slice fits the memory for them: the rule where the
+// kernel is launched) and selects from them; nobody waits.  A slice's list that holds fewer than k elements has to
+// reach below the threshold that comes out, else the row is selected over all elements.
+//
+// What bounds it is latency: of the histograms' picks (9 us for a kernel on 1000 elements), and of a sliced row's way through
+// memory and its list.  Steps, the launches it stands for against this kernel: 1 x 1000 67 and 18 us; 4 x 4096 58 and 25 us; 4 x
+// 16,384 63 and 23 us; 4 x 60,040, k = 600, 68 and 44 us (52 to 60 us with one workgroup per row); 16 x 65,536, k = 66,
+// 66 and 39 us.
+//
+// What workgroups hand to each other goes through device-scope accesses.  The error is v, stored by the slice's own workgroup
+// past its caches, but for the listed elements, which the last workgroup stores.
+constexpr int kSliceTiles = 4, kSlice = kSliceTiles * kSoloTile, kSlicesMost = static_cast<int>(kSoloMax / kSlice);
+constexpr int kDeviceScope = 16;                   // cache policy operand of the buffer instructions: past the caches of one XCD
+
+template <class Src, bool WR>
+__global__ __launch_bounds__(kSoloThreads) void k_topk_slices(Src src, float *buf, int64_t stride, int64_t d, int64_t k,
+                                                              uint32_t sample_rank, uint64_t *slots, int64_t slots_row,
+                                                              uint32_t *bound, int64_t bound_row, DevWord64 *arrived, int64_t arrived_row,
+                                                              u32x2 *pairs, float *x, float gamma)
+{
+    constexpr bool kServer = std::is_same<Src, ServerV>::value;
+    __shared__ __attribute__((aligned(16))) SoloShared sm;
+    __shared__ uint32_t counts[kSlicesMost], bounds[kSlicesMost], last;
+    const int row = blockIdx.y, slices = gridDim.x, lane = lane_id(), tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+    const int dd = static_cast<int>(d), s0 = static_cast<int>(blockIdx.x) * kSlice;
+    const int here = (dd - s0 < kSlice) ? dd - s0 : kSlice;   // elements of the slice
+    const bool one = slices == 1;
+    const uint32_t need = static_cast<uint32_t>(k);
+    u32x2 *prow = pairs + static_cast<int64_t>(row) * k;
+    float *brow = WR ? buf + row * stride : nullptr;
+    f32x4 v[kSliceTiles];
+#pragma unroll
+    for (int t = 0; t < kSliceTiles; ++t) v[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (kServer) solo_server_v<kSliceTiles, kSliceTiles>(src, s0, d, sm.strip, v);
+    else solo_row_v<kSliceTiles>(src, row, s0, dd, v);
+    for (int i = tid; i < kH1; i += kSoloThreads) sm.h[i] = 0u;
+    for (int i = tid; i < kH2; i += kSoloThreads) sm.h2[i] = 0u;
+    if (tid < kH3) sm.h3[tid] = 0u;
+    __syncthreads();
+
+    // the slice's lower bound from a quarter of its elements; to 12 bits where the list holds the whole row if need be
+    uint32_t lo = 1u;
+    if (sample_rank != 0u) {
+        auto sample = [&](auto f) {
+#pragma unroll
+            for (int t = 0; t < kSliceTiles; ++t) {
+                if (t * kSoloTile < here) {                    // uniform
+                    const int c = (lane + t) & 3;
+                    const float s = (c & 2) ? ((c & 1) ? v[t].w : v[t].z) : ((c & 1) ? v[t].y : v[t].x);
+                    if (t * kSoloTile + tid * 4 + c < here) f(key_of(s));
+                }
+            }
+        };
+        sample([&](uint32_t key) { atomicAdd(&sm.h[key >> 19], 1u); });
+        solo_pick<kH1>(sm.h, sample_rank, sm.part, sm.out);
+        const uint32_t b = sm.out[0], rem = sm.out[1];
+        if (b != kNone && one) {                               // uniform
+            if (b != 0u) lo = b << 19;
+        } else if (b != kNone) {
+            sample([&](uint32_t key) { if ((key >> 19) == b) atomicAdd(&sm.h2[(key >> 8) & (kH2 - 1)], 1u); });
+            solo_pick<kH2>(sm.h2, rem, sm.part, sm.out);
+            const uint32_t key = (b << 19) | (sm.out[0] << 8);
+            if (key != 0u) lo = key;
+        }
+    }
+    const float lo_f = __uint_as_float(lo);
+    bool f[kSliceTiles][4];
+#pragma unroll
+    for (int t = 0; t < kSliceTiles; ++t) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f[t][c] = !(fabsf(v[t][c]) < lo_f);        // zero past the end: never
+        const uint32_t n = __popcll(__ballot(f[t][0])) + __popcll(__ballot(f[t][1])) + __popcll(__ballot(f[t][2])) + __popcll(__ballot(f[t][3]));
+        if (lane == 0) sm.cnt[t * kSoloWaves + wave] = n;
+    }
+    __syncthreads();
+    static_assert(kSliceTiles * kSoloWaves == 64, "one count per lane");
+    const uint32_t mine = sm.cnt[lane], upto = wave_inclusive_scan_u32(mine);
+    uint32_t listed = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(upto), 63));
+    uint64_t *list = slots + row * slots_row + s0;             // of a sliced row, in memory
+#pragma unroll
+    for (int t = 0; t < kSliceTiles; ++t) {
+        const int at = t * kSoloTile + tid * 4;                // in the slice
+        uint32_t r = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(upto - mine), t * kSoloWaves + wave)) +
+                     lanes_below(__ballot(f[t][0])) + lanes_below(__ballot(f[t][1])) + lanes_below(__ballot(f[t][2])) + lanes_below(__ballot(f[t][3]));
+        const bool any = f[t][0] || f[t][1] || f[t][2] || f[t][3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (f[t][c]) {
+                const u32x2 pr = {static_cast<uint32_t>(s0 + at + c), __float_as_uint(v[t][c])};
+                if (one) sm.list[r] = pr;
+                else as_shared(list)[r].store(static_cast<uint64_t>(pr.x) | (static_cast<uint64_t>(pr.y) << 32));
+                ++r;
             }
         }
+        if constexpr (WR) {
+            if (one) {
+                if (at < here) st4(brow, at, d, v[t]);
+            } else if (!any && at + 4 <= here) {
+                held_st4<kDeviceScope>(brow + s0, here, t * (kSoloTile / kTile), v[t]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (at + c < here && !f[t][c])
+                        as_shared(reinterpret_cast<uint32_t *>(brow + s0))[at + c].store(__float_as_uint(v[t][c]));
+            }
+        }
+    }
+    if (!one && tid == 0) as_shared(bound + row * bound_row)[blockIdx.x].store(lo);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // stored before another thread goes on with it
+    __syncthreads();
+    if (!one) {
+        // one addition announces the slice and tells its count: 4 x 15 bits, and the arrivals above them
+        static_assert(kSlicesMost == 4 && kSlice < (1 << 15), "the counts share a word with the arrivals");
+        if (tid == 0) {
+            const uint64_t add = (1ull << 60) | (static_cast<uint64_t>(listed) << (15 * blockIdx.x));
+            const uint64_t all = arrived[row * arrived_row].fetch_add(add) + add;
+            last = (all >> 60) == static_cast<uint64_t>(slices) ? 1u : 0u;
+            if (last) arrived[row * arrived_row].store(0ull);  // for the next call
+#pragma unroll
+            for (int q = 0; q < kSlicesMost; ++q) counts[q] = static_cast<uint32_t>(all >> (15 * q)) & 0x7FFFu;
+        }
+        __syncthreads();
+        if (last == 0u) return;                                // uniform
+    }
+    const uint64_t *lists = slots + row * slots_row;
+    if (!one) {
+        listed = 0;
+        for (int q = 0; q < slices; ++q) listed += counts[q];
+        if (tid < slices) bounds[tid] = as_shared(bound + row * bound_row)[tid].load();
+        if (listed <= static_cast<uint32_t>(kSoloList)) {      // uniform
+            for (uint32_t i = tid; i < listed; i += kSoloThreads) {
+                uint32_t r = i;
+                int q = 0;
+                while (r >= counts[q]) r -= counts[q++];
+                const uint64_t w = as_shared(const_cast<uint64_t *>(lists))[q * kSlice + r].load();
+                sm.list[i] = u32x2{static_cast<uint32_t>(w), static_cast<uint32_t>(w >> 32)};
+            }
+        }
+        __syncthreads();
+    }
+    uint32_t T = 0u, k3 = 0u;
+    bool found = listed >= need && listed <= static_cast<uint32_t>(kSoloList);
+    if (found) {                                               // uniform
+        if (!one)
+            for (int q = 0; q < slices; ++q) lo = (bounds[q] < lo) ? bounds[q] : lo;
+        solo_list_threshold(sm, listed, lo, need, T, k3);
+        if (!one)
+            for (int q = 0; q < slices; ++q) found = found && (counts[q] >= need || T >= bounds[q]);
+    }
+    if (found) {
+        if (one) solo_emit<false>(sm, wave, listed, need, T, k3, prow, brow);
+        else solo_emit<true>(sm, wave, listed, need, T, k3, prow, brow);
+    } else {
+        if (WR && !one) {                                      // v of the listed elements goes where the others' is
+            for (int q = 0; q < slices; ++q)
+                for (uint32_t i = tid; i < counts[q]; i += kSoloThreads) {
+                    const uint64_t w = as_shared(const_cast<uint64_t *>(lists))[q * kSlice + i].load();
+                    as_shared(reinterpret_cast<uint32_t *>(brow))[static_cast<uint32_t>(w)].store(static_cast<uint32_t>(w >> 32));
+                }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+        if constexpr (WR)
+            solo_exact(sm, wave, dd, need, [&](int e) {
+                f32x4 w = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (e + c < dd) w[c] = __uint_as_float(as_shared(reinterpret_cast<uint32_t *>(brow))[e + c].load());
+                return w;
+            }, prow, brow);
+        else
+            solo_exact(sm, wave, dd, need, [&](int e) { return ld4(src.g + row * src.gs, e, d); }, prow, brow);
+    }
+    if constexpr (kServer) {
+        if (x) solo_update(prow, need, dd, x, gamma);
     }
 }
 
@@ -1959,10 +2200,21 @@ ds_status_t run_select(ds_ctx *c, int rows, const Src &src, float *buf, int64_t 
         return DS_ERR_DEVICE;
     }
     if (t->solo) {
-        const double part = (c->cfg.d > kSoloThinFrom) ? 0.125 : 0.25;
-        const uint32_t solo_rank = (c->cfg.d > kSoloSampleFrom) ? static_cast<uint32_t>(1.15 * part * static_cast<double>(c->cfg.k) + 32.0) : 0u;
         constexpr bool kWr = !std::is_same<Src, GradV>::value;     // = wr
-        k_topk_solo<Src, kWr><<<rows, kSoloThreads, 0, st>>>(src, buf, stride, c->cfg.d, c->cfg.k, solo_rank, pairs, x, gamma);
+        const int64_t slices = (c->cfg.d + kSlice - 1) / kSlice;
+        // rank of the bound in a sample of the share `part` of the row, with room for what a sample misses
+        auto rank = [&](double part) { return static_cast<uint32_t>(1.15 * part * static_cast<double>(c->cfg.k) + 32.0); };
+        // Slices list 1.15 k + 128 on average each, and beside the lists' room it is their number that counts: one workgroup
+        // takes them all (steps at 8 x 40,000, k = 400 and 2000, a workgroup per row 48 and 54 us, slices 38 and 58 us), and a
+        // workgroup has a compute unit to itself (200 x 60,040: 174 and 184 us; 600 x 20,000: 216 and 260 us).
+        if (slices == 1 || (slices * (c->cfg.k * 5 / 4 + 160) <= kSoloList * 3 / 8 && slices * rows <= 256)) {
+            k_topk_slices<Src, kWr><<<dim3(static_cast<unsigned>(slices), rows), kSoloThreads, 0, st>>>(
+                src, buf, stride, c->cfg.d, c->cfg.k, c->cfg.d > kSoloSampleFrom ? rank(0.25) : 0u, reinterpret_cast<uint64_t *>(t->slots),
+                t->n_reg * kReg, t->reg_cnt, t->reg_pad, as_shared(reinterpret_cast<uint64_t *>(t->done)), kStages / 2, pairs, x, gamma);
+        } else {
+            k_topk_solo<Src, kWr><<<rows, kSoloThreads, 0, st>>>(src, buf, stride, c->cfg.d, c->cfg.k,
+                                                                 rank(c->cfg.d > kSoloThinFrom ? 0.125 : 0.25), pairs, x, gamma);
+        }
         return ds_launch_status();
     }
     const int64_t d = c->cfg.d, k = c->cfg.k, n_sub = t->n_sub, n_reg = t->n_reg, reg_pad = t->reg_pad, n_groups = t->n_groups;

@@ -181,15 +181,15 @@ def test_topk_outliers_far_above_the_bulk(gpu_device):
 @pytest.mark.parametrize("d,n,k,dtype", [
     (1, 2, 1, "f32"), (3, 2, 2, "bf16"), (4, 3, 4, "f32"), (5, 1, 1, "bf16"), (4095, 3, 41, "f32"), (4096, 2, 4096, "f32"),
     (4097, 3, 40, "bf16"), (8192, 3, 82, "f32"), (8193, 3, 82, "bf16"), (16_386, 9, 2000, "f32"), (32_768, 2, 300, "bf16"),
-    (32_769, 3, 1025, "f32"), (49_151, 18, 2500, "f32"), (65_535, 3, 655, "bf16"), (65_536, 2, 65_536, "f32"),
+    (16_384, 2, 200, "f32"), (16_385, 3, 1, "bf16"), (32_769, 3, 1025, "f32"), (40_001, 4, 4100, "f32"), (61_440, 2, 3300, "bf16"), (49_151, 18, 2500, "f32"), (65_535, 3, 655, "bf16"), (65_536, 2, 65_536, "f32"),
     (65_536, 5, 66, "f32"), (65_537, 2, 655, "f32")])
 def test_topk_short_rows(gpu_device, d, n, k, dtype):
-    """One workgroup per row up to 65,536 elements: tiles of 4096, four tiles per load, strips of 32,768 on
-    the server, batches of 1024 entries, sampled from 8193 on."""
+    """Rows of up to 65,536 elements: tiles of 4096, one workgroup for every 16,384 elements or, where k is large, for the
+    row, batches of 1024 entries on the server, sampled from 4097 on."""
     _run(_wl(d, n=n, k=k, grad_dtype=dtype), gpu_device)
 
 
-@pytest.mark.parametrize("what", ["ties", "zeros", "special", "misjudged"])
+@pytest.mark.parametrize("what", ["ties", "equal", "zeros", "special", "misjudged"])
 def test_topk_short_rows_in_hard_cases(gpu_device, what):
     d, n, k = 40_003, 3, 1500
     gen = torch.Generator(device=gpu_device)
@@ -197,6 +197,8 @@ def test_topk_short_rows_in_hard_cases(gpu_device, what):
     g = torch.randn((n, d), device=gpu_device, generator=gen)
     if what == "ties":
         g = torch.sign(g) * 0.5 ** torch.randint(0, 3, (n, d), device=gpu_device, generator=gen)
+    elif what == "equal":                      # more candidates than the list holds
+        g = torch.sign(g)
     elif what == "zeros":                      # fewer than k entries that are not 0
         g = torch.where(torch.rand((n, d), device=gpu_device, generator=gen) < 0.01, g, torch.zeros_like(g))
     elif what == "special":
