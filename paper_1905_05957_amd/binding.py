@@ -99,12 +99,22 @@ def load_library():
     return L
 
 
+_fastcall = None
+
+
 def _load_fastcall():
-    try:
-        from . import _fastcall
-    except ImportError as e:
-        raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not fit this torch: build it with "
-                          "`python -m paper_1905_05957_amd.build`") from e
+    """The extension module's type and the addresses of the library's step calls."""
+    global _fastcall
+    if _fastcall is None:
+        try:
+            from ._fastcall import Calls
+        except ImportError as e:
+            raise ImportError(f"{os.path.join(_HERE, '_fastcall.so')} is missing or does not fit this torch: build it with "
+                              "`python -m paper_1905_05957_amd.build`") from e
+        L = load_library()
+        _fastcall = Calls, [C.cast(f, C.c_void_p).value for f in (
+            L.ds_worker_compress, L.ds_server_aggregate_compress, L.ds_apply_update, L.ds_decompress,
+            L.ds_server_aggregate_compress_update)]
     return _fastcall
 
 
@@ -253,11 +263,10 @@ class Context:
         self.S = sizes[1] // 4
         self.no_error_feedback = bool(int(flags) & FLAG_NO_ERROR_FEEDBACK)
         self.server_identity = bool(int(flags) & FLAG_SERVER_IDENTITY)
-        address = [C.cast(f, C.c_void_p).value for f in (L.ds_worker_compress, L.ds_server_aggregate_compress, L.ds_apply_update,
-                                                         L.ds_decompress, L.ds_server_aggregate_compress_update)]
-        self._calls = _load_fastcall().Calls(self._h.value, self.n, self.d, self.k, self.comp, self.grad_dtype == BF16,
-                                             self.no_error_feedback, self.server_identity, Payload, torch._C._cuda_getDevice,
-                                             torch._C._cuda_getCurrentRawStream, *address)
+        make_calls, address = _load_fastcall()
+        self._calls = make_calls(self._h.value, self.n, self.d, self.k, self.comp, self.grad_dtype == BF16,
+                                 self.no_error_feedback, self.server_identity, Payload, torch._C._cuda_getDevice,
+                                 torch._C._cuda_getCurrentRawStream, *address)
 
     def close(self):
         if getattr(self, "_calls", None) is not None:
