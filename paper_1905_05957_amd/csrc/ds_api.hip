@@ -380,11 +380,12 @@ ds_status_t ds_server_aggregate_compress_update(ds_ctx_t *c, uint64_t step, cons
         if (!guard.ok) return DS_ERR_DEVICE;
         return ds_rsparse_server_update(c, step, in, delta_s, out, x, m, gamma, beta, static_cast<hipStream_t>(hip_stream));
     }
-    if ((c->cfg.comp == DS_COMP_SIGN && (c->sign_fused || c->held_s.T)) || c->cfg.comp == DS_COMP_QSGD) {
+    if ((c->cfg.comp == DS_COMP_SIGN && (c->sign_fused || c->held_s.T)) || c->cfg.comp == DS_COMP_QSGD || c->cfg.comp == DS_COMP_CLIP) {
         // one pass: x (and m) are updated from the registers that hold the server's message
         DeviceGuard guard(c->device);
         if (!guard.ok) return DS_ERR_DEVICE;
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
+        if (c->cfg.comp == DS_COMP_CLIP) return ds_clip_server(c, in, delta_s, out, st, x, m, gamma, beta);
         return (c->cfg.comp == DS_COMP_SIGN) ? ds_sign_server(c, in, delta_s, out, st, x, m, gamma, beta)
                                              : ds_qsgd_server(c, step, in, delta_s, out, st, x, m, gamma, beta);
     }

@@ -148,7 +148,8 @@ int ds_clip_bytes(int bits);   // bytes per element of the message for `bits` cl
 ds_status_t ds_clip_worker(ds_ctx *c, const void *g, int64_t gs, float *delta, int64_t dstr,
                            const ds_payload_t *out, hipStream_t st);
 ds_status_t ds_clip_server(ds_ctx *c, const ds_payload_t *in, float *delta_s,
-                           const ds_payload_t *out, hipStream_t st);
+                           const ds_payload_t *out, hipStream_t st, float *x = nullptr, float *m = nullptr,
+                           float gamma = 0.f, float beta = 0.f);
 ds_status_t ds_clip_update(ds_ctx *c, const ds_payload_t *srv, float *x, float *m, float gamma,
                            float beta, hipStream_t st);
 ds_status_t ds_clip_decode(ds_ctx *c, const ds_payload_t *p, int32_t row, float *out, hipStream_t st);

@@ -44,3 +44,23 @@ def test_clip_many_workers_and_extreme_values(gpu_device):
         pair.compared_step(1, g)
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 17])
+@pytest.mark.parametrize("bits,beta", [(8, None), (16, 0.9), (24, None)])
+def test_clip_batches_of_workers_and_the_update_in_one_call(gpu_device, n, bits, beta):
+    """Partial and full batches of eight messages of every width, rows that end inside a group of four, and the model
+    updated in the server's pass: bit for bit what the two calls give, which are compared with the oracle here."""
+    wl = W.Workload(f"clip{bits}", "clip", n=n, d=2 * 2048 + 1027, clip_bits=bits, dist="normal", sigma=1e-3, gamma=0.05, beta=beta)
+    two, one = Pair(wl, gpu_device), Pair(wl, gpu_device)
+    try:
+        for t in range(2):
+            g = wl.gradients(t, gpu_device)
+            two.compared_step(t, g)
+            one.ctx.worker_compress(t, g, one.delta, one.pw)
+            one.ctx.server_aggregate_compress_update(t, one.pw, one.delta_s, one.ps, one.x, one.m, wl.gamma, beta or 0.0)
+            assert torch.equal(one.x, two.x) and torch.equal(one.delta_s, two.delta_s) and torch.equal(one.ps.levels, two.ps.levels)
+            assert one.m is None or torch.equal(one.m, two.m)
+    finally:
+        two.close()
+        one.close()
