@@ -1885,6 +1885,8 @@ __global__ __launch_bounds__(kSoloThreads) void k_topk_solo(Src src, float *buf,
             if (key != 0u) lo = key;
         }
     }
+    // a bound that is a NaN would let the zeros past the end of the row through
+    lo = (lo < 0x7F800000u) ? lo : 0x7F800000u;
     const float lo_f = __uint_as_float(lo);
     // candidates per tile and wavefront (a NaN is the largest key and a candidate)
 #pragma unroll
@@ -2005,6 +2007,8 @@ __global__ __launch_bounds__(kSoloThreads) void k_topk_slices(Src src, float *bu
             if (key != 0u) lo = key;
         }
     }
+    // a bound that is a NaN would let the zeros past the end of the row through
+    lo = (lo < 0x7F800000u) ? lo : 0x7F800000u;
     const float lo_f = __uint_as_float(lo);
     bool f[kSliceTiles][4];
 #pragma unroll

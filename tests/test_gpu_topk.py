@@ -212,3 +212,23 @@ def test_topk_short_rows_in_hard_cases(gpu_device, what):
         few = sampled & (torch.cumsum(sampled.int(), 0) <= k - 10)
         g = torch.where(few[None, :], g.abs() + 100.0, g * 1e-3)
     _run(_wl(d, n=n, k=k), gpu_device, grads=[g], steps=1 if what == "special" else 2)
+
+
+@pytest.mark.parametrize("d", [100, 4097, 10_001, 16_385, 40_003, 65_535])
+@pytest.mark.parametrize("share", [1.0, 0.5])
+def test_topk_short_rows_of_nans(gpu_device, d, share):
+    """A NaN is the largest key: a row that holds more than k of them keeps the first k, and nothing past its end."""
+    n, k = 2, max(1, d // 100)
+    g = torch.ones((n, d), device=gpu_device)
+    g[:, ::(1 if share == 1.0 else 2)] = float("nan")
+    ctx = P.Context("topk", n, d, k=k, flags=parity_util.CONTEXT_FLAGS)
+    try:
+        guard = torch.zeros(n * d + 4096, device=gpu_device)
+        delta = guard[: n * d].view(n, d)
+        msg = ctx.alloc_payload(n, gpu_device)
+        ctx.worker_compress(0, g, delta, msg)
+        want = list(range(0, k if share == 1.0 else 2 * k, 1 if share == 1.0 else 2))
+        assert msg.to_numpy()["idx"].tolist() == [want] * n
+        assert not guard[n * d:].any()
+    finally:
+        ctx.close()
