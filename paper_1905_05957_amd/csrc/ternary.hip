@@ -428,8 +428,8 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_tern_held(const void 
 // After a held launch: writes the scale of every row from the counts of its workgroups and readies the
 // synchronisation words for the next call.  In a row in which a workgroup gave up (normally none) one
 // workgroup for each of them encodes what it held, and the one that is through last adds up.
-// 8 x 11,173,962 with all waits given up: 172 us, 1259 us with one finishing workgroup for 64 of
-// the held launch.
+// 8 x 11,173,962 with all waits given up: 169 us; with one finishing workgroup for 64 of the held launch it was seven
+// times that.
 template <bool BF16>
 __global__ __launch_bounds__(kBlock) void k_tern_held_finish(const void *g, int64_t gs, int64_t d, int32_t n_tiles, uint32_t *pcnt,
                                                              const float *rowmax, const double *rowsum, TernKey K, uint64_t *neg,
