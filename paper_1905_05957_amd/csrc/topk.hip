@@ -1499,7 +1499,8 @@ __device__ __forceinline__ void solo_pick(uint32_t *h, uint32_t need, uint32_t *
 
 // v = delta_s + (1/n) sum_i Q[v_i] of the server for TILES tiles from element `first` on, as the chain over workers in
 // ascending order: strips of STRIP tiles in LDS, to which the messages are applied one worker after the other (a message
-// lists an element once).  Eight batches of 1024 entries are in flight at a time.
+// lists an element once).  Eight batches of 1024 entries are in flight at a time.  Entries that lie past the row's end, which
+// a message does not hold, are passed over: what follows relies on v being 0 there.
 template <int TILES, int STRIP>
 __device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t first, int64_t d, float *strip, f32x4 (&v)[TILES])
 {
@@ -1510,6 +1511,7 @@ __device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t first,
     for (int q = 0; q < TILES / kTilesOfStrip; ++q) {
         const int64_t base = first + static_cast<int64_t>(q) * STRIP * kSoloTile;
         if (base < d) {                                        // uniform
+            const uint32_t here = static_cast<uint32_t>((d - base < STRIP * kSoloTile) ? d - base : STRIP * kSoloTile);
             f32x4 a[kTilesOfStrip];
 #pragma unroll
             for (int t = 0; t < kTilesOfStrip; ++t) {
@@ -1544,7 +1546,7 @@ __device__ __forceinline__ void solo_server_v(const ServerV &src, int64_t first,
                     if (i >= held) break;
                     if (fresh[i]) __syncthreads();             // what the worker before has added is in
                     const uint32_t rel = pr[i].x - static_cast<uint32_t>(base);
-                    if (rel < static_cast<uint32_t>(STRIP * kSoloTile)) strip[rel] = __fmaf_rn(__uint_as_float(pr[i].y), src.inv_n, strip[rel]);
+                    if (rel < here) strip[rel] = __fmaf_rn(__uint_as_float(pr[i].y), src.inv_n, strip[rel]);
                 }
             }
             __syncthreads();

@@ -232,3 +232,35 @@ def test_topk_short_rows_of_nans(gpu_device, d, share):
         assert not guard[n * d:].any()
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("d,k", [(5000, 60), (16_389, 40), (40_003, 400), (40_003, 4100), (32_765, 3300)])
+@pytest.mark.parametrize("past", [0, 3, 15])
+def test_topk_server_passes_over_entries_past_the_end(gpu_device, d, k, past):
+    """A message whose last entry lies at d + past counts as if that entry were 0: nothing is written behind the server's
+    error or the model, and the server's message names elements of the row only."""
+    n = 3
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(d)
+    ctx = P.Context("topk", n, d, k=k, flags=parity_util.CONTEXT_FLAGS)
+    try:
+        idx = torch.stack([torch.randperm(d - 1, device=gpu_device, generator=gen)[: k - 1].sort().values for _ in range(n)])
+        val = torch.randn((n, k), device=gpu_device, generator=gen)
+        error = torch.randn(d, device=gpu_device, generator=gen).mul_(1e-2)
+        results = []
+        for last, top in ((d - 1, 0.0), (d + past, 1e3)):
+            msg, out = ctx.alloc_payload(n, gpu_device), ctx.alloc_server_payload(gpu_device)
+            msg.pairs[:, : k - 1, 0] = idx.int()
+            msg.pairs[:, k - 1, 0] = last
+            msg.pairs[:, :, 1] = torch.cat([val[:, : k - 1], torch.full((n, 1), top, device=gpu_device)], 1).view(torch.int32)
+            err, x = torch.full((d + 65_536,), 77.0, device=gpu_device), torch.full((d + 65_536,), 55.0, device=gpu_device)
+            err[:d] = error
+            ctx.server_aggregate_compress_update(0, msg, err[:d], out, x[:d], None, 0.5)
+            torch.cuda.synchronize()
+            assert torch.all(err[d:] == 77.0) and torch.all(x[d:] == 55.0)
+            assert int(out.pairs[:, :, 0].max()) < d
+            results.append((err, x, out.pairs))
+        for a, b in zip(*results):
+            assert torch.equal(a, b)
+    finally:
+        ctx.close()
