@@ -95,8 +95,10 @@ typedef enum {
  * (ds_config_t::topk_spin_limit polls).  A launch that gives up a wait raises a flag in
  * host-visible memory; see ds_status for what follows.  ds_config_t::topk_max_workgroups caps
  * the size of the single launch (fewer workgroups than rows selects the chain).
- * Vectors of up to 65,536 elements take one launch per call in which nobody waits, unless this
- * flag or one of those two limits is set.
+ * Unless this flag or one of those two limits is set, vectors of up to 65,536 elements take one
+ * launch in which nobody waits for the worker block, and one for the server block that
+ * compresses (with the update, if it is without momentum) of up to 16 workers, and of more
+ * where that is faster.
  *
  * DS_FLAG_DEFERRED_ERROR: SIGN with scale groups that span workgroups (whole vector,
  * arbitrary segments, chunks that are no multiple of 128 or exceed 2048) needs the group

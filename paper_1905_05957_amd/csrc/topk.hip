@@ -97,6 +97,7 @@ struct ds_topk_scratch {
     int64_t n_reg, reg_pad, n_groups;
     int rows;
     bool solo;            // rows are short: one launch (k_topk_slices, k_topk_solo)
+    bool solo_server;     // and the server's too
     // fused refinement route (k_topk_finish)
     uint32_t *fhist;      // [rows][kFRow], zero between calls
     char *sync;           // [rows][kSyncStride] arrival counters and published picks
@@ -2183,6 +2184,16 @@ unsigned persistent_blocks(int64_t n_tiles, int rows)
     return static_cast<unsigned>(per_row);
 }
 
+// Short rows: slices (k_topk_slices), else one workgroup per row (k_topk_solo).
+bool solo_slices(int64_t d, int64_t k, int64_t rows)
+{
+    const int64_t slices = (d + kSlice - 1) / kSlice;
+    // Slices list 1.15 k + 128 on average each, and beside the lists' room it is their number that counts: one workgroup
+    // takes them all (steps at 8 x 40,000, k = 400 and 2000, a workgroup per row 48 and 54 us, slices 38 and 58 us), and a
+    // workgroup has a compute unit to itself (200 x 60,040: 174 and 184 us; 600 x 20,000: 216 and 260 us).
+    return slices == 1 || (slices * (k * 5 / 4 + 160) <= kSoloList * 3 / 8 && slices * rows <= 256);
+}
+
 // sample -> dense pass -> refinement -> ordered emission, for `rows` vectors
 // wr = false: buf is the vector v itself, read only (no compensation: v = g), for the second look
 // of the exact route; nothing is stored into it.
@@ -2205,15 +2216,12 @@ ds_status_t run_select(ds_ctx *c, int rows, const Src &src, float *buf, int64_t 
         (void)ds_launch_status();
         return DS_ERR_DEVICE;
     }
-    if (t->solo) {
+    if (std::is_same<Src, ServerV>::value ? t->solo_server : t->solo) {
         constexpr bool kWr = !std::is_same<Src, GradV>::value;     // = wr
         const int64_t slices = (c->cfg.d + kSlice - 1) / kSlice;
         // rank of the bound in a sample of the share `part` of the row, with room for what a sample misses
         auto rank = [&](double part) { return static_cast<uint32_t>(1.15 * part * static_cast<double>(c->cfg.k) + 32.0); };
-        // Slices list 1.15 k + 128 on average each, and beside the lists' room it is their number that counts: one workgroup
-        // takes them all (steps at 8 x 40,000, k = 400 and 2000, a workgroup per row 48 and 54 us, slices 38 and 58 us), and a
-        // workgroup has a compute unit to itself (200 x 60,040: 174 and 184 us; 600 x 20,000: 216 and 260 us).
-        if (slices == 1 || (slices * (c->cfg.k * 5 / 4 + 160) <= kSoloList * 3 / 8 && slices * rows <= 256)) {
+        if (solo_slices(c->cfg.d, c->cfg.k, rows)) {
             k_topk_slices<Src, kWr><<<dim3(static_cast<unsigned>(slices), rows), kSoloThreads, 0, st>>>(
                 src, buf, stride, c->cfg.d, c->cfg.k, c->cfg.d > kSoloSampleFrom ? rank(0.25) : 0u, reinterpret_cast<uint64_t *>(t->slots),
                 t->n_reg * kReg, t->reg_cnt, t->reg_pad, as_shared(reinterpret_cast<uint64_t *>(t->done)), kStages / 2, pairs, x, gamma);
@@ -2287,6 +2295,29 @@ ds_status_t run_select(ds_ctx *c, int rows, const Src &src, float *buf, int64_t 
     return ds_launch_status();
 }
 
+// Whether the server's block of a short row is one launch.  Its workgroups go through the messages one worker after the
+// other, with a barrier for each and another round for every 1024 entries, and where a workgroup has the whole row,
+// once for every strip in LDS; the launches for long rows take the entries of 64 workers together, 64 at a time.  The model, in
+// us, follows the measured times of either (n = 1 .. 4096, d = 500 .. 65,536, k = 1 .. d / 4; server and update, one launch :
+// apart) closely enough to choose:
+//   n = 64, d = 1000, k = 1 24.4 : 30.0, k = 100 25.4 : 141; d = 40,000, k = 1 35.6 : 33.0, k = 400 36.4 : 50.3;
+//   n = 64, d = 65,536, k = 6553 274 : 245; n = 256, d = 16,000, k = 16 74 : 44, k = 160 75.5 : 90.9, k = 1600 160 : 575;
+//   n = 1024, d = 4096, k = 4 259 : 78, k = 409 294 : 1949; d = 60,040, k = 600 319 : 277; k = 6004 3608 : 2459;
+//   n = 4096, d = 1000, k = 1 1001 : 178, k = 100 1018 : 7227.
+// Up to 16 workers it is always the one launch (n = 8: 11 .. 64 us, apart 32 .. 322 us).
+bool solo_for_server(int64_t n, int64_t d, int64_t k)
+{
+    if (n <= 16) return true;
+    const bool sliced = solo_slices(d, k, 1);
+    const double dn = static_cast<double>(n), dk = static_cast<double>(k);
+    const double dd = static_cast<double>(d < 1024 ? 1024 : d);        // a wavefront takes 1024 elements
+    const double strips = sliced ? 1.0 : static_cast<double>((d + kSoloStrip - 1) / kSoloStrip);
+    const double rounds = static_cast<double>((k + kSoloThreads - 1) / kSoloThreads);
+    const double one = (!sliced ? 40.0 : d > kSlice ? 21.0 : d > kSoloTile ? 12.0 : 9.0) + dn * strips * (0.04 + 0.2 * rounds + 0.08 * dk / kSoloThreads);
+    const double apart = (k > kSoloThreads ? 100.0 : 30.0) + dn * (0.035 + (d > 2 * kSoloTile ? 22.0 : 16.0) * dk / dd);
+    return one <= apart;
+}
+
 }  // namespace
 
 ds_status_t ds_topk_init(ds_ctx *c)
@@ -2300,6 +2331,7 @@ ds_status_t ds_topk_init(ds_ctx *c)
     // A context that states limits of the single launch asks for that route.
     t->solo = c->cfg.d <= kSoloMax && !(c->cfg.flags & DS_FLAG_TOPK_MULTI_LAUNCH) && c->cfg.topk_max_workgroups == 0 &&
               c->cfg.topk_spin_limit == 0;
+    t->solo_server = t->solo && solo_for_server(c->cfg.n, c->cfg.d, c->cfg.k);
     t->n_sub = (c->cfg.d + kSub - 1) / kSub;
     t->n_reg = c->n_tiles;
     t->n_groups = (t->n_reg + kGroupRegs - 1) / kGroupRegs;
@@ -2412,7 +2444,7 @@ ds_status_t ds_topk_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
     ds_topk_scratch *t = c->topk;
     const u32x2 *pairs_in = reinterpret_cast<const u32x2 *>(in->pairs);
     const int64_t k = c->cfg.k;
-    if (!t->solo) build_sub_starts(c, pairs_in, st);
+    if (!t->solo_server) build_sub_starts(c, pairs_in, st);
     const ServerV src{pairs_in, t->sub_start, delta_s, k, t->n_sub, c->cfg.n, c->inv_n};
     return run_select(c, 1, src, delta_s, c->cfg.d, reinterpret_cast<u32x2 *>(out->pairs), st, t->prev_T + t->rows, x, gamma);
 }

@@ -3,8 +3,8 @@
 // memory, a clear is carried out when something waits for the default stream, as late as the
 // runtime may do it, and a launch is written down instead of carried out.  Called by test_create_cpu.py:
 //   create_check           ds_create and ds_destroy; one line per check, exit status 0 if all hold
-//   create_check launches  reads "block comp n d dtype flags" lines (block w: worker, s: server and update in one
-//                          call) and prints the launches of that call: name and grid, one line each, then a dot
+//   create_check launches  reads "block comp n d dtype flags [k]" lines (block w: worker, s: server and update in one
+//                          call; k: top-k entries, else d / 100 + 1) and prints the launches of that call: name and grid, one line each, then a dot
 #include "../include/ds.h"
 
 #include <cstdio>
@@ -157,9 +157,13 @@ int launches()
 {
     char block;
     int comp, n, dtype, flags;
-    long long d;
-    while (scanf(" %c %d %d %lld %d %d", &block, &comp, &n, &d, &dtype, &flags) == 6) {
+    long long d, k;
+    char line[256];
+    while (fgets(line, sizeof line, stdin)) {
+        const int fields = sscanf(line, " %c %d %d %lld %d %d %lld", &block, &comp, &n, &d, &dtype, &flags, &k);
+        if (fields < 6) return 1;
         ds_config_t cfg = config(comp, n, d, flags);
+        if (fields == 7) cfg.k = k;
         cfg.grad_dtype = dtype;
         ds_ctx_t *c = nullptr;
         if (ds_create(&cfg, &c) != DS_OK) return 1;

@@ -11,7 +11,7 @@ import held_shapes as H
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.join(os.path.dirname(HERE), "paper_1905_05957_amd")
-SIGN, TERNARY = 1, 6
+SIGN, TOPK, TERNARY = 1, 2, 6
 RMS, NOFB_SID = 4, 8 | 16
 
 
@@ -89,3 +89,21 @@ def test_every_size_is_listed(program):
     assert {t for *_, t, w in H.SIGN_WORKER if w == 1} == {1, 2, 4, 8, 14}
     assert {t for *_, t, w in H.SIGN_SERVER if w == 1} == {1, 2, 4}
     assert {t for *_, t, w in H.TERNARY if w == 1} == {1, 2, 4}
+
+
+@pytest.mark.parametrize("n,d,k,one", [
+    (1, 65_536, 1, True), (16, 65_536, 6553, True), (16, 1000, 1, True), (64, 1000, 1, True), (64, 65_536, 1, False), (64, 40_000, 400, True),
+    (64, 65_536, 6553, False), (256, 4096, 4, False), (256, 16_000, 16, False), (256, 16_000, 160, True), (256, 16_000, 1600, True),
+    (1024, 1000, 1, False), (1024, 1000, 100, True), (1024, 60_040, 600, False), (1024, 65_536, 6553, False), (4096, 16_000, 16, False),
+    (4096, 16_000, 1600, True), (8, 65_537, 655, False)])
+def test_short_topk_rows_of_many_workers(program, n, d, k, one):
+    """The worker block of a short row is one launch whatever the number of workers; the server's is where that is the
+    faster way, and keeps to the launches of long rows where many messages hold few entries, or very many."""
+    worker, server = _launches(program, [("w", TOPK, n, d, 0, 0, k), ("s", TOPK, n, d, 0, 0, k)])
+    short = [name for name, _, _ in worker if "k_topk_slices" in name or "k_topk_solo" in name]
+    assert len(short) == (len(worker) if d <= 65_536 else 0), worker
+    kernels = [name for name, _, _ in server if "k_topk_dense_apply" not in name]       # that one is the update
+    if one:
+        assert len(kernels) == 1 and ("k_topk_slices" in kernels[0] or "k_topk_solo" in kernels[0]), server
+    else:
+        assert "k_topk_sub_starts" in kernels[0] and not any("k_topk_slices" in name or "k_topk_solo" in name for name in kernels), server

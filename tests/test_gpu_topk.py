@@ -264,3 +264,10 @@ def test_topk_server_passes_over_entries_past_the_end(gpu_device, d, k, past):
             assert torch.equal(a, b)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("n,d,k", [(63, 5000, 2), (64, 40_003, 3), (70, 4097, 41), (200, 16_385, 5), (300, 1000, 1), (130, 33_000, 3400)])
+def test_topk_short_rows_of_many_workers(gpu_device, n, d, k):
+    """Either way of the server, beside the one launch of the worker block: both leave the context's scratch memory as
+    the other expects it."""
+    _run(_wl(d, n=n, k=k), gpu_device, steps=3)
