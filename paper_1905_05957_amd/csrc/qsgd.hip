@@ -17,6 +17,8 @@
 #include "ds_device.h"
 #include "ds_internal.h"
 
+#include <type_traits>
+
 using namespace ds;
 
 namespace {
@@ -203,13 +205,19 @@ __device__ __forceinline__ f32x4 chain4(f32x4 a, uint32_t codes, uint32_t bits, 
 // SID: the server does not compress: the average is written to dense_out (if not null) and / or
 // applied to x, m (if x is not null), and nothing else happens.
 //
-// Every thread loads its own 16 bits of codes and its byte of sign bits, of eight workers at a time.  (Fetched for several
-// workers by one instruction and handed out by lane exchanges, as it was before, their index arithmetic cost more than
-// the decoding: 190 and 147 us at 16 x 25.6 M, bound by vector issue, and whole steps of 17 shapes 1.00 to 1.07 times as
-// fast but for 16 x 1,000,003, 47.0 and 48.4 us.  Eight elements per thread, which halves the loads but has the
-// average change hands through LDS before it is quantised: 148 us, and slower below 5 M elements.)
-template <int UPD, bool SID>
-__global__ __launch_bounds__(kBlock, 8) void k_qsgd_server(const uint8_t *levels_in, const uint64_t *words_in,
+// Two ways to the messages of the wavefront's 256 elements, 128 bytes of codes and 32 bytes of sign bits per worker, eight
+// workers at a time.
+// EXCHANGE: one 32-bit load fetches the sign words of all eight (lane L: word L & 7 of worker L >> 3) and four 32-bit loads
+// fetch the codes of two workers each (lane L: word L & 31 of worker L >> 5); ds_bpermute hands every lane its own.
+// Else every thread loads its own 16 bits of codes and its byte of sign bits: sixteen loads instead of five, but without
+// the exchange's index arithmetic, which costs more than the decoding, and in few enough registers for eight wavefronts per
+// SIMD.  The exchange is ahead where latency counts, the other where vector issue does (qsgd_exchange).  Server block alone,
+// exchange : else, 8 x 20,001 4.8 : 5.3 us, 64 x 20,001 13.6 : 20.9 us, 16 x 1,000,003 9.0 : 10.2 us, 8 x 10 M 40.1 : 36.8 us,
+// 16 x 25.6 M 126 : 116 us; with the update through momentum 16 x 3,000,001 29.5 : 25.7 us, 16 x 25.6 M 187 : 155 us.
+// (Eight elements per thread, which halves the loads but has the average change hands through LDS before it is quantised,
+// was behind both below 5 M elements.)
+template <int UPD, bool SID, bool EXCHANGE>
+__global__ __launch_bounds__(kBlock, EXCHANGE ? 4 : 8) void k_qsgd_server(const uint8_t *levels_in, const uint64_t *words_in,
                                                            const float *norms_in, int n, float inv_n, float *delta_s,
                                                            QParams P, uint8_t *levels_out, uint64_t *words_out,
                                                            float *norms_out, float *x, float *m, float gamma, float beta,
@@ -241,7 +249,9 @@ __global__ __launch_bounds__(kBlock, 8) void k_qsgd_server(const uint8_t *levels
             }
         }
     };
-    if (whole) fetch(0, n);
+    if (!EXCHANGE && whole) fetch(0, n);
+    const int lane = lane_id();
+    const int64_t wave_first = tile_base + wave_id() * 256;
     f32x4 xv = {0.f, 0.f, 0.f, 0.f}, mv = {0.f, 0.f, 0.f, 0.f};      // fetched up front, beside the error
     if constexpr (UPD != 0) xv = ld4_stream(x, e, P.d);
     if constexpr (UPD == 2) mv = ld4_stream(m, e, P.d);
@@ -254,7 +264,29 @@ __global__ __launch_bounds__(kBlock, 8) void k_qsgd_server(const uint8_t *levels
             units[t] = (B < P.Bq) ? __fdiv_rn(norms_in[(i0 + i) * P.Bq + B], static_cast<float>(P.s)) : 0.f;
         }
         __syncthreads();
-        if (whole) {
+        if (EXCHANGE && wave_first + 256 <= P.d) {
+            for (int j0 = 0; j0 < cnt; j0 += 8) {
+                const int nb = (cnt - j0 < 8) ? cnt - j0 : 8;
+                uint32_t sw = 0u;
+                if ((lane >> 3) < nb)
+                    sw = reinterpret_cast<const uint32_t *>(words_in + (i0 + j0 + (lane >> 3)) * P.W)[(wave_first >> 5) + (lane & 7)];
+                uint32_t cw[4];
+#pragma unroll
+                for (int p2 = 0; p2 < 4; ++p2) {
+                    const int wk = 2 * p2 + (lane >> 5);
+                    cw[p2] = 0u;
+                    if (wk < nb)
+                        cw[p2] = reinterpret_cast<const u32_byte *>(levels_in + (i0 + j0 + wk) * lev_stride + (wave_first >> 1))[lane & 31];
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (j >= nb) break;                      // uniform
+                    const uint32_t sb = __shfl(sw, j * 8 + (lane >> 3), 64) >> (4 * (lane & 7));
+                    const uint32_t c32 = __shfl(cw[j >> 1], (j & 1) * 32 + (lane >> 1), 64);
+                    a = chain4(a, c32 >> (16 * (lane & 1)), sb, units[(j0 + j) * bpt + my_b], inv_n);
+                }
+            }
+        } else if (!EXCHANGE && whole) {
             for (int j0 = 0; j0 < cnt; j0 += 8) {
                 if (i0 + j0 > 0) fetch(i0 + j0, cnt - j0);
 #pragma unroll
@@ -316,6 +348,20 @@ QParams make_params(const ds_ctx *c, uint64_t step)
     return P;
 }
 
+// Whether the server's block exchanges the messages between lanes.  Measured at n = 1 .. 128 and d = 20,001 .. 25.6 M, odd
+// lengths and even; the time without the exchange over that with it:
+//  * n up to 8: 0.99 .. 1.11 up to 1 M elements, 0.79 .. 1.05 from 1.5 M on;
+//  * n = 9 .. 16: 1.01 .. 1.22 up to 1 M; at 1.5 M 1.03 .. 1.09, from 2 M on 0.87 .. 1.07;
+//  * n = 17 .. 32: 1.08 .. 1.37 up to 1.5 M, 0.95 .. 1.09 at 2 .. 2.5 M, 0.92 .. 1.04 beyond;
+//  * more: 1.29 .. 1.61 up to 1.5 M and 0.93 .. 1.20 beyond;
+//  * with momentum, n up to 32: 0.79 .. 0.94 from 1.5 M on; more: 1.10 .. 1.13 at 1.5 M, 0.85 .. 1.09 beyond.
+bool qsgd_exchange(const ds_ctx *c, bool momentum)
+{
+    const int32_t n = c->cfg.n;
+    if (n > 32) return !momentum || c->n_tiles <= 1024;
+    return c->n_tiles <= ((n <= 8 || momentum) ? 512 : n <= 16 ? 768 : 1280);
+}
+
 }  // namespace
 
 ds_status_t ds_qsgd_worker(ds_ctx *c, uint64_t step, const void *g, int64_t gs, float *delta, int64_t dstr,
@@ -341,16 +387,18 @@ ds_status_t ds_qsgd_server(ds_ctx *c, uint64_t step, const ds_payload_t *in, flo
 {
     if (!bucket_ok(c->cfg.bucket)) return DS_ERR_UNSUPPORTED;
     const QParams P = make_params(c, step);
-    const unsigned blocks = static_cast<unsigned>(c->n_tiles);
-    if (!x)
-        k_qsgd_server<0, false><<<blocks, kBlock, 0, st>>>(in->levels, in->sign_words, in->scales, c->cfg.n, c->inv_n, delta_s, P,
-                                                           out->levels, out->sign_words, out->scales, x, m, gamma, beta, nullptr);
-    else if (!m)
-        k_qsgd_server<1, false><<<blocks, kBlock, 0, st>>>(in->levels, in->sign_words, in->scales, c->cfg.n, c->inv_n, delta_s, P,
-                                                           out->levels, out->sign_words, out->scales, x, m, gamma, beta, nullptr);
-    else
-        k_qsgd_server<2, false><<<blocks, kBlock, 0, st>>>(in->levels, in->sign_words, in->scales, c->cfg.n, c->inv_n, delta_s, P,
-                                                           out->levels, out->sign_words, out->scales, x, m, gamma, beta, nullptr);
+    auto go = [&](auto upd, auto exchange) {
+        k_qsgd_server<decltype(upd)::value, false, decltype(exchange)::value><<<static_cast<unsigned>(c->n_tiles), kBlock, 0, st>>>(
+            in->levels, in->sign_words, in->scales, c->cfg.n, c->inv_n, delta_s, P, out->levels, out->sign_words, out->scales, x, m,
+            gamma, beta, nullptr);
+    };
+    auto with_upd = [&](auto exchange) {
+        if (!x) go(std::integral_constant<int, 0>{}, exchange);
+        else if (!m) go(std::integral_constant<int, 1>{}, exchange);
+        else go(std::integral_constant<int, 2>{}, exchange);
+    };
+    if (qsgd_exchange(c, m != nullptr)) with_upd(std::true_type{});
+    else with_upd(std::false_type{});
     return ds_launch_status();
 }
 
@@ -358,9 +406,13 @@ ds_status_t ds_qsgd_server_identity(ds_ctx *c, const ds_payload_t *in, float *de
 {
     if (!bucket_ok(c->cfg.bucket)) return DS_ERR_UNSUPPORTED;
     const QParams P = make_params(c, 0);
-    k_qsgd_server<0, true><<<static_cast<unsigned>(c->n_tiles), kBlock, 0, st>>>(
-        in->levels, in->sign_words, in->scales, c->cfg.n, c->inv_n, nullptr, P, nullptr, nullptr, nullptr, u.x, u.m, u.gamma,
-        u.beta, dense_out);
+    auto go = [&](auto exchange) {
+        k_qsgd_server<0, true, decltype(exchange)::value><<<static_cast<unsigned>(c->n_tiles), kBlock, 0, st>>>(
+            in->levels, in->sign_words, in->scales, c->cfg.n, c->inv_n, nullptr, P, nullptr, nullptr, nullptr, u.x, u.m, u.gamma,
+            u.beta, dense_out);
+    };
+    if (qsgd_exchange(c, u.m != nullptr)) go(std::true_type{});
+    else go(std::false_type{});
     return ds_launch_status();
 }
 

@@ -4,7 +4,7 @@
 // runtime may do it, and a launch is written down instead of carried out.  Called by test_create_cpu.py:
 //   create_check           ds_create and ds_destroy; one line per check, exit status 0 if all hold
 //   create_check launches  reads "block comp n d dtype flags [k]" lines (block w: worker, s: server and update in one
-//                          call; k: top-k entries, else d / 100 + 1) and prints the launches of that call: name and grid, one line each, then a dot
+//                          call, p: the same without momentum; k: top-k entries, else d / 100 + 1) and prints the launches of that call: name and grid, one line each, then a dot
 #include "../include/ds.h"
 
 #include <cstdio>
@@ -177,7 +177,7 @@ int launches()
         p.dense = reinterpret_cast<float *>(any);
         float *f = reinterpret_cast<float *>(any);
         const ds_status_t rc = block == 'w' ? ds_worker_compress(c, 0, any, d, f, d, &p, nullptr)
-                                            : ds_server_aggregate_compress_update(c, 0, &p, f, &p, f, f, 0.1f, 0.9f, nullptr);
+                                            : ds_server_aggregate_compress_update(c, 0, &p, f, &p, f, block == 's' ? f : nullptr, 0.1f, 0.9f, nullptr);
         printf(rc == DS_OK ? ".\n" : "failed\n");
         ds_destroy(c);
     }

@@ -62,3 +62,23 @@ def test_qsgd_bf16_momentum_and_zero_bucket(gpu_device):
         pair.compared_step(1, g)
     finally:
         pair.close()
+
+
+# Servers on both sides of the choice of how the messages reach a lane (512, 768 and 1280 tiles), partial and full
+# batches of eight workers, more than are staged at a time, rows that end inside a group of four.
+@pytest.mark.parametrize("n,d,beta", [(1, 512 * 2048 + 3, None), (3, 512 * 2048 - 1, 0.9), (8, 512 * 2048 + 2, 0.9), (9, 512 * 2048 + 5, None),
+                                      (9, 768 * 2048 + 6, None), (17, 4099, 0.9), (65, 2050, None), (70, 6145, 0.9)])
+def test_qsgd_servers_of_either_way(gpu_device, n, d, beta):
+    wl = _wl(d, n=n, beta=beta)
+    two, one = Pair(wl, gpu_device), Pair(wl, gpu_device)
+    try:
+        for t in range(2):
+            g = wl.gradients(t, gpu_device)
+            two.compared_step(t, g)
+            one.ctx.worker_compress(t, g, one.delta, one.pw)
+            one.ctx.server_aggregate_compress_update(t, one.pw, one.delta_s, one.ps, one.x, one.m, wl.gamma, beta or 0.0)
+            assert torch.equal(one.x, two.x) and torch.equal(one.delta_s, two.delta_s) and torch.equal(one.ps.levels, two.ps.levels)
+            assert one.m is None or torch.equal(one.m, two.m)
+    finally:
+        two.close()
+        one.close()
