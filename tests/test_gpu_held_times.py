@@ -126,3 +126,15 @@ def test_ternary_times_follow_the_work(gpu_device, less, more, factor):
         us.append(best_us(lambda: ctx.worker_compress(0, g, None, msg), 20))
         ctx.close()
     assert us[0] < factor * us[1], us
+
+
+@pytest.mark.parametrize("d", [5000, 2_500_001])
+def test_a_ternary_server_of_one_worker_costs_what_the_decoder_costs(gpu_device, d):
+    """Both read one message and write it out."""
+    ctx = P.Context("ternary", 1, d, flags=NOFB_SID)
+    msg, out, dense = ctx.alloc_payload(1, gpu_device), ctx.alloc_server_payload(gpu_device), torch.empty(d, device=gpu_device)
+    ctx.worker_compress(0, torch.randn((1, d), device=gpu_device), None, msg)
+    server = best_us(lambda: ctx.server_aggregate_compress(0, msg, None, out), 50)
+    decoder = best_us(lambda: ctx.decompress(msg, 0, dense), 50)
+    ctx.close()
+    assert server < 1.12 * decoder, (server, decoder)
