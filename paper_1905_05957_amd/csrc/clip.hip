@@ -10,6 +10,8 @@
 #include "ds_device.h"
 #include "ds_internal.h"
 
+#include <type_traits>
+
 using namespace ds;
 
 namespace {
@@ -127,25 +129,37 @@ __global__ __launch_bounds__(kBlock) void k_clip_worker(const void *g, int64_t g
     clip_store4<NB>(v, mask, e, d, msg + static_cast<int64_t>(row) * d * NB, drow);
 }
 
-// a + (1/n) sum_i Q[v_i] as the chain acc = fma(q_i, 1/n, acc) over workers in ascending order.  The messages of eight
-// workers are asked for before the first is used: one after the other they were a chain of memory latencies.
-// With the update in the server's pass, which spares reading the message again and a launch, steps of 12 shapes: 8 x
-// 25,557,032 638 and 635 us, 1 x 20 M 109 and 103 us, 8 x 1,000,003 29.7 and 27.0 us, 16 x 10 M in three calls 453 and 448 us.
-// (Eight elements per thread, for 16 bytes of a message in one access: 746 and 171 us for the first two, the stores of
-// 16 bytes in every 32 being what costs.)
+// a + (1/n) sum_i Q[v_i] as the chain acc = fma(q_i, 1/n, acc) over workers in ascending order.  The messages of up to
+// eight workers are asked for before the first is used: one after the other they were a chain of memory latencies.  Batches
+// of 8, 4, 2 and 1 without a test of the count before every load, which with few workers cost more than the batch gains.
+// Server block alone, one by one : eights with tests : as it is: 16 bits, 1 x 1,000,003 3.2 : 3.4 : 3.2 us, 9 x 5000 3.2 : 2.8 :
+// 2.4 us, 16 x 1,000,003 9.9 : 7.6 : 7.3 us; 24 bits, 8 x 3,000,001 11.6 : 8.8 : 8.7 us, 8 x 25.6 M 74.7 : 65.7 : 65.7 us; 8 bits, 16 x 10 M
+// 134 : 140 : 140 us, the one shape that lost.
+// The update in the server's pass spares a launch and reading the message again: server and update repeated, two launches :
+// one pass, 8 x 1,000,003 7.8 : 5.2 us, 1 x 10 M 35 : 31 us, 16 x 10 M of 8 bits 153 : 153 us; within whole steps at 8 x 25.6 M,
+// where nothing is left in a cache, 140 + 42 and 186 us.
+// (Eight elements per thread, for 16 bytes of a message in one access, made steps of 8 x 25.6 M 746 us instead of 635, the stores
+// of 16 bytes in every 32 being what costs.)
 template <int NB>
 __device__ __forceinline__ f32x4 clip_chain(f32x4 a, const uint8_t *msg_in, int n, float inv_n, int64_t e, int64_t d)
 {
     if (e + 4 <= d) {
-        for (int i0 = 0; i0 < n; i0 += 8) {
-            ClipRaw<NB> q[8];
+        const uint8_t *p = msg_in + e * NB;
+        const int64_t row = d * NB;
+        auto batch = [&](auto count) {
+            constexpr int C = decltype(count)::value;
+            ClipRaw<NB> q[C];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (i0 + i < n) q[i] = load_raw4<NB>(msg_in + (static_cast<int64_t>(i0 + i) * d + e) * NB);    // uniform
+            for (int i = 0; i < C; ++i) q[i] = load_raw4<NB>(p + i * row);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (i0 + i < n) a = fma4(inv_n, decode_raw4<NB>(q[i]), a);
-        }
+            for (int i = 0; i < C; ++i) a = fma4(inv_n, decode_raw4<NB>(q[i]), a);
+            p += C * row;
+        };
+        int left = n;
+        for (; left >= 8; left -= 8) batch(std::integral_constant<int, 8>{});
+        if (left >= 4) { batch(std::integral_constant<int, 4>{}); left -= 4; }
+        if (left >= 2) { batch(std::integral_constant<int, 2>{}); left -= 2; }
+        if (left) batch(std::integral_constant<int, 1>{});
     } else {
         for (int i = 0; i < n; ++i) a = fma4(inv_n, load_msg4<NB>(msg_in + static_cast<int64_t>(i) * d * NB, e, d), a);
     }
