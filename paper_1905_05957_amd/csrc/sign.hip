@@ -523,7 +523,8 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t strid
 // A workgroup keeps v of T consecutive tiles in registers and LDS, hands their sums over, waits for
 // the row's scale and stores delta' = v - Q[v]: the row is read once and written once, where pass 1
 // / reduce / pass 2 move v through memory twice more.  The workgroup whose arrival completes the
-// row adds the sums up and publishes the scale.
+// row adds the sums up and publishes the scale.  The sums are of tiles and are added in the order of k_sign_reduce: a
+// scale does not depend on the route, nor on how many tiles a workgroup holds.
 //
 // The host takes this route when the device holds all workgroups of a row at once, and they are
 // dispatched in row order, so a wait normally lasts as long as the rest of the row takes to load.
@@ -536,46 +537,94 @@ __global__ __launch_bounds__(kBlock) void k_sign_pass2(float *buf, int64_t strid
 // (T = 14), 213 us with 2.25 (T = 24), at 171 us for its bytes at the copy kernel's rate and 286 us
 // in two looks.  7 x 2,345,679, all rows resident: 35 us against 62 us in two looks (31 us for its
 // bytes; both with the finish launch, 4.8 us).  With all errors of a workgroup loaded up front and the gradients in groups of three the
-// first took 220 us, with D = 4 and 6 tiles in flight instead of 3 213 and 214 us.  With a sum over the
-// wavefront, which is twenty instructions, for every tile instead of once: steps of 8 x 11,173,962 264 and 259 us,
-// bf16 249 and 239 us, 4 x 24,000,000 326 and 315 us.
+// first took 220 us, with D = 4 and 6 tiles in flight instead of 3 213 and 214 us.
+// The tiles' sums cost issue.  Worker call at 8 x 11,173,962 in bf16, at 8 x 24,000,000 in f32 and in bf16, and server and update of
+// 24,000,000: a wave_sum for every tile 200, 461, 412 and 72.9 us; four tiles together (HeldSums), and the last workgroup adding
+// up twelve at a time instead of eight in the largest size, 196, 459, 405 and 69.8 us; eight together nothing more.  One
+// sum per thread over all its tiles, whose order would depend on their number, 191, 444, 389 and 66.7 us.
 //
-// What a workgroup of the held route shares: the wavefronts' sums and per tile the sign words.
+// What a workgroup of the held route shares: per tile the wavefronts' sums and the sign words.
 template <int T>
 struct HeldShared {
-    double sums[kWaves], red[kWaves];
+    double sums[T][kWaves], red[kWaves];
     __attribute__((aligned(16))) uint32_t words[T][kWaves * 8];
     uint32_t sh[2];
 };
 
-template <bool RMS, int T>
-__device__ __forceinline__ void held_look(f32x4 v, int t, HeldShared<T> &m, double &sum)
+// Two tiles' values of a step of wave_sum in one: lanes with `second` go on with y, the others with x, each with the two
+// numbers that wave_sum adds.  CTRL leads to a lane with the other choice.
+template <int CTRL>
+__device__ __forceinline__ double two_sums(double x, double y, bool second)
 {
-    stash_sign_words(m.words[t], wave_sign_word(v.x < 0.f, v.y < 0.f, v.z < 0.f, v.w < 0.f));
-    sum += abs_sum4<RMS>(v);
-    asm volatile("" : "+v"(sum));             // now: put off, the sums of all tiles would keep their values in registers
+    return (second ? y : x) + dpp_f64<CTRL>(second ? x : y);
 }
 
-// After every tile was looked at: sign words and the sum out, the arrival, the row's scale (true) or
-// no scale in time (false).  `sum`: the thread's own elements; it goes over the wavefront and the workgroup once, and one
-// sum per workgroup is handed over.
+// wave_sum of up to four tiles together.  After two steps lane i has that of tile (bit 0 ^ bit 2) + 2 (bit 1 ^ bit 2) of i, which the
+// lanes that the mirrors pair have in common, and lanes 0 .. 3 have the four in order.
+struct HeldSums {
+    double one, pair;
+};
+
+template <bool RMS, int Q, int L, int T>
+__device__ __forceinline__ void held_look(f32x4 v, int t, HeldShared<T> &m, HeldSums &h)
+{
+    stash_sign_words(m.words[t], wave_sign_word(v.x < 0.f, v.y < 0.f, v.z < 0.f, v.w < 0.f));
+    const int lane = lane_id();
+    const bool odd = ((lane ^ (lane >> 2)) & 1) != 0, upper = ((lane ^ (lane >> 1)) & 2) != 0;
+    double s = abs_sum4<RMS>(v);
+    constexpr int at = Q & 3, count = (Q == T - 1 && at != 3) ? at + 1 : 4;       // of the group that is complete with this tile
+    static_assert(count != 3, "no size leaves three");
+    if constexpr (at == 0 && count != 1) {
+        h.one = s;
+        asm volatile("" : "+v"(h.one));       // now: put off, the sums of all tiles would keep their values in registers
+    } else if constexpr (at == 1 && count != 2) {
+        h.pair = two_sums<kDppXor1>(h.one, s, odd);
+        asm volatile("" : "+v"(h.pair));
+    } else if constexpr (at == 2) {
+        h.one = s;
+        asm volatile("" : "+v"(h.one));
+    } else {
+        if constexpr (count == 1) {
+            s += dpp_f64<kDppXor1>(s);
+            s += dpp_f64<kDppXor2>(s);
+        } else if constexpr (count == 2) {
+            s = two_sums<kDppXor1>(h.one, s, odd);
+            s += dpp_f64<kDppXor2>(s);
+        } else {
+            s = two_sums<kDppXor2>(h.pair, two_sums<kDppXor1>(h.one, s, odd), upper);
+        }
+        s += dpp_f64<kDppHalfMirror>(s);
+        s += dpp_f64<kDppRowMirror>(s);
+        s = pair_row_sum<16>(s);
+        s = pair_row_sum<32>(s);
+        if (lane < count) {
+            const int q = Q - at + lane;
+            m.sums[q < L ? T - L + q : q - L][wave_id()] = s;
+        }
+    }
+}
+
+// After every tile was looked at: sign words and sums out, the arrival, the row's scale (true) or
+// no scale in time (false).
 template <bool RMS, int T>
-__device__ __forceinline__ bool held_scale(HeldShared<T> &m, double sum, int64_t tile0, int row, uint64_t *__restrict__ words_row,
+__device__ __forceinline__ bool held_scale(HeldShared<T> &m, int64_t tile0, int row, uint64_t *__restrict__ words_row,
                                            const ds_sign_tables &tb, double *partial_row, float *scale_out, HeldRow *rows,
                                            uint32_t patience, float *s)
 {
-    sum = wave_sum(sum);
-    if (lane_id() == 0) m.sums[wave_id()] = sum;
     __syncthreads();
     const int64_t bit_lim = ((tb.whole_d + 63) / 64) * 64;
     const double len = static_cast<double>(tb.whole_d);
-    sum = m.sums[0];
+    // lane t < T of every wavefront: sum of tile t (zero past the end of the row)
+    double tile_sum = 0.0;
+    if (lane_id() < T) {
+        tile_sum = m.sums[lane_id()][0];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) sum += m.sums[w];
+        for (int w = 1; w < kWaves; ++w) tile_sum += m.sums[lane_id()][w];
+    }
     if (gridDim.x != 1 && wave_id() == 0) {
-        if (lane_id() == 0)
-            as_shared(reinterpret_cast<uint64_t *>(partial_row))[blockIdx.x].store(__double_as_longlong(sum));
-        // the sum is in memory before the arrival is announced
+        if (lane_id() < T && tile0 + lane_id() < tb.n_pieces)
+            as_shared(reinterpret_cast<uint64_t *>(partial_row))[tile0 + lane_id()].store(__double_as_longlong(tile_sum));
+        // the sums are in memory before the arrival is announced
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (lane_id() == 0) m.sh[0] = (rows[row].arrived.fetch_add(1u) + 1u == gridDim.x) ? 1u : 0u;
     }
@@ -583,7 +632,7 @@ __device__ __forceinline__ bool held_scale(HeldShared<T> &m, double sum, int64_t
     const int t16 = threadIdx.x >> 4;
     if (t16 < T) flush_sign_words_at(m.words[t16], words_row, (tile0 + t16) * kTile, bit_lim, threadIdx.x & 15);
     if (gridDim.x == 1) {                                    // the row is this workgroup's
-        *s = group_scale(sum, len, RMS);
+        *s = group_scale(wave_sum(tile_sum), len, RMS);
         if (threadIdx.x == 0) *scale_out = *s;
         return true;
     }
@@ -591,9 +640,18 @@ __device__ __forceinline__ bool held_scale(HeldShared<T> &m, double sum, int64_t
     const bool last = m.sh[0] != 0u;
     __syncthreads();
     if (!last) return held_wait(rows, row, patience, m.sh, s);
+    constexpr int B = T > 16 ? 12 : 8;                       // in flight; what the registers beside the held tiles allow
     double acc = 0.0;
-    for (uint32_t p = threadIdx.x; p < gridDim.x; p += kBlock)
-        acc += __longlong_as_double(static_cast<long long>(as_shared(reinterpret_cast<uint64_t *>(partial_row))[p].load()));
+    for (int32_t p0 = threadIdx.x; p0 < tb.n_pieces; p0 += B * kBlock) {
+        uint64_t b[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            const int32_t p = p0 + j * kBlock;
+            b[j] = (p < tb.n_pieces) ? as_shared(reinterpret_cast<uint64_t *>(partial_row))[p].load() : 0ull;
+        }
+#pragma unroll
+        for (int j = 0; j < B; ++j) acc += __longlong_as_double(static_cast<long long>(b[j]));   // + 0.0 past the end
+    }
     const double total = block_sum(acc, m.red, false);
     *s = group_scale(total, len, RMS);
     if (threadIdx.x == 0) {
@@ -723,7 +781,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
     // The tiles one after the other, those for LDS first, with the loads of D tiles in flight.
     constexpr int D = kHeldDepth < T ? kHeldDepth : T;
     f32x4 v[R], g[D], dl[L ? D : 1];
-    double sum = 0.0;
+    HeldSums sums;
     auto fetch = [&](auto qc) {
         constexpr int q = decltype(qc)::value, t = q < L ? R + q : q - L;
         if constexpr (q < L) dl[q % D] = held_ld4(drow + first, left, t);
@@ -742,11 +800,11 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_worker(Work
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (q < L) far[q][threadIdx.x] = w;
         else v[t] = w;
-        held_look<RMS, T>(w, t, m, sum);
+        held_look<RMS, q, L, T>(w, t, m, sums);
     });
     held_fence(v, left);
     float s;
-    const bool ok = held_scale<RMS, T>(m, sum, tile0, row, words + row * W, tb, partials + static_cast<int64_t>(row) * tb.n_pieces,
+    const bool ok = held_scale<RMS, T>(m, tile0, row, words + row * W, tb, partials + static_cast<int64_t>(row) * tb.n_pieces,
                                        scales + row, rows, patience, &s);
     uint32_t *gave_up_row = gave_up + row * static_cast<int64_t>(gridDim.x);
     if (threadIdx.x == 0 && gridDim.x != 1) as_shared(gave_up_row)[blockIdx.x].store(ok ? 0u : 1u);
@@ -824,7 +882,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(Serv
     constexpr int D = 4 < T ? 4 : T;
     f32x4 v[R], ring[L ? D : 1];
     uint32_t word[D];
-    double sum = 0.0;
+    HeldSums sums;
     auto fetch = [&](auto qc) {
         constexpr int q = decltype(qc)::value, t = q < L ? R + q : q - L;
         if constexpr (q < L) ring[q % D] = held_ld4<0>(delta_s + first, left, t);
@@ -856,7 +914,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(Serv
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (q < L) far[q][threadIdx.x] = w;
         else v[t] = w;
-        held_look<RMS, T>(w, t, m, sum);
+        held_look<RMS, q, L, T>(w, t, m, sums);
     });
     held_fence(v, left);
     const bool mine_cut = cut_at >= 0 && (cut_at & (kTile - 1)) == static_cast<int>(threadIdx.x) * 4;   // `cut` holds its v
@@ -869,7 +927,7 @@ __global__ __launch_bounds__(kBlock, held_waves(R)) void k_sign_held_server(Serv
         if constexpr (UPD == 2) mv[t] = held_ld4<0>(u.m + first, left, t);
     }
     float s;
-    const bool ok = held_scale<RMS, T>(m, sum, tile0, 0, words_out, tb, partials, scale_out, rows, patience, &s);
+    const bool ok = held_scale<RMS, T>(m, tile0, 0, words_out, tb, partials, scale_out, rows, patience, &s);
     if (threadIdx.x == 0 && gridDim.x != 1) as_shared(gave_up)[blockIdx.x].store(ok ? 0u : 1u);
     if (!ok) {                                                // uniform
 #pragma unroll

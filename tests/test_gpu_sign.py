@@ -1,5 +1,6 @@
 """GPU parity: 1-bit compressor and identity, every route, against the CPU oracle."""
 import dataclasses
+import math
 
 import numpy as np
 import pytest
@@ -332,6 +333,62 @@ def test_sign_whole_vector_server_in_one_look(gpu_device, n, d, momentum, rms, p
     finally:
         for c in ctxs:
             c.close()
+
+
+# A vector whose sum of |v| depends on the order of the additions in the one bit that decides the scale.  Two values in one
+# thread's group make up a sum of exactly d (2^24 + 1) 2^-30, a mean halfway between two floats.  In the other tiles that the same
+# workgroup holds (`tiles` of them in a stretch) the same thread has a little less than half a unit in the last place of
+# the sum: added to it one by one they are lost, and the scale is the lower float, two of them together are not.
+def _halfway(d, tiles, at, device):
+    v = torch.zeros(d, device=device)
+    unit = math.ldexp(1.0, math.frexp(d * (2.0 ** 24 + 1) * 2.0 ** -30)[1] - 53)
+    v[::2048][:tiles] = 0.475 * unit
+    v[at * 2048], v[at * 2048 + 1] = d * 2.0 ** -6, d * 2.0 ** -30
+    assert float(v[at * 2048].double() + v[at * 2048 + 1].double()) == d * (2.0 ** 24 + 1) * 2.0 ** -30
+    return v
+
+
+@pytest.mark.parametrize("n,d,tiles", [(2, 5 * 2048 + 2, 8), (2, 8 * 2048 - 1, 8), (8, 700_002, 4), (9, 1_800_003, 8), (9, 2_600_003, 14),
+                                       (3, 9_000_005, 24)])
+def test_sign_scales_do_not_depend_on_the_route(gpu_device, n, d, tiles):
+    """Plain form, deferred form and the call without a context add in the same order."""
+    here = min(tiles, -(-d // 2048) - 1)                        # not the tile that the end of the row cuts
+    first = held_shapes.REGISTERS_AND_LDS[tiles][0] if held_shapes.REGISTERS_AND_LDS[tiles][1] else 0
+    g = torch.stack([_halfway(d, here, (first + i) % here, gpu_device) for i in range(n)])
+    plain, deferred = P.Context("sign", n, d, scale_mode="whole"), P.Context("sign", n, d, scale_mode="whole", flags=P.FLAG_DEFERRED_ERROR)
+    try:
+        a, b = plain.alloc_payload(n, gpu_device), deferred.alloc_payload(n, gpu_device)
+        words, scales = torch.zeros_like(a.sign_words), torch.zeros_like(a.scales)
+        plain.worker_compress(0, g, torch.zeros_like(g), a)
+        deferred.worker_compress(0, g, torch.zeros_like(g), b)
+        P.ds_worker_compress_sign_noalloc(g, torch.zeros_like(g), words, scales)
+        torch.cuda.synchronize()
+        assert torch.equal(a.scales, b.scales) and torch.equal(a.scales, scales)
+    finally:
+        plain.close()
+        deferred.close()
+
+
+@pytest.mark.parametrize("n,d,tiles", [(8, 3 * 2048 + 2, 4), (3, 3_000_001, 4), (2, 9_000_002, 8), (2, 17_000_000, 14), (1, 23_000_000, 24)])
+def test_sign_server_scales_do_not_depend_on_the_route(gpu_device, n, d, tiles):
+    """The same on the server: messages of scale 0 leave v = delta_s."""
+    here = min(tiles, -(-d // 2048) - 1)
+    first = held_shapes.REGISTERS_AND_LDS[tiles][0] if held_shapes.REGISTERS_AND_LDS[tiles][1] else 0
+    plain, deferred = P.Context("sign", n, d, scale_mode="whole"), P.Context("sign", n, d, scale_mode="whole", flags=P.FLAG_DEFERRED_ERROR)
+    try:
+        msg, a, b = plain.alloc_payload(n, gpu_device), plain.alloc_server_payload(), deferred.alloc_server_payload()
+        msg.sign_words.zero_()
+        msg.scales.zero_()
+        for at in (first, 0, here - 1):
+            v = _halfway(d, here, at, gpu_device)
+            plain.server_aggregate_compress(0, msg, v.clone(), a)
+            deferred.server_aggregate_compress(0, msg, error := v.clone(), b)
+            deferred.materialize_error(None, error)
+            torch.cuda.synchronize()
+            assert torch.equal(a.scales, b.scales), at
+    finally:
+        plain.close()
+        deferred.close()
 
 
 def _same_bits_or_nan(a, b):
