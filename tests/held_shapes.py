@@ -39,6 +39,7 @@ TERNARY = [
     (4, 9_000_005, "f32", 14, 314), (2, 11_173_962, "f32", 24, 228), (5, 11_173_963, "f32", 24, 228), (7, 7_826_509, "bf16", 8, 478),
     (3, 9_000_005, "f32", 14, 314), (5, 6_000_002, "bf16", 14, 210), (3, 7_826_508, "bf16", 8, 478),
     (1, 5_000_003, "f32", 0, 2442), (2, 13_000_001, "bf16", 14, 454),
+    (1, 5_000_002, "bf16", 0, 2442), (2, 25_200_001, "f32", 0, 12305), (2, 25_200_003, "bf16", 0, 12305),
 ]
 
 # tiles -> tiles in registers and in LDS, the last template arguments of the kernels

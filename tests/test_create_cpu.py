@@ -81,14 +81,15 @@ def test_ternary_shapes_are_launched_as_listed(program):
 
 
 def test_every_size_is_listed(program):
-    """Several workgroups of every size, one workgroup of every size that is left to one, both types, and separate
-    launches stand in the lists."""
+    """Several workgroups of every size, one workgroup of every size that is left to one, and separate launches stand in
+    the lists; those of the ternary compressor, whose tests compare with the oracle, for one row and several of both types."""
     assert {t for *_, t, w in H.SIGN_WORKER if w > 1} == {0, 1, 2, 4, 8, 14, 24}
     assert {t for *_, t, w in H.SIGN_SERVER if w > 1} == {0, 1, 2, 4, 8, 14, 24}
     assert {t for *_, t, w in H.TERNARY if w > 1} == {0, 1, 2, 4, 8, 14, 24}
     assert {t for *_, t, w in H.SIGN_WORKER if w == 1} == {1, 2, 4, 8, 14}
     assert {t for *_, t, w in H.SIGN_SERVER if w == 1} == {1, 2, 4}
     assert {t for *_, t, w in H.TERNARY if w == 1} == {1, 2, 4}
+    assert {(n > 1, dtype) for n, _, dtype, t, _ in H.TERNARY if t == 0} == {(False, "f32"), (True, "f32"), (False, "bf16"), (True, "bf16")}
 
 
 @pytest.mark.parametrize("n,d,k,one", [

@@ -168,11 +168,11 @@ def _ternary_against_oracle(gpu_device, g, patience, seed=7, step=0):
         ctx.close()
 
 
-# Maxima beyond the range in which the product test decides (every element divides), at its edges, and rows
+# Maxima beyond the range 2^-90 .. 2^90 in which the product test decides (every element divides), at its edges, and rows
 # of subnormals only; one workgroup per row, several, and rows that are looked at twice.
 @pytest.mark.parametrize("n,d,power,patience", [(n, d, p, patience) for n, d in ((2, 5001), (2, 60_003)) for patience in (0, -1)
-                                                for p in (-140, -126, -101, -100, 99, 100, 110, 120)] +
-                         [(1, 5_000_003, -126, 0), (1, 5_000_003, 110, 0)])
+                                                for p in (-140, -126, -101, -100, -91, -90, -89, 89, 90, 91, 99, 100, 110, 120)] +
+                         [(1, 5_000_003, p, 0) for p in (-126, -91, -90, 90, 91, 110)])
 def test_ternary_maxima_over_the_whole_range(gpu_device, n, d, power, patience):
     scale = 2.0 ** power
     rng = np.random.default_rng(3)
