@@ -12,12 +12,15 @@ from parity_util import Pair
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(autouse=True, params=["single_launch", "multi_launch"])
+@pytest.fixture(autouse=True, params=["single_launch", "multi_launch", "as_long_rows"])
 def topk_route(request):
-    """Every test of this module runs on both refinement routes of the library."""
+    """Every test of this module runs on both refinement routes of the library, and short rows, which have a
+    launch of their own, once more on the single launch of longer ones: a context that states the limit of its waits,
+    here the one that is the default, asks for it."""
     parity_util.CONTEXT_FLAGS = P.FLAG_TOPK_MULTI_LAUNCH if request.param == "multi_launch" else 0
+    parity_util.CONTEXT_KW = {"topk_spin_limit": 1 << 22} if request.param == "as_long_rows" else {}
     yield request.param
-    parity_util.CONTEXT_FLAGS = 0
+    parity_util.CONTEXT_FLAGS, parity_util.CONTEXT_KW = 0, {}
 
 
 def _wl(d, n=3, k=None, **kw):
@@ -221,7 +224,7 @@ def test_topk_short_rows_of_nans(gpu_device, d, share):
     n, k = 2, max(1, d // 100)
     g = torch.ones((n, d), device=gpu_device)
     g[:, ::(1 if share == 1.0 else 2)] = float("nan")
-    ctx = P.Context("topk", n, d, k=k, flags=parity_util.CONTEXT_FLAGS)
+    ctx = P.Context("topk", n, d, k=k, flags=parity_util.CONTEXT_FLAGS, **parity_util.CONTEXT_KW)
     try:
         guard = torch.zeros(n * d + 4096, device=gpu_device)
         delta = guard[: n * d].view(n, d)
@@ -242,7 +245,7 @@ def test_topk_server_passes_over_entries_past_the_end(gpu_device, d, k, past):
     n = 3
     gen = torch.Generator(device=gpu_device)
     gen.manual_seed(d)
-    ctx = P.Context("topk", n, d, k=k, flags=parity_util.CONTEXT_FLAGS)
+    ctx = P.Context("topk", n, d, k=k, flags=parity_util.CONTEXT_FLAGS, **parity_util.CONTEXT_KW)
     try:
         idx = torch.stack([torch.randperm(d - 1, device=gpu_device, generator=gen)[: k - 1].sort().values for _ in range(n)])
         val = torch.randn((n, k), device=gpu_device, generator=gen)
