@@ -133,17 +133,17 @@ __global__ __launch_bounds__(kBlock) void k_clip_worker(const void *g, int64_t g
 // eight workers are asked for before the first is used: one after the other they were a chain of memory latencies.  Batches
 // of 8, 4, 2 and 1 without a test of the count before every load, which with few workers cost more than the batch gains.
 // Server block alone, one by one : eights with tests : as it is: 16 bits, 1 x 1,000,003 3.2 : 3.4 : 3.2 us, 9 x 5000 3.2 : 2.8 :
-// 2.4 us, 16 x 1,000,003 9.9 : 7.6 : 7.3 us; 24 bits, 8 x 3,000,001 11.6 : 8.8 : 8.7 us, 8 x 25.6 M 74.7 : 65.7 : 65.7 us; 8 bits, 16 x 10 M
-// 134 : 140 : 140 us, the one shape that lost.
+// 2.4 us, 16 x 1,000,003 9.9 : 7.6 : 7.3 us; 24 bits, 8 x 3,000,001 11.6 : 8.8 : 8.7 us, 8 x 25.6 M 74.7 : 65.7 : 65.7 us.
+// ONE: one by one after all, where it is ahead (clip_one_by_one).
 // The update in the server's pass spares a launch and reading the message again: server and update repeated, two launches :
 // one pass, 8 x 1,000,003 7.8 : 5.2 us, 1 x 10 M 35 : 31 us, 16 x 10 M of 8 bits 153 : 153 us; within whole steps at 8 x 25.6 M,
 // where nothing is left in a cache, 140 + 42 and 186 us.
 // (Eight elements per thread, for 16 bytes of a message in one access, made steps of 8 x 25.6 M 746 us instead of 635, the stores
 // of 16 bytes in every 32 being what costs.)
-template <int NB>
+template <int NB, bool ONE>
 __device__ __forceinline__ f32x4 clip_chain(f32x4 a, const uint8_t *msg_in, int n, float inv_n, int64_t e, int64_t d)
 {
-    if (e + 4 <= d) {
+    if (!ONE && e + 4 <= d) {
         const uint8_t *p = msg_in + e * NB;
         const int64_t row = d * NB;
         auto batch = [&](auto count) {
@@ -169,7 +169,7 @@ __device__ __forceinline__ f32x4 clip_chain(f32x4 a, const uint8_t *msg_in, int 
 // Parameter-server block: v = delta_s + (1/n) sum_i Q[v_i], then the same compression.
 // UPD: 0 = that block alone; 1, 2 = followed by the model update for the same elements (2: through the momentum
 // buffer) from the registers that hold the message.
-template <int NB, int UPD>
+template <int NB, int UPD, bool ONE>
 __global__ __launch_bounds__(kBlock) void k_clip_server(const uint8_t *msg_in, int n, float inv_n, float *delta_s,
                                                         uint8_t *msg_out, int64_t d, uint32_t mask, float *x, float *m,
                                                         float gamma, float beta)
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kBlock) void k_clip_server(const uint8_t *msg_in, i
     f32x4 xv = {0.f, 0.f, 0.f, 0.f}, mv = {0.f, 0.f, 0.f, 0.f};
     if constexpr (UPD != 0) xv = ld4_stream(x, e, d);
     if constexpr (UPD == 2) mv = ld4_stream(m, e, d);
-    f32x4 q = clip_store4<NB>(clip_chain<NB>(a, msg_in, n, inv_n, e, d), mask, e, d, msg_out, delta_s);
+    f32x4 q = clip_store4<NB>(clip_chain<NB, ONE>(a, msg_in, n, inv_n, e, d), mask, e, d, msg_out, delta_s);
     if constexpr (UPD != 0) {
         if constexpr (UPD == 2) {
             q = fma4(beta, mv, q);
@@ -192,13 +192,13 @@ __global__ __launch_bounds__(kBlock) void k_clip_server(const uint8_t *msg_in, i
 }
 
 // Server that does not compress: the average is the message (written and / or applied).
-template <int NB>
+template <int NB, bool ONE>
 __global__ __launch_bounds__(kBlock) void k_clip_server_identity(const uint8_t *msg_in, int n, float inv_n, int64_t d,
                                                                  float *dense_out, ds_update_args u)
 {
     const int64_t e = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) * 4;
     if (e >= d) return;
-    const f32x4 a = clip_chain<NB>(f32x4{0.f, 0.f, 0.f, 0.f}, msg_in, n, inv_n, e, d);
+    const f32x4 a = clip_chain<NB, ONE>(f32x4{0.f, 0.f, 0.f, 0.f}, msg_in, n, inv_n, e, d);
     put_average4(a, e, d, dense_out, u.x, u.m, u.gamma, u.beta);
 }
 
@@ -222,6 +222,29 @@ void with_bytes(int bits, F f)
     if (bits >= 24) f(std::integral_constant<int, 1>{});
     else if (bits >= 16) f(std::integral_constant<int, 2>{});
     else f(std::integral_constant<int, 4>{});
+}
+
+// Whether the server takes the messages one by one.  Messages of four bytes an element that come from memory keep it
+// busy without batches, which then only cost wavefronts.  Server block, one by one : batches, 12 x 10 M 107 : 110 us, 24 x 5 M
+// 97 : 101, 16 x 10 M 136 : 141, 32 x 10 M 251 : 271, 64 x 5 M 245 : 256 us; with the update it starts later, 12 x 25.6 M 311 : 301, 16 x
+// 25.6 M 427 : 416, 24 x 10 M 213 : 218, 32 x 10 M 268 : 288, 64 x 3 M 151 : 160 us.  8 x 10 M 90 : 86 us, 64 x 1,000,003, from the
+// cache, 48.5 : 45.6 us; shorter messages, 16 bits 0.95 .. 1.20 and 24 bits 1.03 .. 1.30 times as long one by one.
+bool clip_one_by_one(const ds_ctx *c, bool update)
+{
+    return c->cfg.n >= (update ? 24 : 12) && c->cfg.n * c->cfg.d >= 100'000'000;
+}
+
+// f(bytes of an element of the message, whether the messages are taken one by one)
+template <class F>
+void with_chain(const ds_ctx *c, bool update, F f)
+{
+    with_bytes(c->cfg.levels, [&](auto nb) {
+        constexpr int NB = decltype(nb)::value;
+        if constexpr (NB == 4) {
+            if (clip_one_by_one(c, update)) return f(nb, std::true_type{});
+        }
+        f(nb, std::false_type{});
+    });
 }
 
 }  // namespace
@@ -248,9 +271,9 @@ ds_status_t ds_clip_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
                            float *m, float gamma, float beta)
 {
     const int bits = c->cfg.levels;
-    with_bytes(bits, [&](auto nb) {
+    with_chain(c, x != nullptr, [&](auto nb, auto one) {
         auto go = [&](auto upd) {
-            k_clip_server<decltype(nb)::value, decltype(upd)::value><<<blocks4(c->cfg.d), kBlock, 0, st>>>(
+            k_clip_server<decltype(nb)::value, decltype(upd)::value, decltype(one)::value><<<blocks4(c->cfg.d), kBlock, 0, st>>>(
                 in->levels, c->cfg.n, c->inv_n, delta_s, out->levels, c->cfg.d, clip_mask(bits), x, m, gamma, beta);
         };
         if (!x) go(std::integral_constant<int, 0>{});
@@ -262,9 +285,9 @@ ds_status_t ds_clip_server(ds_ctx *c, const ds_payload_t *in, float *delta_s, co
 
 ds_status_t ds_clip_server_identity(ds_ctx *c, const ds_payload_t *in, float *dense_out, ds_update_args u, hipStream_t st)
 {
-    with_bytes(c->cfg.levels, [&](auto nb) {
-        constexpr int NB = decltype(nb)::value;
-        k_clip_server_identity<NB><<<blocks4(c->cfg.d), kBlock, 0, st>>>(in->levels, c->cfg.n, c->inv_n, c->cfg.d, dense_out, u);
+    with_chain(c, u.x != nullptr, [&](auto nb, auto one) {
+        k_clip_server_identity<decltype(nb)::value, decltype(one)::value><<<blocks4(c->cfg.d), kBlock, 0, st>>>(
+            in->levels, c->cfg.n, c->inv_n, c->cfg.d, dense_out, u);
     });
     return ds_launch_status();
 }

@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import ds_workloads as W
+import paper_1905_05957_amd as P
 from parity_util import Pair
 
 pytestmark = pytest.mark.gpu
@@ -64,3 +65,36 @@ def test_clip_batches_of_workers_and_the_update_in_one_call(gpu_device, n, bits,
     finally:
         two.close()
         one.close()
+
+
+@pytest.mark.parametrize("n,d,update", [(12, 8_400_003, None), (24, 4_200_003, 1), (24, 4_200_001, 2)])
+def test_clip_servers_that_take_messages_one_by_one(gpu_device, n, d, update):
+    """Many long messages of four bytes an element are taken one by one, short ones in batches; every element stands for
+    itself, so stretches of the long rows are what a short context gives for them.  update: none, without and with momentum."""
+    def server(ctx, msg, e, out, x, m):
+        if update is None:
+            ctx.server_aggregate_compress(0, msg, e, out)
+        else:
+            ctx.server_aggregate_compress_update(0, msg, e, out, x, m if update == 2 else None, 0.05, 0.9)
+
+    gen = torch.Generator(device=gpu_device)
+    gen.manual_seed(1)
+    long = P.Context("clip", n, d, levels=8)
+    try:
+        msg, out = long.alloc_payload(n, gpu_device), long.alloc_server_payload(gpu_device)
+        msg.levels.view(torch.int32).copy_(torch.randn((n, d), device=gpu_device, generator=gen).view(torch.int32) & ~255)
+        err, x, m = (torch.randn(d, device=gpu_device, generator=gen) for _ in range(3))
+        before = [t.clone() for t in (err, x, m)]
+        server(long, msg, err, out, x, m)
+        for first, last in ((0, 5003), (4_000_000, 4_003_000), (d - 2051, d)):
+            short = P.Context("clip", n, last - first, levels=8)
+            part, got = short.alloc_payload(n, gpu_device), short.alloc_server_payload(gpu_device)
+            part.levels.copy_(msg.levels[:, 4 * first: 4 * last])
+            e, xs, ms = (t[first:last].clone() for t in before)
+            server(short, part, e, got, xs, ms)
+            torch.cuda.synchronize()
+            short.close()
+            assert torch.equal(got.levels, out.levels[:, 4 * first: 4 * last])
+            assert torch.equal(e, err[first:last]) and torch.equal(xs, x[first:last]) and torch.equal(ms, m[first:last])
+    finally:
+        long.close()
