@@ -351,15 +351,16 @@ QParams make_params(const ds_ctx *c, uint64_t step)
 // Whether the server's block exchanges the messages between lanes.  Measured at n = 1 .. 128 and d = 20,001 .. 25.6 M, odd
 // lengths and even; the time without the exchange over that with it:
 //  * n up to 8: 0.99 .. 1.11 up to 1 M elements, 0.79 .. 1.05 from 1.5 M on;
-//  * n = 9 .. 16: 1.01 .. 1.22 up to 1 M; at 1.5 M 1.03 .. 1.09, from 2 M on 0.87 .. 1.07;
+//  * n = 9 .. 12: 1.01 .. 1.22 up to 1 M; at 1.5 M 1.03 .. 1.09, from 2 M on 0.87 .. 1.05;
+//  * n = 13 .. 16: the same up to 1.5 M, 1.03 .. 1.09 at 2 .. 2.5 M, 0.87 .. 1.04 beyond;
 //  * n = 17 .. 32: 1.08 .. 1.37 up to 1.5 M, 0.95 .. 1.09 at 2 .. 2.5 M, 0.92 .. 1.04 beyond;
 //  * more: 1.29 .. 1.61 up to 1.5 M and 0.93 .. 1.20 beyond;
-//  * with momentum, n up to 32: 0.79 .. 0.94 from 1.5 M on; more: 1.10 .. 1.13 at 1.5 M, 0.85 .. 1.09 beyond.
+//  * with momentum, n up to 32: 0.79 .. 0.94 from 1.5 M on; more: up to 1.13 until 2.5 M, 0.85 .. 1.00 beyond.
 bool qsgd_exchange(const ds_ctx *c, bool momentum)
 {
     const int32_t n = c->cfg.n;
-    if (n > 32) return !momentum || c->n_tiles <= 1024;
-    return c->n_tiles <= ((n <= 8 || momentum) ? 512 : n <= 16 ? 768 : 1280);
+    if (n > 32) return !momentum || c->n_tiles <= 1280;
+    return c->n_tiles <= ((n <= 8 || momentum) ? 512 : n <= 12 ? 768 : 1280);
 }
 
 }  // namespace

@@ -113,14 +113,15 @@ def test_short_topk_rows_of_many_workers(program, n, d, k, one):
 # the server call that the program makes has a momentum buffer
 @pytest.mark.parametrize("n,d,exchange", [
     (1, 20_001, True), (8, 512 * 2048, True), (8, 512 * 2048 + 1, False), (16, 1_000_003, True), (16, 2_000_001, False), (32, 1_000_003, True),
-    (32, 2_000_001, False), (33, 2_000_001, True), (64, 1024 * 2048 + 1, False), (16, 25_557_032, False)])
+    (32, 2_000_001, False), (33, 2_000_001, True), (48, 1280 * 2048, True), (64, 1280 * 2048 + 1, False),
+    (16, 25_557_032, False)])
 def test_quantiser_servers_take_the_way_that_is_faster(program, n, d, exchange):
     launched, = _launches(program, [("s", QSGD, n, d, 0, 0)])
     (name, x, y), = launched
     assert f"k_qsgd_serverILi2ELb0ELb{int(exchange)}E" in name and (x, y) == (-(-d // 2048), 1), launched
 
 
-@pytest.mark.parametrize("n,d,exchange", [(8, 512 * 2048 + 1, False), (9, 768 * 2048, True), (16, 768 * 2048 + 1, False), (17, 1280 * 2048, True),
+@pytest.mark.parametrize("n,d,exchange", [(8, 512 * 2048 + 1, False), (9, 768 * 2048, True), (12, 768 * 2048 + 1, False), (13, 1280 * 2048, True),
                                           (32, 1280 * 2048 + 1, False), (33, 25_557_032, True)])
 def test_quantiser_servers_without_momentum_take_the_way_that_is_faster(program, n, d, exchange):
     launched, = _launches(program, [("p", QSGD, n, d, 0, 0)])
