@@ -1822,7 +1822,7 @@ __device__ __forceinline__ void solo_emit(SoloShared &sm, int wave, uint32_t lis
     }
 }
 
-// sample_rank: 0 = the row is not sampled.  WR: the error is written to buf.  x != nullptr (one row
+// WR: the error is written to buf.  x != nullptr (one row
 // only): x <- fma(-gamma, val, x) at the kept entries.
 template <class Src, bool WR>
 __global__ __launch_bounds__(kSoloThreads) void k_topk_solo(Src src, float *buf, int64_t stride, int64_t d, int64_t k,
@@ -1860,33 +1860,29 @@ __global__ __launch_bounds__(kSoloThreads) void k_topk_solo(Src src, float *buf,
 
     // lower bound; the elements past the end are 0 and never reach it
     uint32_t lo = 1u;
-    if (sample_rank != 0u) {
-        // f(key) for the sampled elements
-        const int thin = (dd > kSoloThinFrom) ? 1 : 0;
-        auto sample = [&](auto f) {
+    // f(key) for the sampled elements
+    const int thin = (dd > kSoloThinFrom) ? 1 : 0;
+    auto sample = [&](auto f) {
 #pragma unroll
-            for (int t = 0; t < kSoloTiles; ++t) {
-                if (t * kSoloTile < dd && !((t + wave) & thin)) {
-                    solo_fence(v[t], first);
-                    const int c = (lane + t) & 3, e = t * kSoloTile + first + c;
-                    const float s = (c & 2) ? ((c & 1) ? v[t].w : v[t].z) : ((c & 1) ? v[t].y : v[t].x);
-                    if (e < dd) f(key_of(s));
-                }
+        for (int t = 0; t < kSoloTiles; ++t) {
+            if (t * kSoloTile < dd && !((t + wave) & thin)) {
+                solo_fence(v[t], first);
+                const int c = (lane + t) & 3, e = t * kSoloTile + first + c;
+                const float s = (c & 2) ? ((c & 1) ? v[t].w : v[t].z) : ((c & 1) ? v[t].y : v[t].x);
+                if (e < dd) f(key_of(s));
             }
-        };
-        sample([&](uint32_t key) { atomicAdd(&sm.h[key >> 19], 1u); });
-        solo_pick<kH1>(sm.h, sample_rank, sm.part, sm.out);
-        const uint32_t b = sm.out[0], rem = sm.out[1];
-        // Error feedback piles values up just below the threshold: the bound to 12 bits only lets several times k
-        // candidates in once the errors have settled (worker kernel at 60,040 elements: 34 us, 23 us with fresh errors).
-        if (b != kNone && dd <= kSoloList) {
-            if (b != 0u) lo = b << 19;                         // the list holds the whole row if need be
-        } else if (b != kNone) {                               // uniform
-            sample([&](uint32_t key) { if ((key >> 19) == b) atomicAdd(&sm.h2[(key >> 8) & (kH2 - 1)], 1u); });
-            solo_pick<kH2>(sm.h2, rem, sm.part, sm.out);
-            const uint32_t key = (b << 19) | (sm.out[0] << 8);
-            if (key != 0u) lo = key;
         }
+    };
+    sample([&](uint32_t key) { atomicAdd(&sm.h[key >> 19], 1u); });
+    solo_pick<kH1>(sm.h, sample_rank, sm.part, sm.out);
+    const uint32_t b = sm.out[0], rem = sm.out[1];
+    // Error feedback piles values up just below the threshold: the bound to 12 bits only lets several times k
+    // candidates in once the errors have settled (worker kernel at 60,040 elements: 34 us, 23 us with fresh errors).
+    if (b != kNone) {                                          // uniform
+        sample([&](uint32_t key) { if ((key >> 19) == b) atomicAdd(&sm.h2[(key >> 8) & (kH2 - 1)], 1u); });
+        solo_pick<kH2>(sm.h2, rem, sm.part, sm.out);
+        const uint32_t key = (b << 19) | (sm.out[0] << 8);
+        if (key != 0u) lo = key;
     }
     // a bound that is a NaN would let the zeros past the end of the row through
     lo = (lo < 0x7F800000u) ? lo : 0x7F800000u;
