@@ -268,10 +268,11 @@ ds_status_t ds_apply_update(ds_ctx_t *ctx, const ds_payload_t *srv, float *x, fl
 /* The parameter-server block followed by the model update, as one call: the same results, bit
  * for bit, as ds_server_aggregate_compress(ctx, step, in, delta_s, out, stream) followed by
  * ds_apply_update(ctx, out, x, m, gamma, beta, stream), for the library to fold the update
- * into the server's kernels where that saves work (TOPK without momentum: x is updated
- * where the kept entries are emitted; RSPARSE: the update takes the offsets of the packed
- * values from the server pass instead of deriving them from the message again).  Arguments
- * and errors as for those two calls. */
+ * into the server's kernels where that saves work.  TOPK without momentum updates x where the
+ * kept entries are emitted.  SIGN (unless its server block takes separate launches), QSGD, CLIP
+ * and RSPARSE update x and m from the registers that hold the server's message; RSPARSE that
+ * keeps less than 1/16, without momentum, has the update take the offsets of the packed values
+ * from the server pass instead.  Arguments and errors as for those two calls. */
 ds_status_t ds_server_aggregate_compress_update(ds_ctx_t *ctx, uint64_t step, const ds_payload_t *in,
                                                 float *delta_s, const ds_payload_t *out, float *x,
                                                 float *m, float gamma, float beta, void *hip_stream);
